@@ -1046,42 +1046,28 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
       }
     }
   } else {
+    // all branches in one launch, the long block lists and windows of the outer bands first
     const int64_t Nd = c->N * c->d;
-    GenericAttnArgs g{};
+    GAttnArgs g{};
     g.d = c->d; g.scale = scale;
-    if (c->n_list[LOW] > 0) {
-      g.Q = (const float*)c->lowQ; g.K = (const float*)c->lowK; g.V = (const float*)c->lowV; g.O = (float*)c->lowY;
-      g.slice_list = L + c->off_list[LOW]; g.n_slices = c->n_list[LOW];
-      g.slice_stride = g.kv_slice_stride = c->nbar * c->d; g.nq = g.nk = (int)c->nbar; g.mode = 0;
-      HIP_TRY(c, launch_generic_attn(g, st));
+    static const int order[NBMAX] = {HIGH, MID2, MID, LOW};
+    for (int l : order) {
+      if (l >= c->nb || c->n_list[l] == 0) continue;
+      GAttnSeg& s = g.seg[g.nseg++];
+      s.slice_list = L + c->off_list[l]; s.n_slices = c->n_list[l];
+      if (l == LOW) {
+        s.Q = (const float*)c->lowQ; s.K = (const float*)c->lowK; s.V = (const float*)c->lowV; s.O = (float*)c->lowY;
+        s.slice_stride = s.kv_slice_stride = c->nbar * c->d; s.nq = s.nk = (int)c->nbar; s.mode = 0;
+        continue;
+      }
+      const int64_t o = c->band_off[l] * c->d;
+      s.Q = (const float*)c->specQ + o; s.K = (const float*)c->specK + o; s.V = (const float*)c->specV + o; s.O = (float*)c->Y + o;
+      s.slice_stride = s.kv_slice_stride = Nd; s.nq = s.nk = (int)c->band_n[l];
+      s.mode = l == HIGH ? 2 : 1; s.window = c->cfg.high_window; s.block = c->cfg.mid_block;
+      s.row_ptr = l == MID2 ? c->d_row_ptr2 : c->d_row_ptr; s.col_idx = l == MID2 ? c->d_col_idx2 : c->d_col_idx;
     }
-    tm.done("low_attention");
-    if (c->n_list[MID] > 0) {
-      const int64_t o = c->band_off[MID] * c->d;
-      g.Q = (const float*)c->specQ + o; g.K = (const float*)c->specK + o; g.V = (const float*)c->specV + o;
-      g.O = (float*)c->Y + o; g.slice_list = L + c->off_list[MID]; g.n_slices = c->n_list[MID];
-      g.slice_stride = g.kv_slice_stride = Nd; g.nq = g.nk = (int)c->band_n[MID]; g.mode = 1;
-      g.row_ptr = c->d_row_ptr; g.col_idx = c->d_col_idx; g.block = c->cfg.mid_block;
-      HIP_TRY(c, launch_generic_attn(g, st));
-    }
-    if (c->nb > 3 && c->n_list[MID2] > 0) {   // the second mid band: the same operator on its own rows and block list
-      const int64_t o = c->band_off[MID2] * c->d;
-      g.Q = (const float*)c->specQ + o; g.K = (const float*)c->specK + o; g.V = (const float*)c->specV + o;
-      g.O = (float*)c->Y + o; g.slice_list = L + c->off_list[MID2]; g.n_slices = c->n_list[MID2];
-      g.slice_stride = g.kv_slice_stride = Nd; g.nq = g.nk = (int)c->band_n[MID2]; g.mode = 1;
-      g.row_ptr = c->d_row_ptr2; g.col_idx = c->d_col_idx2; g.block = c->cfg.mid_block;
-      HIP_TRY(c, launch_generic_attn(g, st));
-    }
-    tm.done("mid_attention");
-    if (c->n_list[HIGH] > 0) {
-      const int64_t o = c->band_off[HIGH] * c->d;
-      g.Q = (const float*)c->specQ + o; g.K = (const float*)c->specK + o; g.V = (const float*)c->specV + o;
-      g.O = (float*)c->Y + o; g.slice_list = L + c->off_list[HIGH]; g.n_slices = c->n_list[HIGH];
-      g.slice_stride = g.kv_slice_stride = Nd; g.nq = g.nk = (int)c->band_n[HIGH]; g.mode = 2;
-      g.window = c->cfg.high_window;
-      HIP_TRY(c, launch_generic_attn(g, st));
-    }
-    tm.done("high_attention");
+    HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));
+    tm.done("band_attention_fused");
   }
   if (c->n_list[LOW] > 0)
     HIP_TRY(c, launch_expand_low(c->lowY, c->Y, L + c->off_list[LOW], c->n_list[LOW], c->N, c->d, c->band_n[LOW], c->nbar, c->cfg.low_compress, is_half, st));
@@ -1096,17 +1082,19 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
     if (mf) {
       HIP_TRY(c, launch_mfma_attn(ap, (const AttnItem*)(L + c->off_items_xchg), c->n_items_xchg, c->attn_rows, c->num_cu, st));
     } else {
+      GAttnArgs g{};
+      g.d = c->d; g.scale = scale;
       for (int l = 0; l < c->nb; ++l) {
         if (c->n_list[l] == 0 || c->n_c[l] == 0) continue;
-        GenericAttnArgs g{};
-        g.d = c->d; g.scale = scale; g.mode = 0; g.residual = 1;
-        g.Q = (const float*)c->Y + c->band_off[l] * c->d; g.O = (float*)c->Y + c->band_off[l] * c->d;
-        g.K = g.V = (const float*)c->Cbuf + (int64_t)l * ap.m2 * c->d;
-        g.slice_list = L + c->off_list[l]; g.n_slices = c->n_list[l];
-        g.slice_stride = c->N * c->d; g.kv_slice_stride = (int64_t)c->nb * ap.m2 * c->d;
-        g.nq = (int)c->band_n[l]; g.nk = c->n_c[l];
-        HIP_TRY(c, launch_generic_attn(g, st));
+        GAttnSeg& x = g.seg[g.nseg++];
+        x.mode = 0; x.residual = 1;
+        x.Q = (const float*)c->Y + c->band_off[l] * c->d; x.O = (float*)c->Y + c->band_off[l] * c->d;
+        x.K = x.V = (const float*)c->Cbuf + (int64_t)l * ap.m2 * c->d;
+        x.slice_list = L + c->off_list[l]; x.n_slices = c->n_list[l];
+        x.slice_stride = c->N * c->d; x.kv_slice_stride = (int64_t)c->nb * ap.m2 * c->d;
+        x.nq = (int)c->band_n[l]; x.nk = c->n_c[l];
       }
+      HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));
     }
     tm.done("exchange");
   }

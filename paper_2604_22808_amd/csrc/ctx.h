@@ -197,18 +197,20 @@ struct AxisPassArgs {
 };
 hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st);
 
-struct GenericAttnArgs {
+// One branch of a generic attention launch (generic_attn.hip): query rows [0, nq) of every listed slice.
+struct GAttnSeg {
   const float* Q; const float* K; const float* V; float* O;
   const int32_t* slice_list; int n_slices;
-  int64_t slice_stride;     // elements between slices for Q/K/V/O
+  int64_t slice_stride;     // elements between slices for Q/O
   int64_t kv_slice_stride;  // elements between slices for K/V (differs from Q for the exchange)
-  int nq, nk, d;
+  int nq, nk;
   int mode;                 // 0 dense, 1 block list, 2 window
   const int32_t* row_ptr; const int32_t* col_idx; int block; int window;
   int residual;             // O = Q + attention (exchange)
-  float scale;
+  int rows, tiles, first_block;   // filled in by the launcher: query rows per workgroup, workgroups per slice, first workgroup
 };
-hipError_t launch_generic_attn(const GenericAttnArgs& a, hipStream_t st);
+struct GAttnArgs { GAttnSeg seg[NBMAX]; int nseg; int d; float scale; };
+hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st);
 
 hipError_t launch_pool_low(const void* spec, void* low, const int32_t* slice_list, int n_slices, int64_t N, int d,
                            int64_t n_low, int64_t nbar, int c, int is_half, hipStream_t st);

@@ -72,96 +72,6 @@ hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Attention of one query row per wave over a list of contiguous key ranges (sections 3.4.1-3.4.3, 3.6).
-// Lanes first take one key each (dot product over the channels), the wave does the running softmax, then lanes
-// take channels for the weighted sum of values.
-#define GATT_MAXC 4  // channels per lane: head_dim <= 256
-__global__ void __launch_bounds__(64) k_generic_attn(GenericAttnArgs a) {
-  __shared__ float qs[64 * GATT_MAXC];
-  const int lane = threadIdx.x;
-  const int64_t i = blockIdx.x;  // query row
-  const int slice = a.slice_list ? a.slice_list[blockIdx.y] : (int)blockIdx.y;
-  const float* Q = a.Q + (int64_t)slice * a.slice_stride;
-  const float* K = a.K + (int64_t)slice * a.kv_slice_stride;
-  const float* V = a.V + (int64_t)slice * a.kv_slice_stride;
-  float* O = a.O + (int64_t)slice * a.slice_stride;
-  const int d = a.d;
-  for (int c = lane; c < d; c += 64) qs[c] = Q[i * d + c];
-  __syncthreads();
-
-  float acc[GATT_MAXC];
-#pragma unroll
-  for (int u = 0; u < GATT_MAXC; ++u) acc[u] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  int n_ranges = 1, e0 = 0;
-  if (a.mode == 1) {
-    const int I = (int)(i / a.block);
-    e0 = a.row_ptr[I];
-    n_ranges = a.row_ptr[I + 1] - e0;
-  }
-  for (int rg = 0; rg < n_ranges; ++rg) {
-    int64_t k0, k1;
-    if (a.mode == 0) { k0 = 0; k1 = a.nk; }
-    else if (a.mode == 1) {
-      const int64_t J = a.col_idx[e0 + rg];
-      k0 = J * a.block;
-      k1 = k0 + a.block < a.nk ? k0 + a.block : a.nk;
-    } else {
-      k0 = i - a.window > 0 ? i - a.window : 0;
-      k1 = (i + a.window + 1 < a.nk) ? i + a.window + 1 : a.nk;
-    }
-    for (int64_t kb = k0; kb < k1; kb += 64) {
-      const int64_t key = kb + lane;
-      const bool valid = key < k1;
-      float s = -INFINITY;
-      if (valid) {
-        const float* kr = K + key * d;
-        float dot = 0.f;
-        for (int c = 0; c < d; ++c) dot = fmaf(qs[c], kr[c], dot);
-        s = dot * a.scale;
-      }
-      float mx = s;
-      for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      const float m_new = fmaxf(m_run, mx);
-      const float p = valid ? expf(s - m_new) : 0.f;
-      float ps = p;
-      for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-      const float alpha = (m_run == -INFINITY) ? 0.f : expf(m_run - m_new);
-      l_run = l_run * alpha + ps;
-      m_run = m_new;
-#pragma unroll
-      for (int u = 0; u < GATT_MAXC; ++u) acc[u] *= alpha;
-      const int cnt = (int)((k1 - kb) < 64 ? (k1 - kb) : 64);
-      for (int j = 0; j < cnt; ++j) {
-        const float pj = __shfl(p, j);
-        const float* vr = V + (kb + j) * d;
-#pragma unroll
-        for (int u = 0; u < GATT_MAXC; ++u) {
-          const int c = lane + 64 * u;
-          if (c < d) acc[u] = fmaf(pj, vr[c], acc[u]);
-        }
-      }
-    }
-  }
-  const float inv = 1.f / l_run;
-#pragma unroll
-  for (int u = 0; u < GATT_MAXC; ++u) {
-    const int c = lane + 64 * u;
-    if (c < d) {
-      float r = acc[u] * inv;
-      if (a.residual) r += qs[c];
-      O[i * d + c] = r;
-    }
-  }
-}
-
-hipError_t launch_generic_attn(const GenericAttnArgs& a, hipStream_t st) {
-  if (a.nq <= 0 || a.n_slices <= 0 || a.nk <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_generic_attn, dim3((unsigned)a.nq, (unsigned)a.n_slices), dim3(64), 0, st, a);
-  return hipGetLastError();
-}
-
 // Low-band compression (section 3.3): mean of c consecutive band rows.  T is float or fp16.
 template <typename T>
 __global__ void k_pool_low(const T* spec, T* low, const int32_t* slice_list, int64_t N, int d, int64_t n_low,

@@ -1,0 +1,40 @@
+"""The generic fp32 kernels at the edges of their tiles, against the fp64 oracle on whole forwards.
+
+Tolerance: 1e-5 (max-abs and relative L2) as for the fp32 configuration: sums of at most a few hundred terms of
+magnitude 1 in fp32 stay below 1e-6, the exponentials below 2e-7 relative."""
+import numpy as np
+import pytest
+
+from oracle import freqformer as O
+from paper_2604_22808_amd import binding as B
+from paper_2604_22808_amd import workloads as WL
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(grid, d, heads, alloc, dtype="f32", **band):
+    rng = np.random.default_rng(5)
+    cfgd = dict(WL.WORKLOADS["tiny_f32"].band, **band)
+    N = int(np.prod(grid))
+    q, k, v = (WL.round_to_io(0.7 * rng.standard_normal((1, heads, N, d)), dtype) for _ in range(3))
+    ctx = B.Context(1, heads, d, grid, B.F32 if dtype == "f32" else B.BF16, B.make_cfg(**cfgd), path=B.PATH_GENERIC)
+    got = U.run_forward(ctx, q, k, v, dtype, alloc)
+    want = O.forward(q, k, v, grid, O.BandConfig(**cfgd), alloc)
+    mx, rl = U.errors(got, want)
+    print(f"generic {grid} d={d} {dtype} {band}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    tol = (1e-5, 1e-5) if dtype == "f32" else U.TOL["bf16"]
+    assert mx <= tol[0] and rl <= tol[1], (mx, rl)
+
+
+@pytest.mark.parametrize("d", [1, 30, 32, 64, 100, 128, 132, 256])
+def test_generic_attention_head_dims(d):
+    """Head dimensions below, at and above each channel tile, multiples of four and not (unaligned rows)."""
+    _check((5, 9, 11), d, 2, (6, 7), mid_block=17, mid_stride=2, high_window=41, n_summary=5)
+
+
+@pytest.mark.parametrize("block,window,c", [(1, 0, 1), (15, 15, 3), (16, 31, 4), (32, 32, 7), (33, 64, 2), (64, 5000, 5)])
+def test_generic_attention_blocks_and_windows(block, window, c):
+    """Block edges around the 16- and 32-row query tiles and the 32-key tiles, windows of nothing and of everything, on a
+    grid large enough for the 32-row tiles (33 to 260 rows in the mid band, thousands in the high band)."""
+    _check((7, 24, 26), 64, 2, (7, 7), mid_block=block, mid_stride=3, high_window=window, n_summary=9, low_compress=c)
