@@ -40,7 +40,6 @@ static freqattn_status guarded(freqattn_ctx* c, const char* who, F&& body) {
 }
 
 static size_t esize(const Ctx& c) { return c.path == FREQATTN_PATH_MFMA ? sizeof(half_t) : sizeof(float); }
-static int io_kind(const Ctx& c) { return c.shape.dtype == FREQATTN_BF16 ? 1 : 0; }
 
 static bool mfma_shape_ok(const freqattn_shape& s, const freqattn_band_cfg& g) {
   auto ax = [](int n) { return n % 16 == 0 && n >= 16 && n <= 128; };
@@ -244,18 +243,19 @@ static hipError_t device_setup(freqattn_ctx* c, hipStream_t st) {
         A(dev_alloc(*c, &c->d_Ft16[a], (size_t)n * n));
         up(c->d_Ft16[a], ft16.data(), (size_t)n * n * sizeof(half_t));
       } else {
-        std::vector<float> f32((size_t)n * n), ft32((size_t)n * n);
+        const int P = (n + 15) / 16 * 16;   // padded with zeros to whole tiles of the axis pass
+        std::vector<float> f32((size_t)P * P, 0.f), ft32((size_t)P * P, 0.f);
         for (int k = 0; k < n; ++k)
           for (int j = 0; j < n; ++j) {
             const float fv = (float)F[(size_t)k * n + j];
-            f32[(size_t)k * n + j] = fv;
-            ft32[(size_t)j * n + k] = fv;
+            f32[(size_t)k * P + j] = fv;
+            ft32[(size_t)j * P + k] = fv;
             F[(size_t)k * n + j] = (double)fv;
           }
-        A(dev_alloc(*c, &c->d_F32[a], (size_t)n * n));
-        up(c->d_F32[a], f32.data(), (size_t)n * n * 4);
-        A(dev_alloc(*c, &c->d_Ft32[a], (size_t)n * n));
-        up(c->d_Ft32[a], ft32.data(), (size_t)n * n * 4);
+        A(dev_alloc(*c, &c->d_F32[a], (size_t)P * P));
+        up(c->d_F32[a], f32.data(), (size_t)P * P * 4);
+        A(dev_alloc(*c, &c->d_Ft32[a], (size_t)P * P));
+        up(c->d_Ft32[a], ft32.data(), (size_t)P * P * 4);
       }
     }
   }
@@ -768,25 +768,40 @@ static hipError_t inverse_transform_mfma(Ctx& c, void* out, const void* v_in, hi
   return launch_mfma_dct_pass(w, c.num_cu, st);
 }
 
-// Forward transform of one [slices, N, d] tensor into a band-major spectral buffer (sections 3.2, 3.3).
-static hipError_t forward_transform(Ctx& c, const void* x, void* spec, hipStream_t st, int energy_slot = -1) {
-  const int T = c.shape.T, H = c.shape.H, W = c.shape.W, d = c.d;
-  hipError_t e;
-  if (c.path == FREQATTN_PATH_MFMA) {
-    const int full[3] = {T, H, W};
-    return forward_transform_mfma(c, x, spec, st, nullptr, c.slices, full, energy_slot, -1);
-  }
+// One pass of the generic path along axis `ax` (0 T, 1 H, 2 W) of whole [slices, N, d] tensors.
+static AxisPassArgs generic_pass(const Ctx& c, int ax, bool inverse) {
+  const int dims[3] = {c.shape.T, c.shape.H, c.shape.W};
   AxisPassArgs a{};
-  a.Ntok = c.N; a.slice_mod = c.slices;
-  a.in = x; a.out = c.tmp0; a.M = c.d_F32[0]; a.n = a.n_out = T; a.inner = (int64_t)H * W * d; a.outer = 1;
-  a.nslab = c.slices; a.in_kind = io_kind(c); a.out_kind = 0;
-  if ((e = launch_generic_axis_pass(a, st)) != hipSuccess) return e;
-  a.in = c.tmp0; a.out = c.tmp1; a.M = c.d_F32[1]; a.n = a.n_out = H; a.inner = (int64_t)W * d; a.outer = T;
-  a.nslab = (int64_t)c.slices * T; a.in_kind = 0;
-  if ((e = launch_generic_axis_pass(a, st)) != hipSuccess) return e;
-  a.in = c.tmp1; a.out = spec; a.M = c.d_F32[2]; a.n = a.n_out = W; a.inner = d; a.outer = (int64_t)T * H;
-  a.nslab = (int64_t)c.slices * T * H; a.perm_out = c.d_perm;
-  return launch_generic_axis_pass(a, st);
+  a.Ntok = c.N; a.d = c.d;
+  a.n = a.n_out = dims[ax]; a.ldm = (dims[ax] + 15) / 16 * 16;
+  a.M = inverse ? c.d_Ft32[ax] : c.d_F32[ax];
+  a.inner = c.d; a.outer = 1;
+  for (int i = ax + 1; i < 3; ++i) a.inner *= dims[i];
+  for (int i = 0; i < ax; ++i) a.outer *= dims[i];
+  a.nslab = (int64_t)c.slices * a.outer;
+  return a;
+}
+
+// Generic path: Q, K and V [slices, N, d] into the band-major spectral buffers (sections 3.2, 3.3), T axis, H axis, then
+// the W axis, which scatters.  The three tensors share every launch: the T pass leaves its results in the spectral
+// buffers themselves, the H pass in the scratch that is free until the inverse transform (tmp0, tmp1, Y).
+static hipError_t forward_transform_generic(Ctx& c, const void* q, const void* k, const void* v, hipStream_t st) {
+  const void* in[3] = {q, k, v};
+  void* spec[3] = {c.specQ, c.specK, c.specV};
+  void* mid[3] = {c.tmp0, c.tmp1, c.Y};
+  AxisPassArgs t = generic_pass(c, 0, false), h = generic_pass(c, 1, false), w = generic_pass(c, 2, false);
+  t.n_tensors = h.n_tensors = w.n_tensors = 3;
+  for (int i = 0; i < 3; ++i) {
+    t.in[i] = in[i]; t.out[i] = spec[i];
+    h.in[i] = spec[i]; h.out[i] = mid[i];
+    w.in[i] = mid[i]; w.out[i] = spec[i];
+  }
+  t.in_bf16 = c.shape.dtype == FREQATTN_BF16;
+  w.perm_out = c.d_perm;
+  hipError_t e;
+  if ((e = launch_generic_axis_pass(t, st)) != hipSuccess) return e;
+  if ((e = launch_generic_axis_pass(h, st)) != hipSuccess) return e;
+  return launch_generic_axis_pass(w, st);
 }
 
 // Inverse transform (section 3.7): rows of band l of slice s are read from Y when the band is active for s, else
@@ -810,20 +825,16 @@ static hipError_t inverse_transform(Ctx& c, void* out, const void* v_in, hipStre
     if ((e = inverse_transform_mfma(c, out, v_in, st, L + c.off_cls[2], c.n_cls[2], full, false)) != hipSuccess) return e;
     return launch_copy_slices(v_in, out, L + c.off_cls[3], c.n_cls[3], c.N * c.d * 2, st);
   }
-  AxisPassArgs a{};
-  a.Ntok = c.N; a.slice_mod = c.slices;
-  a.in = c.Y; a.in_alt = c.specV; a.masks = masks; a.band_off1 = (int32_t)c.band_off[1];
-  a.band_off2 = (int32_t)c.band_off[2]; a.band_off3 = (int32_t)(c.nb > 3 ? c.band_off[3] : c.N); a.perm_in = c.d_perm;
-  a.out = c.tmp0; a.M = c.d_Ft32[2]; a.n = a.n_out = W; a.inner = d; a.outer = (int64_t)T * H;
-  a.nslab = (int64_t)c.slices * T * H; a.in_kind = 0; a.out_kind = 0;
-  if ((e = launch_generic_axis_pass(a, st)) != hipSuccess) return e;
-  a.perm_in = nullptr; a.masks = nullptr; a.in_alt = nullptr;
-  a.in = c.tmp0; a.out = c.tmp1; a.M = c.d_Ft32[1]; a.n = a.n_out = H; a.inner = (int64_t)W * d; a.outer = T;
-  a.nslab = (int64_t)c.slices * T;
-  if ((e = launch_generic_axis_pass(a, st)) != hipSuccess) return e;
-  a.in = c.tmp1; a.out = out; a.M = c.d_Ft32[0]; a.n = a.n_out = T; a.inner = (int64_t)H * W * d; a.outer = 1;
-  a.nslab = c.slices; a.out_kind = io_kind(c);
-  return launch_generic_axis_pass(a, st);
+  AxisPassArgs w = generic_pass(c, 2, true), h = generic_pass(c, 1, true), t = generic_pass(c, 0, true);
+  w.n_tensors = h.n_tensors = t.n_tensors = 1;
+  w.in[0] = c.Y; w.in_alt = c.specV; w.masks = masks; w.perm_in = c.d_perm; w.out[0] = c.tmp0;
+  w.band_off1 = (int32_t)c.band_off[1]; w.band_off2 = (int32_t)c.band_off[2];
+  w.band_off3 = (int32_t)(c.nb > 3 ? c.band_off[3] : c.N);
+  h.in[0] = c.tmp0; h.out[0] = c.tmp1;
+  t.in[0] = c.tmp1; t.out[0] = out; t.out_bf16 = c.shape.dtype == FREQATTN_BF16;
+  if ((e = launch_generic_axis_pass(w, st)) != hipSuccess) return e;
+  if ((e = launch_generic_axis_pass(h, st)) != hipSuccess) return e;
+  return launch_generic_axis_pass(t, st);
 }
 
 static void fill_attn_params(const Ctx& c, AttnParams& p, float scale) {
@@ -934,9 +945,7 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
     return FREQATTN_OK;
   }
   c->v_full.assign((size_t)c->slices, 1);
-  HIP_TRY(c, forward_transform(*c, q, c->specQ, st));
-  HIP_TRY(c, forward_transform(*c, k, c->specK, st));
-  HIP_TRY(c, forward_transform(*c, v, c->specV, st));
+  HIP_TRY(c, forward_transform_generic(*c, q, k, v, st));
   if (with_stats)
     HIP_TRY(c, launch_band_energy(c->specQ, c->specK, c->specV, c->d_stats, c->slices, c->N, c->d, c->band_off, c->band_n,
                                   0, st));

@@ -84,7 +84,7 @@ struct Ctx {
   int32_t* d_col_idx = nullptr;
   int32_t* d_row_ptr2 = nullptr;
   int32_t* d_col_idx2 = nullptr;
-  float* d_F32[3] = {nullptr, nullptr, nullptr};    // F  [n][n] fp32 (generic path)
+  float* d_F32[3] = {nullptr, nullptr, nullptr};    // F fp32 (generic path), rows and columns padded to multiples of 16 with zeros
   float* d_Ft32[3] = {nullptr, nullptr, nullptr};   // F^T
   half_t* d_F16[3] = {nullptr, nullptr, nullptr};   // F  fp16 (MFMA path)
   half_t* d_Ft16[3] = {nullptr, nullptr, nullptr};  // F^T fp16
@@ -180,20 +180,20 @@ void build_summary_weights(const Ctx& c, int band, std::vector<float>& out);   /
 void pack_vsum_weights(const std::vector<float>& w, int m, int64_t N, std::vector<uint16_t>& out);  // bf16 [N/64][64][64], see mfma_vsum.hip
 
 // ---- generic fp32 kernels (generic_kernels.hip) -----------------------------------------------------------------
-struct AxisPassArgs {
-  const void* in; void* out;
-  const float* M;           // [n_out][n]: out[k] = sum_j M[k][j] in[j]
-  int n, n_out;
+struct AxisPassArgs {      // (generic_axis.hip)
+  const void* in[3]; void* out[3]; int n_tensors;   // Q, K, V go through one launch
+  const float* M;           // [ldm][ldm], zero outside [n_out][n]: out[k] = sum_j M[k][j] in[j]
+  int n, n_out, ldm;        // ldm a multiple of 16, >= n and n_out
   int64_t inner, outer;     // element index ((s*n + j)*inner + i), s in [0, nslab), slab s belongs to slice s/outer
   int64_t nslab;
   const int32_t* perm_in;   // when set (axis W only, inner == d): input row of token (s%outer)*n + j is perm[token]
   const int32_t* perm_out;  // same for output rows
   int64_t Ntok;
+  int d;
   // input source selection per band for the first inverse pass (perm_in set): rows of band l of slice hb come from
   // `in` when bit l of masks[hb] is set, else from `in_alt`.
   const void* in_alt; const int32_t* masks; int32_t band_off1, band_off2, band_off3;   // first rows of bands 1, 2, 3 (band_off3 = Ntok without a fourth band)
-  int in_kind, out_kind;    // 0 float, 1 bf16, 2 fp16
-  int slice_mod;            // number of slices the masks array covers (slab slice index is taken modulo this)
+  int in_bf16, out_bf16;    // element type: bf16 when set, else fp32
 };
 hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st);
 

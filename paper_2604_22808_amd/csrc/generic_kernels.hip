@@ -8,70 +8,6 @@
 
 namespace fa {
 
-__device__ __forceinline__ float bf16_to_f32(uint16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {  // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float load_as_f32(const void* p, int64_t i, int kind) {
-  if (kind == 0) return ((const float*)p)[i];
-  if (kind == 1) return bf16_to_f32(((const uint16_t*)p)[i]);
-  return (float)((const half_t*)p)[i];
-}
-__device__ __forceinline__ void store_from_f32(void* p, int64_t i, float v, int kind) {
-  if (kind == 0) ((float*)p)[i] = v;
-  else if (kind == 1) ((uint16_t*)p)[i] = f32_to_bf16(v);
-  else ((half_t*)p)[i] = (half_t)v;
-}
-
-// One 1-D transform along one grid axis (section 3.2 / 3.7): out[s, k, i] = sum_j M[k][j] in[s, j, i].
-// One thread per output element.  With perm_in / perm_out the rows of the W-axis pass are looked up in the
-// band-major order (section 3.3), and with masks set the row's source buffer is chosen per band (section 3.7:
-// bands that were not processed contribute V~ unchanged).
-__global__ void k_axis_pass(AxisPassArgs a, int64_t total) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int64_t i = idx % a.inner;
-  const int64_t r = idx / a.inner;
-  const int k = (int)(r % a.n_out);
-  const int64_t s = r / a.n_out;
-  const int64_t slice = s / a.outer;
-  const int64_t o = s % a.outer;
-  const float* Mrow = a.M + (int64_t)k * a.n;
-  float acc = 0.f;
-  for (int j = 0; j < a.n; ++j) {
-    int64_t e;
-    const void* src = a.in;
-    if (a.perm_in) {
-      const int32_t row = a.perm_in[o * a.n + j];
-      if (a.masks) {
-        const int band = row < a.band_off1 ? 0 : (row < a.band_off2 ? 1 : (row < a.band_off3 ? 2 : 3));
-        if (!((a.masks[slice % a.slice_mod] >> band) & 1)) src = a.in_alt;
-      }
-      e = (slice * a.Ntok + row) * a.inner + i;
-    } else {
-      e = (s * a.n + j) * a.inner + i;
-    }
-    acc = fmaf(Mrow[j], load_as_f32(src, e, a.in_kind), acc);
-  }
-  int64_t eo;
-  if (a.perm_out) eo = (slice * a.Ntok + a.perm_out[o * a.n_out + k]) * a.inner + i;
-  else eo = (s * a.n_out + k) * a.inner + i;
-  store_from_f32(a.out, eo, acc, a.out_kind);
-}
-
-hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st) {
-  const int64_t total = a.nslab * a.n_out * a.inner;
-  if (total == 0) return hipSuccess;
-  const int bs = 256;
-  const int64_t nb = (total + bs - 1) / bs;
-  hipLaunchKernelGGL(k_axis_pass, dim3((unsigned)nb), dim3(bs), 0, st, a, total);
-  return hipGetLastError();
-}
-
 // Low-band compression (section 3.3): mean of c consecutive band rows.  T is float or fp16.
 template <typename T>
 __global__ void k_pool_low(const T* spec, T* low, const int32_t* slice_list, int64_t N, int d, int64_t n_low,

@@ -38,3 +38,11 @@ def test_generic_attention_blocks_and_windows(block, window, c):
     """Block edges around the 16- and 32-row query tiles and the 32-key tiles, windows of nothing and of everything, on a
     grid large enough for the 32-row tiles (33 to 260 rows in the mid band, thousands in the high band)."""
     _check((7, 24, 26), 64, 2, (7, 7), mid_block=block, mid_stride=3, high_window=window, n_summary=9, low_compress=c)
+
+
+@pytest.mark.parametrize("grid,d,dtype", [((1, 15, 16), 4, "f32"), ((17, 3, 31), 6, "bf16"), ((2, 64, 65), 12, "f32"),
+                                          ((130, 5, 4), 20, "bf16"), ((3, 4, 200), 33, "f32")])
+def test_generic_axis_lengths(grid, d, dtype):
+    """Axis lengths around the 16-row steps and the 64-row groups of an axis pass, beyond two groups, and head dimensions
+    that are no multiple of the 4 (unaligned) or 64 (several slabs per wave) adjacent columns."""
+    _check(grid, d, 3, (0, 5, 7), dtype, n_summary=3)
