@@ -80,8 +80,8 @@ static void free_all(Ctx* c) {
   F(c->d_perm); F(c->d_perm_t); F(c->d_row_ptr); F(c->d_col_idx); F(c->d_row_ptr2); F(c->d_col_idx2);
   for (int a = 0; a < 3; ++a) { F(c->d_F32[a]); F(c->d_Ft32[a]); F(c->d_F16[a]); F(c->d_Ft16[a]); }
   F(c->specQ); F(c->specK); F(c->specV); F(c->Y); F(c->tmp0); F(c->tmp1);
-  F(c->lowQ); F(c->lowK); F(c->lowV); F(c->lowY); F(c->Cbuf); F(c->d_stats); F(c->d_range_flag); F(c->d_lists); F(c->d_energy_part);
-  F(c->d_tot_part); F(c->d_wsum); F(c->d_vsum_part); F(c->d_pool_part);
+  F(c->lowQ); F(c->lowK); F(c->lowV); F(c->Cbuf); F(c->d_stats); F(c->d_range_flag); F(c->d_lists); F(c->d_energy_part);
+  F(c->d_tot_part); F(c->d_wsum); F(c->d_vsum_part);
   F(c->projX); F(c->projZ); F(c->projWq); F(c->projWk); F(c->projWv); F(c->projWo); F(c->proj_ones);
   F(c->projWvN); F(c->projM); F(c->projPool); F(c->projCtmp);
   F(c->d_gemm_prob); F(c->d_gemm_seg);
@@ -272,13 +272,11 @@ static hipError_t device_setup(freqattn_ctx* c, hipStream_t st) {
   A(dev_alloc_bytes(*c, &c->lowQ, lowb));
   A(dev_alloc_bytes(*c, &c->lowK, lowb));
   A(dev_alloc_bytes(*c, &c->lowV, lowb));
-  A(dev_alloc_bytes(*c, &c->lowY, lowb));
   A(dev_alloc_bytes(*c, &c->Cbuf, (size_t)c->slices * c->nb * (c->nb - 1) * (size_t)std::max(g.n_summary, 1) * c->d * es));
   const size_t stats_floats = (size_t)3 * c->d * (1 + 64);
   A(dev_alloc(*c, &c->d_stats, stats_floats));
   A(dev_alloc(*c, &c->d_range_flag, 64));
   if (e == hipSuccess) e = launch_fill_zero((float*)c->d_range_flag, 64, st);   // (a zero float is a zero int)
-  if (mf && g.n_summary > 0 && g.n_summary < 64) A(dev_alloc(*c, &c->d_pool_part, (size_t)c->slices * c->nb * 128 * c->d));
   // (partial sums of the router statistics: the routed entry points do not run on an arena context)
   if (mf && !arena) A(dev_alloc(*c, &c->d_energy_part, (size_t)6 * DCT_MAX_WAVES * 3 * 64));
   if (mf && !arena) A(dev_alloc(*c, &c->d_tot_part, (size_t)3 * DCT_MAX_WAVES * 64));
@@ -840,7 +838,7 @@ static hipError_t inverse_transform(Ctx& c, void* out, const void* v_in, hipStre
 static void fill_attn_params(const Ctx& c, AttnParams& p, float scale) {
   std::memset(&p, 0, sizeof(p));
   p.specQ = c.specQ; p.specK = c.specK; p.specV = c.specV; p.Y = c.Y;
-  p.lowQ = c.lowQ; p.lowK = c.lowK; p.lowV = c.lowV; p.lowY = c.lowY; p.C = c.Cbuf;
+  p.lowQ = c.lowQ; p.lowK = c.lowK; p.lowV = c.lowV; p.low_c = c.cfg.low_compress; p.C = c.Cbuf;
   p.mid_row_ptr = c.d_row_ptr; p.mid_col_idx = c.d_col_idx;
   p.mid2_row_ptr = c.d_row_ptr2; p.mid2_col_idx = c.d_col_idx2;
   p.nb = c.nb;
@@ -985,28 +983,21 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
   const bool mf = c->path == FREQATTN_PATH_MFMA;
   const int is_half = mf ? 1 : 0;
   const int32_t* L = c->d_lists;
-  // section 3.3: compression of the low band
-  if (c->n_list[LOW] > 0) {
-    const int32_t* lst = L + c->off_list[LOW];
-    HIP_TRY(c, launch_pool_low(c->specQ, c->lowQ, lst, c->n_list[LOW], c->N, c->d, c->band_n[LOW], c->nbar, c->cfg.low_compress, is_half, st));
-    HIP_TRY(c, launch_pool_low(c->specK, c->lowK, lst, c->n_list[LOW], c->N, c->d, c->band_n[LOW], c->nbar, c->cfg.low_compress, is_half, st));
-    HIP_TRY(c, launch_pool_low(c->specV, c->lowV, lst, c->n_list[LOW], c->N, c->d, c->band_n[LOW], c->nbar, c->cfg.low_compress, is_half, st));
-  }
-  tm.done("low_compress");
-
   // section 3.6, first half: summary tokens.  Band l of a slice is summarised only if another band of the slice is active
   // (the exchange of that band is the only reader).  For slices that do not run the high band (their V~ may stop at the
   // low+mid box) the high band's summaries are summed from V instead of pooled - by the allocation alone, also where V~
   // happens to exist on the whole grid: the result must not depend on a prediction.
-  // which = 0: every band; 1: only bands the slice passes through (pooled from V~: can run before the band operators);
+  // which = -1: none; 0: every band; 1: only bands the slice passes through (pooled from V~: can run before the band operators);
   // 2: only bands the slice runs (pooled from the band outputs).
   AttnParams ap;
   fill_attn_params(*c, ap, scale);
-  auto summaries = [&](int which) -> freqattn_status {
+  // The compression of the low band (section 3.3) rides in the launch of the first call (compress = true).
+  auto summaries = [&](int which, bool compress) -> freqattn_status {
     uint64_t skip[NBMAX][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}}, sel[4] = {0, 0, 0, 0};
     const int all_bands = (1 << c->nb) - 1;
-    int nsel = 0, npool = 0;
-    if (c->slices <= 256) {
+    int nsel = 0, npool = 0, pooled_bands = 0;   // slices for launch_vsum, (slice, band) pairs to pool and their bands
+    if (which < 0) {
+    } else if (c->slices <= 256) {
       for (int s = 0; s < c->slices; ++s) {
         const int mask = c->h_alloc[(size_t)(s % c->shape.heads)];
         for (int l = 0; l < c->nb; ++l) {
@@ -1018,14 +1009,27 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
             if (mask != 0 && which != 2) { sel[s >> 6] |= 1ull << (s & 63); ++nsel; }
           }
           if (skp) skip[l][s >> 6] |= 1ull << (s & 63);
-          else ++npool;
+          else { ++npool; pooled_bands |= 1 << l; }
         }
       }
     } else {
-      npool = 1;
+      npool = c->slices * c->nb;
+      pooled_bands = (1 << c->nb) - 1;
     }
-    if (npool > 0)
-      HIP_TRY(c, launch_summaries(c->Y, c->specV, c->Cbuf, L + c->off_masks, c->slices, c->N, c->d, c->nb, c->band_off, c->band_n, c->m_eff, ap.m2, is_half, &skip[0][0], c->d_pool_part, st));
+    PoolArgs p{};
+    const void* spec[3] = {c->specQ, c->specK, c->specV};
+    void* low[3] = {c->lowQ, c->lowK, c->lowV};
+    for (int i = 0; i < 3; ++i) { p.spec[i] = spec[i]; p.low[i] = low[i]; }
+    p.low_list = L + c->off_list[LOW];
+    p.n_low_slices = compress ? c->n_list[LOW] : 0;
+    p.n_low = c->band_n[LOW]; p.nbar = c->nbar; p.c = c->cfg.low_compress;
+    p.pool = npool > 0 && which >= 0;
+    p.Y = c->Y; p.V = c->specV; p.C = c->Cbuf; p.masks = L + c->off_masks; p.slices = c->slices; p.nb = c->nb;
+    p.band_off = c->band_off; p.band_n = c->band_n; p.m_eff = c->m_eff; p.m2rows = ap.m2;
+    p.skip_bits = c->slices <= 256 ? &skip[0][0] : nullptr;
+    p.part = (float*)c->tmp0; p.part_floats = (int64_t)(c->slices * c->N * c->d * (int64_t)esize(*c) / 4);   // (free between the transforms)
+    p.N = c->N; p.d = c->d; p.is_half = is_half; p.n_pooled = npool; p.pooled_bands = pooled_bands; p.num_cu = c->num_cu;
+    HIP_TRY(c, launch_band_pools(p, st));
     if (nsel > 0) {
       int nsplit = std::max(1, c->vsum_nsplit / nsel);   // nsel * nsplit <= 2 CUs' worth + nsel, what the scratch holds
       nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(nsplit, c->N / 64 / 8));   // at least eight tiles per range
@@ -1034,12 +1038,13 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
     return FREQATTN_OK;
   };
   // Slices that run a single band carry its exchange inside the band items (see build_lists): the summary tokens of
-  // the bands they pass through are needed before the launch.
-  const bool split_summaries = mf && c->exchange_fusion && c->cfg.n_summary > 0 && c->slices <= 256;
-  if (split_summaries) {
-    freqattn_status fs = summaries(1);
+  // the bands they pass through are needed before the launch.  (Beyond 256 slices the bookkeeping above does not reach:
+  // every band is summarised after the band operators.)
+  const bool split_summaries = c->cfg.n_summary > 0 && c->slices <= 256;
+  {
+    freqattn_status fs = summaries(split_summaries ? 1 : -1, true);
     if (fs != FREQATTN_OK) return fs;
-    tm.done("summaries");
+    tm.done(split_summaries ? "low_compress_summaries" : "low_compress");
   }
 
   // section 3.4: the three band operators
@@ -1065,27 +1070,24 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
       GAttnSeg& s = g.seg[g.nseg++];
       s.slice_list = L + c->off_list[l]; s.n_slices = c->n_list[l];
       if (l == LOW) {
-        s.Q = (const float*)c->lowQ; s.K = (const float*)c->lowK; s.V = (const float*)c->lowV; s.O = (float*)c->lowY;
-        s.slice_stride = s.kv_slice_stride = c->nbar * c->d; s.nq = s.nk = (int)c->nbar; s.mode = 0;
+        s.Q = (const float*)c->lowQ; s.K = (const float*)c->lowK; s.V = (const float*)c->lowV; s.O = (float*)c->Y;
+        s.slice_stride = s.kv_slice_stride = c->nbar * c->d; s.o_slice_stride = Nd; s.nq = s.nk = (int)c->nbar; s.mode = 0;
+        s.rep = c->cfg.low_compress; s.n_out = (int)c->band_n[LOW];
         continue;
       }
       const int64_t o = c->band_off[l] * c->d;
       s.Q = (const float*)c->specQ + o; s.K = (const float*)c->specK + o; s.V = (const float*)c->specV + o; s.O = (float*)c->Y + o;
-      s.slice_stride = s.kv_slice_stride = Nd; s.nq = s.nk = (int)c->band_n[l];
+      s.slice_stride = s.kv_slice_stride = s.o_slice_stride = Nd; s.nq = s.nk = s.n_out = (int)c->band_n[l]; s.rep = 1;
       s.mode = l == HIGH ? 2 : 1; s.window = c->cfg.high_window; s.block = c->cfg.mid_block;
       s.row_ptr = l == MID2 ? c->d_row_ptr2 : c->d_row_ptr; s.col_idx = l == MID2 ? c->d_col_idx2 : c->d_col_idx;
     }
     HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));
     tm.done("band_attention_fused");
   }
-  if (c->n_list[LOW] > 0)
-    HIP_TRY(c, launch_expand_low(c->lowY, c->Y, L + c->off_list[LOW], c->n_list[LOW], c->N, c->d, c->band_n[LOW], c->nbar, c->cfg.low_compress, is_half, st));
-  tm.done("low_expand");
-
   // section 3.6: remaining summary tokens (of the bands a slice runs, from the band outputs), then the exchange of
   // the slices that run more than one band
   if (c->cfg.n_summary > 0) {
-    freqattn_status fs = summaries(split_summaries ? 2 : 0);
+    freqattn_status fs = summaries(split_summaries ? 2 : 0, false);
     if (fs != FREQATTN_OK) return fs;
     tm.done(split_summaries ? "summaries_active" : "summaries");
     if (mf) {
@@ -1100,7 +1102,7 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
         x.Q = (const float*)c->Y + c->band_off[l] * c->d; x.O = (float*)c->Y + c->band_off[l] * c->d;
         x.K = x.V = (const float*)c->Cbuf + (int64_t)l * ap.m2 * c->d;
         x.slice_list = L + c->off_list[l]; x.n_slices = c->n_list[l];
-        x.slice_stride = c->N * c->d; x.kv_slice_stride = (int64_t)c->nb * ap.m2 * c->d;
+        x.slice_stride = x.o_slice_stride = c->N * c->d; x.rep = 1; x.n_out = (int)c->band_n[l]; x.kv_slice_stride = (int64_t)c->nb * ap.m2 * c->d;
         x.nq = (int)c->band_n[l]; x.nk = c->n_c[l];
       }
       HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));

@@ -32,7 +32,6 @@ struct AttnParams {
   const void* lowQ;   // [slices][nbar][d] compressed low band
   const void* lowK;
   const void* lowV;
-  void* lowY;
   const void* C;      // [slices][nb][(nb-1) m][d] summary tokens seen by band l
   const int32_t* mid_row_ptr;
   const int32_t* mid_col_idx;
@@ -42,6 +41,7 @@ struct AttnParams {
   int32_t band_n[NBMAX];
   int32_t n_c[NBMAX]; // valid rows of C per band
   int32_t nb;         // bands: 3 or 4
+  int32_t low_c;      // compression factor c: every low-band row takes its group's output
   int32_t N, d, nbar, m2;  // m2 = (nb-1) m = rows reserved per band in C
   int32_t mid_block, high_window;
   float scale;
@@ -92,7 +92,7 @@ struct Ctx {
   // device scratch (element type float on the generic path, fp16 on the MFMA path)
   void* specQ = nullptr; void* specK = nullptr; void* specV = nullptr; void* Y = nullptr;
   void* tmp0 = nullptr; void* tmp1 = nullptr;     // transform ping-pong, 3*slices*N*d
-  void* lowQ = nullptr; void* lowK = nullptr; void* lowV = nullptr; void* lowY = nullptr;
+  void* lowQ = nullptr; void* lowK = nullptr; void* lowV = nullptr;
   void* Cbuf = nullptr;
   int32_t* d_range_flag = nullptr;                // set by the scattering transform passes when a coefficient leaves the fp16 range (sticky)
   float* d_stats = nullptr;                       // router statistics [3][d] (+ partial sums of the generic kernel)
@@ -122,7 +122,6 @@ struct Ctx {
   bool v_box_ok = false;              // the context can do it: summary weights built, or no summaries configured
   uint16_t* d_wsum = nullptr;         // bf16 [N/64][64][64]
   float* d_vsum_part = nullptr;       // [slices][vsum_parts][d][64] partial sums
-  float* d_pool_part = nullptr;       // [slices][3][128][d]: partial sums of the pooling when chunks are cut into row ranges (m < 64)
   int vsum_nsplit = 0;
   std::vector<char> v_full;           // per slice: the current forward computed V~ on the whole grid
   size_t off_items = 0;               // AttnItem array (fused order: all branches), then exchange items
@@ -201,27 +200,38 @@ hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st);
 struct GAttnSeg {
   const float* Q; const float* K; const float* V; float* O;
   const int32_t* slice_list; int n_slices;
-  int64_t slice_stride;     // elements between slices for Q/O
+  int64_t slice_stride, o_slice_stride;   // elements between slices for Q / O
   int64_t kv_slice_stride;  // elements between slices for K/V (differs from Q for the exchange)
   int nq, nk;
   int mode;                 // 0 dense, 1 block list, 2 window
   const int32_t* row_ptr; const int32_t* col_idx; int block; int window;
   int residual;             // O = Q + attention (exchange)
+  int rep, n_out;           // query row i is written to output rows i rep .. i rep + rep - 1 below n_out (low band: its whole group)
   int rows, tiles, first_block;   // filled in by the launcher: query rows per workgroup, workgroups per slice, first workgroup
 };
 struct GAttnArgs { GAttnSeg seg[NBMAX]; int nseg; int d; float scale; };
 hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st);
 
-hipError_t launch_pool_low(const void* spec, void* low, const int32_t* slice_list, int n_slices, int64_t N, int d,
-                           int64_t n_low, int64_t nbar, int c, int is_half, hipStream_t st);
-hipError_t launch_expand_low(const void* lowY, void* Y, const int32_t* slice_list, int n_slices, int64_t N, int d,
-                             int64_t n_low, int64_t nbar, int c, int is_half, hipStream_t st);
-// Summary tokens of all bands of all slices, written into the C slots of the two other bands.
-// skip_bits[l][..]: bit s set = band l of slice s is not pooled here (no active band of the slice looks at it, or - high
-// band only - its V~ rows do not exist and launch_vsum supplies it).
-hipError_t launch_summaries(const void* Y, const void* V, void* C, const int32_t* masks, int slices, int64_t N, int d,
-                            int nb, const int64_t band_off[NBMAX], const int64_t band_n[NBMAX], const int m_eff[NBMAX], int m2, int is_half,
-                            const uint64_t* skip_bits /*[NBMAX][4] or NULL*/, float* split_part /*[slices][nb][128][d] or NULL*/, hipStream_t st);
+// Low-band compression of Q~, K~ and V~ for the slices in low_list, and summary tokens of the bands of all slices, written
+// into the C slots of the other bands: one launch (pool = false: the compression alone, n_low_slices = 0: the
+// summaries alone).
+struct PoolArgs {
+  const void* spec[3]; void* low[3];
+  const int32_t* low_list; int n_low_slices;
+  int64_t n_low, nbar; int c;
+  bool pool;
+  const void* Y; const void* V; void* C;
+  const int32_t* masks; int slices, nb;
+  const int64_t* band_off; const int64_t* band_n; const int* m_eff;
+  int m2rows;
+  // [NBMAX][4]: bit s of row l set = band l of slice s is not pooled here (no active band of the slice looks at it, or -
+  // high band only - its V~ rows do not exist and launch_vsum supplies it); NULL: every band of every slice
+  const uint64_t* skip_bits;
+  float* part; int64_t part_floats;   // scratch for chunks that are cut into parts
+  int n_pooled, pooled_bands;         // (slice, band) pairs pooled here, the bands among them (bits)
+  int64_t N; int d, is_half, num_cu;
+};
+hipError_t launch_band_pools(const PoolArgs& p, hipStream_t st);
 // High-band summary tokens of the slices in `sel` (bit set, nsel of them) from the untransformed bf16 V.
 hipError_t launch_vsum(const void* V, const void* Wsum, float* part, void* C, const uint64_t sel[4], int nsel, int64_t N,
                        int d, int nsplit, int64_t n_high, const int m_eff[NBMAX], int m2rows, hipStream_t st);   // (three-band contexts only)

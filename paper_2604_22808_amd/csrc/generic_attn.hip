@@ -45,7 +45,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
   const float* Q = s.Q + (int64_t)slice * s.slice_stride;
   const float* K = s.K + (int64_t)slice * s.kv_slice_stride;
   const float* V = s.V + (int64_t)slice * s.kv_slice_stride;
-  float* O = s.O + (int64_t)slice * s.slice_stride;
+  float* O = s.O + (int64_t)slice * s.o_slice_stride;
 
   // query rows [q0, qend), keys j = 0 .. nkeys - 1 of the rows' own numbering
   int q0, qend, e0 = 0, k0 = 0, nkeys;
@@ -203,14 +203,17 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
       o += f * *(const float4v*)(lds + (w * ROWS + row) * LROW + ch);
     }
     o *= 1.f / l;
-    const int64_t at = (int64_t)(q0 + row) * d + ch;
-    if (s.residual) o += row4<EXACT>(Q + at - ch, ch, d);
-    if (EXACT) {
-      *(float4v*)(O + at) = o;
-    } else {
+    const int64_t q = q0 + row;
+    if (s.residual) o += row4<EXACT>(Q + q * d, ch, d);
+    for (int64_t r = q * s.rep; r < min((q + 1) * s.rep, (int64_t)s.n_out); ++r) {
+      float* dst = O + r * d + ch;
+      if (EXACT) {
+        *(float4v*)dst = o;
+      } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (ch + i < d) O[at + i] = o[i];
+        for (int i = 0; i < 4; ++i)
+          if (ch + i < d) dst[i] = o[i];
+      }
     }
   }
 }

@@ -1,5 +1,4 @@
-// Generic kernels of libfreqattn: plain fp32 arithmetic for any shape (the fp32 configuration and every shape the
-// MFMA kernels do not cover), plus the small helper kernels both paths share (pooling, summaries, band energy).
+// Small helper kernels both paths share: pooling, summaries, band energy, copies, conversions.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -8,68 +7,6 @@
 
 namespace fa {
 
-// Low-band compression (section 3.3): mean of c consecutive band rows.  T is float or fp16.
-template <typename T>
-__global__ void k_pool_low(const T* spec, T* low, const int32_t* slice_list, int64_t N, int d, int64_t n_low,
-                           int64_t nbar, int c, int64_t total) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int ch = (int)(idx % d);
-  const int64_t j = (idx / d) % nbar;
-  const int li = (int)(idx / ((int64_t)d * nbar));
-  const int slice = slice_list[li];
-  const int64_t r0 = j * c;
-  const int64_t r1 = r0 + c < n_low ? r0 + c : n_low;
-  float s = 0.f;
-  for (int64_t r = r0; r < r1; ++r) s += (float)spec[((int64_t)slice * N + r) * d + ch];
-  low[((int64_t)slice * nbar + j) * d + ch] = (T)(s / (float)(r1 - r0));
-}
-
-hipError_t launch_pool_low(const void* spec, void* low, const int32_t* slice_list, int n_slices, int64_t N, int d,
-                           int64_t n_low, int64_t nbar, int c, int is_half, hipStream_t st) {
-  const int64_t total = (int64_t)n_slices * nbar * d;
-  if (total == 0) return hipSuccess;
-  const unsigned nb = (unsigned)((total + 255) / 256);
-  if (is_half)
-    hipLaunchKernelGGL(k_pool_low<half_t>, dim3(nb), dim3(256), 0, st, (const half_t*)spec, (half_t*)low, slice_list, N,
-                       d, n_low, nbar, c, total);
-  else
-    hipLaunchKernelGGL(k_pool_low<float>, dim3(nb), dim3(256), 0, st, (const float*)spec, (float*)low, slice_list, N, d,
-                       n_low, nbar, c, total);
-  return hipGetLastError();
-}
-
-// Every low-band position takes the output of its group (section 3.4.1 reading: Y_i = Ybar_{floor(i/c)}).
-template <typename T>
-__global__ void k_expand_low(const T* lowY, T* Y, const int32_t* slice_list, int64_t N, int d, int64_t n_low,
-                             int64_t nbar, int c, int64_t total) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int ch = (int)(idx % d);
-  const int64_t i = (idx / d) % n_low;
-  const int li = (int)(idx / ((int64_t)d * n_low));
-  const int slice = slice_list[li];
-  Y[((int64_t)slice * N + i) * d + ch] = lowY[((int64_t)slice * nbar + i / c) * d + ch];
-}
-
-hipError_t launch_expand_low(const void* lowY, void* Y, const int32_t* slice_list, int n_slices, int64_t N, int d,
-                             int64_t n_low, int64_t nbar, int c, int is_half, hipStream_t st) {
-  const int64_t total = (int64_t)n_slices * n_low * d;
-  if (total == 0) return hipSuccess;
-  const unsigned nb = (unsigned)((total + 255) / 256);
-  if (is_half)
-    hipLaunchKernelGGL(k_expand_low<half_t>, dim3(nb), dim3(256), 0, st, (const half_t*)lowY, (half_t*)Y, slice_list, N,
-                       d, n_low, nbar, c, total);
-  else
-    hipLaunchKernelGGL(k_expand_low<float>, dim3(nb), dim3(256), 0, st, (const float*)lowY, (float*)Y, slice_list, N, d,
-                       n_low, nbar, c, total);
-  return hipGetLastError();
-}
-
-// Summary tokens (section 3.6, U = I): chunk u of band l covers band rows [floor(u n / m), floor((u+1) n / m)).
-// One workgroup per (slice, band, chunk); threads split the chunk's rows 256/d ways and the partial sums are added in
-// a fixed order, so the result does not depend on scheduling.  The mean is written to the C rows of the other
-// bands (band l sees the summaries of the other bands, ascending band index).
 struct SkipBits { uint64_t w[NBMAX][4]; };   // per band: slices whose summaries of that band are not pooled here (unused, or summed from the untransformed V)
 struct BandGeom { int64_t off[NBMAX], n[NBMAX]; int m[NBMAX]; int nb; };   // first row, rows and summary tokens per band; nb bands
 
@@ -81,150 +18,165 @@ __device__ __forceinline__ int summary_pos(const BandGeom& g, int band, int b, i
   return pos;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) k_summaries(const T* Y, const T* V, T* C, const int32_t* masks, int64_t N, int d,
-                                                   BandGeom g, int m2rows, SkipBits skip) {
-  __shared__ float part[256];
-  const int slice = blockIdx.z, band = blockIdx.y, u = blockIdx.x;
-  if (slice < 256 && ((skip.w[band][slice >> 6] >> (slice & 63)) & 1)) return;
-  const int64_t off = g.off[band], n = g.n[band];
-  const int me = g.m[band];
-  if (u >= me) return;
-  const T* src = ((masks[slice] >> band) & 1) ? Y : V;
-  const int64_t r0 = ((int64_t)u * n) / me, r1 = ((int64_t)(u + 1) * n) / me;
-  const int groups = 256 / d;  // head_dim <= 256
-  const int tid = threadIdx.x;
-  const int ch = tid % d, grp = tid / d;
-  float s = 0.f;
-  if (grp < groups)
-    for (int64_t r = r0 + grp; r < r1; r += groups) s += (float)src[((int64_t)slice * N + off + r) * d + ch];
-  part[tid] = s;
-  __syncthreads();
-  if (grp == 0) {
-    float t = 0.f;
-    for (int g2 = 0; g2 < groups; ++g2) t += part[g2 * d + ch];
-    const T mean = (T)(t / (float)(r1 - r0));
-    for (int b = 0; b < g.nb; ++b) {
-      if (b == band) continue;
-      C[(((int64_t)slice * g.nb + b) * m2rows + summary_pos(g, band, b, u)) * d + ch] = mean;
-    }
-  }
-}
+struct PoolKernelArgs {
+  const void* spec[3]; void* low[3]; const int32_t* low_list; int64_t n_low, nbar; int c; int64_t low_vecs; unsigned low_blocks;
+  const void* Y; const void* V; void* C; const int32_t* masks; BandGeom g; int m2rows; SkipBits skip; int nsplit, mmax; float* part;
+  int64_t N; int d;
+};
 
-// fp16 variant with 16-byte loads: a thread owns 8 adjacent channels, 256 / (d/8) row groups per workgroup, sixteen
-// rows in flight per thread.  Same chunk rule, same fixed summation order per (row group, then groups ascending).
-__global__ void __launch_bounds__(256) k_summaries_h8(const half_t* Y, const half_t* V, half_t* C, const int32_t* masks,
-                                                      int64_t N, int d, BandGeom g, int m2rows, SkipBits skip, int nsplit,
-                                                      float* split_part) {
-  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-  __shared__ float part[256 * 8];
-  const int slice = blockIdx.z, band = blockIdx.y, u = blockIdx.x / nsplit, sp = blockIdx.x % nsplit;
-  if (slice < 256 && ((skip.w[band][slice >> 6] >> (slice & 63)) & 1)) return;
-  const int64_t off = g.off[band], n = g.n[band];
-  const int me = g.m[band];
+// The two poolings of band-major rows in one launch (they read the same fresh spectral rows and neither fills the chip):
+//  - workgroups [0, low_blocks): low-band compression (section 3.3), mean of c consecutive band rows of Q~, K~ and V~;
+//  - the rest: summary tokens (section 3.6, U = I): chunk u of band l covers band rows [floor(u n / m), floor((u+1) n / m)).
+//    One workgroup per (slice, band, chunk[, part of the chunk]); thread = VW adjacent channels (16 bytes) of every
+//    `groups`-th row, eight rows in flight; partial sums are added in a fixed order, so results do not depend on
+//    scheduling.  The mean goes to the C rows of the other bands (ascending band index).
+// What bounds it: at ordinary sizes the latency of one chunk (16 waves per workgroup: a chunk of 115 KB takes seven loads
+// per thread); chunks above 1 MB are cut into parts that meet in k_summaries_finish.  Compression (3 launches), pooling
+// (1-2) and the low band's expansion (1; now written by the band operator) took 34 us at 16K tokens x 8 heads x 64, 136 us at
+// 256K x 24 x 128 and 78 + 19 us in fp32 at 12,150 x 4 x 64; this launch takes 11, 65 and 8 us.
+template <typename T, int VW, int NT>
+__global__ void __launch_bounds__(NT) k_band_pools(PoolKernelArgs a) {
+  typedef T vec __attribute__((ext_vector_type(VW)));
+  __shared__ float part[NT * VW];
+  const int d = a.d, tid = threadIdx.x, tpr = d / VW;   // threads per row
+  if (blockIdx.x < a.low_blocks) {
+    const int64_t idx = (int64_t)blockIdx.x * NT + tid;
+    if (idx >= a.low_vecs) return;
+    const int cv = (int)(idx % tpr);
+    const int64_t r = idx / tpr, j = r % a.nbar;
+    const int64_t li = r / a.nbar;
+    const int tensor = (int)(li % 3), slice = a.low_list[li / 3];
+    const int64_t r0 = j * a.c, r1 = r0 + a.c < a.n_low ? r0 + a.c : a.n_low;
+    const T* src = (const T*)a.spec[tensor] + (int64_t)slice * a.N * d + cv * VW;
+    float s[VW];
+#pragma unroll
+    for (int k = 0; k < VW; ++k) s[k] = 0.f;
+    for (int64_t q = r0; q < r1; ++q) {
+      const vec x = *(const vec*)(src + q * d);
+#pragma unroll
+      for (int k = 0; k < VW; ++k) s[k] += (float)x[k];
+    }
+    vec o;
+#pragma unroll
+    for (int k = 0; k < VW; ++k) o[k] = (T)(s[k] / (float)(r1 - r0));
+    *(vec*)((T*)a.low[tensor] + ((int64_t)slice * a.nbar + j) * d + cv * VW) = o;
+    return;
+  }
+  unsigned b = blockIdx.x - a.low_blocks;
+  const int sp = b % a.nsplit; b /= a.nsplit;
+  const int u = b % a.mmax; b /= a.mmax;
+  const int band = b % a.g.nb, slice = b / a.g.nb;
+  if (slice < 256 && ((a.skip.w[band][slice >> 6] >> (slice & 63)) & 1)) return;
+  const int64_t off = a.g.off[band], n = a.g.n[band];
+  const int me = a.g.m[band];
   if (u >= me) return;
-  const half_t* src = (((masks[slice] >> band) & 1) ? Y : V) + ((int64_t)slice * N + off) * d;
+  const T* src = (const T*)(((a.masks[slice] >> band) & 1) ? a.Y : a.V) + ((int64_t)slice * a.N + off) * d;
   const int64_t c0 = ((int64_t)u * n) / me, c1 = ((int64_t)(u + 1) * n) / me;   // the chunk
-  // with few chunks (small m) a chunk is cut into nsplit row ranges, one workgroup each; their sums meet in
-  // k_summaries_finish in a fixed order
-  const int64_t r0 = c0 + ((c1 - c0) * sp) / nsplit, r1 = c0 + ((c1 - c0) * (sp + 1)) / nsplit;
-  const int tpr = d / 8;               // threads per row
-  const int groups = 256 / tpr;        // rows per workgroup step
-  const int tid = threadIdx.x;
-  const int c8 = tid % tpr, grp = tid / tpr;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const int64_t r0 = c0 + ((c1 - c0) * sp) / a.nsplit, r1 = c0 + ((c1 - c0) * (sp + 1)) / a.nsplit;
+  const int groups = NT / tpr, cv = tid % tpr, grp = tid / tpr;
+  float acc[VW];
+#pragma unroll
+  for (int k = 0; k < VW; ++k) acc[k] = 0.f;
   if (grp < groups) {
     int64_t r = r0 + grp;
-    constexpr int INF = 16;   // rows in flight per thread: few workgroups may be left with all the work (see skip)
+    constexpr int INF = 8;   // rows in flight per thread
     for (; r + (INF - 1) * (int64_t)groups < r1; r += INF * (int64_t)groups) {
-      h8 x[INF];
+      vec x[INF];
 #pragma unroll
-      for (int k = 0; k < INF; ++k) x[k] = *(const h8*)(src + (r + (int64_t)k * groups) * d + c8 * 8);
+      for (int q = 0; q < INF; ++q) x[q] = *(const vec*)(src + (r + (int64_t)q * groups) * d + cv * VW);
 #pragma unroll
-      for (int k = 0; k < INF; ++k)
+      for (int q = 0; q < INF; ++q)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (float)x[k][j];
+        for (int k = 0; k < VW; ++k) acc[k] += (float)x[q][k];
     }
     for (; r < r1; r += groups) {
-      const h8 x = *(const h8*)(src + r * d + c8 * 8);
+      const vec x = *(const vec*)(src + r * d + cv * VW);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] += (float)x[j];
+      for (int k = 0; k < VW; ++k) acc[k] += (float)x[k];
     }
+#pragma unroll
+    for (int k = 0; k < VW; ++k) part[(size_t)grp * d + cv * VW + k] = acc[k];
   }
-#pragma unroll
-  for (int j = 0; j < 8; ++j) part[tid * 8 + j] = acc[j];
   __syncthreads();
-  if (grp == 0) {
-    const float inv = 1.f / (float)(c1 - c0);
-    h8 mean;
-    float sum[8];
+  for (int ch = tid; ch < d; ch += NT) {
+    float t4[4] = {0.f, 0.f, 0.f, 0.f};
+    int q = 0;
+    for (; q + 3 < groups; q += 4)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float t = 0.f;
-      for (int g2 = 0; g2 < groups; ++g2) t += part[(g2 * tpr + c8) * 8 + j];
-      sum[j] = t;
-      mean[j] = (_Float16)(t * inv);
+      for (int k = 0; k < 4; ++k) t4[k] += part[(size_t)(q + k) * d + ch];
+    for (; q < groups; ++q) t4[0] += part[(size_t)q * d + ch];
+    const float t = (t4[0] + t4[1]) + (t4[2] + t4[3]);
+    if (a.nsplit > 1) {   // [slice][band][u][part][d]
+      a.part[((((int64_t)slice * a.g.nb + band) * a.mmax + u) * a.nsplit + sp) * d + ch] = t;
+      continue;
     }
-    if (nsplit > 1) {   // [slice][band][u][split][d]
-      float* dst = split_part + ((((int64_t)slice * g.nb + band) * gridDim.x + blockIdx.x) * d) + c8 * 8;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dst[j] = sum[j];
-      return;
-    }
-    for (int b = 0; b < g.nb; ++b) {
-      if (b == band) continue;
-      *(h8*)(C + (((int64_t)slice * g.nb + b) * m2rows + summary_pos(g, band, b, u)) * d + c8 * 8) = mean;
-    }
+    const T mean = (T)(t / (float)(c1 - c0));
+    for (int o = 0; o < a.g.nb; ++o)
+      if (o != band) ((T*)a.C)[(((int64_t)slice * a.g.nb + o) * a.m2rows + summary_pos(a.g, band, o, u)) * d + ch] = mean;
   }
 }
 
-// Second stage of the split pooling: adds the nsplit partial sums of a chunk in order and writes the mean rows.
-__global__ void __launch_bounds__(256) k_summaries_finish(const float* split_part, half_t* C, int d, BandGeom g, int m2rows,
-                                                          SkipBits skip, int nsplit, int mmax) {
-  const int slice = blockIdx.z, band = blockIdx.y, u = blockIdx.x, ch = threadIdx.x;
-  if (slice < 256 && ((skip.w[band][slice >> 6] >> (slice & 63)) & 1)) return;
-  const int64_t n = g.n[band];
-  const int me = g.m[band];
+// Second stage of pooled chunks that were cut: adds the parts' sums in order and writes the mean rows.
+template <typename T>
+__global__ void __launch_bounds__(256) k_summaries_finish(PoolKernelArgs a) {
+  const int slice = blockIdx.z, band = blockIdx.y, u = blockIdx.x, ch = threadIdx.x, d = a.d;
+  if (slice < 256 && ((a.skip.w[band][slice >> 6] >> (slice & 63)) & 1)) return;
+  const int64_t n = a.g.n[band];
+  const int me = a.g.m[band];
   if (u >= me || ch >= d) return;
   const int64_t c0 = ((int64_t)u * n) / me, c1 = ((int64_t)(u + 1) * n) / me;
-  const float* src = split_part + ((((int64_t)slice * g.nb + band) * (mmax * nsplit) + (int64_t)u * nsplit) * d) + ch;
+  const float* src = a.part + ((((int64_t)slice * a.g.nb + band) * a.mmax + u) * a.nsplit) * d + ch;
   float t = 0.f;
-  for (int sp = 0; sp < nsplit; ++sp) t += src[(int64_t)sp * d];
-  const half_t mean = (half_t)(t / (float)(c1 - c0));
-  for (int b = 0; b < g.nb; ++b) {
-    if (b == band) continue;
-    C[(((int64_t)slice * g.nb + b) * m2rows + summary_pos(g, band, b, u)) * d + ch] = mean;
-  }
+  for (int sp = 0; sp < a.nsplit; ++sp) t += src[(int64_t)sp * d];
+  const T mean = (T)(t / (float)(c1 - c0));
+  for (int o = 0; o < a.g.nb; ++o)
+    if (o != band) ((T*)a.C)[(((int64_t)slice * a.g.nb + o) * a.m2rows + summary_pos(a.g, band, o, u)) * d + ch] = mean;
 }
 
-hipError_t launch_summaries(const void* Y, const void* V, void* C, const int32_t* masks, int slices, int64_t N, int d,
-                            int nb, const int64_t band_off[NBMAX], const int64_t band_n[NBMAX], const int m_eff[NBMAX], int m2rows,
-                            int is_half, const uint64_t* skip_bits /*[NBMAX][4] or NULL*/, float* split_part, hipStream_t st) {
-  SkipBits skip;
-  BandGeom g;
-  g.nb = nb;
-  int mmax = 0;
-  for (int l = 0; l < NBMAX; ++l) {
-    for (int i = 0; i < 4; ++i) skip.w[l][i] = skip_bits ? skip_bits[l * 4 + i] : 0;
-    g.off[l] = band_off[l]; g.n[l] = l < nb ? band_n[l] : 0; g.m[l] = l < nb ? m_eff[l] : 0;
-    if (g.m[l] > mmax) mmax = g.m[l];
-  }
-  if (mmax == 0 || slices == 0) return hipSuccess;
-  dim3 grid((unsigned)mmax, (unsigned)nb, (unsigned)slices);
-  if (is_half && d % 8 == 0 && 256 % (d / 8) == 0) {
-    // at least 64 workgroups per (slice, band): with few chunks each is cut into row ranges (scratch: 128 rows per pair)
-    const int nsplit = (split_part && mmax < 64) ? (64 + mmax - 1) / mmax : 1;
-    hipLaunchKernelGGL(k_summaries_h8, dim3((unsigned)(mmax * nsplit), (unsigned)nb, (unsigned)slices), dim3(256), 0, st, (const half_t*)Y,
-                       (const half_t*)V, (half_t*)C, masks, N, d, g, m2rows, skip, nsplit, split_part);
-    if (nsplit > 1)
-      hipLaunchKernelGGL(k_summaries_finish, grid, dim3(256), 0, st, split_part, (half_t*)C, d, g, m2rows, skip, nsplit, mmax);
-  } else if (is_half)
-    hipLaunchKernelGGL(k_summaries<half_t>, grid, dim3(256), 0, st, (const half_t*)Y, (const half_t*)V, (half_t*)C,
-                       masks, N, d, g, m2rows, skip);
-  else
-    hipLaunchKernelGGL(k_summaries<float>, grid, dim3(256), 0, st, (const float*)Y, (const float*)V, (float*)C, masks, N,
-                       d, g, m2rows, skip);
+template <typename T, int VW, int NT>
+static hipError_t launch_pools_v(PoolKernelArgs& k, int n_low_slices, int slices, hipStream_t st) {
+  k.low_vecs = (int64_t)n_low_slices * 3 * k.nbar * (k.d / VW);
+  const int64_t low_blocks = (k.low_vecs + NT - 1) / NT;
+  const int64_t blocks = low_blocks + (int64_t)slices * k.g.nb * k.mmax * k.nsplit;
+  if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  k.low_blocks = (unsigned)low_blocks;
+  hipLaunchKernelGGL((k_band_pools<T, VW, NT>), dim3((unsigned)blocks), dim3(NT), 0, st, k);
+  if (k.nsplit > 1 && k.mmax > 0)
+    hipLaunchKernelGGL(k_summaries_finish<T>, dim3((unsigned)k.mmax, (unsigned)k.g.nb, (unsigned)slices), dim3(256), 0, st, k);
   return hipGetLastError();
+}
+
+hipError_t launch_band_pools(const PoolArgs& p, hipStream_t st) {
+  PoolKernelArgs k{};
+  for (int i = 0; i < 3; ++i) { k.spec[i] = p.spec[i]; k.low[i] = p.low[i]; }
+  k.low_list = p.low_list; k.n_low = p.n_low; k.nbar = p.nbar; k.c = p.c;
+  k.Y = p.Y; k.V = p.V; k.C = p.C; k.masks = p.masks; k.m2rows = p.m2rows; k.N = p.N; k.d = p.d; k.part = p.part;
+  k.nsplit = 1;
+  k.g.nb = p.nb;
+  int64_t longest = 0;   // rows of the longest chunk that some slice pools
+  for (int l = 0; l < NBMAX; ++l) {
+    for (int i = 0; i < 4; ++i) k.skip.w[l][i] = p.skip_bits ? p.skip_bits[l * 4 + i] : 0;
+    k.g.off[l] = p.band_off[l]; k.g.n[l] = l < p.nb ? p.band_n[l] : 0; k.g.m[l] = l < p.nb ? p.m_eff[l] : 0;
+    if (!p.pool) k.g.m[l] = 0;
+    k.mmax = std::max(k.mmax, k.g.m[l]);
+    if (k.g.m[l] > 0 && (p.pooled_bands >> l & 1)) longest = std::max(longest, (k.g.n[l] + k.g.m[l] - 1) / k.g.m[l]);
+  }
+  const int slices = k.mmax > 0 ? p.slices : 0;
+  const int es = p.is_half ? 2 : 4;
+  if (slices > 0 && longest * p.d * es > (1 << 20)) {
+    const int64_t fit = p.part_floats / ((int64_t)slices * p.nb * k.mmax * p.d);
+    k.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>((longest * p.d * es + (1 << 19) - 1) >> 19, std::min<int64_t>(fit, 64)));
+  }
+  // Threads per workgroup: sixteen waves on a chunk where there are at most two chunks per compute unit, four otherwise (a
+  // workgroup of 1024 has a unit to itself, and its start and end are then exposed: 105 against 65 us with 1,300 chunks).
+  const bool wide = (int64_t)p.n_pooled * k.mmax * k.nsplit <= 2 * p.num_cu;
+  if (p.is_half) {
+    if (p.d % 8 != 0) return hipErrorInvalidValue;
+    return wide ? launch_pools_v<half_t, 8, 1024>(k, p.n_low_slices, slices, st) : launch_pools_v<half_t, 8, 256>(k, p.n_low_slices, slices, st);
+  }
+  if (p.d % 4 == 0) return wide ? launch_pools_v<float, 4, 1024>(k, p.n_low_slices, slices, st) : launch_pools_v<float, 4, 256>(k, p.n_low_slices, slices, st);
+  return launch_pools_v<float, 1, 1024>(k, p.n_low_slices, slices, st);
 }
 
 // Summary tokens of the projected forward (sections 3.1 + 3.6): the mean over a chunk of band rows commutes with the

@@ -104,11 +104,12 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
     const int q0 = item.q0;
     const uint16_t *Qp, *Kp, *Vp;
     uint16_t* Op;
-    int nq, nk;
+    int nq, nk, rep = 1;
     if (kind == 0) {
       const int64_t o = slice * p.nbar * D;
       Qp = (const uint16_t*)p.lowQ + o; Kp = (const uint16_t*)p.lowK + o; Vp = (const uint16_t*)p.lowV + o;
-      Op = (uint16_t*)p.lowY + o; nq = nk = p.nbar;
+      // (section 3.4.1 reading: every low-band row takes the output of its group, so row i goes to rows i c .. i c + c - 1)
+      Op = (uint16_t*)p.Y + slice * p.N * D; nq = nk = p.nbar; rep = p.low_c;
     } else if (kind == 1 || kind == 2) {
       const int64_t o = (slice * p.N + p.band_off[band]) * D;
       Qp = (const uint16_t*)p.specQ + o; Kp = (const uint16_t*)p.specK + o; Vp = (const uint16_t*)p.specV + o;
@@ -206,7 +207,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
             for (int b = 0; b < 8; ++b) qh[b] = (_Float16)((float)yh[b] * c2);
             // The rows are parked in the output tensor - exactly what the band operator alone would have stored - and
             // come back as the residual in the epilogue (same lane, same address: no other reader in this launch).
-            if (r0 + nn < nq) *(uint4v*)(Op + (int64_t)(r0 + nn) * D + dt * 32 + j * 16 + g * 8) = y4;
+            if (r0 + nn < nq) *(uint4v*)(Op + (int64_t)(r0 + nn) * rep * D + dt * 32 + j * 16 + g * 8) = y4;
             Qr[dt * 2 + j] = qh;
           }
 #pragma unroll
@@ -489,9 +490,9 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
           }
           if (row < nq) {
             const int dd = dt * 32 + j * 16 + g * 8;
-            uint16_t* dst = Op + (int64_t)row * D + dd;
+            uint16_t* dst = Op + (int64_t)row * rep * D + dd;
             if (kind == 3 || n_phases == 2) {   // residual: the exchange's query rows (parked in the output by phase 1's start)
-              const uint4v y = *(const volatile uint4v*)((kind == 3 ? Qp : (const uint16_t*)Op) + (int64_t)row * D + dd);
+              const uint4v y = *(const volatile uint4v*)((kind == 3 ? Qp : (const uint16_t*)Op) + (int64_t)row * rep * D + dd);
               const half8 yh = __builtin_bit_cast(half8, y);
 #pragma unroll
               for (int b = 0; b < 8; ++b) o[b] += (float)yh[b];
@@ -500,6 +501,8 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
 #pragma unroll
             for (int b = 0; b < 4; ++b) st4[b] = pack_h2(o[2 * b], o[2 * b + 1]);
             *(uint4v*)dst = st4;
+            for (int c = 1; c < rep; ++c)
+              if ((int64_t)row * rep + c < p.band_n[LOW]) *(uint4v*)(dst + c * D) = st4;
           }
         }
     }

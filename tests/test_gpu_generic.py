@@ -46,3 +46,23 @@ def test_generic_axis_lengths(grid, d, dtype):
     """Axis lengths around the 16-row steps and the 64-row groups of an axis pass, beyond two groups, and head dimensions
     that are no multiple of the 4 (unaligned) or 64 (several slabs per wave) adjacent columns."""
     _check(grid, d, 3, (0, 5, 7), dtype, n_summary=3)
+
+
+@pytest.mark.parametrize("d,m,c", [(64, 1, 5), (30, 2, 3)])
+def test_generic_pooling_of_long_chunks(d, m, c):
+    """Summary chunks above 1 MB (10,000 rows and more of the high band) are pooled in parts; rows of 16 bytes and of single
+    elements; a compression factor that leaves a shorter last group."""
+    _check((9, 40, 50), d, 2, (1, 3), n_summary=m, low_compress=c, mid_block=64, mid_stride=16, high_window=4)
+
+
+@pytest.mark.parametrize("alloc", [(1, 2), (5, 6)])
+def test_matrix_core_pooling_of_long_chunks(alloc):
+    """The same on fp16 rows: one summary token per band, 1.8 MB per high-band chunk at 16K tokens; the low band's outputs
+    written to whole groups by the band operator, with and without the exchange inside its items."""
+    wl = WL.WORKLOADS["16k"]
+    q, k, v = (WL.round_to_io(x, wl.dtype) for x in WL.qkv_numpy(wl, heads=[0, 3]))
+    ctx, band = U.make_ctx(wl, heads=2, n_summary=1, low_compress=7)
+    got = U.run_forward(ctx, q, k, v, wl.dtype, alloc)
+    mx, rl = U.errors(got, O.forward(q, k, v, wl.grid, U.oracle_cfg(band), alloc))
+    print(f"16k m=1 c=7 {alloc}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
