@@ -683,38 +683,68 @@ static int keep_rows(int box, int n) {
   return (r < n && mfma_dct_supported(n, r) && mfma_dct_supported(r, n)) ? r : n;
 }
 
-// MFMA path, forward, for `ns` slices (slice_list on the device, NULL = slices 0..ns-1): W axis (tmp0), H axis (tmp1,
-// left in [h][t] order so that the rows of the T pass are W*d elements apart), T axis, which scatters into the
-// band-major spectral buffer.  keep[] = coefficients computed per axis (T, H, W): a head that only runs the low (low
-// and mid) band needs Q~ and K~ on that box only, and every pass after the first then moves a fraction of the tensor.
-// energy_slot >= 0 adds up the router's band statistics in the T pass, tot_slot >= 0 the input's sum of squares in
-// the W pass.
-// `width` > 0 transforms a tensor of that many channels per token instead of head_dim (the projected forward transforms X,
+// One tensor of a forward transform: `ns` slices (slice_list on the device, NULL = slices 0..ns-1) of x into the band-major
+// buffer spec.
+struct TransformSeg { const void* x; void* spec; const int32_t* slice_list; int ns; };
+
+// MFMA path, forward, for up to three tensors that share `keep`: W and H axes in one pass where wh_fits says so, else W axis
+// (tmp0) and H axis pass by pass; both leave [h][t] order behind so that the rows of the T pass are W*d elements apart.
+// The T pass scatters into the band-major spectral buffers.  keep[] = coefficients computed per axis (T, H, W): a head
+// that only runs the low (low and mid) band needs Q~ and K~ on that box only, and every pass after the first then moves a
+// fraction of the tensor.  energy_slot >= 0 adds up the router's band statistics in the T pass, tot_slot >= 0 the inputs'
+// sum of squares in the first pass (of all tensors together: the router adds them anyway).
+// `width` > 0 transforms tensors of that many channels per token instead of head_dim (the projected forward transforms X,
 // [batch][N][d_model], as `ns` = batch slices).
-static hipError_t forward_transform_mfma(Ctx& c, const void* x, void* spec, hipStream_t st, const int32_t* slice_list,
-                                         int ns, const int keep[3], int energy_slot, int tot_slot, int width = 0) {
-  if (ns <= 0) return hipSuccess;
+static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int nseg, hipStream_t st, const int keep[3],
+                                         int energy_slot, int tot_slot, int width = 0) {
   const int T = c.shape.T, H = c.shape.H, W = c.shape.W, d = width > 0 ? width : c.d;
   const int kt = keep[0], kh = keep[1], kw = keep[2];
   hipError_t e;
-  DctPassArgs a{};
-  a.d = d; a.Ntok = c.N; a.slice_elems = c.N * d;
-  a.in = x; a.slice_list = slice_list; a.list_in = 1; a.out = c.tmp0; a.M = c.d_F16[2]; a.ldm = W; a.n = W; a.n_out = kw;
-  a.inner = d; a.outer = (int64_t)T * H; a.nslab = (int64_t)ns * T * H; a.in_bf16 = 1;
-  if (tot_slot >= 0) a.tot_part = c.d_tot_part + (size_t)tot_slot * DCT_MAX_WAVES * 64;
-  int w_dummy = 0;
-  if ((e = launch_mfma_dct_pass(a, c.num_cu, st, tot_slot >= 0 ? &c.tot_waves[tot_slot] : &w_dummy)) != hipSuccess) return e;
-
-  DctPassArgs b{};
-  b.d = d; b.Ntok = c.N;
-  b.in = c.tmp0; b.out = c.tmp1; b.M = c.d_F16[1]; b.ldm = H; b.n = H; b.n_out = kh; b.inner = (int64_t)kw * d;
-  b.nslab = (int64_t)ns * T; b.outer = b.nslab; b.out_swap = 1; b.sw = T; b.sw_total = T; b.sw_off = 0;
-  if ((e = launch_mfma_dct_pass(b, c.num_cu, st)) != hipSuccess) return e;
-
+  WhPassArgs f{};
   DctPassArgs t{};
+  void* const scratch3[3] = {c.tmp1, c.tmp0, c.Y};   // (Y is free until the band operators)
+  int n = 0, total = 0;
+  for (int i = 0; i < nseg; ++i) {
+    if (segs[i].ns <= 0) continue;
+    total += segs[i].ns;
+    f.in[n] = segs[i].x; f.out[n] = scratch3[n]; f.slice_list[n] = segs[i].slice_list; f.seg_end[n] = total;
+    t.in_seg[n] = scratch3[n]; t.out_seg[n] = segs[i].spec; t.list_seg[n] = segs[i].slice_list; t.seg_end[n] = total;
+    ++n;
+  }
+  if (n == 0) return hipSuccess;
+  for (int i = n; i < 3; ++i) f.seg_end[i] = t.seg_end[i] = total;
+  f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw;
+  int slots = 0;
+  const bool fused = wh_fits(f);
+  if (fused) {
+    f.Mh = c.d_F16[1]; f.Mw = c.d_F16[2];
+    f.range_flag = c.d_range_flag;
+    if (tot_slot >= 0) f.tot_part = c.d_tot_part + (size_t)tot_slot * DCT_MAX_WAVES * 64;
+    if ((e = launch_wh_pass(f, c.num_cu, st, &slots)) != hipSuccess) return e;
+    if (tot_slot >= 0) c.tot_waves[tot_slot] = slots;
+  } else if (n > 1) {   // one after the other: the passes share tmp0 and tmp1
+    for (int i = 0; i < nseg; ++i)
+      if ((e = forward_transform_mfma(c, segs + i, 1, st, keep, energy_slot >= 0 ? energy_slot + i : -1, tot_slot >= 0 ? tot_slot + i : -1, width)) != hipSuccess) return e;
+    return hipSuccess;
+  } else {
+    DctPassArgs a{};
+    a.d = d; a.Ntok = c.N; a.slice_elems = c.N * d;
+    a.in = f.in[0]; a.slice_list = f.slice_list[0]; a.list_in = 1; a.out = c.tmp0; a.M = c.d_F16[2]; a.ldm = W; a.n = W; a.n_out = kw;
+    a.inner = d; a.outer = (int64_t)T * H; a.nslab = (int64_t)total * T * H; a.in_bf16 = 1;
+    if (tot_slot >= 0) a.tot_part = c.d_tot_part + (size_t)tot_slot * DCT_MAX_WAVES * 64;
+    if ((e = launch_mfma_dct_pass(a, c.num_cu, st, &slots)) != hipSuccess) return e;
+    if (tot_slot >= 0) c.tot_waves[tot_slot] = slots;
+
+    DctPassArgs b{};
+    b.d = d; b.Ntok = c.N;
+    b.in = c.tmp0; b.out = c.tmp1; b.M = c.d_F16[1]; b.ldm = H; b.n = H; b.n_out = kh; b.inner = (int64_t)kw * d;
+    b.nslab = (int64_t)total * T; b.outer = b.nslab; b.out_swap = 1; b.sw = T; b.sw_total = T; b.sw_off = 0;
+    if ((e = launch_mfma_dct_pass(b, c.num_cu, st)) != hipSuccess) return e;
+  }
+
   t.d = d; t.Ntok = c.N;
-  t.in = c.tmp1; t.out = spec; t.M = c.d_F16[0]; t.ldm = T; t.n = T; t.n_out = kt; t.inner = (int64_t)kw * d;
-  t.nslab = (int64_t)ns * kh; t.outer = kh; t.slice_list = slice_list;
+  t.M = c.d_F16[0]; t.ldm = T; t.n = T; t.n_out = kt; t.inner = (int64_t)kw * d;
+  t.nslab = (int64_t)total * kh; t.outer = kh;
   t.perm_out = c.d_perm_t; t.perm_k = 1; t.perm_o = W; t.perm_scale = T;
   t.range_flag = c.d_range_flag;
   if (energy_slot >= 0) {
@@ -723,7 +753,9 @@ static hipError_t forward_transform_mfma(Ctx& c, const void* x, void* spec, hipS
     t.low_u = c.low_box[1]; t.low_v = c.low_box[2]; t.low_a = c.low_box[0];
     t.mid_u = c.mid_box[1]; t.mid_v = c.mid_box[2]; t.mid_a = c.mid_box[0];
   }
-  return launch_mfma_dct_pass(t, c.num_cu, st, energy_slot >= 0 ? &c.energy_waves[energy_slot] : &w_dummy);
+  if ((e = launch_mfma_dct_pass(t, c.num_cu, st, &slots)) != hipSuccess) return e;
+  if (energy_slot >= 0) c.energy_waves[energy_slot] = slots;
+  return hipSuccess;
 }
 
 // MFMA path, inverse (section 3.7) for `ns` slices: the T axis pass gathers band-major rows into tmp1 in [h][t]
@@ -899,18 +931,22 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
       const int32_t* L = c->d_lists;
       const int32_t* hl = c->h_lists + c->off_cls[2];
       for (int i = 0; i < c->n_cls[2]; ++i) c->qk_full[(size_t)hl[i]] = c->v_full[(size_t)hl[i]] = 1;
-      HIP_TRY(c, forward_transform_mfma(*c, q, c->specQ, st, L + c->off_nonhigh, c->n_nonhigh, mid, 0, 0));
-      HIP_TRY(c, forward_transform_mfma(*c, k, c->specK, st, L + c->off_nonhigh, c->n_nonhigh, mid, 1, 1));
-      if (vbox) HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, L + c->off_nonhigh, c->n_nonhigh, mid, 2, 2));
-      HIP_TRY(c, forward_transform_mfma(*c, q, c->specQ, st, L + c->off_cls[2], c->n_cls[2], full, 3, -1));
-      HIP_TRY(c, forward_transform_mfma(*c, k, c->specK, st, L + c->off_cls[2], c->n_cls[2], full, 4, -1));
-      if (vbox) HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, L + c->off_cls[2], c->n_cls[2], full, 5, -1));
+      const int32_t *lo = L + c->off_nonhigh, *hi = L + c->off_cls[2];
+      const int nl = c->n_nonhigh, nh = c->n_cls[2];
+      const TransformSeg box[3] = {{q, c->specQ, lo, nl}, {k, c->specK, lo, nl}, {v, c->specV, lo, nl}};
+      const TransformSeg whole[3] = {{q, c->specQ, hi, nh}, {k, c->specK, hi, nh},
+                                     vbox ? TransformSeg{v, c->specV, hi, nh} : TransformSeg{v, c->specV, nullptr, c->slices}};
+      HIP_TRY(c, forward_transform_mfma(*c, box, vbox ? 3 : 2, st, mid, 0, 0));
+      HIP_TRY(c, forward_transform_mfma(*c, whole, 3, st, full, 3, -1));
     } else {
-      HIP_TRY(c, forward_transform_mfma(*c, q, c->specQ, st, nullptr, c->slices, pruned ? mid : full, 0, pruned ? 0 : -1));
-      HIP_TRY(c, forward_transform_mfma(*c, k, c->specK, st, nullptr, c->slices, pruned ? mid : full, 1, pruned ? 1 : -1));
-      if (vbox) HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, nullptr, c->slices, mid, 2, 2));
+      const TransformSeg all[3] = {{q, c->specQ, nullptr, c->slices}, {k, c->specK, nullptr, c->slices}, {v, c->specV, nullptr, c->slices}};
+      if (!pruned) {
+        HIP_TRY(c, forward_transform_mfma(*c, all, 3, st, full, 0, -1));
+      } else {
+        HIP_TRY(c, forward_transform_mfma(*c, all, vbox ? 3 : 2, st, mid, 0, 0));
+        if (!vbox) HIP_TRY(c, forward_transform_mfma(*c, all + 2, 1, st, full, 5, -1));
+      }
     }
-    if (!vbox) HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, nullptr, c->slices, full, pruned ? 5 : 2, -1));
     EnergyWaves nw;
     for (int i = 0; i < 6; ++i) nw.en[i] = c->energy_waves[i];
     for (int i = 0; i < 3; ++i) nw.tot[i] = c->tot_waves[i];
@@ -923,23 +959,21 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
     int low[3], mid[3];
     for (int a = 0; a < 3; ++a) { low[a] = keep_rows(c->low_box[a], full[a]); mid[a] = keep_rows(c->mid_box[a], full[a]); }
     const int32_t* L = c->d_lists;
-    const void* xs[2] = {q, k};
-    void* sp[2] = {c->specQ, c->specK};
-    for (int i = 0; i < 2; ++i) {
-      HIP_TRY(c, forward_transform_mfma(*c, xs[i], sp[i], st, L + c->off_cls[0], c->n_cls[0], low, -1, -1));
-      HIP_TRY(c, forward_transform_mfma(*c, xs[i], sp[i], st, L + c->off_cls[1], c->n_cls[1], mid, -1, -1));
-      HIP_TRY(c, forward_transform_mfma(*c, xs[i], sp[i], st, L + c->off_cls[2], c->n_cls[2], full, -1, -1));
-    }
-    if (c->v_box_ok) {   // V~ of a slice without the high band: the low+mid box (its high summaries come from V itself)
-      c->v_full.assign((size_t)c->slices, 0);
-      const int32_t* hl = c->h_lists + c->off_cls[2];
-      for (int i = 0; i < c->n_cls[2]; ++i) c->v_full[(size_t)hl[i]] = 1;
-      HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, L + c->off_nonhigh, c->n_nonhigh, mid, -1, -1));
-      HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, L + c->off_cls[2], c->n_cls[2], full, -1, -1));
-    } else {
-      c->v_full.assign((size_t)c->slices, 1);
-      HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, nullptr, c->slices, full, -1, -1));
-    }
+    const int32_t *l0 = L + c->off_cls[0], *l1 = L + c->off_cls[1], *l2 = L + c->off_cls[2];
+    const int n0 = c->n_cls[0], n1 = c->n_cls[1], n2 = c->n_cls[2];
+    // V~ of a slice without the high band: the low+mid box where the context can do that (its high summaries come from V
+    // itself), else the whole grid like the rest
+    const bool vbox = c->v_box_ok;
+    c->v_full.assign((size_t)c->slices, vbox ? 0 : 1);
+    if (vbox)
+      for (int i = 0; i < n2; ++i) c->v_full[(size_t)(c->h_lists + c->off_cls[2])[i]] = 1;
+    const TransformSeg lows[2] = {{q, c->specQ, l0, n0}, {k, c->specK, l0, n0}};
+    const TransformSeg mids[3] = {{q, c->specQ, l1, n1}, {k, c->specK, l1, n1}, {v, c->specV, L + c->off_nonhigh, vbox ? c->n_nonhigh : 0}};
+    const TransformSeg fulls[3] = {{q, c->specQ, l2, n2}, {k, c->specK, l2, n2},
+                                   vbox ? TransformSeg{v, c->specV, l2, n2} : TransformSeg{v, c->specV, nullptr, c->slices}};
+    HIP_TRY(c, forward_transform_mfma(*c, lows, 2, st, low, -1, -1));
+    HIP_TRY(c, forward_transform_mfma(*c, mids, 3, st, mid, -1, -1));
+    HIP_TRY(c, forward_transform_mfma(*c, fulls, 3, st, full, -1, -1));
     return FREQATTN_OK;
   }
   c->v_full.assign((size_t)c->slices, 1);
@@ -964,14 +998,13 @@ static freqattn_status complete_qk_for_high(freqattn_ctx* c, const void* q, cons
   if (n_fix == 0) return FREQATTN_OK;
   HIP_TRY(c, hipMemcpyAsync(c->d_lists + c->off_fix, fix, (size_t)n_fix * sizeof(int32_t), hipMemcpyHostToDevice, st));
   const int32_t* list = c->d_lists + c->off_fix;
-  HIP_TRY(c, forward_transform_mfma(*c, q, c->specQ, st, list, n_fix, full, -1, -1));
-  HIP_TRY(c, forward_transform_mfma(*c, k, c->specK, st, list, n_fix, full, -1, -1));
   bool v_too = false;
   for (int i = 0; i < n_fix; ++i) {
     v_too = v_too || !c->v_full[(size_t)fix[i]];
     c->v_full[(size_t)fix[i]] = 1;
   }
-  if (v_too) HIP_TRY(c, forward_transform_mfma(*c, v, c->specV, st, list, n_fix, full, -1, -1));
+  const TransformSeg segs[3] = {{q, c->specQ, list, n_fix}, {k, c->specK, list, n_fix}, {v, c->specV, list, v_too ? n_fix : 0}};
+  HIP_TRY(c, forward_transform_mfma(*c, segs, 3, st, full, -1, -1));
   return FREQATTN_OK;
 }
 
@@ -1442,7 +1475,8 @@ extern "C" freqattn_status freqattn_forward_projected(freqattn_ctx* c, const voi
     }
     tm.done("weights");
     const int full[3] = {c->shape.T, c->shape.H, c->shape.W};
-    HIP_TRY(c, forward_transform_mfma(*c, x, c->projX, st, nullptr, B, full, -1, -1, d_model));
+    const TransformSeg xseg{x, c->projX, nullptr, B};
+    HIP_TRY(c, forward_transform_mfma(*c, &xseg, 1, st, full, -1, -1, d_model));
     tm.done("x_transform");
     fs = products(0);
     if (fs != FREQATTN_OK) return fs;

@@ -267,6 +267,9 @@ struct DctPassArgs {
   // band-major buffers and of masks; list_in / list_out make the regular-layout input / output use it too
   // (element offset slice*slice_elems + slab_in_slice*rows*inner), otherwise those are compact scratch.
   const int32_t* slice_list; int list_in, list_out; int64_t slice_elems;
+  // Scatter passes: up to three tensors per launch, segment i is slices [seg_end[i-1], seg_end[i]) of the launch with its own
+  // input, output and slice list (instead of in, out, slice_list).
+  const void* in_seg[3]; void* out_seg[3]; const int32_t* list_seg[3]; int seg_end[3];
   int delta;                // gather side: read (in - in_alt) on active bands and zero elsewhere instead of selecting
   const void* resid;        // bf16, addressed like out: out = resid + result (the sum is formed in fp32)
   float* tot_part;          // [global wave][64]: sum of squares of the input per column (pass with inner == d only)
@@ -295,6 +298,24 @@ struct DctPassArgs {
 #define DCT_MAX_WAVES 65536   // upper bound of waves in one launch of the DCT pass (sizes energy_part)
 hipError_t launch_mfma_dct_pass(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out = nullptr);
 bool mfma_dct_supported(int n_in, int n_out);
+// W and H axes of the forward transform in one pass (mfma_wh_impl.h).
+struct WhPassArgs {
+  // up to three tensors: segment i is slices [seg_end[i-1], seg_end[i]) of the launch, slice sl of a segment is
+  // slice_list[i][sl] of in[i] (NULL: sl itself) and slice sl of out[i]
+  const void* in[3]; void* out[3];                  // in: bf16 [slices][T][H][W][d]; out: fp16 [segment's slices][kh][T][kw][d]
+  const int32_t* slice_list[3]; int seg_end[3];
+  int T, H, W, d, kh, kw;                           // d: channels per token; kh, kw: coefficients kept (multiples of 16)
+  const half_t* Mh; const half_t* Mw;               // fp16 [H][H], [W][W]: rows are coefficients
+  float* tot_part;                                  // [slot][64]: sum of squares of the inputs per channel, or NULL
+  int32_t* range_flag;                              // set when an input value leaves the fp16 range
+  int members;                                      // (filled in by the launcher) workgroups that share a plane
+};
+bool wh_fits(const WhPassArgs& a);   // whether the pass takes these sizes and is the faster way
+hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W <= 64
+hipError_t launch_wh_pass_1(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W > 64
+inline hipError_t launch_wh_pass(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
+  return a.W <= 64 ? launch_wh_pass_0(a, num_cu, st, slots_out) : launch_wh_pass_1(a, num_cu, st, slots_out);
+}
 hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, hipStream_t st);
 hipError_t launch_transpose_bf16_to_f16(const void* in /*[R][Cc] bf16*/, void* out /*[Cc][R] fp16*/, int R, int Cc, hipStream_t st);
 hipError_t launch_mfma_attn(const AttnParams& p, const AttnItem* items, int n_items, int rows_per_item, int num_cu,

@@ -123,6 +123,7 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
     int64_t out_off;                              // regular / swapped output (element offset into out / resid)
     int64_t bm_off;                               // band-major side: (slice*Ntok*d + col0 % d) elements, and
     int32_t pidx, mask;                           // o*perm_o + col0/d, band mask of the slice
+    char* out_base;                               // scatter: the segment's band-major buffer
   };
   auto tile_addr = [&](uint32_t tile) -> TileAddr {
     TileAddr t;
@@ -130,8 +131,12 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
     const int32_t col0 = (int32_t)(tile % (uint32_t)chunks_per_slab) * 64;
     const uint32_t sl = s / (uint32_t)a.outer;              // slice within this launch
     const int32_t o = (int32_t)(s % (uint32_t)a.outer);     // slab within the slice
-    const int64_t slice = a.slice_list ? a.slice_list[sl] : (int64_t)sl;   // slice of the caller's tensors
-    t.pidx = 0; t.bm_off = 0; t.mask = 7; t.in_base = nullptr; t.out_off = 0;
+    // slice of the caller's tensors; scatter passes: of the segment's tensor
+    const int seg = !PERM_OUT || (int)sl < a.seg_end[0] ? 0 : (int)sl < a.seg_end[1] ? 1 : 2;
+    const int first = seg == 0 ? 0 : a.seg_end[seg - 1];
+    const int32_t* list = PERM_OUT ? a.list_seg[seg] : a.slice_list;
+    const int64_t slice = list ? list[sl - first] : (int64_t)sl - first;
+    t.pidx = 0; t.bm_off = 0; t.mask = 7; t.in_base = nullptr; t.out_off = 0; t.out_base = nullptr;
     if (PERM_IN || PERM_OUT) {
       const int32_t ctok = col0 / a.d;
       t.pidx = o * (int32_t)a.perm_o + ctok;
@@ -144,10 +149,13 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
       t.in_base = (const char*)((const uint16_t*)a.in + (((int64_t)sa * NI * a.sw_total + sb + a.sw_off) * a.inner + col0));
     } else if (a.list_in) {
       t.in_base = (const char*)((const uint16_t*)a.in + (slice * a.slice_elems + (int64_t)o * NI * a.inner + col0));
+    } else if (PERM_OUT) {
+      t.in_base = (const char*)((const uint16_t*)a.in_seg[seg] + (((int64_t)s - (int64_t)first * a.outer) * NI * a.inner + col0));
     } else {
       t.in_base = (const char*)((const uint16_t*)a.in + ((int64_t)s * NI * a.inner + col0));
     }
     if (PERM_OUT) {
+      t.out_base = (char*)a.out_seg[seg];
     } else if (a.out_swap) {
       const uint32_t sa = s / (uint32_t)a.sw, sb = s % (uint32_t)a.sw;
       t.out_off = ((int64_t)sa * NO * a.sw_total + sb + a.sw_off) * a.inner + col0;
@@ -356,7 +364,7 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
         if (k0 + lrow_t < NO) {
           uint4v v = *(const uint4v*)(Xo + (it * 8 + lrow) * DCT_XO_STRIDE + lcol);
           char* dst;   // wave-uniform base plus this lane's 32-bit offset
-          if (PERM_OUT) dst = (char*)((uint16_t*)a.out + cur.bm_off) + ((uint64_t)(uint32_t)prow[mt][it] * (uint32_t)a.d + (uint32_t)lcol) * 2u;
+          if (PERM_OUT) dst = (char*)((uint16_t*)cur.out_base + cur.bm_off) + ((uint64_t)(uint32_t)prow[mt][it] * (uint32_t)a.d + (uint32_t)lcol) * 2u;
           else dst = (char*)((uint16_t*)a.out + cur.out_off + (int64_t)k0 * out_stride) + lane_out;
           if (!PERM_OUT && a.resid) {   // out = resid + result, both bf16 in memory, the sum formed in fp32
             const uint4v rs = rsd[it];
@@ -414,6 +422,7 @@ static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int
     // permutation table (band-major rows times the row width are formed in 64 bits)
     const int64_t stride = (a.in_swap || a.out_swap) ? (int64_t)a.sw_total * a.inner : a.inner;
     if (stride * 8 * 2 + 128 > 0xffffffffLL) return hipErrorInvalidValue;
+    if (a.perm_out && (a.in_swap || a.list_in || (int64_t)a.seg_end[2] * a.outer != a.nslab)) return hipErrorInvalidValue;
     if ((a.perm_in || a.perm_out) && (a.Ntok > 0x7fffffffLL || a.perm_k * 8 * 4 > 0xffffffffLL)) return hipErrorInvalidValue;
   }
   // workgroups per CU: bounded by the 160 KB of LDS of a gfx950 CU (the runtime's occupancy query assumes 64 KB)

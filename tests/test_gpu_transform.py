@@ -1,0 +1,64 @@
+"""Spectral coefficients of the matrix-core path at the edges of the transform passes' tiles, against scipy's orthonormal
+DCT-II of the stored bf16 values.
+
+Tolerance 2e-3 relative L2, the bound the other transform tests use: three axis passes whose fp16 matrices and fp16
+intermediates each carry a relative rounding error of 2^-12 to 2^-11 (measured 4.6e-4)."""
+import numpy as np
+import pytest
+
+from oracle import freqformer as O
+from paper_2604_22808_amd import binding as B
+from paper_2604_22808_amd import workloads as WL
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+ALLOC = (1, 2, 4, 6, 0)   # low box, low+mid box, whole grid (twice), nothing
+
+
+# W of every number of 32-deep steps with and without a remainder; H keeping one to four coefficient tiles on the low box,
+# the low+mid box or the whole axis, and five (two passes); both head dimensions; more planes than workgroups and fewer
+@pytest.mark.parametrize("grid,d", [((16, 16, 16), 64), ((16, 32, 48), 128), ((16, 48, 80), 64), ((32, 64, 112), 64),
+                                    ((16, 16, 128), 128), ((16, 128, 32), 64), ((48, 64, 64), 64), ((16, 96, 96), 64),
+                                    ((16, 80, 64), 128), ((64, 48, 16), 64)])
+def test_spectral_coefficients(grid, d):
+    from scipy.fft import dctn
+    rng = np.random.default_rng(11)
+    N, heads = int(np.prod(grid)), len(ALLOC)
+    q, k, v = (WL.round_to_io(rng.standard_normal((1, heads, N, d)), "bf16") for _ in range(3))
+    band = WL.WORKLOADS["16k"].band
+    ctx = B.Context(1, heads, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    U.run_forward(ctx, q, k, v, "bf16", ALLOC)
+    index = O.band_partition(*grid, U.oracle_cfg(band))
+    worst = 0.0
+    for which, x in enumerate((q, k, v)):
+        for h in range(heads):
+            want = dctn(x[0, h].reshape(grid + (d,)), type=2, norm="ortho", axes=(0, 1, 2)).reshape(N, d)
+            for l, idx in enumerate(index):
+                if len(idx) == 0 or (which < 2 and not (ALLOC[h] >> l) & 1):
+                    continue   # Q~ and K~ exist on the bands a head runs
+                try:
+                    got = ctx.read_spectral(which, h, l)
+                except B.FreqAttnError as e:   # V~ of a slice without the high band may stop at the low+mid box
+                    assert e.status == B.EUNSUPPORTED and which == 2 and l == 2
+                    continue
+                worst = max(worst, U.errors(got, want[idx])[1])
+    print(f"spectral {grid} d={d}: rel-L2 {worst:.3e}", flush=True)
+    assert worst <= 2e-3, worst
+
+
+@pytest.mark.parametrize("value", [65536.0, float("inf"), float("nan")])
+def test_input_outside_fp16_is_reported(value):
+    """One input value that fp16 cannot hold, in a plane that several workgroups share."""
+    import torch
+    ctx, _ = U.make_ctx(WL.WORKLOADS["16k"], path=B.PATH_MFMA)
+    q = torch.zeros((1, 8, 16 * 32 * 32, 64), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty_like(q)
+    v = q.clone()
+    ctx.forward(q, q, v, [4] * 8, out)
+    ctx.check_range()
+    v[0, 3, 4321, 17] = value
+    ctx.forward(q, q, v, [4] * 8, out)
+    with pytest.raises(B.FreqAttnError) as e:
+        ctx.check_range()
+    assert e.value.status == B.ERANGE
