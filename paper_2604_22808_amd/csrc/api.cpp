@@ -273,7 +273,8 @@ static hipError_t device_setup(freqattn_ctx* c, hipStream_t st) {
   A(dev_alloc_bytes(*c, &c->lowK, lowb));
   A(dev_alloc_bytes(*c, &c->lowV, lowb));
   A(dev_alloc_bytes(*c, &c->Cbuf, (size_t)c->slices * c->nb * (c->nb - 1) * (size_t)std::max(g.n_summary, 1) * c->d * es));
-  const size_t stats_floats = (size_t)3 * c->d * (1 + 64);
+  // (the routed entry points do not run on an arena context: no stage-1 sums of launch_energy_reduce there)
+  const size_t stats_floats = (size_t)3 * c->d + std::max<size_t>((size_t)3 * c->d * 64, mf && !arena ? ENERGY_PART_FLOATS : 0);
   A(dev_alloc(*c, &c->d_stats, stats_floats));
   A(dev_alloc(*c, &c->d_range_flag, 64));
   if (e == hipSuccess) e = launch_fill_zero((float*)c->d_range_flag, 64, st);   // (a zero float is a zero int)

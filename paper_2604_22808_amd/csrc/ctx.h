@@ -253,9 +253,10 @@ hipError_t launch_probe_mfma(float* out, int blocks, int iters, hipStream_t st);
 hipError_t launch_convert_16(const void* in, void* out, int64_t n, int to_bf16, hipStream_t st);
 hipError_t launch_copy_slices(const void* in, void* out, const int32_t* slice_list, int n_slices, int64_t slice_bytes,
                               hipStream_t st);
+#define ENERGY_PART_FLOATS 49152
 struct EnergyWaves { int en[6]; int tot[3]; };   // waves whose slots hold this forward's partial sums, per statistics slot
 hipError_t launch_energy_reduce(const float* energy_part /*[6][DCT_MAX_WAVES][3][64]: Q, K, V (box), Q, K, V (whole grid)*/,
-                                const float* tot_part /*[3][DCT_MAX_WAVES][64] or NULL*/, float* stats /*[3][d] + 3*d*64 floats of scratch*/, int d,
+                                const float* tot_part /*[3][DCT_MAX_WAVES][64] or NULL*/, float* stats /*[3][d] + ENERGY_PART_FLOATS of scratch*/, int d,
                                 const EnergyWaves& nw, hipStream_t st);
 
 // ---- MFMA kernels (mfma_dct.hip, mfma_attn.hip) -------------------------------------------------------------------

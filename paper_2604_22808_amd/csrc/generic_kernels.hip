@@ -424,13 +424,17 @@ hipError_t launch_convert_16(const void* in, void* out, int64_t n, int to_bf16, 
 // whole.  Stage 2: one thread per (band, channel) adds the stage-1 sums of its chunk in ascending workgroup order.
 // With tot_part set, the tensors in slots 0..2 were only computed on the low+mid box: their high-band energy is the
 // energy of the input (Parseval, the transform is orthonormal) minus their low and mid energies.
+// What bounds the two stages is latency: stage 1 has a few MB of slots to read, so it is spread over the whole chip (one
+// workgroup per channel took 13 us of the routed forward at 64K tokens and 41 at 1M, now 6 and 23), and stage 2 shares the
+// sums of a channel among 16 threads (one thread walking through them took 16 us, now 5).
+#define ENERGY_PARTS 256   // stage-1 workgroups (a multiple of the channel chunks of a token)
 __global__ void __launch_bounds__(768) k_energy_reduce1(const float* __restrict__ part, const float* __restrict__ tot_part,
-                                                        float* __restrict__ part1 /*[d][3][64]*/, int d, EnergyWaves nw) {
+                                                        float* __restrict__ part1 /*[ENERGY_PARTS][3][64]*/, EnergyWaves nw) {
   // four groups of 192 threads share a workgroup's waves (group q takes every fourth of them), four loads in flight each
   __shared__ float red[4][192];
   const int b = blockIdx.x, q = threadIdx.x / 192, tid = threadIdx.x % 192, band = tid >> 6, col = tid & 63;
   const bool parseval = tot_part != nullptr && band == 2;
-  const int first = b + q * d, step = 4 * d;
+  const int first = b + q * ENERGY_PARTS, step = 4 * ENERGY_PARTS;
   float t[4] = {0.f, 0.f, 0.f, 0.f};
   for (int tensor = 0; tensor < 6; ++tensor) {   // slots: Q, K, V on the box (Parseval for the high band), Q, K, V on the whole grid
     const float* base = part + (size_t)tensor * DCT_MAX_WAVES * 192;
@@ -460,25 +464,31 @@ __global__ void __launch_bounds__(768) k_energy_reduce1(const float* __restrict_
   if (q == 0) part1[(size_t)b * 192 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
-__global__ void __launch_bounds__(384) k_energy_reduce2(const float* __restrict__ part1, float* __restrict__ stats, int d, int parseval) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= 3 * d) return;
-  const int band = idx / d, ch = idx % d;
-  const int chunks = d / 64, chunk = ch / 64, col = ch % 64;
+// One workgroup per band and channel chunk: 16 rows of 64 threads share the chunk's partial sums.
+__global__ void __launch_bounds__(1024) k_energy_reduce2(const float* __restrict__ part1, float* __restrict__ stats, int d, int parseval) {
+  __shared__ float red[16][64];
+  const int chunks = d / 64, band = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
+  const int row = threadIdx.x >> 6, col = threadIdx.x & 63;
   float t = 0.f;
-  for (int b = chunk; b < d; b += chunks) t += part1[(size_t)b * 192 + band * 64 + col];
+#pragma unroll 4
+  for (int b = chunk + row * chunks; b < ENERGY_PARTS; b += 16 * chunks) t += part1[(size_t)b * 192 + band * 64 + col];
+  red[row][col] = t;
+  __syncthreads();
+  if (row != 0) return;
+  for (int r = 1; r < 16; ++r) t += red[r][col];
   // The Parseval difference of a band that holds (almost) no energy can come out slightly negative (the low and mid
   // sums carry the rounding of the fp16 transform): an energy is never below zero.
-  stats[idx] = (parseval && band == 2 && t < 0.f) ? 0.f : t;   // (a NaN stays a NaN: the host reports it)
+  stats[band * d + chunk * 64 + col] = (parseval && band == 2 && t < 0.f) ? 0.f : t;   // (a NaN stays a NaN: the host reports it)
 }
 
-// stats: [3][d] results followed by at least 3 * d * 64 floats of scratch (the stage-1 sums)
+// stats: [3][d] results followed by ENERGY_PART_FLOATS of scratch (the stage-1 sums)
 hipError_t launch_energy_reduce(const float* energy_part, const float* tot_part, float* stats, int d, const EnergyWaves& nw,
                                 hipStream_t st) {
-  if (d % 64 != 0 || d <= 0) return hipErrorInvalidValue;
+  if (d <= 0 || d % 64 != 0 || ENERGY_PARTS % (d / 64) != 0) return hipErrorInvalidValue;
+  static_assert(ENERGY_PARTS * 192 == ENERGY_PART_FLOATS, "scratch of the stage-1 sums");
   float* part1 = stats + 3 * d;
-  hipLaunchKernelGGL(k_energy_reduce1, dim3(d), dim3(768), 0, st, energy_part, tot_part, part1, d, nw);
-  hipLaunchKernelGGL(k_energy_reduce2, dim3((3 * d + 383) / 384), dim3(384), 0, st, part1, stats, d, tot_part != nullptr ? 1 : 0);
+  hipLaunchKernelGGL(k_energy_reduce1, dim3(ENERGY_PARTS), dim3(768), 0, st, energy_part, tot_part, part1, nw);
+  hipLaunchKernelGGL(k_energy_reduce2, dim3(3 * (d / 64)), dim3(1024), 0, st, part1, stats, d, tot_part != nullptr ? 1 : 0);
   return hipGetLastError();
 }
 

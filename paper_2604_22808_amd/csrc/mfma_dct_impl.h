@@ -133,8 +133,8 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
     const int32_t o = (int32_t)(s % (uint32_t)a.outer);     // slab within the slice
     // slice of the caller's tensors; scatter passes: of the segment's tensor
     const int seg = !PERM_OUT || (int)sl < a.seg_end[0] ? 0 : (int)sl < a.seg_end[1] ? 1 : 2;
-    const int first = seg == 0 ? 0 : a.seg_end[seg - 1];
-    const int32_t* list = PERM_OUT ? a.list_seg[seg] : a.slice_list;
+    const int first = seg == 0 ? 0 : seg == 1 ? a.seg_end[0] : a.seg_end[1];
+    const int32_t* list = !PERM_OUT ? a.slice_list : seg == 0 ? a.list_seg[0] : seg == 1 ? a.list_seg[1] : a.list_seg[2];
     const int64_t slice = list ? list[sl - first] : (int64_t)sl - first;
     t.pidx = 0; t.bm_off = 0; t.mask = 7; t.in_base = nullptr; t.out_off = 0; t.out_base = nullptr;
     if (PERM_IN || PERM_OUT) {
@@ -150,12 +150,12 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
     } else if (a.list_in) {
       t.in_base = (const char*)((const uint16_t*)a.in + (slice * a.slice_elems + (int64_t)o * NI * a.inner + col0));
     } else if (PERM_OUT) {
-      t.in_base = (const char*)((const uint16_t*)a.in_seg[seg] + (((int64_t)s - (int64_t)first * a.outer) * NI * a.inner + col0));
+      t.in_base = (const char*)((const uint16_t*)(seg == 0 ? a.in_seg[0] : seg == 1 ? a.in_seg[1] : a.in_seg[2]) + (((int64_t)s - (int64_t)first * a.outer) * NI * a.inner + col0));
     } else {
       t.in_base = (const char*)((const uint16_t*)a.in + ((int64_t)s * NI * a.inner + col0));
     }
     if (PERM_OUT) {
-      t.out_base = (char*)a.out_seg[seg];
+      t.out_base = (char*)(seg == 0 ? a.out_seg[0] : seg == 1 ? a.out_seg[1] : a.out_seg[2]);
     } else if (a.out_swap) {
       const uint32_t sa = s / (uint32_t)a.sw, sb = s % (uint32_t)a.sw;
       t.out_off = ((int64_t)sa * NO * a.sw_total + sb + a.sw_off) * a.inner + col0;
