@@ -785,6 +785,11 @@ static hipError_t inverse_transform_mfma(Ctx& c, void* out, const void* v_in, hi
   a.nslab = (int64_t)ns * kh; a.outer = kh;
   if ((e = launch_mfma_dct_pass(a, c.num_cu, st)) != hipSuccess) return e;
 
+  IwhPassArgs f{};
+  f.in = c.tmp1; f.out = out; f.resid = delta ? v_in : nullptr; f.slice_list = slice_list; f.n_slices = ns;
+  f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw; f.Fh = c.d_Ft16[1]; f.Fw = c.d_Ft16[2];
+  if (!wide && iwh_fits(f)) return launch_iwh_pass(f, c.num_cu, st);   // H and W axes in one pass
+
   DctPassArgs b{};
   b.d = d; b.Ntok = c.N;
   b.in = c.tmp1; b.out = c.tmp0; b.M = c.d_Ft16[1]; b.ldm = H; b.n = kh; b.n_out = H; b.inner = (int64_t)kw * d;

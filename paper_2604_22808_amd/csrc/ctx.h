@@ -317,6 +317,16 @@ hipError_t launch_wh_pass_1(const WhPassArgs& a, int num_cu, hipStream_t st, int
 inline hipError_t launch_wh_pass(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
   return a.W <= 64 ? launch_wh_pass_0(a, num_cu, st, slots_out) : launch_wh_pass_1(a, num_cu, st, slots_out);
 }
+// H and W axes of the inverse transform in one pass (mfma_iwh_impl.h).
+struct IwhPassArgs {
+  const void* in; void* out; const void* resid;     // in: fp16 [n_slices][kh][T][kw][d]; out: bf16 [slices][T][H][W][d]; resid: like out, added, or NULL
+  const int32_t* slice_list; int n_slices;          // slices of out and resid
+  int T, H, W, d, kh, kw;                           // d: channels per token; kh, kw: coefficients (multiples of 16)
+  const half_t* Fh; const half_t* Fw;               // fp16 [H][H], [W][W]: rows are positions
+  int parts;                                        // (filled in by the launcher) workgroups that share a plane
+};
+bool iwh_fits(const IwhPassArgs& a);
+hipError_t launch_iwh_pass(const IwhPassArgs& a, int num_cu, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, hipStream_t st);
 hipError_t launch_transpose_bf16_to_f16(const void* in /*[R][Cc] bf16*/, void* out /*[Cc][R] fp16*/, int R, int Cc, hipStream_t st);
 hipError_t launch_mfma_attn(const AttnParams& p, const AttnItem* items, int n_items, int rows_per_item, int num_cu,

@@ -47,6 +47,26 @@ def test_spectral_coefficients(grid, d):
     assert worst <= 2e-3, worst
 
 
+# boxes of one and two 16-coefficient tiles per axis (n low and n low+mid heads: enough planes for the one-pass inverse), whole
+# planes and parts of planes per workgroup, added to V and - where the box is the whole grid - not
+@pytest.mark.parametrize("grid,d,n", [((16, 16, 16), 64, 32), ((32, 64, 48), 64, 4), ((16, 64, 32), 128, 4), ((32, 32, 64), 64, 8),
+                                      ((16, 128, 64), 64, 4), ((64, 32, 16), 128, 9)])
+def test_outputs_of_boxed_inverse(grid, d, n):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    N, alloc = int(np.prod(grid)), [1] * n + [2] * n
+    q, k, v = ((0.5 * torch.randn((1, 2 * n, N, d), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(3))
+    band = WL.WORKLOADS["16k"].band
+    ctx = B.Context(1, 2 * n, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    out = torch.empty_like(q)
+    ctx.forward(q, k, v, alloc, out)
+    heads = [0, n - 1, n, 2 * n - 1]
+    got, qh, kh, vh = (U.to_host64(x[:, heads]) for x in (out, q, k, v))
+    mx, rl = U.errors(got, O.forward(qh, kh, vh, grid, U.oracle_cfg(band), [alloc[h] for h in heads]))
+    print(f"boxed inverse {grid} d={d}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (mx, rl)
+
+
 @pytest.mark.parametrize("value", [65536.0, float("inf"), float("nan")])
 def test_input_outside_fp16_is_reported(value):
     """One input value that fp16 cannot hold, in a plane that several workgroups share."""
