@@ -703,7 +703,7 @@ static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int n
   hipError_t e;
   WhPassArgs f{};
   DctPassArgs t{};
-  void* const scratch3[3] = {c.tmp1, c.tmp0, c.Y};   // (Y is free until the band operators)
+  void* const scratch3[3] = {c.tmp1, c.tmp0, c.Y};   // (Y is free until the band operators, unless keep_outputs)
   int n = 0, total = 0;
   for (int i = 0; i < nseg; ++i) {
     if (segs[i].ns <= 0) continue;
@@ -717,6 +717,10 @@ static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int n
   f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw;
   int slots = 0;
   const bool fused = wh_fits(f);
+  if (fused && n == 3 && c.keep_outputs) {   // the third tensor's scratch is taken: two tensors, then one
+    if ((e = forward_transform_mfma(c, segs, 2, st, keep, energy_slot, tot_slot, width)) != hipSuccess) return e;
+    return forward_transform_mfma(c, segs + 2, 1, st, keep, energy_slot >= 0 ? energy_slot + 2 : -1, tot_slot >= 0 ? tot_slot + 2 : -1, width);
+  }
   if (fused) {
     f.Mh = c.d_F16[1]; f.Mw = c.d_F16[2];
     f.range_flag = c.d_range_flag;
@@ -836,6 +840,13 @@ static hipError_t forward_transform_generic(Ctx& c, const void* q, const void* k
   w.perm_out = c.d_perm;
   hipError_t e;
   if ((e = launch_generic_axis_pass(t, st)) != hipSuccess) return e;
+  if (c.keep_outputs) {   // the third tensor's scratch is taken: two tensors, then one
+    h.n_tensors = w.n_tensors = 2;
+    if ((e = launch_generic_axis_pass(h, st)) != hipSuccess) return e;
+    if ((e = launch_generic_axis_pass(w, st)) != hipSuccess) return e;
+    h.n_tensors = w.n_tensors = 1;
+    h.in[0] = h.in[2]; h.out[0] = mid[0]; w.in[0] = mid[0]; w.out[0] = w.out[2];
+  }
   if ((e = launch_generic_axis_pass(h, st)) != hipSuccess) return e;
   return launch_generic_axis_pass(w, st);
 }
@@ -1716,6 +1727,11 @@ extern "C" freqattn_status freqattn_route_mlp(freqattn_ctx* c, const void* q, co
   if (c->d % 64 != 0) return fail(c, FREQATTN_EUNSUPPORTED, "freqattn_route_mlp: head_dim must be a multiple of 64");
   if (c->nb != 3) return fail(c, FREQATTN_EUNSUPPORTED, "freqattn_route_mlp: the router scores three bands (section 3.5); a four-band context takes its allocation from the caller");
   hipStream_t st = (hipStream_t)stream;
+  struct KeepOutputs {   // Y^ of the last forward stays readable
+    Ctx& c;
+    explicit KeepOutputs(Ctx& c_) : c(c_) { c.keep_outputs = true; }
+    ~KeepOutputs() { c.keep_outputs = false; }
+  } keep(*c);
   freqattn_status fs = transforms_phase(c, q, k, v, st, true);
   if (fs != FREQATTN_OK) return fs;
   bool redo = false;

@@ -99,6 +99,7 @@ struct Ctx {
   float* d_energy_part = nullptr;                 // per-wave partial sums of the fused statistics (MFMA path)
   float* d_tot_part = nullptr;                    // per-wave partial sums of the inputs' squares (Q, K), MFMA path
   int tot_waves[3] = {0, 0, 0};                   // waves that stored sums of squares in the last W-axis pass, per statistics slot
+  bool keep_outputs = false;                      // transforms leave Y alone (routing without a forward: the last forward's Y^ stays readable)
   bool qk_on_mid_box = false;                     // the last routed transforms left Q~, K~ on the low+mid box only
   int energy_waves[6] = {0, 0, 0, 0, 0, 0};       // waves that stored band statistics in the last T-axis pass, per statistics slot
   int low_box[3] = {0, 0, 0}, mid_box[3] = {0, 0, 0};  // extent of the low / low+mid box per axis

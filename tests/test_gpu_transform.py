@@ -67,6 +67,22 @@ def test_outputs_of_boxed_inverse(grid, d, n):
     assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (mx, rl)
 
 
+@pytest.mark.parametrize("path", [B.PATH_MFMA, B.PATH_GENERIC])
+def test_routing_leaves_the_band_outputs_readable(path, monkeypatch):
+    """The transforms of a routing call that is no forward use scratch that is not the last forward's result."""
+    monkeypatch.setenv("FREQATTN_V_BOX", "1")   # (Q, K and V on the same box also at this size: three tensors per launch)
+    rng = np.random.default_rng(13)
+    grid, d, alloc = (16, 16, 32), 64, (1, 2, 4)
+    band = WL.WORKLOADS["16k"].band
+    q, k, v = (WL.round_to_io(rng.standard_normal((1, 3, int(np.prod(grid)), d)), "bf16") for _ in range(3))
+    ctx = B.Context(1, 3, d, grid, B.BF16, B.make_cfg(**band), path=path)
+    U.run_forward(ctx, q, k, v, "bf16", alloc)
+    before = [ctx.read_spectral(3, h, h) for h in range(3)]
+    ctx.route_mlp(*(U.to_device(2.0 * x, "bf16") for x in (v, q, k)), 0.5, *WL.router_weights())
+    for h in range(3):
+        assert np.array_equal(ctx.read_spectral(3, h, h), before[h]), h
+
+
 @pytest.mark.parametrize("value", [65536.0, float("inf"), float("nan")])
 def test_input_outside_fp16_is_reported(value):
     """One input value that fp16 cannot hold, in a plane that several workgroups share."""
