@@ -360,13 +360,26 @@ def main():
                    any(m & 4 for m in masks)]
     vbox = ctx.get_v_box()   # V~ of a slice without the high band on the low+mid box: V follows Q and K class by class
     nonhigh_present = cls_present[0] or cls_present[1] or any(m == 0 for m in masks)
+    # Launches: tensors that keep the same coefficient box share a W + H pass and a T pass where the one-pass kernels take the
+    # box (csrc/mfma_wh_0.hip, csrc/mfma_iwh.hip), else every axis of every tensor is a launch.
+    T, H, W = wl.grid
+    def kept(num):   # coefficients kept of an axis of n for the box num/4 of it
+        return [min(n, -(-(-(-num * n // 4)) // 16) * 16) for n in (T, H, W)]
+    def fwd_group(tensors, k):
+        return 0 if tensors == 0 else 2 if k[1] <= 64 and k[2] // 16 <= (8 if k[1] <= 32 else 5) else 3 * tensors
+    def inv_group(mask_of_class, k):
+        n = sum(1 for m in masks if mask_of_class(m)) * wl.batch
+        one = k[1] <= 32 and k[2] <= 32 and W <= 64 and n * T * (wl.head_dim // 64) * (H // 16) >= 512
+        return 0 if n == 0 else 2 if one else 3
+    low_k, mid_k, full_k = kept(1), kept(2), [T, H, W]
     if router is not None:   # routed: slices split into "ran the high band last time" and the rest
-        fwd_launches = (9 if nonhigh_present else 0) + ((9 if vbox else 6) if cls_present[2] else 0) + (0 if vbox else 3)
-    elif vbox:
-        fwd_launches = 6 * sum(cls_present) + (3 if nonhigh_present else 0) + (3 if cls_present[2] else 0)
+        fwd_launches = fwd_group((3 if vbox else 2) if nonhigh_present else 0, mid_k) + fwd_group(3 if cls_present[2] or not vbox else 0, full_k)
     else:
-        fwd_launches = 3 + 6 * sum(cls_present)
-    inv_launches = 3 * sum(cls_present) + (1 if any(m == 0 for m in masks) else 0)
+        fwd_launches = (fwd_group(2 if cls_present[0] else 0, low_k)
+                        + fwd_group((2 if cls_present[1] else 0) + (1 if vbox and nonhigh_present else 0), mid_k)
+                        + fwd_group(3 if cls_present[2] else 0 if vbox else 1, full_k))
+    inv_launches = (inv_group(lambda m: m & 1 and not m & 6, low_k) + inv_group(lambda m: m & 2 and not m & 4, mid_k)
+                    + inv_group(lambda m: m & 4, full_k) + (1 if any(m == 0 for m in masks) else 0))
     # single-band slices run their exchange inside the band items: its flops then belong to the band attention launch
     one_band = [m in (1, 2, 4) for m in masks]
     if any(one_band):
