@@ -458,6 +458,19 @@ static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int
     }
     blocks = std::max<int64_t>(1, (n_tiles + (int64_t)tpw * DCT_WAVES - 1) / ((int64_t)tpw * DCT_WAVES));
     if (blocks < cap) blocks = std::min<int64_t>(cap, (n_tiles + DCT_WAVES - 1) / DCT_WAVES);   // small launches: fill the machine first
+    if (MODE == DCT_SCATTER_EN || MODE == DCT_PLAIN_TOT) {
+      // Long-lived waves: a few workgroups beyond a whole number of rounds of the chip's places cost a round of their own
+      // (T pass of 67,584 tiles at 64K tokens: 1,056 workgroups on 1,024 places 109 us, 1,024 workgroups 82 us), so the
+      // grid is rounded down to whole rounds of what registers and LDS let a compute unit hold.
+      static int places = 0;
+      if (places == 0) {
+        hipFuncAttributes at;
+        if (hipFuncGetAttributes(&at, (const void*)k_dct_pass<NI, MT, MODE>) != hipSuccess || at.numRegs <= 0) { (void)hipGetLastError(); places = occ; }
+        else places = std::max(1, std::min(512 / ((at.numRegs + 7) / 8 * 8), (160 * 1024) / lds_bytes));
+      }
+      const int64_t round = (int64_t)num_cu * places;
+      if (blocks > round) blocks -= blocks % round;
+    }
   } else if (blocks > cap) {
     blocks = cap;
   }
