@@ -312,7 +312,7 @@ struct WhPassArgs {
   int32_t* range_flag;                              // set when an input value leaves the fp16 range
   int members;                                      // (filled in by the launcher) workgroups that share a plane
 };
-bool wh_fits(const WhPassArgs& a);   // whether the pass takes these sizes and is the faster way
+bool wh_fits(const WhPassArgs& a);   // whether the pass takes planes of this size and is the faster way (the same for every box of them)
 hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W <= 64
 hipError_t launch_wh_pass_1(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W > 64
 inline hipError_t launch_wh_pass(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {

@@ -20,9 +20,8 @@
 //
 // What bounds it and what it measured (one tensor, against the two passes it replaces): HBM where few workgroups share a
 // plane - 22 slices of 64^3 x 128 on the 32 x 32 box 631 -> 378 us (4.9 TB/s); LDS traffic, matrix instructions and the
-// barrier per two rows, one after the other, where four do - 17 slices of 64^3 x 128 with 64 x 64 kept 838 -> 710 us, 12 of
-// 64 x 128 x 128 x 128 with 64 x 64 kept 1373 -> 1380 us.  Stores of 8 bytes per lane straight from the accumulators
-// cost half of the second figure's time again (844 us): hence the trip through LDS.
+// barrier per two rows, one after the other, where four do - 17 slices of 64^3 x 128 with 64 x 64 kept 838 -> 710 us.  Stores
+// of 8 bytes per lane straight from the accumulators made that 844 us: hence the trip through LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -374,7 +373,8 @@ static hipError_t wh_dispatch(const WhPassArgs& a, int num_cu, hipStream_t st, i
   const int kht = a.kh / 16;
   if (kht == 1) return a.kw > 16 ? wh_launch<NW16, 1, 2, 1>(a, num_cu, st, slots_out) : wh_launch<NW16, 1, 1, 1>(a, num_cu, st, slots_out);
   if (kht == 2) return a.kw > 16 ? wh_launch<NW16, 2, 2, 1>(a, num_cu, st, slots_out) : wh_launch<NW16, 2, 1, 1>(a, num_cu, st, slots_out);
-  if (kht <= 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
+  if constexpr (NW16 <= 5)   // (wider planes are taken with at most 32 rows: wh_fits)
+    if (kht <= 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
   return hipErrorInvalidValue;
 }
 

@@ -83,6 +83,32 @@ def test_routing_leaves_the_band_outputs_readable(path, monkeypatch):
         assert np.array_equal(ctx.read_spectral(3, h, h), before[h]), h
 
 
+# planes of which the whole, or all but the low box, is beyond the one-pass kernel; the last one is taken by it whole
+@pytest.mark.parametrize("grid", [(16, 128, 64), (16, 128, 96), (16, 64, 128), (16, 32, 128)])
+@pytest.mark.parametrize("noise", [1.0, 1e-3])   # (with little noise the high band's energy has to be taken again, on the whole grid)
+def test_outputs_do_not_depend_on_the_box(grid, noise, monkeypatch):
+    """The routed forward computes a head's coefficients on the low+mid box or the whole grid by what it guessed, and the forward
+    with the allocation given on the low box where that is enough: the outputs are the same bits after right and wrong guesses."""
+    import torch
+    monkeypatch.setenv("FREQATTN_V_BOX", "1")
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    T, H, W = grid
+    wave = [torch.cos(torch.arange(n, device="cuda") * (2.5 / n)) for n in grid]
+    smooth = (wave[0][:, None, None] * wave[1][:, None] * wave[2]).reshape(-1, 1)
+    q, k, v = ((smooth + noise * torch.randn((1, 6, T * H * W, 64), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(3))
+    band = WL.WORKLOADS["64k"].band
+    ctx, ref = (B.Context(1, 6, 64, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA) for _ in range(2))
+    out, plain = torch.empty_like(q), torch.empty_like(q)
+    seen = set()
+    for t in (0.05, 0.05, 0.95, 0.95, 0.5, 0.05):   # nothing to guess from; then right and wrong guesses
+        alloc, _ = ctx.forward_routed(q, k, v, t, *WL.router_weights(), out)
+        ref.forward(q, k, v, alloc, plain)
+        torch.cuda.synchronize()
+        assert torch.equal(out, plain), (t, list(alloc), float((out.float() - plain.float()).abs().max()))
+        seen.add(tuple(int(a) for a in alloc))
+    assert len(seen) >= 2, seen   # the sequence really changes the allocation
+
+
 @pytest.mark.parametrize("value", [65536.0, float("inf"), float("nan")])
 def test_input_outside_fp16_is_reported(value):
     """One input value that fp16 cannot hold, in a plane that several workgroups share."""
