@@ -884,10 +884,17 @@ static hipError_t inverse_transform(Ctx& c, void* out, const void* v_in, hipStre
   return launch_generic_axis_pass(t, st);
 }
 
+// Rows of a low-band group that the band operator writes itself: the lanes that hold a group's output store them one after the
+// other, which costs less than a launch for short groups and more for long ones.  Whole forwards of low heads, written by
+// the operator / by a launch of its own: 64K tokens x 24 heads x 64, c = 4 321 / 325 us, 16 321 / 325, 32 330 / 329, 64
+// 351 / 345, 256 486 / 446; 256K x 12 x 128, c = 4 1229 / 1234, 16 1208 / 1207, 32 1213 / 1206, 256 1498 / 1332.
+#define LOW_FILL_MAX 16
+static int low_fill(const Ctx& c) { return c.cfg.low_compress <= LOW_FILL_MAX ? c.cfg.low_compress : 1; }
+
 static void fill_attn_params(const Ctx& c, AttnParams& p, float scale) {
   std::memset(&p, 0, sizeof(p));
   p.specQ = c.specQ; p.specK = c.specK; p.specV = c.specV; p.Y = c.Y;
-  p.lowQ = c.lowQ; p.lowK = c.lowK; p.lowV = c.lowV; p.low_c = c.cfg.low_compress; p.C = c.Cbuf;
+  p.lowQ = c.lowQ; p.lowK = c.lowK; p.lowV = c.lowV; p.low_c = c.cfg.low_compress; p.low_fill = low_fill(c); p.C = c.Cbuf;
   p.mid_row_ptr = c.d_row_ptr; p.mid_col_idx = c.d_col_idx;
   p.mid2_row_ptr = c.d_row_ptr2; p.mid2_col_idx = c.d_col_idx2;
   p.nb = c.nb;
@@ -1122,17 +1129,21 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
       if (l == LOW) {
         s.Q = (const float*)c->lowQ; s.K = (const float*)c->lowK; s.V = (const float*)c->lowV; s.O = (float*)c->Y;
         s.slice_stride = s.kv_slice_stride = c->nbar * c->d; s.o_slice_stride = Nd; s.nq = s.nk = (int)c->nbar; s.mode = 0;
-        s.rep = c->cfg.low_compress; s.n_out = (int)c->band_n[LOW];
+        s.rep = c->cfg.low_compress; s.fill = low_fill(*c); s.n_out = (int)c->band_n[LOW];
         continue;
       }
       const int64_t o = c->band_off[l] * c->d;
       s.Q = (const float*)c->specQ + o; s.K = (const float*)c->specK + o; s.V = (const float*)c->specV + o; s.O = (float*)c->Y + o;
-      s.slice_stride = s.kv_slice_stride = s.o_slice_stride = Nd; s.nq = s.nk = s.n_out = (int)c->band_n[l]; s.rep = 1;
+      s.slice_stride = s.kv_slice_stride = s.o_slice_stride = Nd; s.nq = s.nk = s.n_out = (int)c->band_n[l]; s.rep = s.fill = 1;
       s.mode = l == HIGH ? 2 : 1; s.window = c->cfg.high_window; s.block = c->cfg.mid_block;
       s.row_ptr = l == MID2 ? c->d_row_ptr2 : c->d_row_ptr; s.col_idx = l == MID2 ? c->d_col_idx2 : c->d_col_idx;
     }
     HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));
     tm.done("band_attention_fused");
+  }
+  if (low_fill(*c) < c->cfg.low_compress && c->n_list[LOW] > 0) {
+    HIP_TRY(c, launch_expand_low(c->Y, L + c->off_list[LOW], c->n_list[LOW], c->N, c->band_n[LOW], c->cfg.low_compress, c->d * (int64_t)esize(*c), st));
+    tm.done("low_expand");
   }
   // section 3.6: remaining summary tokens (of the bands a slice runs, from the band outputs), then the exchange of
   // the slices that run more than one band
@@ -1152,7 +1163,7 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
         x.Q = (const float*)c->Y + c->band_off[l] * c->d; x.O = (float*)c->Y + c->band_off[l] * c->d;
         x.K = x.V = (const float*)c->Cbuf + (int64_t)l * ap.m2 * c->d;
         x.slice_list = L + c->off_list[l]; x.n_slices = c->n_list[l];
-        x.slice_stride = x.o_slice_stride = c->N * c->d; x.rep = 1; x.n_out = (int)c->band_n[l]; x.kv_slice_stride = (int64_t)c->nb * ap.m2 * c->d;
+        x.slice_stride = x.o_slice_stride = c->N * c->d; x.rep = x.fill = 1; x.n_out = (int)c->band_n[l]; x.kv_slice_stride = (int64_t)c->nb * ap.m2 * c->d;
         x.nq = (int)c->band_n[l]; x.nk = c->n_c[l];
       }
       HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));

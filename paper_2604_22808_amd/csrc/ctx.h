@@ -41,7 +41,8 @@ struct AttnParams {
   int32_t band_n[NBMAX];
   int32_t n_c[NBMAX]; // valid rows of C per band
   int32_t nb;         // bands: 3 or 4
-  int32_t low_c;      // compression factor c: every low-band row takes its group's output
+  int32_t low_c;      // compression factor c: group i's output belongs to low-band rows i c .. i c + c - 1
+  int32_t low_fill;   // rows of a group the band operator writes itself: c, or 1 when launch_expand_low fills the rest
   int32_t N, d, nbar, m2;  // m2 = (nb-1) m = rows reserved per band in C
   int32_t mid_block, high_window;
   float scale;
@@ -207,7 +208,7 @@ struct GAttnSeg {
   int mode;                 // 0 dense, 1 block list, 2 window
   const int32_t* row_ptr; const int32_t* col_idx; int block; int window;
   int residual;             // O = Q + attention (exchange)
-  int rep, n_out;           // query row i is written to output rows i rep .. i rep + rep - 1 below n_out (low band: its whole group)
+  int rep, fill, n_out;     // query row i is written to output rows i rep .. i rep + fill - 1 below n_out (low band: its group)
   int rows, tiles, first_block;   // filled in by the launcher: query rows per workgroup, workgroups per slice, first workgroup
 };
 struct GAttnArgs { GAttnSeg seg[NBMAX]; int nseg; int d; float scale; };
@@ -233,6 +234,9 @@ struct PoolArgs {
   int64_t N; int d, is_half, num_cu;
 };
 hipError_t launch_band_pools(const PoolArgs& p, hipStream_t st);
+// Rows of the low band that the band operator left out (low_fill = 1): rows i c + 1 .. i c + c - 1 take row i c.
+hipError_t launch_expand_low(void* Y, const int32_t* slice_list, int n_slices, int64_t N, int64_t n_low, int c, int64_t row_bytes,
+                             hipStream_t st);
 // High-band summary tokens of the slices in `sel` (bit set, nsel of them) from the untransformed bf16 V.
 hipError_t launch_vsum(const void* V, const void* Wsum, float* part, void* C, const uint64_t sel[4], int nsel, int64_t N,
                        int d, int nsplit, int64_t n_high, const int m_eff[NBMAX], int m2rows, hipStream_t st);   // (three-band contexts only)

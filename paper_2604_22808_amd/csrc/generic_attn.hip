@@ -205,7 +205,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
     o *= 1.f / l;
     const int64_t q = q0 + row;
     if (s.residual) o += row4<EXACT>(Q + q * d, ch, d);
-    for (int64_t r = q * s.rep; r < min((q + 1) * s.rep, (int64_t)s.n_out); ++r) {
+    for (int64_t r = q * s.rep; r < min(q * s.rep + s.fill, (int64_t)s.n_out); ++r) {
       float* dst = O + r * d + ch;
       if (EXACT) {
         *(float4v*)dst = o;

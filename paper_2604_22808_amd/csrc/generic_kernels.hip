@@ -32,7 +32,7 @@ struct PoolKernelArgs {
 //    scheduling.  The mean goes to the C rows of the other bands (ascending band index).
 // What bounds it: at ordinary sizes the latency of one chunk (16 waves per workgroup: a chunk of 115 KB takes seven loads
 // per thread); chunks above 1 MB are cut into parts that meet in k_summaries_finish.  Compression (3 launches), pooling
-// (1-2) and the low band's expansion (1; now written by the band operator) took 34 us at 16K tokens x 8 heads x 64, 136 us at
+// (1-2) and the low band's expansion (1; groups of up to 16 rows are now written by the band operator) took 34 us at 16K tokens x 8 heads x 64, 136 us at
 // 256K x 24 x 128 and 78 + 19 us in fp32 at 12,150 x 4 x 64; this launch takes 11, 65 and 8 us.
 template <typename T, int VW, int NT>
 __global__ void __launch_bounds__(NT) k_band_pools(PoolKernelArgs a) {
@@ -177,6 +177,28 @@ hipError_t launch_band_pools(const PoolArgs& p, hipStream_t st) {
   }
   if (p.d % 4 == 0) return wide ? launch_pools_v<float, 4, 1024>(k, p.n_low_slices, slices, st) : launch_pools_v<float, 4, 256>(k, p.n_low_slices, slices, st);
   return launch_pools_v<float, 1, 1024>(k, p.n_low_slices, slices, st);
+}
+
+// Rows of a low-band group behind its first one, which holds the band operator's output.  One thread per VEC and row.
+template <typename VEC>
+__global__ void __launch_bounds__(256) k_expand_low(VEC* Y, const int32_t* slice_list, int64_t slice_vecs, int64_t n_low, int c,
+                                                    int row_vecs, int64_t total) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= total) return;
+  const int64_t r = idx / row_vecs, i = r % n_low, first = i - i % c;
+  if (i == first) return;
+  VEC* Ys = Y + slice_list[r / n_low] * slice_vecs + idx % row_vecs;
+  Ys[i * row_vecs] = Ys[first * row_vecs];
+}
+hipError_t launch_expand_low(void* Y, const int32_t* slice_list, int n_slices, int64_t N, int64_t n_low, int c, int64_t row_bytes,
+                             hipStream_t st) {
+  const int vec = row_bytes % 16 == 0 ? 16 : 4;
+  const int64_t row_vecs = row_bytes / vec, total = n_slices * n_low * row_vecs, blocks = (total + 255) / 256;
+  if (total == 0) return hipSuccess;
+  if (row_bytes % 4 != 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
+  if (vec == 16) hipLaunchKernelGGL(k_expand_low<uint4>, dim3((unsigned)blocks), dim3(256), 0, st, (uint4*)Y, slice_list, N * row_vecs, n_low, c, (int)row_vecs, total);
+  else hipLaunchKernelGGL(k_expand_low<uint32_t>, dim3((unsigned)blocks), dim3(256), 0, st, (uint32_t*)Y, slice_list, N * row_vecs, n_low, c, (int)row_vecs, total);
+  return hipGetLastError();
 }
 
 // Summary tokens of the projected forward (sections 3.1 + 3.6): the mean over a chunk of band rows commutes with the

@@ -104,12 +104,13 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
     const int q0 = item.q0;
     const uint16_t *Qp, *Kp, *Vp;
     uint16_t* Op;
-    int nq, nk, rep = 1;
+    int nq, nk, rep = 1, fill = 1;
     if (kind == 0) {
       const int64_t o = slice * p.nbar * D;
       Qp = (const uint16_t*)p.lowQ + o; Kp = (const uint16_t*)p.lowK + o; Vp = (const uint16_t*)p.lowV + o;
-      // (section 3.4.1 reading: every low-band row takes the output of its group, so row i goes to rows i c .. i c + c - 1)
-      Op = (uint16_t*)p.Y + slice * p.N * D; nq = nk = p.nbar; rep = p.low_c;
+      // (section 3.4.1 reading: every low-band row takes the output of its group, so row i goes to rows i c .. i c + c - 1,
+      // or to the first of them when there are many: launch_expand_low)
+      Op = (uint16_t*)p.Y + slice * p.N * D; nq = nk = p.nbar; rep = p.low_c; fill = p.low_fill;
     } else if (kind == 1 || kind == 2) {
       const int64_t o = (slice * p.N + p.band_off[band]) * D;
       Qp = (const uint16_t*)p.specQ + o; Kp = (const uint16_t*)p.specK + o; Vp = (const uint16_t*)p.specV + o;
@@ -501,7 +502,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
 #pragma unroll
             for (int b = 0; b < 4; ++b) st4[b] = pack_h2(o[2 * b], o[2 * b + 1]);
             *(uint4v*)dst = st4;
-            for (int c = 1; c < rep; ++c)
+            for (int c = 1; c < fill; ++c)
               if ((int64_t)row * rep + c < p.band_n[LOW]) *(uint4v*)(dst + c * D) = st4;
           }
         }

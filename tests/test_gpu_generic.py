@@ -66,3 +66,18 @@ def test_matrix_core_pooling_of_long_chunks(alloc):
     mx, rl = U.errors(got, O.forward(q, k, v, wl.grid, U.oracle_cfg(band), alloc))
     print(f"16k m=1 c=7 {alloc}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
     assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
+
+
+@pytest.mark.parametrize("c", [16, 17, 2 ** 31 - 1])
+@pytest.mark.parametrize("dtype,path,d", [("bf16", B.PATH_MFMA, 64), ("f32", B.PATH_GENERIC, 64), ("f32", B.PATH_GENERIC, 6)])
+def test_long_low_band_groups(dtype, path, d, c):
+    """Low-band groups whose rows the band operator writes itself (up to 16), the first longer one (the last group shorter
+    still) and a group length far beyond the band; with and without the exchange inside the band items."""
+    rng = np.random.default_rng(6)
+    grid, alloc = (16, 16, 32), (1, 3)
+    cfgd = dict(WL.WORKLOADS["16k"].band, low_compress=c)
+    q, k, v = (WL.round_to_io(0.7 * rng.standard_normal((1, 2, int(np.prod(grid)), d)), dtype) for _ in range(3))
+    ctx = B.Context(1, 2, d, grid, B.F32 if dtype == "f32" else B.BF16, B.make_cfg(**cfgd), path=path)
+    mx, rl = U.errors(U.run_forward(ctx, q, k, v, dtype, alloc), O.forward(q, k, v, grid, O.BandConfig(**cfgd), alloc))
+    print(f"low groups of {c} {dtype} d={d}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= U.TOL[dtype][0] and rl <= U.TOL[dtype][1], (mx, rl)
