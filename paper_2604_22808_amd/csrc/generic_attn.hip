@@ -55,7 +55,8 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
     qend = min(min(q0 + ROWS, (I + 1) * s.block), s.nq);
     if (q0 >= qend) return;   // (uniform over the workgroup)
     e0 = s.row_ptr[I];
-    nkeys = (s.row_ptr[I + 1] - e0) * s.block;
+    const int e1 = s.row_ptr[I + 1];   // (columns ascend: only the last block of the list can be the band's short one)
+    nkeys = e1 > e0 ? (e1 - 1 - e0) * s.block + min(s.block, s.nk - s.col_idx[e1 - 1] * s.block) : 0;
   } else {
     q0 = tile * ROWS;
     qend = min(q0 + ROWS, s.nq);
@@ -255,6 +256,7 @@ hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st) {
   int64_t blocks = 0;
   for (int i = 0; i < n; ++i) {
     GAttnSeg& s = a.seg[i];
+    if (s.mode == 1) s.block = std::min(s.block, s.nq);   // (one block longer than the band is one block of the band's length)
     s.rows = (a.d > 128 || (s.mode == 1 && s.block <= 16) || blocks32 < 2 * num_cu) ? 16 : 32;
     int64_t tiles = ((int64_t)s.nq + s.rows - 1) / s.rows;
     if (s.mode == 1) tiles = (((int64_t)s.nq + s.block - 1) / s.block) * ((s.block + s.rows - 1) / s.rows);

@@ -40,6 +40,15 @@ def test_generic_attention_blocks_and_windows(block, window, c):
     _check((7, 24, 26), 64, 2, (7, 7), mid_block=block, mid_stride=3, high_window=window, n_summary=9, low_compress=c)
 
 
+@pytest.mark.parametrize("block", [100, 1190, 1200, 100000, 2 ** 31 - 1])
+def test_generic_attention_blocks_beyond_the_band(block):
+    """Mid blocks of which the last is cut short by the band (1,199 rows), down to one block that holds all of it (a dense mid
+    band) or is longer than it by any amount: the keys and query tiles end with the band."""
+    cfgd = dict(WL.WORKLOADS["tiny_f32"].band, mid_block=block)
+    assert len(O.band_partition(9, 26, 44, O.BandConfig(**cfgd))[1]) == 1199
+    _check((9, 26, 44), 64, 2, (2, 6), mid_block=block, mid_diag=0, mid_stride=3, n_summary=5)
+
+
 @pytest.mark.parametrize("grid,d,dtype", [((1, 15, 16), 4, "f32"), ((17, 3, 31), 6, "bf16"), ((2, 64, 65), 12, "f32"),
                                           ((130, 5, 4), 20, "bf16"), ((3, 4, 200), 33, "f32")])
 def test_generic_axis_lengths(grid, d, dtype):
