@@ -258,7 +258,10 @@ freqattn_status freqattn_dense_forward(freqattn_ctx* ctx, const void* q, const v
 /* ---- per-stage timing of the forward ---------------------------------------------------------------------------
  * When enabled, every forward records HIP events on its stream around each stage (the last 64 forwards are kept).
  * freqattn_stage_times waits for the last forward's events and returns, for stage s < *n_stages, its name and the
- * milliseconds between its events averaged over the kept forwards since timing was enabled.  names_out HOST
+ * milliseconds between its events averaged over the kept forwards since timing was enabled.  Stages of a forward, in order:
+ * forward_transform (routed: then router, forward_transform_high_qk); low_compress_summaries (the low band's compression with the summary tokens that do not wait
+ * for a band operator; low_compress without any); band_attention_fused, or low_attention, mid_attention (both mid bands) and
+ * high_attention; low_expand (low_compress above 16); summaries_active or summaries; exchange; inverse_transform.  names_out HOST
  * [max_stages] receives pointers to static strings; ms_out HOST [max_stages]. */
 freqattn_status freqattn_set_stage_timing(freqattn_ctx* ctx, int32_t enabled);
 freqattn_status freqattn_stage_times(freqattn_ctx* ctx, int32_t max_stages, const char** names_out, float* ms_out,

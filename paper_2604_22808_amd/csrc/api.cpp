@@ -1122,9 +1122,11 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
     GAttnArgs g{};
     g.d = c->d; g.scale = scale;
     static const int order[NBMAX] = {HIGH, MID2, MID, LOW};
-    for (int l : order) {
+    g.nseg = NBMAX;   // (a band without slices stays an empty segment)
+    for (int i = 0; i < NBMAX; ++i) {
+      const int l = order[i];
       if (l >= c->nb || c->n_list[l] == 0) continue;
-      GAttnSeg& s = g.seg[g.nseg++];
+      GAttnSeg& s = g.seg[i];
       s.slice_list = L + c->off_list[l]; s.n_slices = c->n_list[l];
       if (l == LOW) {
         s.Q = (const float*)c->lowQ; s.K = (const float*)c->lowK; s.V = (const float*)c->lowV; s.O = (float*)c->Y;
@@ -1138,8 +1140,18 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
       s.mode = l == HIGH ? 2 : 1; s.window = c->cfg.high_window; s.block = c->cfg.mid_block;
       s.row_ptr = l == MID2 ? c->d_row_ptr2 : c->d_row_ptr; s.col_idx = l == MID2 ? c->d_col_idx2 : c->d_col_idx;
     }
-    HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));
-    tm.done("band_attention_fused");
+    if (c->launch_mode == FREQATTN_LAUNCH_FUSED) {
+      HIP_TRY(c, launch_generic_attn(g, c->num_cu, st));
+      tm.done("band_attention_fused");
+    } else {
+      HIP_TRY(c, launch_generic_attn(g, c->num_cu, st, 3, 1));
+      tm.done("low_attention");
+      HIP_TRY(c, launch_generic_attn(g, c->num_cu, st, 2, 1));
+      HIP_TRY(c, launch_generic_attn(g, c->num_cu, st, 1, 1));
+      tm.done("mid_attention");
+      HIP_TRY(c, launch_generic_attn(g, c->num_cu, st, 0, 1));
+      tm.done("high_attention");
+    }
   }
   if (low_fill(*c) < c->cfg.low_compress && c->n_list[LOW] > 0) {
     HIP_TRY(c, launch_expand_low(c->Y, L + c->off_list[LOW], c->n_list[LOW], c->N, c->band_n[LOW], c->cfg.low_compress, c->d * (int64_t)esize(*c), st));

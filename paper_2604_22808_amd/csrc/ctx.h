@@ -212,7 +212,9 @@ struct GAttnSeg {
   int rows, tiles, first_block;   // filled in by the launcher: query rows per workgroup, workgroups per slice, first workgroup
 };
 struct GAttnArgs { GAttnSeg seg[NBMAX]; int nseg; int d; float scale; };
-hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st);
+// Launches the branches [first, first + count) of `a`; how their rows are split is decided for all of them together, so a branch
+// gives the same bits alone.
+hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st, int first = 0, int count = NBMAX);
 
 // Low-band compression of Q~, K~ and V~ for the slices in low_list, and summary tokens of the bands of all slices, written
 // into the C slots of the other bands: one launch (pool = false: the compression alone, n_low_slices = 0: the

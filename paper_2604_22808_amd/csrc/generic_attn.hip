@@ -240,7 +240,7 @@ hipError_t launch_dc(const GAttnArgs& a, int blocks, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st) {
+hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st, int first, int count) {
   // Query rows per workgroup.  32 rows load every key and value once for twice the queries, but a block list with at most
   // 16 rows per query block would leave half of them empty, and a launch that does not fill the compute units twice over
   // gains more from twice the workgroups.  (head_dim > 128: the registers hold 16 rows only.)
@@ -248,8 +248,8 @@ hipError_t launch_generic_attn(GAttnArgs a, int num_cu, hipStream_t st) {
   int n = 0;
   for (int i = 0; i < a.nseg; ++i) {
     if (a.seg[i].nq <= 0 || a.seg[i].nk <= 0 || a.seg[i].n_slices <= 0) continue;
-    a.seg[n++] = a.seg[i];
-    blocks32 += (int64_t)((a.seg[n - 1].nq + 31) / 32) * a.seg[n - 1].n_slices;
+    blocks32 += (int64_t)((a.seg[i].nq + 31) / 32) * a.seg[i].n_slices;
+    if (i >= first && i < first + count) a.seg[n++] = a.seg[i];
   }
   a.nseg = n;
   if (n == 0) return hipSuccess;

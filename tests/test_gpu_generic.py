@@ -57,6 +57,27 @@ def test_generic_axis_lengths(grid, d, dtype):
     _check(grid, d, 3, (0, 5, 7), dtype, n_summary=3)
 
 
+@pytest.mark.parametrize("bands", [3, 4])
+def test_generic_branches_in_launches_of_their_own(bands):
+    """One launch per branch: the stages are the branches' own and the outputs the same bits as from one launch."""
+    import torch
+    grid, d, alloc = (9, 20, 24), 64, (1, 2, 4, 7 if bands == 3 else 14)
+    gen = torch.Generator(device="cuda").manual_seed(15)
+    q, k, v = (torch.randn((1, 4, int(np.prod(grid)), d), device="cuda", generator=gen) for _ in range(3))
+    cfgd = dict(WL.WORKLOADS["tiny_f32"].band, high_window=50, **(dict(mid2_num=3, mid2_den=4) if bands == 4 else {}))
+    ctx = B.Context(1, 4, d, grid, B.F32, B.make_cfg(**cfgd), path=B.PATH_GENERIC)
+    outs, names = [], []
+    for mode in (B.LAUNCH_FUSED, B.LAUNCH_SEPARATE):
+        ctx.set_launch_mode(mode)
+        ctx.set_stage_timing(True)
+        outs.append(torch.empty_like(q))
+        ctx.forward(q, k, v, alloc, outs[-1])
+        torch.cuda.synchronize()
+        names.append([n for n, _ in ctx.stage_times() if n.endswith("attention") or n.endswith("fused")])
+    assert names == [["band_attention_fused"], ["low_attention", "mid_attention", "high_attention"]], names
+    assert torch.equal(*outs)
+
+
 @pytest.mark.parametrize("d,m,c", [(64, 1, 5), (30, 2, 3)])
 def test_generic_pooling_of_long_chunks(d, m, c):
     """Summary chunks above 1 MB (10,000 rows and more of the high band) are pooled in parts; rows of 16 bytes and of single
