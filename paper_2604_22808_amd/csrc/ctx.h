@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "freqattn.h"
+#include "per_device.h"
 
 namespace fa {
 
@@ -265,6 +266,14 @@ struct EnergyWaves { int en[6]; int tot[3]; };   // waves whose slots hold this 
 hipError_t launch_energy_reduce(const float* energy_part /*[6][DCT_MAX_WAVES][3][64]: Q, K, V (box), Q, K, V (whole grid)*/,
                                 const float* tot_part /*[3][DCT_MAX_WAVES][64] or NULL*/, float* stats /*[3][d] + ENERGY_PART_FLOATS of scratch*/, int d,
                                 const EnergyWaves& nw, hipStream_t st);
+
+// Lets `kernel` ask for `bytes` of dynamic LDS on the current device.
+inline hipError_t allow_lds(OncePerDevice& limit, const void* kernel, int bytes) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return (hipError_t)limit.run(dev, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 // ---- MFMA kernels (mfma_dct.hip, mfma_attn.hip) -------------------------------------------------------------------
 struct DctPassArgs {

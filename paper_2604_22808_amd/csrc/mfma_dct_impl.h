@@ -462,12 +462,13 @@ static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int
       // Long-lived waves: a few workgroups beyond a whole number of rounds of the chip's places cost a round of their own
       // (T pass of 67,584 tiles at 64K tokens: 1,056 workgroups on 1,024 places 109 us, 1,024 workgroups 82 us), so the
       // grid is rounded down to whole rounds of what registers and LDS let a compute unit hold.
-      static int places = 0;
-      if (places == 0) {
+      static const int places = [] {
         hipFuncAttributes at;
-        if (hipFuncGetAttributes(&at, (const void*)k_dct_pass<NI, MT, MODE>) != hipSuccess || at.numRegs <= 0) { (void)hipGetLastError(); places = occ; }
-        else places = std::max(1, std::min(512 / ((at.numRegs + 7) / 8 * 8), (160 * 1024) / lds_bytes));
-      }
+        if (hipFuncGetAttributes(&at, (const void*)k_dct_pass<NI, MT, MODE>) == hipSuccess && at.numRegs > 0)
+          return std::max(1, std::min(512 / ((at.numRegs + 7) / 8 * 8), (160 * 1024) / lds_bytes));
+        (void)hipGetLastError();
+        return occ;
+      }();
       const int64_t round = (int64_t)num_cu * places;
       if (blocks > round) blocks -= blocks % round;
     }
@@ -487,19 +488,16 @@ static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int
   // (three or four per SIMD: a tile is 8 KB, and the loads in flight are what keeps the memory system busy); the passes
   // over 128 rows measured 3 % faster held to two workgroups per unit, which is enforced by asking for LDS the kernel does
   // not use.  FREQATTN_DCT_WGS / FREQATTN_DCT_WGS_128 override (0 = no limit).
-  static int dyn_lds = -1;
-  if (dyn_lds < 0) {
+  static const int dyn_lds = [] {
     const char* e = getenv(NI >= 128 ? "FREQATTN_DCT_WGS_128" : "FREQATTN_DCT_WGS");
     const int wgs = e ? atoi(e) : (NI >= 128 ? 2 : 0);
-    dyn_lds = 0;
-    if (wgs > 0) {
-      const int per = (160 * 1024 / wgs) / 1024 * 1024;
-      if (per > lds_bytes) dyn_lds = per - lds_bytes;
-      if (dyn_lds > 0) {
-        const hipError_t e2 = hipFuncSetAttribute((const void*)k_dct_pass<NI, MT, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_lds);
-        if (e2 != hipSuccess) { dyn_lds = -1; return e2; }
-      }
-    }
+    const int per = wgs > 0 ? (160 * 1024 / wgs) / 1024 * 1024 : 0;
+    return std::max(0, per - lds_bytes);
+  }();
+  if (dyn_lds > 0) {
+    static OncePerDevice limit;
+    const hipError_t e = allow_lds(limit, (const void*)k_dct_pass<NI, MT, MODE>, dyn_lds);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_dct_pass<NI, MT, MODE>), dim3((unsigned)blocks), dim3(64 * DCT_WAVES), (size_t)dyn_lds, st, a, n_tiles, chunks);
   return hipGetLastError();

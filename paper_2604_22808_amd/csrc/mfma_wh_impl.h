@@ -357,12 +357,9 @@ static hipError_t wh_launch(WhPassArgs a, int num_cu, hipStream_t st, int* slots
   const int per_cu = std::min(2 / (KT * HT), 160 * 1024 / lds);
   const int64_t per_xcd = (planes + 7) / 8 * a.members;   // items of the fullest XCD
   const int grid = 8 * (int)std::min<int64_t>(per_xcd, std::max(1, num_cu / 8) * per_cu);
-  static bool attr = false;
-  if (!attr) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_wh_pass<NW16, KHT, KT, HT>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice limit;
+  hipError_t e = allow_lds(limit, (const void*)k_wh_pass<NW16, KHT, KT, HT>, 160 * 1024);
+  if (e != hipSuccess) return e;
   if (slots_out) *slots_out = grid * KT * HT;
   hipLaunchKernelGGL((k_wh_pass<NW16, KHT, KT, HT>), dim3((unsigned)grid), dim3(256 * KT * HT), (size_t)lds, st, a);
   return hipGetLastError();
