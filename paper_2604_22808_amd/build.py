@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -14,6 +15,10 @@ SOURCES = ["mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_iwh.hip", "mfma_dct_plain.hip
            "mfma_dct_scatter.hip",
            "mfma_dct_scatter_en.hip", "mfma_dct_gather.hip", "mfma_attn.hip", "mfma_vsum.hip", "mfma_gemm.hip", "api.cpp", "tables.cpp", "generic_kernels.hip",
            "generic_attn.hip", "generic_axis.hip", "mfma_dct.hip"]
+
+
+# Kernels that wait for their own copies into LDS by count: a spilled register's reload would wait for all of them.
+NO_SCRATCH = ("mfma_wh_0.hip", "mfma_wh_1.hip")
 
 
 def hipcc() -> str:
@@ -36,6 +41,8 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
         objs.append(obj)
         cmd = [hipcc()] + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
+        if src in NO_SCRATCH:
+            cmd.insert(1, "-Rpass-analysis=kernel-resource-usage")
         # compiler output goes to a file: a pipe nobody reads while the build waits would block a chatty compile
         log = open(obj + ".log", "w+")
         procs.append((src, subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT), log))
@@ -51,10 +58,14 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
         out = log.read()
         log.close()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
+        if p.returncode == 0 and src in NO_SCRATCH:
+            scratch = [int(n) for n in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", out)]
+            out = "" if scratch and max(scratch) == 0 else f"scratch bytes per lane of its kernels, none allowed: {scratch}"
+            failed = failed or bool(out)
         if p.returncode != 0:
             failed = True
             sys.stderr.write(f"--- {src} failed\n{out}\n")
-        elif verbose and out.strip():
+        elif (verbose or src in NO_SCRATCH) and out.strip():
             sys.stderr.write(f"--- {src}\n{out}\n")
     if failed:
         raise RuntimeError("hipcc failed")

@@ -56,6 +56,16 @@ template <int NW16, int SETS> constexpr int wh_slots() {
   return 8 * WH_GR * ((NW16 + 1) / 2) * 4096 <= (SETS == 1 ? 64 : 128) * 1024 ? 8 : 4;
 }
 
+// The lane's number, worked out where it is used: addresses formed from it ahead of the main loop cost registers the loop needs.
+// A spilled one is reloaded there, and the wait for it, which counts in order, takes the copies in flight along.  (Only the
+// variants at the register limit do this: 12 slices of 32 x 32 x 128 x 128 on the whole grid, forward transforms 1186 us with three
+// registers spilled, 1139 with none; the others are 0.5 % faster with the addresses kept.)
+__device__ __forceinline__ int wh_lane() {
+  unsigned all = ~0u;
+  asm volatile("" : "+s"(all));
+  return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+
 template <int NW16, int KHT, int KT, int HT>
 __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
   constexpr int W = 16 * NW16;
@@ -66,6 +76,7 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
   constexpr int NI = GR * NW16 * 2;            // copy instructions (8 rows of 128 bytes each) per group
   constexpr int NWV = 4 * SETS;                // waves
   constexpr int NPW = (NI + NWV - 1) / NWV;    // copies per wave and group
+  constexpr bool TIGHT = KHT == 2 && NW16 > 6;   // (would spill registers)
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   uint16_t* ring = smem;                                        // [SLOTS][GR][SROWS][64]
   const int mstr = a.H + 8;                                 // row stride of the H matrix in LDS
@@ -188,9 +199,9 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
       a_tile = kw0;
 #pragma unroll
       for (int s = 0; s < KW; ++s) {
-        const int k = 32 * s + 8 * q;
+        const int ln = TIGHT ? wh_lane() : lane, k = 32 * s + 8 * (ln >> 4);
         half8 m = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (kw0 < a.kw && k < W) m = *(const half8*)((const char*)(a.Mw + (size_t)kw0 * W) + (uint32_t)(l16 * W + k) * 2u);
+        if (kw0 < a.kw && k < W) m = *(const half8*)((const char*)(a.Mw + (size_t)kw0 * W) + (uint32_t)((ln & 15) * W + k) * 2u);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           const float f = (float)m[j];
@@ -273,8 +284,9 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
         if (++turn == nm) turn = 0;
       }
       half4 B[KHT];
+      const int ln = TIGHT ? wh_lane() : lane;
 #pragma unroll
-      for (int n = 0; n < KHT; ++n) B[n] = *(const half4*)(Mh + (16 * (ht * KHT + n) + l16) * mstr + h0 + 4 * q);
+      for (int n = 0; n < KHT; ++n) B[n] = *(const half4*)(Mh + (16 * (ht * KHT + n) + (ln & 15)) * mstr + h0 + 4 * (ln >> 4));
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         // block b of lane group g: rows 4 b .. of kw 4 g + r  ->  block g of kw 4 b + r
@@ -304,8 +316,9 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
     {
       const bool mine = kw0 < a.kw;
       const int64_t kh_stride = (int64_t)a.T * a.kw * a.d;
-      const int row = wc * 8 + (lane >> 3);   // kw = row / 16, kh = row % 16
-      const uint32_t lane_out = ((uint32_t)(row & 15) * (uint32_t)kh_stride + (uint32_t)((row >> 4) * a.d + (lane & 7) * 8)) * 2u;
+      const int ln = TIGHT ? wh_lane() : lane, l16 = ln & 15, q = ln >> 4;
+      const int row = wc * 8 + (ln >> 3);   // kw = row / 16, kh = row % 16
+      const uint32_t lane_out = ((uint32_t)(row & 15) * (uint32_t)kh_stride + (uint32_t)((row >> 4) * a.d + (ln & 7) * 8)) * 2u;
 #pragma unroll
       for (int n = 0; n < KHT; ++n) {
         const bool store = mine && 16 * (ht * KHT + n) < a.kh;
@@ -325,7 +338,7 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
             *(uint2v*)(sb + (kk * 16 + l16) * WH_EROW + wc * 32 + q * 8) = v;
           }
           asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-          const uint4v v = *(const uint4v*)(sb + row * WH_EROW + (lane & 7) * 16);
+          const uint4v v = *(const uint4v*)(sb + row * WH_EROW + (ln & 7) * 16);
           if (store) *(uint4v*)(dst + lane_out) = v;
           dst += (size_t)a.d * 4;
         }

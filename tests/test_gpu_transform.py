@@ -20,7 +20,7 @@ ALLOC = (1, 2, 4, 6, 0)   # low box, low+mid box, whole grid (twice), nothing
 # the low+mid box or the whole axis, and five (two passes); both head dimensions; more planes than workgroups and fewer
 @pytest.mark.parametrize("grid,d", [((16, 16, 16), 64), ((16, 32, 48), 128), ((16, 48, 80), 64), ((32, 64, 112), 64),
                                     ((16, 16, 128), 128), ((16, 128, 32), 64), ((48, 64, 64), 64), ((16, 96, 96), 64),
-                                    ((16, 80, 64), 128), ((64, 48, 16), 64)])
+                                    ((16, 80, 64), 128), ((64, 48, 16), 64), ((16, 32, 96), 64), ((16, 32, 112), 64), ((16, 32, 128), 128)])
 def test_spectral_coefficients(grid, d):
     from scipy.fft import dctn
     rng = np.random.default_rng(11)
