@@ -684,11 +684,37 @@ static int keep_rows(int box, int n) {
   return (r < n && mfma_dct_supported(n, r) && mfma_dct_supported(r, n)) ? r : n;
 }
 
+// The box kept for the low and mid bands per axis; false when that is the whole grid.
+static bool mid_keep(const Ctx& c, int keep[3]) {
+  const int full[3] = {c.shape.T, c.shape.H, c.shape.W};
+  bool smaller = false;
+  for (int a = 0; a < 3; ++a) {
+    keep[a] = keep_rows(c.mid_box[a], full[a]);
+    smaller = smaller || keep[a] < full[a];
+  }
+  return smaller;
+}
+
+// Whether the W and H axes of a forward transform go through the one-pass kernel, for the boxes of the grid (low, low+mid) and for
+// the whole of it.  The kernel and the two passes it replaces sum in another order and round another input, so this is
+// decided once for both boxes: a low head's coefficients come from either, by the entry point, and must be the same bits
+// (settle_forms takes care of the whole grid where it goes the other way).
+// Each workgroup that shares a plane reads it again from the L2.  Forward transforms with more than 32 H coefficients, one pass /
+// two, us, whole grid: W = 80 (five workgroups; 12 slices of 32 x 48 x 80 x 128) 4 % faster; 96 (six; 12 of 32 x 64 x 96 x 64)
+// 972 / 1054; 112 (seven; 8 of 32 x 64 x 112 x 128) 1782 / 1720; 128 (eight; 12 of 16 x 64 x 128 x 128) 1597 / 1453.  Hence six
+// for the whole grid; the boxes take what their kernel takes, because the low box gains more than a wide low+mid box loses
+// (12 slices of 16 x 64 x 128 x 128, low box 336 / 480, low+mid box 447 / 649; 8 of 32 x 128 x 96 x 128 1272 / 1785, 1771 / 1966).
+static bool one_pass(const Ctx& c, bool box, int d) {
+  int mid[3];
+  const int H = c.shape.H, W = c.shape.W;
+  return box && mid_keep(c, mid) ? wh_fits(d, H, W, mid[1], mid[2], 8) : wh_fits(d, H, W, H, W, 6);
+}
+
 // One tensor of a forward transform: `ns` slices (slice_list on the device, NULL = slices 0..ns-1) of x into the band-major
 // buffer spec.
 struct TransformSeg { const void* x; void* spec; const int32_t* slice_list; int ns; };
 
-// MFMA path, forward, for up to three tensors that share `keep`: W and H axes in one pass where wh_fits says so, else W axis
+// MFMA path, forward, for up to three tensors that share `keep`: W and H axes in one pass where one_pass says so, else W axis
 // (tmp0) and H axis pass by pass; both leave [h][t] order behind so that the rows of the T pass are W*d elements apart.
 // The T pass scatters into the band-major spectral buffers.  keep[] = coefficients computed per axis (T, H, W): a head
 // that only runs the low (low and mid) band needs Q~ and K~ on that box only, and every pass after the first then moves a
@@ -716,7 +742,7 @@ static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int n
   for (int i = n; i < 3; ++i) f.seg_end[i] = t.seg_end[i] = total;
   f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw;
   int slots = 0;
-  const bool fused = wh_fits(f);
+  const bool fused = one_pass(c, kt < T || kh < H || kw < W, d);
   if (fused && n == 3 && c.keep_outputs) {   // the third tensor's scratch is taken: two tensors, then one
     if ((e = forward_transform_mfma(c, segs, 2, st, keep, energy_slot, tot_slot, width)) != hipSuccess) return e;
     return forward_transform_mfma(c, segs + 2, 1, st, keep, energy_slot >= 0 ? energy_slot + 2 : -1, tot_slot >= 0 ? tot_slot + 2 : -1, width);
@@ -935,14 +961,14 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
     // Router in the loop: the allocation is not known yet.  Q~ and K~ - and V~ where the context keeps it on the box
     // for slices without the high band (v_box_ok; otherwise V~ is computed everywhere) - are computed on the low+mid
     // box only, which gives their low and mid statistics exactly and their high-band energy by Parseval; slices that
-    // turn out to run the high band get them completed afterwards (complete_qk_for_high).
+    // turn out to run the high band get them completed afterwards (settle_forms).
     // With `predict`, the slices that ran the high band under the context's last allocation (allocations move
     // slowly along a sampling trajectory) get the whole-grid transform straight away, with all three statistics
-    // taken directly; whatever the router then decides, only slices that are newly high need the completion.
+    // taken directly; whatever the router then decides, slices that are newly high need the completion (and, on some
+    // grids, slices that are no longer high their box: settle_forms).
     const int full[3] = {c->shape.T, c->shape.H, c->shape.W};
     int mid[3];
-    bool pruned = false;
-    for (int a = 0; a < 3; ++a) { mid[a] = keep_rows(c->mid_box[a], full[a]); pruned = pruned || mid[a] < full[a]; }
+    bool pruned = mid_keep(*c, mid);
     if (whole_grid) pruned = false;   // every statistic taken directly from whole-grid transforms
     for (int i = 0; i < 6; ++i) c->energy_waves[i] = 0;
     for (int i = 0; i < 3; ++i) c->tot_waves[i] = 0;
@@ -1008,27 +1034,38 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
   return FREQATTN_OK;
 }
 
-// After routing with Q~ and K~ (and V~) on the low+mid box only: the slices that run the high band get the full transforms.
+// After routing: with Q~ and K~ (and V~) on the low+mid box only, the slices that run the high band get the full transforms.  And
+// slices without the high band that have theirs from the whole grid (a wrong guess, or statistics taken there) get them
+// from the box where the whole grid is transformed another way: outputs must not depend on what was guessed.
 // (The caller has synchronised the stream since the first phase was queued - the router reads the statistics back -
 // so the fix list's region of the pinned host buffer is not the source of a copy still in flight.)
-static freqattn_status complete_qk_for_high(freqattn_ctx* c, const void* q, const void* k, const void* v, hipStream_t st) {
-  if (c->path != FREQATTN_PATH_MFMA || !c->qk_on_mid_box || c->n_cls[2] == 0) return FREQATTN_OK;
+static freqattn_status settle_forms(freqattn_ctx* c, const void* q, const void* k, const void* v, hipStream_t st) {
+  if (c->path != FREQATTN_PATH_MFMA) return FREQATTN_OK;
   const int full[3] = {c->shape.T, c->shape.H, c->shape.W};
-  int32_t* fix = c->h_lists + c->off_fix;
+  int mid[3];
+  (void)mid_keep(*c, mid);
+  int32_t* fix = c->h_lists + c->off_fix;   // slices to complete, then slices to take from the box
   const int32_t* high = c->h_lists + c->off_cls[2];
-  int n_fix = 0;
-  for (int i = 0; i < c->n_cls[2]; ++i)
-    if (!c->qk_full[(size_t)high[i]]) fix[n_fix++] = high[i];
-  if (n_fix == 0) return FREQATTN_OK;
-  HIP_TRY(c, hipMemcpyAsync(c->d_lists + c->off_fix, fix, (size_t)n_fix * sizeof(int32_t), hipMemcpyHostToDevice, st));
-  const int32_t* list = c->d_lists + c->off_fix;
+  const int32_t* nonhigh = c->h_lists + c->off_nonhigh;
+  int n_full = 0, n_box = 0;
   bool v_too = false;
-  for (int i = 0; i < n_fix; ++i) {
-    v_too = v_too || !c->v_full[(size_t)fix[i]];
-    c->v_full[(size_t)fix[i]] = 1;
+  for (int i = 0; i < c->n_cls[2]; ++i) {
+    const size_t s = (size_t)high[i];
+    if (c->qk_full[s]) continue;
+    fix[n_full++] = high[i];
+    v_too = v_too || !c->v_full[s];
+    c->v_full[s] = 1;
   }
-  const TransformSeg segs[3] = {{q, c->specQ, list, n_fix}, {k, c->specK, list, n_fix}, {v, c->specV, list, v_too ? n_fix : 0}};
-  HIP_TRY(c, forward_transform_mfma(*c, segs, 3, st, full, -1, -1));
+  if (one_pass(*c, true, c->d) != one_pass(*c, false, c->d))
+    for (int i = 0; i < c->n_nonhigh; ++i)
+      if (c->qk_full[(size_t)nonhigh[i]]) fix[n_full + n_box++] = nonhigh[i];
+  if (n_full + n_box == 0) return FREQATTN_OK;
+  HIP_TRY(c, hipMemcpyAsync(c->d_lists + c->off_fix, fix, (size_t)(n_full + n_box) * sizeof(int32_t), hipMemcpyHostToDevice, st));
+  const int32_t *lf = c->d_lists + c->off_fix, *lb = lf + n_full;
+  const TransformSeg whole[3] = {{q, c->specQ, lf, n_full}, {k, c->specK, lf, n_full}, {v, c->specV, lf, v_too ? n_full : 0}};
+  const TransformSeg box[3] = {{q, c->specQ, lb, n_box}, {k, c->specK, lb, n_box}, {v, c->specV, lb, c->v_box_ok ? n_box : 0}};
+  HIP_TRY(c, forward_transform_mfma(*c, whole, 3, st, full, -1, -1));
+  HIP_TRY(c, forward_transform_mfma(*c, box, 3, st, mid, -1, -1));
   return FREQATTN_OK;
 }
 
@@ -1578,7 +1615,7 @@ extern "C" freqattn_status freqattn_forward_routed(freqattn_ctx* c, const void* 
   fs = ensure_lists(c, head_alloc_out, st);
   if (fs != FREQATTN_OK) return fs;
   tm.done("router");
-  fs = complete_qk_for_high(c, q, k, v, st);
+  fs = settle_forms(c, q, k, v, st);
   if (fs != FREQATTN_OK) return fs;
   tm.done("forward_transform_high_qk");
   return bands_phase(c, scale, v, out, st, tm);

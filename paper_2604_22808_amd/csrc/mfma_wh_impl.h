@@ -383,8 +383,7 @@ static hipError_t wh_dispatch(const WhPassArgs& a, int num_cu, hipStream_t st, i
   const int kht = a.kh / 16;
   if (kht == 1) return a.kw > 16 ? wh_launch<NW16, 1, 2, 1>(a, num_cu, st, slots_out) : wh_launch<NW16, 1, 1, 1>(a, num_cu, st, slots_out);
   if (kht == 2) return a.kw > 16 ? wh_launch<NW16, 2, 2, 1>(a, num_cu, st, slots_out) : wh_launch<NW16, 2, 1, 1>(a, num_cu, st, slots_out);
-  if constexpr (NW16 <= 5)   // (wider planes are taken with at most 32 rows: wh_fits)
-    if (kht <= 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
+  if (kht <= 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
   return hipErrorInvalidValue;
 }
 
