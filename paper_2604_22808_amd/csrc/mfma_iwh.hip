@@ -2,7 +2,7 @@
 #include "mfma_iwh_impl.h"
 namespace fa {
 bool iwh_fits(const IwhPassArgs& a) {
-  if (a.H % 16 != 0 || a.W % 16 != 0 || a.H > 128 || a.W > 64) return false;
+  if (a.H % 16 != 0 || a.H > 128 || (a.W != 16 && a.W != 32 && a.W != 64)) return false;   // (an axis of 48 is kept whole)
   // A workgroup expands its rows one after the other: with fewer than two items of 16 rows per compute unit (256 of them)
   // the two passes are faster (6 slices of 16 x 64 x 64 x 64 from the 32 x 32 box: 42 us, one pass 66; 16K tokens 10 us, one
   // pass 18).  Larger boxes do not fit the registers, wider axes neither (W = 128 spills).
@@ -13,7 +13,6 @@ hipError_t launch_iwh_pass(const IwhPassArgs& a, int num_cu, hipStream_t st) {
   switch (a.W / 16) {
     case 1: return iwh_dispatch<1>(a, num_cu, st);
     case 2: return iwh_dispatch<2>(a, num_cu, st);
-    case 3: return iwh_dispatch<3>(a, num_cu, st);
     case 4: return iwh_dispatch<4>(a, num_cu, st);
   }
   return hipErrorInvalidValue;

@@ -381,9 +381,16 @@ static hipError_t wh_launch(WhPassArgs a, int num_cu, hipStream_t st, int* slots
 template <int NW16>
 static hipError_t wh_dispatch(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
   const int kht = a.kh / 16;
-  if (kht == 1) return a.kw > 16 ? wh_launch<NW16, 1, 2, 1>(a, num_cu, st, slots_out) : wh_launch<NW16, 1, 1, 1>(a, num_cu, st, slots_out);
-  if (kht == 2) return a.kw > 16 ? wh_launch<NW16, 2, 2, 1>(a, num_cu, st, slots_out) : wh_launch<NW16, 2, 1, 1>(a, num_cu, st, slots_out);
-  if (kht <= 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
+  // A single W tile: the whole axis of 16, or the box of an axis that can be cut that far (a power of two).
+  if constexpr ((NW16 & (NW16 - 1)) == 0) {
+    if (a.kw == 16 && kht == 1) return wh_launch<NW16, 1, 1, 1>(a, num_cu, st, slots_out);
+    if (a.kw == 16 && kht == 2) return wh_launch<NW16, 2, 1, 1>(a, num_cu, st, slots_out);
+  }
+  if constexpr (NW16 > 1) {
+    if (a.kw > 16 && kht == 1) return wh_launch<NW16, 1, 2, 1>(a, num_cu, st, slots_out);
+    if (a.kw > 16 && kht == 2) return wh_launch<NW16, 2, 2, 1>(a, num_cu, st, slots_out);
+  }
+  if (kht == 3 || kht == 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
   return hipErrorInvalidValue;
 }
 

@@ -50,7 +50,8 @@ def test_spectral_coefficients(grid, d):
 
 
 # boxes of one and two 16-coefficient tiles per axis (n low and n low+mid heads: enough planes for the one-pass inverse), whole
-# planes and parts of planes per workgroup, added to V and - where the box is the whole grid - not
+# planes and parts of planes per workgroup, added to V and - where the box is the whole grid - not; an axis of 48, which is kept
+# whole and takes the two passes
 @pytest.mark.parametrize("grid,d,n", [((16, 16, 16), 64, 32), ((32, 64, 48), 64, 4), ((16, 64, 32), 128, 4), ((32, 32, 64), 64, 8),
                                       ((16, 128, 64), 64, 4), ((64, 32, 16), 128, 9)])
 def test_outputs_of_boxed_inverse(grid, d, n):
