@@ -818,7 +818,7 @@ static hipError_t inverse_transform_mfma(Ctx& c, void* out, const void* v_in, hi
   IwhPassArgs f{};
   f.in = c.tmp1; f.out = out; f.resid = delta ? v_in : nullptr; f.slice_list = slice_list; f.n_slices = ns;
   f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw; f.Fh = c.d_Ft16[1]; f.Fw = c.d_Ft16[2];
-  if (!wide && iwh_fits(f)) return launch_iwh_pass(f, c.num_cu, st);   // H and W axes in one pass
+  if (!wide && iwh_fits(f, c.num_cu)) return launch_iwh_pass(f, c.num_cu, st);   // H and W axes in one pass
 
   DctPassArgs b{};
   b.d = d; b.Ntok = c.N;

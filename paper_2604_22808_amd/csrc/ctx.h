@@ -343,7 +343,7 @@ struct IwhPassArgs {
   const half_t* Fh; const half_t* Fw;               // fp16 [H][H], [W][W]: rows are positions
   int parts;                                        // (filled in by the launcher) workgroups that share a plane
 };
-bool iwh_fits(const IwhPassArgs& a);
+bool iwh_fits(const IwhPassArgs& a, int num_cu);   // whether the pass takes these sizes and is the faster way
 hipError_t launch_iwh_pass(const IwhPassArgs& a, int num_cu, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, hipStream_t st);
 hipError_t launch_transpose_bf16_to_f16(const void* in /*[R][Cc] bf16*/, void* out /*[Cc][R] fp16*/, int R, int Cc, hipStream_t st);

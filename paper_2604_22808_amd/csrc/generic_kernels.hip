@@ -441,9 +441,10 @@ hipError_t launch_convert_16(const void* in, void* out, int64_t n, int to_bf16, 
 
 // Fixed-order sum of the per-wave partial statistics written by the fused forward passes of Q, K and V.
 // Wave w of a launch worked on column chunk w % (d/64) only, and left [3 bands][64 columns] floats behind (768 bytes).
-// Two stages.  Stage 1: d workgroups of 4 x 192 threads (thread = band, column); workgroup b takes the waves w = b, b + d,
-// ... of every slot (d is a multiple of d/64, so all of them belong to chunk b % (d/64)) and reads their 768 bytes
-// whole.  Stage 2: one thread per (band, channel) adds the stage-1 sums of its chunk in ascending workgroup order.
+// Two stages.  Stage 1: ENERGY_PARTS workgroups of 4 x 192 threads (thread = band, column); workgroup b takes the waves
+// w = b, b + ENERGY_PARTS, ... of every slot, shared among its four groups of threads (ENERGY_PARTS is a multiple of
+// d/64, so all of them belong to chunk b % (d/64)), and reads their 768 bytes whole.  Stage 2: a workgroup per band and
+// chunk; 16 threads per channel add the stage-1 sums of every 16th workgroup of the chunk each, then their sums in order.
 // With tot_part set, the tensors in slots 0..2 were only computed on the low+mid box: their high-band energy is the
 // energy of the input (Parseval, the transform is orthonormal) minus their low and mid energies.
 // What bounds the two stages is latency: stage 1 has a few MB of slots to read, so it is spread over the whole chip (one

@@ -42,8 +42,8 @@ __device__ __forceinline__ uint32_t iwh_bf16(float f) {   // round to nearest ev
 template <int KHS, int KWT> constexpr int iwh_waves() { return KHS * KWT == 1 ? 3 : KHS * KWT == 2 ? 2 : 1; }
 constexpr int IWH_ROW = 144;   // bytes per staged row of 64 channels (128 + 16: rows side by side take all LDS banks once)
 
-// (RESID is a template argument also because no branch may stand between a product and the first use of its result: the
-// wait states it needs have been seen missing there.)
+// (RESID is a template argument: with the branch inside, between a product and the first use of its result, a draft of the forward
+// kernel gave wrong sums; see there.)
 template <int NW16, int KHS, int KWT, bool RESID>   // W / 16, kh / 16, kw / 16
 __global__ void __launch_bounds__(256, (iwh_waves<KHS, KWT>())) k_iwh_pass(IwhPassArgs a) {
   constexpr int W = 16 * NW16, KH = 16 * KHS, KW = 16 * KWT;

@@ -50,16 +50,16 @@ __device__ __forceinline__ void wh_dma16(const void* base, uint32_t lane_off, un
 constexpr int WH_EROW = 144;   // bytes per staged output row (128 + 16: the 16 rows a wave writes side by side take all banks once)
 template <int NW16> constexpr int wh_out_buffers() { return (NW16 + 1) / 2 % 2 == 0 ? 1 : 2; }   // (what LDS has room for beside the ring)
 constexpr int WH_GR = 2;   // rows h per ring slot (a group)
-// Ring slots (8 or 4: slots are numbered by their place in a block of 16 rows).
-// Workgroups of four waves share a compute unit with a second one.
+// Ring slots (8 or 4: slots are numbered by their place in a block of 16 rows).  Up to W = 64, workgroups of four waves leave
+// room for a second one on the compute unit; from W = 80 on the ring alone is 96 or 128 KB of its 160.
 template <int NW16, int SETS> constexpr int wh_slots() {
   return 8 * WH_GR * ((NW16 + 1) / 2) * 4096 <= (SETS == 1 ? 64 : 128) * 1024 ? 8 : 4;
 }
 
 // The lane's number, worked out where it is used: addresses formed from it ahead of the main loop cost registers the loop needs.
 // A spilled one is reloaded there, and the wait for it, which counts in order, takes the copies in flight along.  (Only the
-// variants at the register limit do this: 12 slices of 32 x 32 x 128 x 128 on the whole grid, forward transforms 1186 us with three
-// registers spilled, 1139 with none; the others are 0.5 % faster with the addresses kept.)
+// variants at the register limit do this: 12 slices of 32 x 32 x 128 x 128 on the whole grid, forward transforms 1199 us with three
+// registers spilled, 1155 with none; the others are 0.5 % faster with the addresses kept.)
 __device__ __forceinline__ int wh_lane() {
   unsigned all = ~0u;
   asm volatile("" : "+s"(all));
@@ -247,8 +247,9 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
 #pragma unroll
           for (int s = 0; s < KW; ++s) b[u ^ 1][s] = operand(((p + u) % SLOTS) * GR + (u ^ 1), s);
           __builtin_amdgcn_sched_barrier(0);
-          // (in front of the products: no branch between a product and the first use of its result, where the wait states it
-          // needs have been seen missing)
+          // (In front of the products: a draft with this branch behind them gave wrong sums.  Its cause was not shown - the
+          // compiler keeps the wait states between a product and the first use of its result on both ways of a branch, 8 here
+          // as in that form - so the order stays.)
           if (turn == me) {
 #pragma unroll
             for (int s = 0; s < KW; ++s)
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
         }
       }
     }
-    // (the wait states the last products need before their accumulators are read, in front of any branch)
+    // (wait states between the last products and the first use of their accumulators, whatever way leads there)
     asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     tot += te[0] + te[1];
