@@ -742,7 +742,9 @@ static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int n
   for (int i = n; i < 3; ++i) f.seg_end[i] = t.seg_end[i] = total;
   f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw;
   int slots = 0;
-  const bool fused = one_pass(c, kt < T || kh < H || kw < W, d);
+  // (its copies into LDS move whole 16-byte pieces of the caller's tensors; a view that starts between them takes the two passes)
+  bool fused = one_pass(c, kt < T || kh < H || kw < W, d);
+  for (int i = 0; i < n; ++i) fused = fused && (uintptr_t)f.in[i] % 16 == 0;
   if (fused && n == 3 && c.keep_outputs) {   // the third tensor's scratch is taken: two tensors, then one
     if ((e = forward_transform_mfma(c, segs, 2, st, keep, energy_slot, tot_slot, width)) != hipSuccess) return e;
     return forward_transform_mfma(c, segs + 2, 1, st, keep, energy_slot >= 0 ? energy_slot + 2 : -1, tot_slot >= 0 ? tot_slot + 2 : -1, width);

@@ -29,7 +29,8 @@ __device__ __forceinline__ uint32_t gx_bf16(float f) {   // round to nearest eve
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
-// IN / OUT: 0 fp32, 1 bf16.  VEC: head_dim is a multiple of 4, so four columns are adjacent, aligned and of one slab.
+// IN / OUT: 0 fp32, 1 bf16.  VEC: head_dim is a multiple of 4 and the tensors start at a multiple of four elements, so four
+// columns are adjacent, aligned and of one slab.
 template <int KT, int IN, int OUT, bool VEC>
 __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -179,7 +180,9 @@ hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st) {
   const int64_t ncols = a.nslab * a.inner;
   if (ncols == 0 || a.n_tensors == 0) return hipSuccess;
   if (a.ldm < a.n || a.ldm % 16 != 0 || (a.perm_in && a.perm_out)) return hipErrorInvalidValue;
-  const bool vec = a.d % 4 == 0;
+  bool vec = a.d % 4 == 0;
+  for (int i = 0; i < a.n_tensors; ++i)   // (a caller's tensor may be a view that starts anywhere)
+    vec = vec && (uintptr_t)a.in[i] % (a.in_bf16 ? 8 : 16) == 0 && (uintptr_t)a.out[i] % (a.out_bf16 ? 8 : 16) == 0;
   switch ((std::min(a.n_out, 64) + 15) / 16) {
     case 1: return launch_kt<1>(a, ncols, vec, st);
     case 2: return launch_kt<2>(a, ncols, vec, st);

@@ -111,3 +111,26 @@ def test_long_low_band_groups(dtype, path, d, c):
     mx, rl = U.errors(U.run_forward(ctx, q, k, v, dtype, alloc), O.forward(q, k, v, grid, O.BandConfig(**cfgd), alloc))
     print(f"low groups of {c} {dtype} d={d}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
     assert mx <= U.TOL[dtype][0] and rl <= U.TOL[dtype][1], (mx, rl)
+
+
+@pytest.mark.parametrize("dtype,path,grid,skip", [("f32", B.PATH_GENERIC, (5, 9, 11), 1), ("bf16", B.PATH_GENERIC, (5, 9, 11), 1),
+                                                  ("bf16", B.PATH_MFMA, (16, 32, 32), 2)])
+def test_tensors_that_start_between_16_byte_pieces(dtype, path, grid, skip):
+    """Contiguous views that start `skip` elements into their storage: no kernel may take their alignment for granted."""
+    import torch
+    rng = np.random.default_rng(7)
+    N, d, alloc = int(np.prod(grid)), 64, (3, 4)
+    cfgd = dict(WL.WORKLOADS["16k"].band)
+    ctx = B.Context(1, 2, d, grid, B.F32 if dtype == "f32" else B.BF16, B.make_cfg(**cfgd), path=path)
+    host = [WL.round_to_io(0.7 * rng.standard_normal((1, 2, N, d)), dtype) for _ in range(3)]
+
+    def view(x):
+        t = torch.zeros(x.size + 8, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+        v = t[skip:skip + x.size].view(x.shape)
+        return v.copy_(torch.from_numpy(x))
+    q, k, v = (view(x) for x in host)
+    out = view(np.zeros_like(host[0]))
+    ctx.forward(q, k, v, alloc, out)
+    mx, rl = U.errors(U.to_host64(out), O.forward(*host, grid, O.BandConfig(**cfgd), alloc))
+    print(f"unaligned {dtype} {grid}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= U.TOL[dtype][0] and rl <= U.TOL[dtype][1], (mx, rl)
