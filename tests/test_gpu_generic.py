@@ -134,3 +134,28 @@ def test_tensors_that_start_between_16_byte_pieces(dtype, path, grid, skip):
     mx, rl = U.errors(U.to_host64(out), O.forward(*host, grid, O.BandConfig(**cfgd), alloc))
     print(f"unaligned {dtype} {grid}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
     assert mx <= U.TOL[dtype][0] and rl <= U.TOL[dtype][1], (mx, rl)
+
+
+@pytest.mark.parametrize("dtype,path,grid,d", [("f32", B.PATH_GENERIC, (3, 10, 12), 8), ("bf16", B.PATH_MFMA, (16, 16, 16), 64)])
+def test_more_than_256_slices(dtype, path, grid, d):
+    """Batch x heads beyond the 256 slices whose unused summary tokens are left out: every band is pooled behind the band
+    operators."""
+    import torch
+    heads, batch, N = 130, 2, int(np.prod(grid))
+    alloc = [h % 8 for h in range(heads)]
+    cfgd = dict(WL.WORKLOADS["16k"].band)
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    q, k, v = ((0.7 * torch.randn((batch, heads, N, d), device="cuda", generator=gen)).to(t) for _ in range(3))
+    ctx = B.Context(batch, heads, d, grid, B.F32 if dtype == "f32" else B.BF16, B.make_cfg(**cfgd), path=path)
+    out = torch.empty_like(q)
+    ctx.forward(q, k, v, alloc, out)
+    pick = [0, 1, 2, 3, 4, 5, 6, 7, 122, 125, 129]
+    got, qh, kh, vh = (U.to_host64(x[:, pick]) for x in (out, q, k, v))
+    want = O.forward(qh, kh, vh, grid, O.BandConfig(**cfgd), [alloc[h] for h in pick])
+    mx, rl = U.errors(got, want)
+    print(f"{batch * heads} slices {dtype}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    # Summary tokens of white noise make outputs of up to 10, where a bf16 is rounded by up to 2^-8 of its value; the other tests'
+    # bound is for values below 4, 2^-6 of it that rounding.
+    assert mx <= U.TOL[dtype][0] + (2.0 ** -8 * np.abs(want).max() - 2.0 ** -6 if dtype == "bf16" else 0.0), mx
+    assert rl <= U.TOL[dtype][1], rl

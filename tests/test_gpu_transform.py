@@ -128,3 +128,22 @@ def test_input_outside_fp16_is_reported(value):
     with pytest.raises(B.FreqAttnError) as e:
         ctx.check_range()
     assert e.value.status == B.ERANGE
+
+
+@pytest.mark.parametrize("d_model", [64, 128])
+def test_projected_forward_of_narrow_models(d_model):
+    """A model width of 64 or 128 channels goes through the one-pass transform like a head does."""
+    import torch
+    rng = np.random.default_rng(17)
+    grid, d, heads, alloc = (16, 32, 48), 64, 3, (1, 2, 4)
+    N, hd = int(np.prod(grid)), heads * d
+    x = WL.round_to_io(0.5 * rng.standard_normal((1, N, d_model)), "bf16")
+    w = [WL.round_to_io(rng.standard_normal(s) / np.sqrt(s[0]), "bf16") for s in ((d_model, hd),) * 3 + ((hd, d_model),)]
+    band = WL.WORKLOADS["16k"].band
+    ctx = B.Context(1, heads, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    dx, *dw = (U.to_device(a, "bf16") for a in [x] + w)
+    out = torch.empty_like(dx)
+    ctx.forward_projected(dx, *dw, alloc, out)
+    mx, rl = U.errors(U.to_host64(out), O.forward_projected(x, *w, grid, O.BandConfig(**band), alloc))
+    print(f"projected d_model={d_model}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
