@@ -361,19 +361,25 @@ def main():
     vbox = ctx.get_v_box()   # V~ of a slice without the high band on the low+mid box: V follows Q and K class by class
     nonhigh_present = cls_present[0] or cls_present[1] or any(m == 0 for m in masks)
     # Launches: tensors that keep the same coefficient box share a W + H pass and a T pass where the one-pass kernels take the
-    # box (csrc/mfma_wh_0.hip, csrc/mfma_iwh.hip), else every axis of every tensor is a launch.
+    # box (one_pass in csrc/api.cpp, csrc/mfma_iwh.hip), else every axis of every tensor is a launch.
     T, H, W = wl.grid
-    def kept(num):   # coefficients kept of an axis of n for the box num/4 of it
-        return [min(n, -(-(-(-num * n // 4)) // 16) * 16) for n in (T, H, W)]
+    def passes(n_in, n_out):   # the axis pass exists: any number of rows for powers of two, square otherwise
+        return n_in & (n_in - 1) == 0 or (n_out + 31) // 32 == (n_in + 31) // 32
+    def kept(num):   # coefficients kept per axis for the box num/4 of it
+        rounded = [min(n, -(-(-(-num * n // 4)) // 16) * 16) for n in (T, H, W)]
+        return [r if passes(n, r) and passes(r, n) else n for r, n in zip(rounded, (T, H, W))]
+    low_k, mid_k, full_k = kept(1), kept(2), [T, H, W]
     def fwd_group(tensors, k):
-        return 0 if tensors == 0 else 2 if k[1] <= 64 and k[2] // 16 <= (8 if k[1] <= 32 else 5) else 3 * tensors
+        kh, kw, most = (mid_k[1], mid_k[2], 8) if k != full_k and mid_k != full_k else (H, W, 6)
+        one = kh <= 64 and kw // 16 <= (8 if kh <= 32 else most)
+        return 0 if tensors == 0 else 2 if one else 3 * tensors
     def inv_group(mask_of_class, k):
         n = sum(1 for m in masks if mask_of_class(m)) * wl.batch
-        one = k[1] <= 32 and k[2] <= 32 and W <= 64 and n * T * (wl.head_dim // 64) * (H // 16) >= 512
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+        one = max(k[1], k[2]) <= 32 and W in (16, 32, 64) and n * T * (wl.head_dim // 64) * (H // 16) >= 2 * cus
         return 0 if n == 0 else 2 if one else 3
-    low_k, mid_k, full_k = kept(1), kept(2), [T, H, W]
     if router is not None:   # routed: slices split into "ran the high band last time" and the rest
-        fwd_launches = fwd_group((3 if vbox else 2) if nonhigh_present else 0, mid_k) + fwd_group(3 if cls_present[2] or not vbox else 0, full_k)
+        fwd_launches = fwd_group((3 if vbox else 2) if nonhigh_present else 0, mid_k) + fwd_group(3 if cls_present[2] else 0 if vbox else 1, full_k)
     else:
         fwd_launches = (fwd_group(2 if cls_present[0] else 0, low_k)
                         + fwd_group((2 if cls_present[1] else 0) + (1 if vbox and nonhigh_present else 0), mid_k)
