@@ -699,15 +699,13 @@ static bool mid_keep(const Ctx& c, int keep[3]) {
 // the whole of it.  The kernel and the two passes it replaces sum in another order and round another input, so this is
 // decided once for both boxes: a low head's coefficients come from either, by the entry point, and must be the same bits
 // (settle_forms takes care of the whole grid where it goes the other way).
-// Each workgroup that shares a plane reads it again from the L2.  Forward transforms with more than 32 H coefficients, one pass /
-// two, us, whole grid: W = 80 (five workgroups; 12 slices of 32 x 48 x 80 x 128) 4 % faster; 96 (six; 12 of 32 x 64 x 96 x 64)
-// 972 / 1054; 112 (seven; 8 of 32 x 64 x 112 x 128) 1782 / 1720; 128 (eight; 12 of 16 x 64 x 128 x 128) 1597 / 1453.  Hence six
-// for the whole grid; the boxes take what their kernel takes, because the low box gains more than a wide low+mid box loses
-// (12 slices of 16 x 64 x 128 x 128, low box 336 / 480, low+mid box 447 / 649; 8 of 32 x 128 x 96 x 128 1272 / 1785, 1771 / 1966).
+// Up to 64 H coefficients it is the faster one with any number of workgroups on a plane; forward transforms, two passes / one, us,
+// whole grid: W = 96 (six workgroups; 12 slices of 32 x 64 x 96 x 64) 1054 / 791; 112 (seven; 8 of 32 x 64 x 112 x 128)
+// 1722 / 1344; 128 (eight; 12 of 16 x 64 x 128 x 128) 1436 / 1229; low+mid box of 8 of 32 x 128 x 96 x 128 1966 / 1391.
 static bool one_pass(const Ctx& c, bool box, int d) {
   int mid[3];
   const int H = c.shape.H, W = c.shape.W;
-  return box && mid_keep(c, mid) ? wh_fits(d, H, W, mid[1], mid[2], 8) : wh_fits(d, H, W, H, W, 6);
+  return box && mid_keep(c, mid) ? wh_fits(d, H, W, mid[1], mid[2]) : wh_fits(d, H, W, H, W);
 }
 
 // One tensor of a forward transform: `ns` slices (slice_list on the device, NULL = slices 0..ns-1) of x into the band-major

@@ -327,9 +327,8 @@ struct WhPassArgs {
   int32_t* range_flag;                              // set when an input value leaves the fp16 range
   int members;                                      // (filled in by the launcher) workgroups that share a plane
 };
-// Whether the pass takes kh x kw coefficients of H x W planes with d channels per token; more than 32 H coefficients only with at
-// most `most` workgroups (16 W coefficients each) on a plane.
-bool wh_fits(int d, int H, int W, int kh, int kw, int most);
+// Whether the pass takes kh x kw coefficients of H x W planes with d channels per token.
+bool wh_fits(int d, int H, int W, int kh, int kw);
 hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W <= 64
 hipError_t launch_wh_pass_1(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W > 64
 inline hipError_t launch_wh_pass(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {

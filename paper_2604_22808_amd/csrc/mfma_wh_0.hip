@@ -1,11 +1,9 @@
 // W + H pass of the forward transform, W = 16 .. 64 (see mfma_wh_impl.h).
 #include "mfma_wh_impl.h"
 namespace fa {
-bool wh_fits(int d, int H, int W, int kh, int kw, int most) {
+bool wh_fits(int d, int H, int W, int kh, int kw) {
   if (H % 16 != 0 || W % 16 != 0 || H > 128 || W > 128 || kh % 16 != 0 || kw % 16 != 0) return false;
-  // More than 64 H coefficients do not fit the accumulators.  Wider tensors (the projected forward's X) have their 128-byte
-  // pieces a whole row apart: 16 x 128 channels measured 805 us in two passes, 810 in one.
-  return kh <= 64 && (d == 64 || d == 128) && kw / 16 <= (kh <= 32 ? 8 : most);
+  return kh <= 64 && d % 64 == 0;   // (more than 64 H coefficients do not fit the accumulators)
 }
 hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
   switch (a.W / 16) {

@@ -3,25 +3,28 @@
 //   out[kh, t, kw, c] = sum_h Mh[kh][h] * fp16( sum_w Mw[kw][w] * x[t, h, w, c] )
 // for up to three tensors (Q, K, V) per launch.  The plane between the two axes never reaches memory.
 //
-// A work item is 64 channels of one (tensor, slice, t) plane and KT tiles of 16 W coefficients, all H coefficients of
-// them kept as accumulators for as long as the plane's rows stream by:
-//   rows      x[t, h, :, 64 channels] (W pieces of 128 bytes) are copied straight into a ring of LDS slots, several groups
-//             of rows ahead, across items too; the 32-byte column groups of a piece are permuted through the source
-//             address so that the transposing reads below are free of bank conflicts
-//   W axis    per row, a wave multiplies its 16 channels: v_mfma_f32_16x16x32_bf16 on the bf16 input as it is, the fp16
-//             matrix split exactly into two bf16 terms (11 significant bits = 8 + 3), so nothing is converted and
-//             nothing is rounded that an fp16 product would not round
-//   between   rounded to fp16; a lane collects 16 rows h of its 4 kw x 1 channel, then a 4 x 4 exchange of lane groups
-//             (v_permlane32_swap, v_permlane16_swap) turns them into operands that hold 16 consecutive h per kw
-//   H axis    v_mfma_f32_16x16x16_f16, channels as rows, kh as columns: a lane ends up with 4 consecutive channels
-// The accumulators (64 KHT registers per wave) bound the tile: KHT <= 2, two waves per SIMD.  A workgroup is KT x HT sets of
-// four waves, a set for each W tile and each half of the H coefficients.  A plane is read by ceil(kw / (16 KT)) workgroups,
-// which run side by side on one XCD: the first of them fetches the rows into its L2.
+// A work item is 64 channels of one (tensor, slice, t) plane and KT tiles of 16 W coefficients, all 16 KH H coefficients of
+// them kept as accumulators (32 KT KH registers per wave) for as long as the plane's rows stream by, 16 rows per round:
+//   W axis    a wave takes two rows h of the round by itself, 32 positions w at a time, straight from memory into registers: 8 lanes
+//             hold a position's 128 bytes.  Lanes 8 apart exchange halves of what they hold (a lane then has 4 channels of twice the
+//             positions, one DPP move per register), and pairing the positions' halfwords (v_perm_b32, one per register) makes
+//             operands of v_mfma_f32_16x16x32_bf16 for 4 x 16 channels.  Positions within a step go in the order the loads leave
+//             them in; the matrix, in LDS, has its columns in the same order.  The bf16 input is multiplied as it is, the
+//             fp16 matrix split exactly into two bf16 terms (11 significant bits = 8 + 3), so nothing is converted and nothing
+//             is rounded that an fp16 product would not round
+//   between   rounded to fp16 and left in LDS, [h][kw][channel], for everybody (two buffers, one barrier per round)
+//   H axis    a wave takes 2 KT of the W coefficients, 64 channels and all H coefficients: transposing LDS reads,
+//             v_mfma_f32_16x16x16_f16 with channels as rows, kh as columns
+// The next steps' rows (up to 4 steps of 4 KB per wave) are always on their way, across rounds and items.  A plane is read by
+// ceil(kw / (16 KT)) workgroups, which run side by side on one XCD: the first of them fetches the rows into its L2.
 //
-// What bounds it and what it measured (one tensor, against the two passes it replaces): HBM where few workgroups share a
-// plane - 22 slices of 64^3 x 128 on the 32 x 32 box 631 -> 378 us (4.9 TB/s); LDS traffic, matrix instructions and the
-// barrier per two rows, one after the other, where four do - 17 slices of 64^3 x 128 with 64 x 64 kept 838 -> 710 us.  Stores
-// of 8 bytes per lane straight from the accumulators made that 844 us: hence the trip through LDS.
+// What bounds it: where one or two workgroups share a plane, memory (22 slices of 64^3 x 128 on the 32 x 32 box: 5.0 TB/s); where
+// four and more do, what a compute unit takes in from its L2.  Copying the rows through LDS and reading operands from
+// there moved 48 KB of LDS per row of 128 x 64, with a barrier every two rows; this moves 14.  One tensor's share of a launch, rows
+// through LDS -> this: 12 slices of 64 x 128 x 128 x 128 on the 64 x 64 box 1.33 -> 0.98 ms; 17 of 64^3 x 128 whole 0.70 -> 0.54; 12 of
+// 32 x 48 x 80 x 128 whole 0.27 -> 0.18.  On the way there (first / second of these): 8 bytes per lane and load, which the L1 serves at
+// 36 bytes per cycle instead of 64, 1.18 / 0.68; stores as the products leave them (16 bytes per lane, neighbouring lanes in different
+// rows) 1.01 / 0.60; all workgroups of a plane taking its rows in the same order (all wait for memory at once) +10 / +3 %.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,81 +38,62 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short short4v __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 typedef __fp16 fp16x4 __attribute__((__vector_size__(4 * sizeof(__fp16))));
 
-// One wave-wide copy of 16 bytes per lane from global memory into LDS: base (wave-uniform) + this lane's byte offset, lane l's
-// piece at LDS byte dst + 16 l (issued as assembly: the kernel does its own waiting, see k_attn).
-__device__ __forceinline__ void wh_dma16(const void* base, uint32_t lane_off, unsigned dst) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(dst) : "memory", "m0");
+constexpr int WH_WAVES = 8;
+// Steps requested ahead.  They live in registers (16 each) beside the accumulators; the number divides the steps of a round.
+template <int KW, int KT, int KH> constexpr int wh_depth() {
+  if (KT * KH == 1 || KT * KT * KH > 4) return 2;
+  return KW == 1 ? 2 : KW == 3 ? 3 : 4;
+}
+constexpr int wh_row_bytes(int KT) { return KT * 2048 + 64; }   // a row between the axes: [16 KT][64] fp16, and 64 bytes against bank conflicts
+constexpr int wh_waves_per_simd(int KW, int KT, int KH) { return KT * KH == 1 && KW <= 2 ? 4 : 2; }
+
+// `own`, but lanes of the banks (4 lanes of each 16) in the mask take `other` of the lane 8 places on in their 16.
+__device__ __forceinline__ uint32_t wh_from_other(uint32_t own, uint32_t other, int banks) {
+  return banks == 0xc ? __builtin_amdgcn_update_dpp((int)own, (int)other, 0x128, 0xf, 0xc, false)
+                      : __builtin_amdgcn_update_dpp((int)own, (int)other, 0x128, 0xf, 0x3, false);
 }
 
-constexpr int WH_EROW = 144;   // bytes per staged output row (128 + 16: the 16 rows a wave writes side by side take all banks once)
-template <int NW16> constexpr int wh_out_buffers() { return (NW16 + 1) / 2 % 2 == 0 ? 1 : 2; }   // (what LDS has room for beside the ring)
-constexpr int WH_GR = 2;   // rows h per ring slot (a group)
-// Ring slots (8 or 4: slots are numbered by their place in a block of 16 rows).  Up to W = 64, workgroups of four waves leave
-// room for a second one on the compute unit; from W = 80 on the ring alone is 96 or 128 KB of its 160.
-template <int NW16, int SETS> constexpr int wh_slots() {
-  return 8 * WH_GR * ((NW16 + 1) / 2) * 4096 <= (SETS == 1 ? 64 : 128) * 1024 ? 8 : 4;
-}
-
-// The lane's number, worked out where it is used: addresses formed from it ahead of the main loop cost registers the loop needs.
-// A spilled one is reloaded there, and the wait for it, which counts in order, takes the copies in flight along.  (Only the
-// variants at the register limit do this: 12 slices of 32 x 32 x 128 x 128 on the whole grid, forward transforms 1199 us with three
-// registers spilled, 1155 with none; the others are 0.5 % faster with the addresses kept.)
-__device__ __forceinline__ int wh_lane() {
-  unsigned all = ~0u;
-  asm volatile("" : "+s"(all));
-  return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
-}
-
-template <int NW16, int KHT, int KT, int HT>
-__global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
+template <int NW16, int KT, int KH>
+__global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 2, KT, KH)) k_wh_pass(WhPassArgs a) {
   constexpr int W = 16 * NW16;
-  constexpr int KW = (NW16 + 1) / 2;           // 32-deep steps over w
-  constexpr int SROWS = 32 * KW;               // LDS rows per h (rows beyond W stay zero)
-  constexpr int GR = WH_GR, SETS = KT * HT;
-  constexpr int SLOTS = wh_slots<NW16, SETS>();
-  constexpr int NI = GR * NW16 * 2;            // copy instructions (8 rows of 128 bytes each) per group
-  constexpr int NWV = 4 * SETS;                // waves
-  constexpr int NPW = (NI + NWV - 1) / NWV;    // copies per wave and group
-  constexpr bool TIGHT = KHT == 2 && NW16 > 6;   // (would spill registers)
-  extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  uint16_t* ring = smem;                                        // [SLOTS][GR][SROWS][64]
-  const int mstr = a.H + 8;                                 // row stride of the H matrix in LDS
-  half_t* Mh = (half_t*)(smem + SLOTS * GR * SROWS * 64);   // [16 KHT HT][mstr]
+  constexpr int KW = (NW16 + 1) / 2;           // steps of 32 positions w per row (the last one of 16 when NW16 is odd)
+  constexpr int U = 2 * KW;                    // steps of a wave per round
+  constexpr int D = wh_depth<KW, KT, KH>();
+  static_assert(U % D == 0, "a step's registers are known at compile time");
+  constexpr int RB = wh_row_bytes(KT);
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  char* Ys = smem;                                              // [2][16] rows between the axes
+  uint4v* Aw = (uint4v*)(Ys + 2 * 16 * RB);                     // [KT][KW][hi, lo][lane]: matrix operands of the W axis
+  float* tot = (float*)(Aw + KT * KW * 2 * 64);                 // [wave][64]: sums of squares of the rows a wave has taken
+  half_t* Mh = (half_t*)(tot + WH_WAVES * 64);                  // [16 KH][mstr]
+  const int mstr = a.H + 8;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wc = wave & 3, set = wave >> 2;    // this wave's 16 channels and set
-  const int kt = set % KT, ht = set / KT;      // W tile of the workgroup, half of the H coefficients
   const int l16 = lane & 15, q = lane >> 4;
-  constexpr int EB = wh_out_buffers<NW16>();
-  char* stage = (char*)(Mh + 16 * KHT * HT * mstr) + set * (EB * 32 * WH_EROW);   // output rows on their way out
 
-  for (int e = tid; e < 16 * KHT * HT * (a.H / 8); e += 64 * NWV) {
+  for (int e = tid; e < 16 * KH * (a.H / 8); e += 64 * WH_WAVES) {
     const int row = e / (a.H / 8), c8 = e % (a.H / 8);
     uint4v v = {0u, 0u, 0u, 0u};
     if (row < a.kh) v = *(const uint4v*)(a.Mh + (size_t)row * a.H + c8 * 8);
     *(uint4v*)(Mh + row * mstr + c8 * 8) = v;
   }
-  if constexpr (W < SROWS)
-    for (int e = tid; e < SLOTS * GR * (SROWS - W) * 8; e += 64 * NWV) {
-      const int r = e / 8, hr = r / (SROWS - W), w = W + r % (SROWS - W);
-      *(uint4v*)(ring + ((size_t)hr * SROWS + w) * 64 + (e % 8) * 8) = uint4v{0u, 0u, 0u, 0u};
-    }
 
   // Items of this workgroup.  Planes are dealt to the XCDs by their index mod 8 (workgroups are dealt round-robin by
-  // blockIdx); the R workgroups of a plane have neighbouring places in their XCD's list.  With 64 or 128 channels per
+  // blockIdx); the R workgroups of a plane have neighbouring places in their XCD's list.  With 64, 128, 256 or 512 channels per
   // token the channel chunk (plane index mod channels / 64) is then the same for all items of a workgroup.
   const int cpt = a.d >> 6, R = a.members;
   const int xcd = blockIdx.x & 7, J = gridDim.x >> 3;
   const int n_planes = a.seg_end[2] * a.T * cpt;
   const int n_items = n_planes > xcd ? ((n_planes - xcd + 7) >> 3) * R : 0;
-  const int64_t row_stride = (int64_t)W * a.d;   // elements between rows h
-  struct Item { const uint16_t* in; half_t* out; int r; };
+  const int64_t row_bytes = (int64_t)W * a.d * 2;   // between rows h
+  struct Item { const char* in; half_t* out; int r; };
   auto decode = [&](int l) -> Item {
     Item it;
     it.r = l % R;
@@ -119,263 +103,279 @@ __global__ void __launch_bounds__(256 * KT * HT, 2) k_wh_pass(WhPassArgs a) {
     const int seg = p < a.seg_end[0] ? 0 : p < a.seg_end[1] ? 1 : 2;
     const int sl = p - (seg == 0 ? 0 : seg == 1 ? a.seg_end[0] : a.seg_end[1]);
     const int32_t* list = seg == 0 ? a.slice_list[0] : seg == 1 ? a.slice_list[1] : a.slice_list[2];
-    const int64_t slice = list ? list[sl] : sl;
-    it.in = (const uint16_t*)(seg == 0 ? a.in[0] : seg == 1 ? a.in[1] : a.in[2]) + (slice * a.T + t) * a.H * row_stride + chunk * 64;
+    const int64_t slice = __builtin_amdgcn_readfirstlane(list ? list[sl] : sl);   // (addresses stay in scalar registers)
+    it.in = (const char*)(seg == 0 ? a.in[0] : seg == 1 ? a.in[1] : a.in[2]) + (slice * a.T + t) * a.H * row_bytes + chunk * 128;
     it.out = (half_t*)(seg == 0 ? a.out[0] : seg == 1 ? a.out[1] : a.out[2]) + ((int64_t)sl * a.kh * a.T + t) * a.kw * a.d + chunk * 64;
     return it;
   };
-
-  // Copies: instruction i of a group fills rows w = 8 (i % (W / 8)) .. + 7 of row h = i / (W / 8); a lane's 16-byte piece
-  // comes from the column group its place stands for.  Column group of place p in row w: p ^ f(w), f from bits 1 and 3 of w.
-  // (instruction i is copied by wave i mod the number of waves, which fixes bit 3 of w per wave)
-  const uint32_t src = ((uint32_t)((lane >> 3) * a.d + (((lane & 7) ^ (((lane >> 4) & 1) << 1)) << 3)) * 2u) ^ ((wave & 1) << 6);
-  const unsigned ring_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)ring;
-  uint32_t c_src[NPW], c_dst[NPW];   // bytes from the group's first row / from the slot's start
-#pragma unroll
-  for (int n = 0; n < NPW; ++n) {
-    int i = wave + n * NWV;
-    if (NI % NWV != 0) i %= NI;   // (the same bytes twice; NI is even, so bit 3 of w stays the wave's)
-    const int hr = i / (2 * NW16), w8 = i - hr * (2 * NW16);
-    c_src[n] = (uint32_t)(hr * W + w8 * 8) * (uint32_t)a.d * 2u;
-    c_dst[n] = ring_at + (uint32_t)(hr * SROWS + w8 * 8) * 128u;
-  }
-  auto copy_group = [&](const uint16_t* base, int slot) {
-#pragma unroll
-    for (int n = 0; n < NPW; ++n) wh_dma16((const char*)base + c_src[n], src, c_dst[n] + slot * (GR * SROWS * 128));
-  };
-
   if ((int)(blockIdx.x >> 3) >= n_items) {   // nothing to do: zero sums
-    if (a.tot_part && tid < 64 * SETS) a.tot_part[((size_t)(tid >> 6) * gridDim.x + blockIdx.x) * 64 + (tid & 63)] = 0.f;
+    if (a.tot_part) a.tot_part[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = 0.f;
     return;
   }
 
-  // Rows are requested SLOTS - 1 groups ahead of their use: `pf` is the group requested next, `pnext` the first group of
-  // the item after the one `pf` is in (of the last item: its own last group again and again, so that the count of copies
-  // in flight stays what the waits assume).
-  const int64_t group_stride = GR * row_stride;
-  const int n_groups = a.H / GR;   // at least SLOTS (H is at least 16)
-  const uint16_t* pf = decode(blockIdx.x >> 3).in;
-#pragma unroll
-  for (int s = 0; s < SLOTS - 1; ++s) { copy_group(pf, s); pf += group_stride; }
-
-  // transposing reads: lane j of a group of 16 names row j / 4, columns 4 (j % 4) .. + 3 of the wave's 16 channels
-  const int trow = 8 * q + (l16 >> 2);                                       // + 4 for the second half of an operand
-  const int fz = ((trow >> 1) & 1) | (((trow >> 3) & 1) << 1);               // (the same for trow + 4, and + 32 s)
-  const int boff = trow * 64 + ((wc ^ fz) << 4) + ((lane & 3) << 2);         // halfs
-
-  // (one address register per 64 KB of the ring: what an LDS instruction's own offset reaches)
-  constexpr int RING = SLOTS * GR * SROWS * 128, NBASE = (RING + 65535) / 65536;
-  uint32_t rbase[NBASE];
-#pragma unroll
-  for (int i = 0; i < NBASE; ++i) {
-    rbase[i] = ring_at + (uint32_t)boff * 2u + 65536u * i;
-    asm volatile("" : "+v"(rbase[i]));
-  }
-  auto operand = [&](int lds_row, int s) -> uint4v {   // w = 32 s + 8 q .. + 7 of one channel
-    uint4v b;
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int at = (lds_row * SROWS + 32 * s + 4 * hh) * 128;
-      typedef fp16x4 __attribute__((address_space(3))) * lds_ptr;
-      const fp16x4 t4 = __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_ptr)(uintptr_t)(rbase[at >> 16] + (uint32_t)(at & 65535)));
-      const uint2v u2 = __builtin_bit_cast(uint2v, t4);
-      b[2 * hh] = u2[0]; b[2 * hh + 1] = u2[1];
-    }
-    return b;
+  // Step u of a round: the wave's row u / KW, positions 32 (u % KW) + 16 hh + 4 q + 2 j + l16 / 8, channels 8 (l16 % 8) .. + 7.
+  const int late8 = l16 >> 3, piece = 2 * (l16 & 7) + late8;   // the lane's operand column: channels 4 piece .. + 3
+  const uint32_t src = (uint32_t)((4 * q + late8) * a.d + 8 * (l16 & 7)) * 2u;   // this lane's bytes of its first position
+  // The workgroups of a plane go through a round's rows in different orders, so that each is the first one to ask memory for
+  // a part of them and finds the rest in the L2: half of them take the second eight rows first (nothing else depends on
+  // it), and for every other pair of W tiles the halves of a row change places (the order of the sum, so it goes by the tile
+  // and not by the workgroup: the same coefficient may come from another grouping of tiles).
+  const uint32_t step16 = (uint32_t)a.d * 32u;   // bytes of 16 positions
+  uint4v x[D][2][2];
+  struct Order { int64_t second; int32_t lo, hi; int first; };   // bytes from the first row of a round to the second, of the changes; the first row
+  auto order = [&](int r) -> Order {
+    Order o;
+    const int late = (KT == 1 ? r : r >> 1) & 1, turned = KW % 2 == 0 && NW16 % 2 == 0 ? (KT == 1 ? r >> 1 : r) & 1 : 0;
+    o.first = wave + 8 * late;
+    o.second = (late ? -8 : 8) * row_bytes;
+    o.lo = turned * (W / 2) * a.d * 2;
+    o.hi = -o.lo;
+    return o;
   };
-  bf16x8 Ah[KW], Al[KW];   // matrix terms of the W tile: rows kw, k = w
-  int a_tile = -1;
-  float tot = 0.f;
-  ushort2v amax = {0, 0};
-  // the first row's operands (and everybody's part of the H matrix and the zero rows)
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((SLOTS - 2) * NPW) : "memory");
-  uint4v b[2][KW];   // operands of two rows
+  auto request = [&](const char* rows, const Order& o, int u) {
+    uint32_t at = src;
+    asm("" : "+v"(at));   // (a 32-bit offset to the compiler, which the load itself adds to a base in scalar registers)
 #pragma unroll
-  for (int s = 0; s < KW; ++s) b[0][s] = operand(0, s);
-  for (int l = blockIdx.x >> 3; l < n_items; l += J) {
-    const Item it = decode(l);
-    const int kw0 = (it.r * KT + kt) * 16;     // first W coefficient of this wave
-    if (kw0 != a_tile) {
-      a_tile = kw0;
-#pragma unroll
-      for (int s = 0; s < KW; ++s) {
-        const int ln = TIGHT ? wh_lane() : lane, k = 32 * s + 8 * (ln >> 4);
-        half8 m = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (kw0 < a.kw && k < W) m = *(const half8*)((const char*)(a.Mw + (size_t)kw0 * W) + (uint32_t)((ln & 15) * W + k) * 2u);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float f = (float)m[j];
-          const float hi = __uint_as_float(__float_as_uint(f) & 0xffff0000u);
-          Ah[s][j] = (__bf16)hi;
-          Al[s][j] = (__bf16)(f - hi);
-        }
-      }
-    }
-    // The sets of waves that read a plane share the sums and the range check of its rows: a set takes every nm-th group.
-    const int nm = R * SETS, me = it.r * SETS + set;
-    int turn = 0;   // group of the plane mod nm
-    const bool more = l + J < n_items;
-    const uint16_t* pnext = more ? decode(l + J).in : nullptr;
-    int left = n_groups - (SLOTS - 1);   // groups of this item still to be requested
-
-    float4v acc[16][KHT];
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-#pragma unroll
-      for (int n = 0; n < KHT; ++n) acc[k][n] = float4v{0.f, 0.f, 0.f, 0.f};
-
-    float te[2] = {0.f, 0.f};
-    for (int h0 = 0; h0 < a.H; h0 += 16) {
-      uint32_t st[4][4][2];   // [kw 4 q + r][4 rows h][pair of rows]
-#pragma unroll
-      for (int p = 0; p < 8; ++p) {   // pairs of rows = groups
-        uint32_t first[4];   // the first row's results
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          float4v y[2];
-          // The operands of a row are requested while the row before it is multiplied: the second row of the group, then
-          // the first row of the next group, behind the barrier that says it has arrived - and that everybody has done
-          // with the slot of the group before this one (its operands have been multiplied), which the next copies go into.
-          if (u == 1) {
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((SLOTS - 3) * NPW) : "memory");
-            if (left == 0 && more) pf = pnext;
-            if (left <= 0 && !more) pf -= group_stride;
-            copy_group(pf, (p + SLOTS - 1) % SLOTS);
-            pf += group_stride;
-            --left;
-          }
-#pragma unroll
-          for (int s = 0; s < KW; ++s) b[u ^ 1][s] = operand(((p + u) % SLOTS) * GR + (u ^ 1), s);
-          __builtin_amdgcn_sched_barrier(0);
-          // (In front of the products: a draft with this branch behind them gave wrong sums.  Its cause was not shown - the
-          // compiler keeps the wait states between a product and the first use of its result on both ways of a branch, 8 here
-          // as in that form - so the order stays.)
-          if (turn == me) {
-#pragma unroll
-            for (int s = 0; s < KW; ++s)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const uint32_t x = b[u][s][j];
-                const uint32_t m = x & 0x7fff7fffu;
-                amax = __builtin_elementwise_max(amax, __builtin_bit_cast(ushort2v, m));
-                te[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, x), te[j & 1], false);
-              }
-          }
-          y[0] = y[1] = float4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s = 0; s < KW; ++s) {
-            y[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Al[s], __builtin_bit_cast(bf16x8, b[u][s]), y[0], 0, 0, 0);
-            y[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah[s], __builtin_bit_cast(bf16x8, b[u][s]), y[1], 0, 0, 0);
-          }
-          // (pinned here: postponed to the exchange below, the rounding would keep twice the registers alive)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const _Float16 h = (_Float16)(y[0][r] + y[1][r]);
-            const uint32_t bits = __builtin_bit_cast(uint16_t, h);
-            if (u == 0) {
-              first[r] = bits;
-              asm volatile("" : "+v"(first[r]));
-            } else {
-              uint32_t pk = first[r] | (bits << 16);
-              asm volatile("" : "+v"(pk));
-              st[r][p >> 1][p & 1] = pk;
-            }
-          }
-        }
-        if (++turn == nm) turn = 0;
-      }
-      half4 B[KHT];
-      const int ln = TIGHT ? wh_lane() : lane;
-#pragma unroll
-      for (int n = 0; n < KHT; ++n) B[n] = *(const half4*)(Mh + (16 * (ht * KHT + n) + (ln & 15)) * mstr + h0 + 4 * (ln >> 4));
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        // block b of lane group g: rows 4 b .. of kw 4 g + r  ->  block g of kw 4 b + r
+    for (int hh = 0; hh < 2; ++hh)
+      if (32 * (u % KW) + 16 * hh < W)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          auto s0 = __builtin_amdgcn_permlane32_swap(st[r][0][j], st[r][2][j], false, false);
-          auto s1 = __builtin_amdgcn_permlane32_swap(st[r][1][j], st[r][3][j], false, false);
-          auto t0 = __builtin_amdgcn_permlane16_swap(s0[0], s1[0], false, false);
-          auto t1 = __builtin_amdgcn_permlane16_swap(s0[1], s1[1], false, false);
-          st[r][0][j] = t0[0]; st[r][1][j] = t0[1]; st[r][2][j] = t1[0]; st[r][3][j] = t1[1];
+          typedef const char __attribute__((address_space(1))) * ptr;
+          ptr p = (ptr)(rows + (u / KW ? o.second : 0) + (KW % 2 ? 0 : 2 * (u % KW) < KW ? o.lo : o.hi) + (size_t)(2 * (u % KW) + hh) * step16 + j * (step16 >> 3));
+          asm("" : "+s"(p));
+          x[u % D][hh][j] = *(const uint4v __attribute__((address_space(1)))*)(p + at);
         }
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const half4 A = __builtin_bit_cast(half4, uint2v{st[r][b][0], st[r][b][1]});
-#pragma unroll
-          for (int n = 0; n < KHT; ++n) acc[4 * b + r][n] = __builtin_amdgcn_mfma_f32_16x16x16f16(A, B[n], acc[4 * b + r][n], 0, 0, 0);
-        }
-      }
-    }
-    // (wait states between the last products and the first use of their accumulators, whatever way leads there)
-    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    tot += te[0] + te[1];
+  };
 
-    // A lane holds channels 4 q .. + 3 of the wave's 16 at kh = 16 (ht KHT + n) + l16.  Two kw at a time go through LDS, where the
-    // four waves of a set put their channels together: whole 128-byte rows are stored.
-    {
-      const bool mine = kw0 < a.kw;
-      const int64_t kh_stride = (int64_t)a.T * a.kw * a.d;
-      const int ln = TIGHT ? wh_lane() : lane, l16 = ln & 15, q = ln >> 4;
-      const int row = wc * 8 + (ln >> 3);   // kw = row / 16, kh = row % 16
-      const uint32_t lane_out = ((uint32_t)(row & 15) * (uint32_t)kh_stride + (uint32_t)((row >> 4) * a.d + (ln & 7) * 8)) * 2u;
+  // between the axes: piece of 4 channels p4 of (row h, coefficient k) sits at h RB + (k ^ (k / 4 & 1)) 128 + (p4 ^ (h / 4 & 1)) 8,
+  // which spreads what half a wave writes (two groups of 4 coefficients) and reads (8 rows) over all banks
+  const unsigned ys_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)Ys;
+  uint32_t put[2];   // (coefficients 4 q and 4 q + 1 of a tile)
 #pragma unroll
-      for (int n = 0; n < KHT; ++n) {
-        const bool store = mine && 16 * (ht * KHT + n) < a.kh;
-        char* dst = (char*)(it.out + 16 * (ht * KHT + n) * kh_stride + (int64_t)kw0 * a.d);
+  for (int r = 0; r < 2; ++r) put[r] = (uint32_t)(wave * RB + ((4 * q + r) ^ (q & 1)) * 128 + ((piece ^ ((wave >> 2) & 1)) * 8));
+  // (transposing read: lane 4 k + c of a group of 16 names row k, piece c of the four; row 4 q + k, pieces 8 p + 2 c + b)
+  const uint32_t get0 = ys_at + (uint32_t)((4 * q + (l16 >> 2)) * RB + ((2 * (l16 & 3) + (q & 1)) * 8));
+  const uint32_t get1 = get0 ^ 8u;   // (b = 1)
+
+  int l = blockIdx.x >> 3;
+  Item it = decode(l);
+  Order ord = order(it.r);
+  const char* rows = it.in + ord.first * row_bytes;   // this wave's first row of the round
 #pragma unroll
-        for (int k = 0; k < 16; k += 2) {
-          char* sb = stage + ((k >> 1) % EB) * (32 * WH_EROW);
-          if (EB == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  for (int u = 0; u < D; ++u) request(rows, ord, u);
+
+  tot[tid] = 0.f;   // (a wave's own)
+  ushort2v amax = {0, 0};
+  int a_r = -1, buf = 0;
+  for (;;) {
+    if (it.r != a_r) {   // (everybody's last reads of the operands that go: behind the barrier of the last round)
+      a_r = it.r;
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      for (int e = tid; e < KT * KW * 64; e += 64 * WH_WAVES) {
+        const int ln = e & 63, s = (e >> 6) % KW, kt = (e >> 6) / KW;
+        const int kw0 = (it.r * KT + kt) * 16;
+        bf16x8 hi, lo;
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk) {
-            uint2v v;
+        for (int hh = 0; hh < 2; ++hh) {
+          const int w = 32 * s + (KW % 2 ? 0 : 2 * s < KW ? ord.lo : ord.hi) / (2 * a.d) + 16 * hh + 4 * (ln >> 4);
+          half4 m = {0, 0, 0, 0};
+          if (kw0 < a.kw && w < W) m = *(const half4*)(a.Mw + (size_t)(kw0 + (ln & 15)) * W + w);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const _Float16 lo = (_Float16)acc[k + kk][n][2 * j], hi = (_Float16)acc[k + kk][n][2 * j + 1];
-              v[j] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
-            }
-            *(uint2v*)(sb + (kk * 16 + l16) * WH_EROW + wc * 32 + q * 8) = v;
+          for (int j = 0; j < 4; ++j) {
+            const float f = (float)m[j];
+            const float h = __uint_as_float(__float_as_uint(f) & 0xffff0000u);
+            hi[4 * hh + j] = (__bf16)h;
+            lo[4 * hh + j] = (__bf16)(f - h);
           }
-          asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-          const uint4v v = *(const uint4v*)(sb + row * WH_EROW + (ln & 7) * 16);
-          if (store) *(uint4v*)(dst + lane_out) = v;
-          dst += (size_t)a.d * 4;
+        }
+        Aw[((kt * KW + s) * 2 + 0) * 64 + ln] = __builtin_bit_cast(uint4v, hi);
+        Aw[((kt * KW + s) * 2 + 1) * 64 + ln] = __builtin_bit_cast(uint4v, lo);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    const bool more = l + J < n_items;
+    Item next = it;
+    if (more) next = decode(l + J);
+    const Order ord_next = order(next.r);
+
+    float4v acc[2 * KT][4][KH];
+#pragma unroll
+    for (int k = 0; k < 2 * KT; ++k)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int n = 0; n < KH; ++n) acc[k][c][n] = float4v{0.f, 0.f, 0.f, 0.f};
+    float te[4] = {0.f, 0.f, 0.f, 0.f};
+    int turn = it.r;   // the workgroups of a plane share the sums and the range check of its rows, round by round
+    for (int h0 = 0; h0 < a.H; h0 += 16) {
+      // (behind the last item its rows once more, so that the code does not depend on it)
+      const char* rows_next = h0 + 16 < a.H ? rows + 16 * row_bytes : next.in + ord_next.first * row_bytes;
+      const bool mine = turn == 0;
+      turn = turn == 0 ? R - 1 : turn - 1;
+      float4v y[KT][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int s = u % KW;
+        constexpr int LAST = NW16 & 1;   // the last step of a row has 16 positions
+        const bool half = LAST && s == KW - 1;
+        if (s == 0)
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) y[kt][c] = float4v{0.f, 0.f, 0.f, 0.f};
+        uint4v A[KT][2];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) A[kt][1] = Aw[((kt * KW + s) * 2 + 1) * 64 + lane];
+        uint4v B[4];   // channels 4 piece + c
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {   // positions 4 q + 2 (i % 2), + 1 of 16
+          if (half && i >= 2) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) B[c][i] = 0u;
+            continue;
+          }
+          const uint4v v = x[u % D][i >> 1][i & 1];
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {   // words of the lane's 4 channels: of the even and of the odd position
+            const uint32_t lo = v[w], hi = v[2 + w];
+            const uint32_t even = wh_from_other(lo, hi, 0xc), odd = wh_from_other(hi, lo, 0x3);
+            B[2 * w][i] = __builtin_amdgcn_perm(odd, even, 0x05040100u);
+            B[2 * w + 1][i] = __builtin_amdgcn_perm(odd, even, 0x07060302u);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (mine) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < (half ? 2 : 4); ++i) {
+              const uint32_t xx = B[c][i], m = xx & 0x7fff7fffu;
+              amax = __builtin_elementwise_max(amax, __builtin_bit_cast(ushort2v, m));
+              te[c] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, xx), __builtin_bit_cast(bf16x2, xx), te[c], false);
+            }
+        }
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) A[kt][0] = Aw[((kt * KW + s) * 2 + 0) * 64 + lane];
+#pragma unroll
+        for (int t = 1; t >= 0; --t)   // the small terms first
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              if (half) {
+                const short4v Ah = __builtin_bit_cast(short4v, uint2v{A[kt][t][0], A[kt][t][1]}), Bh = __builtin_bit_cast(short4v, uint2v{B[c][0], B[c][1]});
+                y[kt][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ah, Bh, y[kt][c], 0, 0, 0);
+              } else {
+                y[kt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[kt][t]), __builtin_bit_cast(bf16x8, B[c]), y[kt][c], 0, 0, 0);
+              }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        request(u + D < U ? rows : rows_next, u + D < U || h0 + 16 < a.H ? ord : ord_next, (u + D) % U);   // (here its registers are free)
+        if (s == KW - 1)
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              half4 v;
+#pragma unroll
+              for (int c = 0; c < 4; ++c) v[c] = (_Float16)y[kt][c][r];
+              *(half4*)(Ys + (buf * 16 + 8 * ((u / KW) ^ (ord.first >> 3))) * RB + kt * 2048 + (r >> 1) * 256 + put[r & 1]) = v;
+            }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      rows = rows_next;
+      // Rows are there; and whoever is past this has read the buffer the next round writes into.
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      half4 Bm[KH];
+#pragma unroll
+      for (int n = 0; n < KH; ++n) Bm[n] = *(const half4*)(Mh + (16 * n + l16) * mstr + h0 + 4 * q);
+#pragma unroll
+      for (int k = 0; k < 2 * KT; ++k) {
+        const int kw = wave * 2 * KT + k;
+        const uint32_t at = (uint32_t)(buf * 16 * RB + (kw ^ ((kw >> 2) & 1)) * 128);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {   // 16 channels 32 (c / 2) + 8 (i / 4) + 4 (c % 2) + i % 4
+          typedef fp16x4 __attribute__((address_space(3))) * lds_ptr;
+          const fp16x4 t4 = __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_ptr)(uintptr_t)((c & 1 ? get1 : get0) + at + 64u * (c >> 1)));
+          const half4 Ay = __builtin_bit_cast(half4, t4);
+#pragma unroll
+          for (int n = 0; n < KH; ++n) acc[k][c][n] = __builtin_amdgcn_mfma_f32_16x16x16f16(Ay, Bm[n], acc[k][c][n], 0, 0, 0);
+        }
+      }
+      buf ^= 1;
+    }
+    if (a.tot_part) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        te[c] += __shfl_xor(te[c], 16);
+        te[c] += __shfl_xor(te[c], 32);
+      }
+      if (q == 0) *(float4v*)(tot + wave * 64 + 4 * piece) += float4v{te[0], te[1], te[2], te[3]};
+    }
+    {
+      const int64_t kh_stride = (int64_t)a.T * a.kw * a.d;
+      // A lane holds channels 32 p + 8 q .. + 7 at kh = 16 n + l16.  Sixteen rows at a time go through LDS, so that eight neighbouring
+      // lanes store a row's 128 bytes.
+      // The place is the wave's own: the row it writes first in the next round.
+      char* stage = Ys + (buf * 16 + wave) * RB;
+      char* const put_at = stage + l16 * 128;
+      const char* const get_at = stage + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
+      const uint32_t lane_out = ((uint32_t)(lane >> 3) * (uint32_t)kh_stride + 8u * (uint32_t)(lane & 7)) * 2u;
+#pragma unroll
+      for (int k = 0; k < 2 * KT; ++k) {
+        const int kw = it.r * 16 * KT + wave * 2 * KT + k;
+        if (kw >= a.kw) continue;
+#pragma unroll
+        for (int n = 0; n < KH; ++n) {
+          if (16 * n >= a.kh) continue;
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            half8 v;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = (_Float16)acc[k][2 * p + (i >> 2)][n][i & 3];
+            *(half8*)(put_at + (((4 * p + q) ^ (l16 & 7)) * 16)) = v;
+          }
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          char* dst = (char*)(it.out + 16 * n * kh_stride + (int64_t)kw * a.d) + lane_out;
+#pragma unroll
+          for (int p = 0; p < 2; ++p) *(uint4v*)(dst + 16 * p * kh_stride) = *(const uint4v*)(get_at + p * 1024);
+          __builtin_amdgcn_wave_barrier();
         }
       }
     }
+    if (!more) break;
+    l += J;
+    it = next;
+    ord = ord_next;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may land in LDS that another workgroup owns by then
   // an input that fp16 cannot hold (the spectral buffers' range contract), infinities and NaN included
   if (a.range_flag && (amax[0] >= 0x4780 || amax[1] >= 0x4780)) *a.range_flag = 1;
-  if (a.tot_part) {   // per channel of the workgroup's chunk, this wave's rows
-    tot += __shfl_xor(tot, 16);
-    tot += __shfl_xor(tot, 32);
-    if (q == 0) a.tot_part[((size_t)set * gridDim.x + blockIdx.x) * 64 + wc * 16 + l16] = tot;
-  }
+  if (a.tot_part) a.tot_part[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = tot[tid];   // per channel of the workgroup's chunk
 }
 
-template <int NW16, int KHT, int KT, int HT>
+template <int NW16, int KT, int KH>
 static hipError_t wh_launch(WhPassArgs a, int num_cu, hipStream_t st, int* slots_out) {
-  constexpr int RING = wh_slots<NW16, KT * HT>() * WH_GR * ((NW16 + 1) / 2) * 4096;
-  constexpr int STAGE = KT * HT * wh_out_buffers<NW16>() * 32 * WH_EROW;
-  static_assert(RING + STAGE + 16 * KHT * HT * (128 + 8) * 2 <= 160 * 1024, "LDS of one compute unit");
-  const int lds = RING + STAGE + 16 * KHT * HT * (a.H + 8) * 2;
+  constexpr int FIXED = 2 * 16 * wh_row_bytes(KT) + KT * ((NW16 + 1) / 2) * 2048 + WH_WAVES * 64 * 4;
+  static_assert(FIXED + 16 * KH * (128 + 8) * 2 <= 160 * 1024, "LDS of one compute unit");
+  const int lds = FIXED + 16 * KH * (a.H + 8) * 2;
   a.members = (a.kw / 16 + KT - 1) / KT;
   const int64_t planes = (int64_t)a.seg_end[2] * a.T * (a.d / 64);
   if (planes <= 0) return hipSuccess;
   if (planes * a.members > 0x3fffffff) return hipErrorInvalidValue;
-  // per-lane byte offsets are unsigned 32-bit numbers: 16 rows kh of the output, the rows of a group of the input
-  if ((int64_t)a.T * a.kw * a.d * 2 * 16 > 0xffffffffLL || (int64_t)WH_GR * 16 * NW16 * a.d * 2 > 0xffffffffLL) return hipErrorInvalidValue;
-  const int per_cu = std::min(2 / (KT * HT), 160 * 1024 / lds);
+  // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
+  if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
+  // per-lane byte offsets are unsigned 32-bit numbers: 16 rows kh of the output, 16 positions of the input
+  if ((int64_t)a.T * a.kw * a.d * 2 * 16 > 0xffffffffLL) return hipErrorInvalidValue;
+  const int per_cu = std::min(wh_waves_per_simd((NW16 + 1) / 2, KT, KH) / 2, 160 * 1024 / lds);
   const int64_t per_xcd = (planes + 7) / 8 * a.members;   // items of the fullest XCD
   const int grid = 8 * (int)std::min<int64_t>(per_xcd, std::max(1, num_cu / 8) * per_cu);
   static OncePerDevice limit;
-  hipError_t e = allow_lds(limit, (const void*)k_wh_pass<NW16, KHT, KT, HT>, 160 * 1024);
+  hipError_t e = allow_lds(limit, (const void*)k_wh_pass<NW16, KT, KH>, 160 * 1024);
   if (e != hipSuccess) return e;
-  if (slots_out) *slots_out = grid * KT * HT;
-  hipLaunchKernelGGL((k_wh_pass<NW16, KHT, KT, HT>), dim3((unsigned)grid), dim3(256 * KT * HT), (size_t)lds, st, a);
+  if (slots_out) *slots_out = grid * WH_WAVES;
+  hipLaunchKernelGGL((k_wh_pass<NW16, KT, KH>), dim3((unsigned)grid), dim3(64 * WH_WAVES), (size_t)lds, st, a);
   return hipGetLastError();
 }
 
@@ -384,14 +384,15 @@ static hipError_t wh_dispatch(const WhPassArgs& a, int num_cu, hipStream_t st, i
   const int kht = a.kh / 16;
   // A single W tile: the whole axis of 16, or the box of an axis that can be cut that far (a power of two).
   if constexpr ((NW16 & (NW16 - 1)) == 0) {
-    if (a.kw == 16 && kht == 1) return wh_launch<NW16, 1, 1, 1>(a, num_cu, st, slots_out);
-    if (a.kw == 16 && kht == 2) return wh_launch<NW16, 2, 1, 1>(a, num_cu, st, slots_out);
+    if (a.kw == 16 && kht == 1) return wh_launch<NW16, 1, 1>(a, num_cu, st, slots_out);
+    if (a.kw == 16 && kht == 2) return wh_launch<NW16, 1, 2>(a, num_cu, st, slots_out);
   }
   if constexpr (NW16 > 1) {
-    if (a.kw > 16 && kht == 1) return wh_launch<NW16, 1, 2, 1>(a, num_cu, st, slots_out);
-    if (a.kw > 16 && kht == 2) return wh_launch<NW16, 2, 2, 1>(a, num_cu, st, slots_out);
+    if (a.kw > 16 && kht == 1) return wh_launch<NW16, 2, 1>(a, num_cu, st, slots_out);
+    if (a.kw > 16 && kht == 2) return wh_launch<NW16, 2, 2>(a, num_cu, st, slots_out);
   }
-  if (kht == 3 || kht == 4) return wh_launch<NW16, 2, 1, 2>(a, num_cu, st, slots_out);
+  if (kht == 3) return wh_launch<NW16, 1, 3>(a, num_cu, st, slots_out);
+  if (kht == 4) return wh_launch<NW16, 1, 4>(a, num_cu, st, slots_out);
   return hipErrorInvalidValue;
 }
 

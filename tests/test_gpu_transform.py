@@ -49,6 +49,19 @@ def test_spectral_coefficients(grid, d):
     assert worst <= 2e-3, worst
 
 
+# whole planes of three and four tiles of H coefficients with one to eight workgroups on a plane, an odd number of them, and a last
+# step of a row that is half empty; fewer planes than an XCD has workgroups
+@pytest.mark.parametrize("grid,d", [((16, 64, 16), 128), ((16, 48, 48), 128), ((16, 48, 112), 128), ((16, 64, 112), 64), ((16, 64, 128), 64),
+                                    ((16, 48, 128), 128)])
+def test_spectral_coefficients_of_whole_planes(grid, d):
+    test_spectral_coefficients(grid, d)
+
+
+# a model width that is no power of two times 64: chunks of 64 channels in other places of the XCDs' lists
+def test_projected_forward_of_a_model_of_192_channels():
+    test_projected_forward_of_narrow_models(192)
+
+
 # boxes of one and two 16-coefficient tiles per axis (n low and n low+mid heads: enough planes for the one-pass inverse), whole
 # planes and parts of planes per workgroup, added to V and - where the box is the whole grid - not; an axis of 48, which is kept
 # whole and takes the two passes
