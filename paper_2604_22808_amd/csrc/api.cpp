@@ -738,7 +738,7 @@ static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int n
   }
   if (n == 0) return hipSuccess;
   for (int i = n; i < 3; ++i) f.seg_end[i] = t.seg_end[i] = total;
-  f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw;
+  f.T = T; f.d = d; f.rows = f.ldh = H; f.cols = f.ldw = W; f.out_rows = kh; f.out_cols = kw;
   int slots = 0;
   // (its copies into LDS move whole 16-byte pieces of the caller's tensors; a view that starts between them takes the two passes)
   bool fused = one_pass(c, kt < T || kh < H || kw < W, d);
@@ -819,6 +819,12 @@ static hipError_t inverse_transform_mfma(Ctx& c, void* out, const void* v_in, hi
   f.in = c.tmp1; f.out = out; f.resid = delta ? v_in : nullptr; f.slice_list = slice_list; f.n_slices = ns;
   f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw; f.Fh = c.d_Ft16[1]; f.Fw = c.d_Ft16[2];
   if (!wide && iwh_fits(f, c.num_cu)) return launch_iwh_pass(f, c.num_cu, st);   // H and W axes in one pass
+  WhPassArgs g{};
+  g.in[0] = c.tmp1; g.out[0] = out; g.slice_list[0] = slice_list; g.resid = delta ? v_in : nullptr;
+  for (int i = 0; i < 3; ++i) g.seg_end[i] = ns;
+  g.T = T; g.d = d; g.rows = kh; g.cols = kw; g.out_rows = g.ldh = H; g.out_cols = g.ldw = W;
+  g.Mh = c.d_Ft16[1]; g.Mw = c.d_Ft16[2];
+  if (hw_fits(g)) return launch_hw_inverse(g, c.num_cu, st);   // the same, boxes of any size
 
   DctPassArgs b{};
   b.d = d; b.Ntok = c.N;

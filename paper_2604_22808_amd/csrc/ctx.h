@@ -315,25 +315,31 @@ struct DctPassArgs {
 #define DCT_MAX_WAVES 65536   // upper bound of waves in one launch of the DCT pass (sizes energy_part)
 hipError_t launch_mfma_dct_pass(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out = nullptr);
 bool mfma_dct_supported(int n_in, int n_out);
-// W and H axes of the forward transform in one pass (mfma_wh_impl.h).
+// W and H axes of the forward transform in one pass, or those of the inverse (mfma_wh_impl.h): input rows of `cols` values
+// through the W matrix, `rows` of them through the H matrix.
 struct WhPassArgs {
-  // up to three tensors: segment i is slices [seg_end[i-1], seg_end[i]) of the launch, slice sl of a segment is
-  // slice_list[i][sl] of in[i] (NULL: sl itself) and slice sl of out[i]
-  const void* in[3]; void* out[3];                  // in: bf16 [slices][T][H][W][d]; out: fp16 [segment's slices][kh][T][kw][d]
+  // up to three tensors: segment i is slices [seg_end[i-1], seg_end[i]) of the launch, slice sl of a segment is slice_list[i][sl]
+  // (NULL: sl itself) of the caller's tensor and slice sl of the compact one
+  // forward: in (caller's) bf16 [slices][T][rows][cols][d], out (compact) fp16 [segment's slices][out_rows][T][out_cols][d]
+  // inverse: in (compact) fp16 [segment's slices][rows][T][cols][d], out (caller's) bf16 [slices][T][out_rows][out_cols][d]
+  const void* in[3]; void* out[3];
   const int32_t* slice_list[3]; int seg_end[3];
-  int T, H, W, d, kh, kw;                           // d: channels per token; kh, kw: coefficients kept (multiples of 16)
-  const half_t* Mh; const half_t* Mw;               // fp16 [H][H], [W][W]: rows are coefficients
-  float* tot_part;                                  // [slot][64]: sum of squares of the inputs per channel, or NULL
-  int32_t* range_flag;                              // set when an input value leaves the fp16 range
-  int members;                                      // (filled in by the launcher) workgroups that share a plane
+  int T, d, rows, cols, out_rows, out_cols;         // d: channels per token (a multiple of 64); the rest multiples of 16
+  const half_t* Mh; const half_t* Mw; int ldh, ldw; // fp16 [out_rows][>= rows], [out_cols][>= cols] with their row strides
+  const void* resid;                                // inverse: bf16, addressed like out, added, or NULL
+  float* tot_part;                                  // forward: [slot][64]: sum of squares of the inputs per channel, or NULL
+  int32_t* range_flag;                              // forward: set when an input value leaves the fp16 range
+  int members, col_parts;                           // (filled in by the launcher) workgroups that share a plane
 };
 // Whether the pass takes kh x kw coefficients of H x W planes with d channels per token.
 bool wh_fits(int d, int H, int W, int kh, int kw);
 hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W <= 64
 hipError_t launch_wh_pass_1(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W > 64
 inline hipError_t launch_wh_pass(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
-  return a.W <= 64 ? launch_wh_pass_0(a, num_cu, st, slots_out) : launch_wh_pass_1(a, num_cu, st, slots_out);
+  return a.cols <= 64 ? launch_wh_pass_0(a, num_cu, st, slots_out) : launch_wh_pass_1(a, num_cu, st, slots_out);
 }
+bool hw_fits(const WhPassArgs& a);   // whether the inverse takes these sizes and is faster than an axis at a time
+hipError_t launch_hw_inverse(const WhPassArgs& a, int num_cu, hipStream_t st);
 // H and W axes of the inverse transform in one pass (mfma_iwh_impl.h).
 struct IwhPassArgs {
   const void* in; void* out; const void* resid;     // in: fp16 [n_slices][kh][T][kw][d]; out: bf16 [slices][T][H][W][d]; resid: like out, added, or NULL

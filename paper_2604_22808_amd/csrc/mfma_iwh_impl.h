@@ -8,9 +8,8 @@
 // row of the output goes through LDS, where the four waves put their channels together, and is added to the row of V that
 // was requested some rows earlier.  The tensor between the axes never reaches memory.
 //
-// Bound by HBM: it reads V and writes the output, the coefficients are 1/16 or 1/4 of that.  16 slices of 64^3 x 128 from the
-// 16 x 16 box 507 (two passes) -> 412 us, 6 from the 32 x 32 box 278 -> 232 us (one wave per SIMD: the plane takes half the
-// registers), 16 slices of 16 x 64 x 64 x 64 from the 16 x 16 box 68 -> 51 us.
+// Bound by HBM: it reads V and writes the output, the coefficients are a small part of that.  16 slices of 64^3 x 128 from the
+// 16 x 16 box 507 (two passes) -> 412 us, 16 slices of 16 x 64 x 64 x 64 from the 16 x 16 box 68 -> 51 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,7 +38,7 @@ __device__ __forceinline__ uint32_t iwh_bf16(float f) {   // round to nearest ev
 }
 
 // Waves per SIMD, and workgroups per compute unit: the plane takes 32 registers per 256 coefficients.
-template <int KHS, int KWT> constexpr int iwh_waves() { return KHS * KWT == 1 ? 3 : KHS * KWT == 2 ? 2 : 1; }
+template <int KHS, int KWT> constexpr int iwh_waves() { return KHS * KWT == 1 ? 3 : 2; }
 constexpr int IWH_ROW = 144;   // bytes per staged row of 64 channels (128 + 16: rows side by side take all LDS banks once)
 
 // (RESID is a template argument: with the branch inside, between a product and the first use of its result, a draft of the forward
@@ -50,7 +49,7 @@ __global__ void __launch_bounds__(256, (iwh_waves<KHS, KWT>())) k_iwh_pass(IwhPa
   constexpr int NP = (NW16 + 1) / 2;    // 16-byte pieces of an output row per thread
   constexpr int SKW = 4;                // kw per slice of the plane on its way into registers
   constexpr int NS = KH * SKW * 8 / 256;   // 16-byte pieces of a slice per thread
-  constexpr int VD = KHS * KWT > 2 ? 4 : 2;   // rows of V requested ahead
+  constexpr int VD = 2;   // rows of V requested ahead
   constexpr int ROWS = 2 * W > SKW * KH ? 2 * W : SKW * KH;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   char* stage = smem;                                       // [ROWS][IWH_ROW]
@@ -243,7 +242,6 @@ static hipError_t iwh_dispatch(const IwhPassArgs& a, int num_cu, hipStream_t st)
   if (s == 1 && u == 1) return iwh_launch<NW16, 1, 1>(a, num_cu, st);
   if constexpr (NW16 >= 2) {
     if (s == 1 && u == 2) return iwh_launch<NW16, 1, 2>(a, num_cu, st);
-    if (s == 2 && u == 2) return iwh_launch<NW16, 2, 2>(a, num_cu, st);
   }
   if (s == 2 && u == 1) return iwh_launch<NW16, 2, 1>(a, num_cu, st);
   return hipErrorInvalidValue;

@@ -1,7 +1,10 @@
 #pragma once
 // The W and H axes of the forward transform (paper section 3.2) in one pass over the input:
 //   out[kh, t, kw, c] = sum_h Mh[kh][h] * fp16( sum_w Mw[kw][w] * x[t, h, w, c] )
-// for up to three tensors (Q, K, V) per launch.  The plane between the two axes never reaches memory.
+// for up to three tensors (Q, K, V) per launch.  The plane between the two axes never reaches memory.  And (INV) those of the
+// inverse transform (section 3.7), the same contraction from fp16 coefficients to bf16 values:
+//   out[t, h, w, c] = (v[t, h, w, c] +) fp16( sum_kh Fh[h][kh] * fp16( sum_kw Fw[w][kw] * y[kh, t, kw, c] ) )
+// where the comments below say coefficients for the output's rows and columns, positions for the input's.
 //
 // A work item is 64 channels of one (tensor, slice, t) plane and KT tiles of 16 W coefficients, all 16 KH H coefficients of
 // them kept as accumulators (32 KT KH registers per wave) for as long as the plane's rows stream by, 16 rows per round:
@@ -25,6 +28,8 @@
 // 32 x 48 x 80 x 128 whole 0.27 -> 0.18.  On the way there (first / second of these): 8 bytes per lane and load, which the L1 serves at
 // 36 bytes per cycle instead of 64, 1.18 / 0.68; stores as the products leave them (16 bytes per lane, neighbouring lanes in different
 // rows) 1.01 / 0.60; all workgroups of a plane taking its rows in the same order (all wait for memory at once) +10 / +3 %.
+// Inverse, against two passes: 17 slices of 64^3 x 128 whole 0.82 -> 0.56 ms; 6 of 64 x 128 x 128 x 128 from the 64 x 64 box 1.18 -> 1.02, from
+// the 32 x 32 box 1.00 -> 0.72; 24 of 32 x 48 x 80 x 128 whole 0.66 -> 0.48.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,9 +51,9 @@ typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 typedef __fp16 fp16x4 __attribute__((__vector_size__(4 * sizeof(__fp16))));
 
 constexpr int WH_WAVES = 8;
-// Steps requested ahead.  They live in registers (16 each) beside the accumulators; the number divides the steps of a round.
-template <int KW, int KT, int KH> constexpr int wh_depth() {
-  if (KT * KH == 1 || KT * KT * KH > 4) return 2;
+// Steps requested ahead (the inverse's rows come from the L2 more often than from memory, and V's take registers in between).  They live in registers (16 each) beside the accumulators; the number divides the steps of a round.
+template <int KW, int KT, int KH, bool INV> constexpr int wh_depth() {
+  if (KT * KH == 1 || KT * KT * KH > 4 || (INV && KH == 4)) return 2;
   return KW == 1 ? 2 : KW == 3 ? 3 : 4;
 }
 constexpr int wh_row_bytes(int KT) { return KT * 2048 + 64; }   // a row between the axes: [16 KT][64] fp16, and 64 bytes against bank conflicts
@@ -60,30 +65,24 @@ __device__ __forceinline__ uint32_t wh_from_other(uint32_t own, uint32_t other, 
                       : __builtin_amdgcn_update_dpp((int)own, (int)other, 0x128, 0xf, 0x3, false);
 }
 
-template <int NW16, int KT, int KH>
+template <int NW16, int KT, int KH, bool INV>
 __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 2, KT, KH)) k_wh_pass(WhPassArgs a) {
-  constexpr int W = 16 * NW16;
+  constexpr int W = 16 * NW16;                 // positions (inverse: coefficients) of an input row
+  constexpr int TERMS = INV ? 1 : 2;           // terms the W matrix is split into
   constexpr int KW = (NW16 + 1) / 2;           // steps of 32 positions w per row (the last one of 16 when NW16 is odd)
   constexpr int U = 2 * KW;                    // steps of a wave per round
-  constexpr int D = wh_depth<KW, KT, KH>();
+  constexpr int D = wh_depth<KW, KT, KH, INV>();
   static_assert(U % D == 0, "a step's registers are known at compile time");
   constexpr int RB = wh_row_bytes(KT);
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   char* Ys = smem;                                              // [2][16] rows between the axes
   uint4v* Aw = (uint4v*)(Ys + 2 * 16 * RB);                     // [KT][KW][hi, lo][lane]: matrix operands of the W axis
-  float* tot = (float*)(Aw + KT * KW * 2 * 64);                 // [wave][64]: sums of squares of the rows a wave has taken
+  float* tot = (float*)(Aw + KT * KW * TERMS * 64);             // [wave][64]: sums of squares of the rows a wave has taken
   half_t* Mh = (half_t*)(tot + WH_WAVES * 64);                  // [16 KH][mstr]
-  const int mstr = a.H + 8;
+  const int mstr = a.rows + 8;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q = lane >> 4;
-
-  for (int e = tid; e < 16 * KH * (a.H / 8); e += 64 * WH_WAVES) {
-    const int row = e / (a.H / 8), c8 = e % (a.H / 8);
-    uint4v v = {0u, 0u, 0u, 0u};
-    if (row < a.kh) v = *(const uint4v*)(a.Mh + (size_t)row * a.H + c8 * 8);
-    *(uint4v*)(Mh + row * mstr + c8 * 8) = v;
-  }
 
   // Items of this workgroup.  Planes are dealt to the XCDs by their index mod 8 (workgroups are dealt round-robin by
   // blockIdx); the R workgroups of a plane have neighbouring places in their XCD's list.  With 64, 128, 256 or 512 channels per
@@ -92,8 +91,10 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
   const int xcd = blockIdx.x & 7, J = gridDim.x >> 3;
   const int n_planes = a.seg_end[2] * a.T * cpt;
   const int n_items = n_planes > xcd ? ((n_planes - xcd + 7) >> 3) * R : 0;
-  const int64_t row_bytes = (int64_t)W * a.d * 2;   // between rows h
-  struct Item { const char* in; half_t* out; int r; };
+  // Rows of the caller's tensors are [slice][t][h][w], rows of the other side [segment's slice][kh][t][kw].
+  const int64_t row_bytes = (INV ? (int64_t)a.T : 1) * W * a.d * 2;                    // between input rows
+  const int64_t out_stride = (INV ? 1 : (int64_t)a.T) * a.out_cols * a.d;              // between output rows, elements
+  struct Item { const char* in; uint16_t* out; int r; };
   auto decode = [&](int l) -> Item {
     Item it;
     it.r = l % R;
@@ -104,10 +105,14 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
     const int sl = p - (seg == 0 ? 0 : seg == 1 ? a.seg_end[0] : a.seg_end[1]);
     const int32_t* list = seg == 0 ? a.slice_list[0] : seg == 1 ? a.slice_list[1] : a.slice_list[2];
     const int64_t slice = __builtin_amdgcn_readfirstlane(list ? list[sl] : sl);   // (addresses stay in scalar registers)
-    it.in = (const char*)(seg == 0 ? a.in[0] : seg == 1 ? a.in[1] : a.in[2]) + (slice * a.T + t) * a.H * row_bytes + chunk * 128;
-    it.out = (half_t*)(seg == 0 ? a.out[0] : seg == 1 ? a.out[1] : a.out[2]) + ((int64_t)sl * a.kh * a.T + t) * a.kw * a.d + chunk * 64;
+    const int64_t whole = (slice * a.T + t) * (INV ? a.out_rows : a.rows) * (int64_t)((INV ? a.out_cols : W) * a.d);
+    const int64_t compact = ((int64_t)sl * (INV ? a.rows : a.out_rows) * a.T + t) * (int64_t)((INV ? W : a.out_cols) * a.d);
+    it.in = (const char*)((const uint16_t*)(seg == 0 ? a.in[0] : seg == 1 ? a.in[1] : a.in[2]) + (INV ? compact : whole) + chunk * 64);
+    it.out = (uint16_t*)(seg == 0 ? a.out[0] : seg == 1 ? a.out[1] : a.out[2]) + (INV ? whole : compact) + chunk * 64;
     return it;
   };
+  // Workgroup r of a plane: column part r % Rc (KT tiles of 16), row part r / Rc (KH tiles of 16; forward passes have one)
+  const int Rc = a.col_parts;
   if ((int)(blockIdx.x >> 3) >= n_items) {   // nothing to do: zero sums
     if (a.tot_part) a.tot_part[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = 0.f;
     return;
@@ -123,8 +128,9 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
   const uint32_t step16 = (uint32_t)a.d * 32u;   // bytes of 16 positions
   uint4v x[D][2][2];
   struct Order { int64_t second; int32_t lo, hi; int first; };   // bytes from the first row of a round to the second, of the changes; the first row
-  auto order = [&](int r) -> Order {
+  auto order = [&](int member) -> Order {
     Order o;
+    const int r = INV ? member % Rc : member;
     const int late = (KT == 1 ? r : r >> 1) & 1, turned = KW % 2 == 0 && NW16 % 2 == 0 ? (KT == 1 ? r >> 1 : r) & 1 : 0;
     o.first = wave + 8 * late;
     o.second = (late ? -8 : 8) * row_bytes;
@@ -173,23 +179,37 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       for (int e = tid; e < KT * KW * 64; e += 64 * WH_WAVES) {
         const int ln = e & 63, s = (e >> 6) % KW, kt = (e >> 6) / KW;
-        const int kw0 = (it.r * KT + kt) * 16;
-        bf16x8 hi, lo;
+        const int c0 = ((INV ? it.r % Rc : it.r) * KT + kt) * 16;   // first output column of the tile
+        half8 m8;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
           const int w = 32 * s + (KW % 2 ? 0 : 2 * s < KW ? ord.lo : ord.hi) / (2 * a.d) + 16 * hh + 4 * (ln >> 4);
           half4 m = {0, 0, 0, 0};
-          if (kw0 < a.kw && w < W) m = *(const half4*)(a.Mw + (size_t)(kw0 + (ln & 15)) * W + w);
+          if (c0 < a.out_cols && w < W) m = *(const half4*)(a.Mw + (size_t)(c0 + (ln & 15)) * a.ldw + w);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float f = (float)m[j];
-            const float h = __uint_as_float(__float_as_uint(f) & 0xffff0000u);
-            hi[4 * hh + j] = (__bf16)h;
-            lo[4 * hh + j] = (__bf16)(f - h);
-          }
+          for (int j = 0; j < 4; ++j) m8[4 * hh + j] = m[j];
         }
-        Aw[((kt * KW + s) * 2 + 0) * 64 + ln] = __builtin_bit_cast(uint4v, hi);
-        Aw[((kt * KW + s) * 2 + 1) * 64 + ln] = __builtin_bit_cast(uint4v, lo);
+        if constexpr (INV) {
+          Aw[(kt * KW + s) * 64 + ln] = __builtin_bit_cast(uint4v, m8);
+        } else {
+          bf16x8 hi, lo;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float f = (float)m8[j];
+            const float h = __uint_as_float(__float_as_uint(f) & 0xffff0000u);
+            hi[j] = (__bf16)h;
+            lo[j] = (__bf16)(f - h);
+          }
+          Aw[((kt * KW + s) * 2 + 0) * 64 + ln] = __builtin_bit_cast(uint4v, hi);
+          Aw[((kt * KW + s) * 2 + 1) * 64 + ln] = __builtin_bit_cast(uint4v, lo);
+        }
+      }
+      const int row0 = INV ? it.r / Rc * 16 * KH : 0;
+      for (int e = tid; e < 16 * KH * (a.rows / 8); e += 64 * WH_WAVES) {
+        const int row = e / (a.rows / 8), c8 = e % (a.rows / 8);
+        uint4v v = {0u, 0u, 0u, 0u};
+        if (row0 + row < a.out_rows) v = *(const uint4v*)(a.Mh + (size_t)(row0 + row) * a.ldh + c8 * 8);
+        *(uint4v*)(Mh + row * mstr + c8 * 8) = v;
       }
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
@@ -207,9 +227,9 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
         for (int n = 0; n < KH; ++n) acc[k][c][n] = float4v{0.f, 0.f, 0.f, 0.f};
     float te[4] = {0.f, 0.f, 0.f, 0.f};
     int turn = it.r;   // the workgroups of a plane share the sums and the range check of its rows, round by round
-    for (int h0 = 0; h0 < a.H; h0 += 16) {
+    for (int h0 = 0; h0 < a.rows; h0 += 16) {
       // (behind the last item its rows once more, so that the code does not depend on it)
-      const char* rows_next = h0 + 16 < a.H ? rows + 16 * row_bytes : next.in + ord_next.first * row_bytes;
+      const char* rows_next = h0 + 16 < a.rows ? rows + 16 * row_bytes : next.in + ord_next.first * row_bytes;
       const bool mine = turn == 0;
       turn = turn == 0 ? R - 1 : turn - 1;
       float4v y[KT][4];
@@ -225,7 +245,7 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
             for (int c = 0; c < 4; ++c) y[kt][c] = float4v{0.f, 0.f, 0.f, 0.f};
         uint4v A[KT][2];
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) A[kt][1] = Aw[((kt * KW + s) * 2 + 1) * 64 + lane];
+        for (int kt = 0; kt < KT; ++kt) A[kt][TERMS - 1] = Aw[((kt * KW + s) * TERMS + TERMS - 1) * 64 + lane];
         uint4v B[4];   // channels 4 piece + c
 #pragma unroll
         for (int i = 0; i < 4; ++i) {   // positions 4 q + 2 (i % 2), + 1 of 16
@@ -244,7 +264,7 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
           }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (mine) {
+        if (!INV && mine) {
 #pragma unroll
           for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -254,15 +274,23 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
               te[c] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, xx), __builtin_bit_cast(bf16x2, xx), te[c], false);
             }
         }
+        if constexpr (!INV)
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) A[kt][0] = Aw[((kt * KW + s) * 2 + 0) * 64 + lane];
+          for (int kt = 0; kt < KT; ++kt) A[kt][0] = Aw[((kt * KW + s) * 2 + 0) * 64 + lane];
 #pragma unroll
-        for (int t = 1; t >= 0; --t)   // the small terms first
+        for (int t = TERMS - 1; t >= 0; --t)   // the small terms first
 #pragma unroll
           for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-              if (half) {
+              if constexpr (INV) {
+                if (half) {
+                  const half4 Ah = __builtin_bit_cast(half4, uint2v{A[kt][0][0], A[kt][0][1]}), Bh = __builtin_bit_cast(half4, uint2v{B[c][0], B[c][1]});
+                  y[kt][c] = __builtin_amdgcn_mfma_f32_16x16x16f16(Ah, Bh, y[kt][c], 0, 0, 0);
+                } else {
+                  y[kt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, A[kt][0]), __builtin_bit_cast(half8, B[c]), y[kt][c], 0, 0, 0);
+                }
+              } else if (half) {
                 const short4v Ah = __builtin_bit_cast(short4v, uint2v{A[kt][t][0], A[kt][t][1]}), Bh = __builtin_bit_cast(short4v, uint2v{B[c][0], B[c][1]});
                 y[kt][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ah, Bh, y[kt][c], 0, 0, 0);
               } else {
@@ -270,7 +298,7 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
               }
             }
         __builtin_amdgcn_sched_barrier(0);
-        request(u + D < U ? rows : rows_next, u + D < U || h0 + 16 < a.H ? ord : ord_next, (u + D) % U);   // (here its registers are free)
+        request(u + D < U ? rows : rows_next, u + D < U || h0 + 16 < a.rows ? ord : ord_next, (u + D) % U);   // (here its registers are free)
         if (s == KW - 1)
 #pragma unroll
           for (int kt = 0; kt < KT; ++kt)
@@ -304,7 +332,7 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
       }
       buf ^= 1;
     }
-    if (a.tot_part) {
+    if (!INV && a.tot_part) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         te[c] += __shfl_xor(te[c], 16);
@@ -313,34 +341,74 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
       if (q == 0) *(float4v*)(tot + wave * 64 + 4 * piece) += float4v{te[0], te[1], te[2], te[3]};
     }
     {
-      const int64_t kh_stride = (int64_t)a.T * a.kw * a.d;
-      // A lane holds channels 32 p + 8 q .. + 7 at kh = 16 n + l16.  Sixteen rows at a time go through LDS, so that eight neighbouring
+      // A lane holds channels 32 p + 8 q .. + 7 of row 16 n + l16.  Sixteen rows at a time go through LDS, so that eight neighbouring
       // lanes store a row's 128 bytes.
       // The place is the wave's own: the row it writes first in the next round.
       char* stage = Ys + (buf * 16 + wave) * RB;
-      char* const put_at = stage + l16 * 128;
-      const char* const get_at = stage + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
-      const uint32_t lane_out = ((uint32_t)(lane >> 3) * (uint32_t)kh_stride + 8u * (uint32_t)(lane & 7)) * 2u;
-#pragma unroll
-      for (int k = 0; k < 2 * KT; ++k) {
-        const int kw = it.r * 16 * KT + wave * 2 * KT + k;
-        if (kw >= a.kw) continue;
-#pragma unroll
-        for (int n = 0; n < KH; ++n) {
-          if (16 * n >= a.kh) continue;
+      int ln = lane;   // (addresses formed from it here: kept through the rounds they would cost registers that the rounds need)
+      asm volatile("" : "+v"(ln));
+      char* const put_at = stage + (ln & 15) * 128;
+      const char* const get_at = stage + (ln >> 3) * 128 + ((ln & 7) ^ (ln >> 3)) * 16;
+      const uint32_t lane_out = ((uint32_t)(ln >> 3) * (uint32_t)out_stride + 8u * (uint32_t)(ln & 7)) * 2u;
+      const int col0 = (INV ? it.r % Rc : it.r) * 16 * KT + wave * 2 * KT, row0 = INV ? it.r / Rc * 16 * KH : 0;
+      uint16_t* const first = it.out + row0 * out_stride + (int64_t)col0 * a.d;
+      // (V where the output goes, requested one group of 16 rows ahead)
+      const bool add = INV && a.resid;
+      uint4v rs[2][2];
+      auto request_v = [&](int i) {
+        const int k = i / KH, n = i % KH;
+        if (row0 + 16 * n < a.out_rows)
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
-            half8 v;
+            typedef const char __attribute__((address_space(1))) * ptr;
+            ptr at = (ptr)((const uint16_t*)a.resid + (first - (const uint16_t*)a.out[0]) + (16 * n + 8 * p) * out_stride + k * a.d);
+            asm("" : "+s"(at));
+            rs[i & 1][p] = *(const uint4v __attribute__((address_space(1)))*)(at + lane_out);
+          }
+      };
+      if (col0 < a.out_cols) {   // (of whole tiles)
+        if (INV && add) request_v(0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = (_Float16)acc[k][2 * p + (i >> 2)][n][i & 3];
-            *(half8*)(put_at + (((4 * p + q) ^ (l16 & 7)) * 16)) = v;
+        for (int i = 0; i < 2 * KT * KH; ++i) {
+          const int k = i / KH, n = i % KH;
+          if (INV && add && i + 1 < 2 * KT * KH) request_v(i + 1);
+          if (row0 + 16 * n >= a.out_rows) continue;
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            if (INV && !add) {
+              bf16x8 v;
+#pragma unroll
+              for (int j = 0; j < 8; ++j) v[j] = (__bf16)acc[k][2 * p + (j >> 2)][n][j & 3];
+              *(bf16x8*)(put_at + (((4 * p + (ln >> 4)) ^ (ln & 7)) * 16)) = v;
+            } else {
+              half8 v;
+#pragma unroll
+              for (int j = 0; j < 8; ++j) v[j] = (_Float16)acc[k][2 * p + (j >> 2)][n][j & 3];
+              *(half8*)(put_at + (((4 * p + (ln >> 4)) ^ (ln & 7)) * 16)) = v;
+            }
           }
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
           __builtin_amdgcn_wave_barrier();
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-          char* dst = (char*)(it.out + 16 * n * kh_stride + (int64_t)kw * a.d) + lane_out;
 #pragma unroll
-          for (int p = 0; p < 2; ++p) *(uint4v*)(dst + 16 * p * kh_stride) = *(const uint4v*)(get_at + p * 1024);
+          for (int p = 0; p < 2; ++p) {
+            uint4v v = *(const uint4v*)(get_at + p * 1024);
+            if (INV && add) {   // out = resid + result, both bf16 in memory, the sum formed in fp32
+              const half8 h = __builtin_bit_cast(half8, v);
+              bf16x8 b;
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                const uint32_t w = rs[i & 1][p][j];
+                b[2 * j] = (__bf16)(__uint_as_float(w << 16) + (float)h[2 * j]);
+                b[2 * j + 1] = (__bf16)(__uint_as_float(w & 0xffff0000u) + (float)h[2 * j + 1]);
+              }
+              v = __builtin_bit_cast(uint4v, b);
+            }
+            typedef char __attribute__((address_space(1))) * ptr;
+            ptr at = (ptr)(first + (16 * n + 8 * p) * out_stride + k * a.d);
+            asm("" : "+s"(at));
+            *(uint4v __attribute__((address_space(1)))*)(at + lane_out) = v;
+          }
           __builtin_amdgcn_wave_barrier();
         }
       }
@@ -350,49 +418,63 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
     it = next;
     ord = ord_next;
   }
+  if constexpr (INV) return;
   // an input that fp16 cannot hold (the spectral buffers' range contract), infinities and NaN included
   if (a.range_flag && (amax[0] >= 0x4780 || amax[1] >= 0x4780)) *a.range_flag = 1;
   if (a.tot_part) a.tot_part[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = tot[tid];   // per channel of the workgroup's chunk
 }
 
-template <int NW16, int KT, int KH>
+template <int NW16, int KT, int KH, bool INV>
 static hipError_t wh_launch(WhPassArgs a, int num_cu, hipStream_t st, int* slots_out) {
-  constexpr int FIXED = 2 * 16 * wh_row_bytes(KT) + KT * ((NW16 + 1) / 2) * 2048 + WH_WAVES * 64 * 4;
+  constexpr int FIXED = 2 * 16 * wh_row_bytes(KT) + KT * ((NW16 + 1) / 2) * (INV ? 1024 : 2048) + WH_WAVES * 64 * 4;
   static_assert(FIXED + 16 * KH * (128 + 8) * 2 <= 160 * 1024, "LDS of one compute unit");
-  const int lds = FIXED + 16 * KH * (a.H + 8) * 2;
-  a.members = (a.kw / 16 + KT - 1) / KT;
+  const int lds = FIXED + 16 * KH * (a.rows + 8) * 2;
+  a.col_parts = (a.out_cols / 16 + KT - 1) / KT;
+  a.members = a.col_parts * ((a.out_rows / 16 + KH - 1) / KH);
   const int64_t planes = (int64_t)a.seg_end[2] * a.T * (a.d / 64);
   if (planes <= 0) return hipSuccess;
   if (planes * a.members > 0x3fffffff) return hipErrorInvalidValue;
   // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
   if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
-  // per-lane byte offsets are unsigned 32-bit numbers: 16 rows kh of the output, 16 positions of the input
-  if ((int64_t)a.T * a.kw * a.d * 2 * 16 > 0xffffffffLL) return hipErrorInvalidValue;
+  // per-lane byte offsets are unsigned 32-bit numbers: 16 rows of the output, 16 positions of the input
+  if ((INV ? 1 : (int64_t)a.T) * a.out_cols * a.d * 2 * 16 > 0xffffffffLL) return hipErrorInvalidValue;
   const int per_cu = std::min(wh_waves_per_simd((NW16 + 1) / 2, KT, KH) / 2, 160 * 1024 / lds);
   const int64_t per_xcd = (planes + 7) / 8 * a.members;   // items of the fullest XCD
   const int grid = 8 * (int)std::min<int64_t>(per_xcd, std::max(1, num_cu / 8) * per_cu);
   static OncePerDevice limit;
-  hipError_t e = allow_lds(limit, (const void*)k_wh_pass<NW16, KT, KH>, 160 * 1024);
+  hipError_t e = allow_lds(limit, (const void*)k_wh_pass<NW16, KT, KH, INV>, 160 * 1024);
   if (e != hipSuccess) return e;
   if (slots_out) *slots_out = grid * WH_WAVES;
-  hipLaunchKernelGGL((k_wh_pass<NW16, KT, KH>), dim3((unsigned)grid), dim3(64 * WH_WAVES), (size_t)lds, st, a);
+  hipLaunchKernelGGL((k_wh_pass<NW16, KT, KH, INV>), dim3((unsigned)grid), dim3(64 * WH_WAVES), (size_t)lds, st, a);
   return hipGetLastError();
 }
 
-template <int NW16>
+// Tiles of output rows and columns (16 each) of a workgroup: as many as the accumulators take, the rows first; rows beyond four
+// tiles are cut into equal parts (the inverse only: the forward pass keeps at most 64 rows).
+static inline void wh_tiles(const WhPassArgs& a, int* kt, int* kh, int* members) {
+  const int tiles = a.out_rows / 16, parts = (tiles + 3) / 4, h = (tiles + parts - 1) / parts;
+  const int t = h <= 2 && a.out_cols > 16 ? 2 : 1;
+  if (kt) *kt = t;
+  if (kh) *kh = h;
+  if (members) *members = (a.out_cols / 16 + t - 1) / t * ((tiles + h - 1) / h);
+}
+
+template <int NW16, bool INV>
 static hipError_t wh_dispatch(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
-  const int kht = a.kh / 16;
-  // A single W tile: the whole axis of 16, or the box of an axis that can be cut that far (a power of two).
-  if constexpr ((NW16 & (NW16 - 1)) == 0) {
-    if (a.kw == 16 && kht == 1) return wh_launch<NW16, 1, 1>(a, num_cu, st, slots_out);
-    if (a.kw == 16 && kht == 2) return wh_launch<NW16, 1, 2>(a, num_cu, st, slots_out);
+  int kt, kh;
+  wh_tiles(a, &kt, &kh, nullptr);
+  if (!INV && a.out_rows > 64) return hipErrorInvalidValue;
+  // A single W tile: the whole axis of 16, or (forward) the box of an axis that can be cut that far (a power of two).
+  if constexpr (INV ? NW16 == 1 : (NW16 & (NW16 - 1)) == 0) {
+    if (kt == 1 && kh == 1) return wh_launch<NW16, 1, 1, INV>(a, num_cu, st, slots_out);
+    if (kt == 1 && kh == 2) return wh_launch<NW16, 1, 2, INV>(a, num_cu, st, slots_out);
   }
-  if constexpr (NW16 > 1) {
-    if (a.kw > 16 && kht == 1) return wh_launch<NW16, 2, 1>(a, num_cu, st, slots_out);
-    if (a.kw > 16 && kht == 2) return wh_launch<NW16, 2, 2>(a, num_cu, st, slots_out);
+  if constexpr (INV || NW16 > 1) {
+    if (kt == 2 && kh == 1) return wh_launch<NW16, 2, 1, INV>(a, num_cu, st, slots_out);
+    if (kt == 2 && kh == 2) return wh_launch<NW16, 2, 2, INV>(a, num_cu, st, slots_out);
   }
-  if (kht == 3) return wh_launch<NW16, 1, 3>(a, num_cu, st, slots_out);
-  if (kht == 4) return wh_launch<NW16, 1, 4>(a, num_cu, st, slots_out);
+  if (kh == 3) return wh_launch<NW16, 1, 3, INV>(a, num_cu, st, slots_out);
+  if (kh == 4) return wh_launch<NW16, 1, 4, INV>(a, num_cu, st, slots_out);
   return hipErrorInvalidValue;
 }
 

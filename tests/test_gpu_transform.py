@@ -83,6 +83,43 @@ def test_outputs_of_boxed_inverse(grid, d, n):
     assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (mx, rl)
 
 
+# outputs from whole planes and from boxes through the pass that keeps the output in its accumulators: one to four tiles of rows per
+# workgroup, rows in one and two parts (an odd number of tiles among them), every number of tiles of columns, an input row
+# whose last step is half empty, fewer planes than an XCD has workgroups and more; and a plane that takes an axis at a time
+@pytest.mark.parametrize("grid,d,n", [((16, 48, 80), 64, 1), ((32, 80, 48), 128, 1), ((16, 112, 16), 64, 2), ((16, 128, 64), 128, 1),
+                                      ((16, 64, 112), 64, 1), ((48, 64, 64), 64, 3), ((16, 128, 128), 64, 2), ((32, 32, 96), 64, 1),
+                                      ((16, 16, 128), 64, 1), ((16, 96, 96), 64, 1)])
+def test_outputs_of_one_pass_inverse(grid, d, n):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(19)
+    N, alloc = int(np.prod(grid)), [1] * n + [2] * n + [4] * n
+    q, k, v = ((0.5 * torch.randn((1, 3 * n, N, d), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(3))
+    band = dict(WL.WORKLOADS["16k"].band, n_summary=0, high_window=16)
+    ctx = B.Context(1, 3 * n, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    out = torch.empty_like(q)
+    ctx.forward(q, k, v, alloc, out)
+    # The inverse alone: the band outputs and V~ as the library left them, through scipy's inverse transform.  Tolerance of the
+    # other output tests: fp16 matrices and intermediates in three passes (5e-4 relative) and the bf16 rounding of the result.
+    from scipy.fft import idctn
+    index = O.band_partition(*grid, U.oracle_cfg(band))
+    host_v = U.to_host64(v)
+    for h in range(3 * n):
+        spec = np.zeros((N, d))
+        for l, idx in enumerate(index):
+            if len(idx) and (alloc[h] >> l) & 1:
+                spec[idx] = ctx.read_spectral(3, h, l)
+                if alloc[h] != 4:
+                    spec[idx] -= ctx.read_spectral(2, h, l)
+            elif len(idx) and alloc[h] == 4:
+                spec[idx] = ctx.read_spectral(2, h, l)
+        want = idctn(spec.reshape(grid + (d,)), type=2, norm="ortho", axes=(0, 1, 2)).reshape(N, d)
+        if alloc[h] != 4:
+            want += host_v[0, h]
+        mx, rl = U.errors(U.to_host64(out[0, h]), want)
+        print(f"one-pass inverse {grid} d={d} head {h}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+        assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (h, mx, rl)
+
+
 @pytest.mark.parametrize("path", [B.PATH_MFMA, B.PATH_GENERIC])
 def test_routing_leaves_the_band_outputs_readable(path, monkeypatch):
     """The transforms of a routing call that is no forward use scratch that is not the last forward's result."""
