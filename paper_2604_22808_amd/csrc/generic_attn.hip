@@ -2,7 +2,7 @@
 // operands and accumulation throughout, on the fp32 matrix instruction v_mfma_f32_16x16x4_f32.
 //
 // One launch serves up to four branches (segments) of a forward.  A workgroup owns 16 or 32 query rows of one slice; its
-// four waves take the key tiles (32 keys) of those rows in turn and their partial results meet in LDS at the end, so
+// four waves take the key tiles (16 keys) of those rows in turn and their partial results meet in LDS at the end, so
 // that a small problem still puts four waves on every query tile.  Per key tile and wave, scores are kept transposed
 // (S^T = K Q^T: lane = query, registers = keys 4 g + r of a 16-key group, g = lane / 16), which makes the probabilities the B
 // operand of O^T += V^T P^T as they stand.  Operands come straight from global memory: a lane reads 16 bytes of its own key
@@ -10,11 +10,12 @@
 // channels of four value rows per 16-lane group (V; channel n DC + dc belongs to output tile dc), i.e. whole row segments
 // of 64 to 512 bytes, and no LDS traffic or barrier is left in the key loop.
 //
-// What bounds it: the matrix instruction's issue at 64 flops per cycle and SIMD, and at small sizes the latency of a
-// wave's few dependent tiles.  The kernel before it gave a wave to every query row with a lane per key (a row of K per
-// lane: 64 cache lines per load) and summed values one key at a time.  Band operators and exchange together, 12,150 tokens
-// x 4 heads x 64 in fp32 (window +-128, 16-row blocks): 1.56 ms before, 56 us now; 6,160 tokens x 6 heads x 128 with
-// several bands per head: 2.91 ms before, 103 us now (about 35 TFLOP/s of the 157 nominal).
+// What bounds it: at small sizes, where it is used, the latency of a wave's few dependent tiles - leaving out the loads or the
+// products of either half changes less than a quarter of the time.  Band operators and exchange together, 12,150 tokens
+// x 4 heads x 64 in fp32 (window +-128, 16-row blocks): 59 us with tiles of 32 keys, expf, a mask on every score and a division per
+// key of a block list, 39 us now (tiles of 16 keys leave registers for another wave per SIMD; masks on edge tiles only); 6,160
+// tokens x 6 heads x 128 with several bands per head: 109 -> 72 us.  Key rows loaded whole and turned into operands in LDS measured
+// the same, and 16 query rows per workgroup at 12,150 tokens 42 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -82,7 +83,8 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
     for (int c = 0; c < DC; ++c) Qr[u][c] = row4<EXACT>(row, 16 * c + 4 * g, d);
   }
   float4v acc[NQ][DC];
-  float m_run[NQ], l_run[NQ];   // maximum over the tiles of this wave; sum of this lane's keys only
+  const float scale2 = scale * 1.44269504088896341f;
+  float m_run[NQ], l_run[NQ];   // maximum over the tiles of this wave (an exponent of two); sum of this lane's keys only
 #pragma unroll
   for (int u = 0; u < NQ; ++u) {
     m_run[u] = -INFINITY; l_run[u] = 0.f;
@@ -90,88 +92,91 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
     for (int c = 0; c < DC; ++c) acc[u][c] = float4v{0.f, 0.f, 0.f, 0.f};
   }
 
-  float4v Kr[2][DC];
-  auto load_k = [&](int jt) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const float* row = K + (int64_t)min(key_of(jt + 16 * t + n), s.nk - 1) * d;
-#pragma unroll
-      for (int c = 0; c < DC; ++c) Kr[t][c] = row4<EXACT>(row, 16 * c + 4 * g, d);
-    }
+  // A tile of 16 keys per wave and step, the four waves' tiles side by side.  Its rows follow one another, from a row that all
+  // lanes share, unless the blocks of a list are no multiples of 16.
+  constexpr int TK = 16, STEP = 4 * TK;
+  const bool scattered = s.mode == 1 && s.block % TK != 0;
+  // first key row of the tile at list position jt (for tiles whose rows follow one another)
+  auto base_of = [&](int jt) -> int {
+    if (s.mode != 1) return k0 + jt;
+    const int b = jt / s.block;
+    return s.col_idx[e0 + b] * s.block + (jt - b * s.block);
   };
-  if (32 * wave < nkeys) load_k(32 * wave);
-  for (int jt = 32 * wave; jt < nkeys; jt += 128) {
-    // value rows of this lane's four keys per 16-key group: requested first, used after the softmax
-    int key[2][4];
-    float Vr[2][4][DC];
+  float4v Kr[DC];
+  int kb = 0;   // (tile whose keys are in Kr)
+  auto load_k = [&](int jt) {
+    const float* row;
+    if (scattered) {
+      row = K + (int64_t)min(key_of(jt + n), s.nk - 1) * d;
+    } else {
+      kb = base_of(jt);
+      row = K + (int64_t)kb * d + min(n, s.nk - 1 - kb) * d;
+    }
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int c = 0; c < DC; ++c) Kr[c] = row4<EXACT>(row, 16 * c + 4 * g, d);
+  };
+  if (TK * wave < nkeys) load_k(TK * wave);
+  for (int jt = TK * wave; jt < nkeys; jt += STEP) {
+    // value rows of this lane's four keys: requested first, used after the softmax
+    float Vr[4][DC];
+    int key[4];
+    const int kt = kb;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        key[t][r] = key_of(jt + 16 * t + 4 * g + r);
-        const float* row = V + (int64_t)min(key[t][r], s.nk - 1) * d;
-        if (EXACT && DC % 4 == 0) {
+    for (int r = 0; r < 4; ++r) {
+      key[r] = scattered ? key_of(jt + 4 * g + r) : kt + 4 * g + r;
+      const float* row = scattered ? V + (int64_t)min(key[r], s.nk - 1) * d : V + (int64_t)kt * d + min(4 * g + r, s.nk - 1 - kt) * d;
+      if (EXACT && DC % 4 == 0) {
 #pragma unroll
-          for (int c = 0; c < DC; c += 4) *(float4v*)&Vr[t][r][c] = *(const float4v*)(row + n * DC + c);
-        } else {
+        for (int c = 0; c < DC; c += 4) *(float4v*)&Vr[r][c] = *(const float4v*)(row + n * DC + c);
+      } else {
 #pragma unroll
-          for (int c = 0; c < DC; ++c) Vr[t][r][c] = (EXACT || n * DC + c < d) ? row[n * DC + c] : 0.f;
-        }
+        for (int c = 0; c < DC; ++c) Vr[r][c] = (EXACT || n * DC + c < d) ? row[n * DC + c] : 0.f;
       }
-    float4v S[2][NQ];
+    }
+    float4v S[NQ];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int u = 0; u < NQ; ++u) S[t][u] = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < NQ; ++u) S[u] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < DC; ++c)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int u = 0; u < NQ; ++u)
-            S[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(Kr[t][c][r], Qr[u][c][r], S[t][u], 0, 0, 0);
-    if (jt + 128 < nkeys) load_k(jt + 128);
+        for (int u = 0; u < NQ; ++u)
+          S[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(Kr[c][r], Qr[u][c][r], S[u], 0, 0, 0);
+    if (jt + STEP < nkeys) load_k(jt + STEP);
+    // (tiles inside the list and inside every row's window need no masks)
+    const bool inside = jt + TK <= nkeys && !scattered && kt + TK <= s.nk &&
+                        (s.mode != 2 || (kt + s.window >= qend - 1 && kt + TK - 1 - s.window <= q0));
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       const int q = q0 + 16 * u + n;
-      float mx = m_run[u];
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
+      if (!inside)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          bool ok = jt + 16 * t + 4 * g + r < nkeys && key[t][r] < s.nk;
-          if (s.mode == 2) ok = ok && key[t][r] >= q - s.window && key[t][r] - s.window <= q;
-          S[t][u][r] = ok ? S[t][u][r] * scale : -INFINITY;
-          mx = fmaxf(mx, S[t][u][r]);
+          bool ok = jt + 4 * g + r < nkeys && key[r] < s.nk;
+          if (s.mode == 2) ok = ok && key[r] >= q - s.window && key[r] - s.window <= q;
+          S[u][r] = ok ? S[u][r] : -INFINITY;
         }
+      // Scores times scale2 are exponents of two; the product and the difference to the running maximum are one rounding.
+      float mx = fmaxf(fmaxf(S[u][0], S[u][1]), fmaxf(S[u][2], S[u][3]));
       mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      mx = fmaxf(m_run[u], fmaxf(mx, __shfl_xor(mx, 32)) * scale2);
       const float ref = mx == -INFINITY ? 0.f : mx;   // (no valid key for this query yet: every probability below is 0)
-      const float alpha = expf(m_run[u] - ref);
-      float sum = 0.f;
+      const float alpha = __builtin_amdgcn_exp2f(m_run[u] - ref);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          S[t][u][r] = expf(S[t][u][r] - ref);
-          sum += S[t][u][r];
-        }
-      l_run[u] = l_run[u] * alpha + sum;
+      for (int r = 0; r < 4; ++r) S[u][r] = __builtin_amdgcn_exp2f(fmaf(S[u][r], scale2, -ref));
+      l_run[u] = l_run[u] * alpha + ((S[u][0] + S[u][1]) + (S[u][2] + S[u][3]));
       m_run[u] = mx;
 #pragma unroll
       for (int c = 0; c < DC; ++c) acc[u][c] *= alpha;
     }
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int c = 0; c < DC; ++c)
 #pragma unroll
-        for (int c = 0; c < DC; ++c)
-#pragma unroll
-          for (int u = 0; u < NQ; ++u)
-            acc[u][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(Vr[t][r][c], S[t][u][r], acc[u][c], 0, 0, 0);
+        for (int u = 0; u < NQ; ++u)
+          acc[u][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(Vr[r][c], S[u][r], acc[u][c], 0, 0, 0);
   }
 
   // the four waves' results -> LDS (lane: query n, channels (4 g + r) DC + c), then every thread combines 4 channels
@@ -199,7 +204,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
     float4v o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float f = expf(ml[(w * ROWS + row) * 2] - m);
+      const float f = __builtin_amdgcn_exp2f(ml[(w * ROWS + row) * 2] - m);
       l += f * ml[(w * ROWS + row) * 2 + 1];
       o += f * *(const float4v*)(lds + (w * ROWS + row) * LROW + ch);
     }
@@ -220,7 +225,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
 }
 
 template <int DC, bool EXACT>
-__global__ void __launch_bounds__(256, DC <= 4 ? 2 : 1) k_gattn(GAttnArgs a) {
+__global__ void __launch_bounds__(256, DC <= 4 ? 3 : DC <= 8 ? 2 : 1) k_gattn(GAttnArgs a) {
   constexpr int NQMAX = DC <= 8 ? 2 : 1;
   __shared__ __attribute__((aligned(16))) float lds[4 * 16 * NQMAX * (16 * DC + 4) + 4 * 16 * NQMAX * 2];
   int k = 0;

@@ -40,6 +40,13 @@ def test_generic_attention_blocks_and_windows(block, window, c):
     _check((7, 24, 26), 64, 2, (7, 7), mid_block=block, mid_stride=3, high_window=window, n_summary=9, low_compress=c)
 
 
+@pytest.mark.parametrize("block,window", [(16, 48), (48, 100), (80, 17), (40, 16)])
+def test_generic_attention_of_large_scores(block, window):
+    """Scores of up to about +-40 before the softmax (rounded at 2^-24 of themselves: 2.4e-6 in a probability), block lists whose
+    tiles follow one another and not, windows with and without tiles that need no mask."""
+    _check((7, 24, 26), 64, 2, (6, 7), mid_block=block, mid_stride=2, high_window=window, n_summary=9, softmax_scale=2.0)
+
+
 @pytest.mark.parametrize("block", [100, 1190, 1200, 100000, 2 ** 31 - 1])
 def test_generic_attention_blocks_beyond_the_band(block):
     """Mid blocks of which the last is cut short by the band (1,199 rows), down to one block that holds all of it (a dense mid
