@@ -361,7 +361,8 @@ def main():
     vbox = ctx.get_v_box()   # V~ of a slice without the high band on the low+mid box: V follows Q and K class by class
     nonhigh_present = cls_present[0] or cls_present[1] or any(m == 0 for m in masks)
     # Launches: tensors that keep the same coefficient box share a W + H pass and a T pass where the one-pass kernels take the
-    # box (one_pass in csrc/api.cpp, csrc/mfma_iwh.hip), else every axis of every tensor is a launch.
+    # box (one_pass in csrc/api.cpp, csrc/mfma_iwh.hip, csrc/mfma_wh_2.hip), else every axis of every tensor is a launch.  (Classes
+    # of slices too small to fill the chip share launches among them: not counted here.)
     T, H, W = wl.grid
     def passes(n_in, n_out):   # the axis pass exists: any number of rows for powers of two, square otherwise
         return n_in & (n_in - 1) == 0 or (n_out + 31) // 32 == (n_in + 31) // 32
@@ -370,14 +371,16 @@ def main():
         return [r if passes(n, r) and passes(r, n) else n for r, n in zip(rounded, (T, H, W))]
     low_k, mid_k, full_k = kept(1), kept(2), [T, H, W]
     def fwd_group(tensors, k):
-        kh, kw, most = (mid_k[1], mid_k[2], 8) if k != full_k and mid_k != full_k else (H, W, 6)
-        one = kh <= 64 and kw // 16 <= (8 if kh <= 32 else most)
-        return 0 if tensors == 0 else 2 if one else 3 * tensors
+        kh = mid_k[1] if k != full_k and mid_k != full_k else H
+        return 0 if tensors == 0 else 2 if kh <= 64 else 3 * tensors
     def inv_group(mask_of_class, k):
         n = sum(1 for m in masks if mask_of_class(m)) * wl.batch
         cus = torch.cuda.get_device_properties(0).multi_processor_count
-        one = max(k[1], k[2]) <= 32 and W in (16, 32, 64) and n * T * (wl.head_dim // 64) * (H // 16) >= 2 * cus
-        return 0 if n == 0 else 2 if one else 3
+        small = k[1] * k[2] <= 512 and W in (16, 32, 64) and n * T * (wl.head_dim // 64) * (H // 16) >= 2 * cus
+        parts = (H // 16 + 3) // 4                                          # of a plane's rows, 3 or 4 tiles of 16 each
+        cols = 2 if (H // 16 + parts - 1) // parts <= 2 and W > 16 else 1   # tiles of 16 columns per workgroup
+        readers = parts * -(-(W // 16) // cols)
+        return 0 if n == 0 else 2 if small or readers * k[1] * k[2] <= 10 * H * W else 3
     if router is not None:   # routed: slices split into "ran the high band last time" and the rest
         fwd_launches = fwd_group((3 if vbox else 2) if nonhigh_present else 0, mid_k) + fwd_group(3 if cls_present[2] else 0 if vbox else 1, full_k)
     else:

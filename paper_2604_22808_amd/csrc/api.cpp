@@ -712,132 +712,258 @@ static bool one_pass(const Ctx& c, bool box, int d) {
 // buffer spec.
 struct TransformSeg { const void* x; void* spec; const int32_t* slice_list; int ns; };
 
-// MFMA path, forward, for up to three tensors that share `keep`: W and H axes in one pass where one_pass says so, else W axis
-// (tmp0) and H axis pass by pass; both leave [h][t] order behind so that the rows of the T pass are W*d elements apart.
-// The T pass scatters into the band-major spectral buffers.  keep[] = coefficients computed per axis (T, H, W): a head
-// that only runs the low (low and mid) band needs Q~ and K~ on that box only, and every pass after the first then moves a
-// fraction of the tensor.  energy_slot >= 0 adds up the router's band statistics in the T pass, tot_slot >= 0 the inputs'
-// sum of squares in the first pass (of all tensors together: the router adds them anyway).
-// `width` > 0 transforms tensors of that many channels per token instead of head_dim (the projected forward transforms X,
-// [batch][N][d_model], as `ns` = batch slices).
-static hipError_t forward_transform_mfma(Ctx& c, const TransformSeg* segs, int nseg, hipStream_t st, const int keep[3],
-                                         int energy_slot, int tot_slot, int width = 0) {
-  const int T = c.shape.T, H = c.shape.H, W = c.shape.W, d = width > 0 ? width : c.d;
-  const int kt = keep[0], kh = keep[1], kw = keep[2];
-  hipError_t e;
+// Up to three tensors (Q, K, V) that keep the same coefficients: keep[] per axis (T, H, W).  A head that only runs the low (low and
+// mid) band needs Q~ and K~ on that box only, and every pass after the first then moves a fraction of the tensor.
+// energy_slot >= 0 adds up the router's band statistics in the T pass, tot_slot >= 0 the inputs' sum of squares in the first
+// pass (of all tensors together: the router adds them anyway).
+struct TransformClass { TransformSeg seg[3]; const int* keep; int energy_slot, tot_slot; };
+
+static WhPassArgs wh_pass_args(const Ctx& c, const TransformClass& k, int d) {
   WhPassArgs f{};
+  f.T = c.shape.T; f.d = d; f.rows = f.ldh = c.shape.H; f.cols = f.ldw = c.shape.W; f.out_rows = k.keep[1]; f.out_cols = k.keep[2];
+  f.Mh = c.d_F16[1]; f.Mw = c.d_F16[2];
+  f.range_flag = c.d_range_flag;
+  if (k.tot_slot >= 0) f.tot_part = c.d_tot_part + (size_t)k.tot_slot * DCT_MAX_WAVES * 64;
+  return f;
+}
+static DctPassArgs t_pass_args(const Ctx& c, const TransformClass& k, int d) {
   DctPassArgs t{};
-  void* const scratch3[3] = {c.tmp1, c.tmp0, c.Y};   // (Y is free until the band operators, unless keep_outputs)
-  int n = 0, total = 0;
-  for (int i = 0; i < nseg; ++i) {
-    if (segs[i].ns <= 0) continue;
-    total += segs[i].ns;
-    f.in[n] = segs[i].x; f.out[n] = scratch3[n]; f.slice_list[n] = segs[i].slice_list; f.seg_end[n] = total;
-    t.in_seg[n] = scratch3[n]; t.out_seg[n] = segs[i].spec; t.list_seg[n] = segs[i].slice_list; t.seg_end[n] = total;
-    ++n;
-  }
-  if (n == 0) return hipSuccess;
-  for (int i = n; i < 3; ++i) f.seg_end[i] = t.seg_end[i] = total;
-  f.T = T; f.d = d; f.rows = f.ldh = H; f.cols = f.ldw = W; f.out_rows = kh; f.out_cols = kw;
-  int slots = 0;
-  // (its copies into LDS move whole 16-byte pieces of the caller's tensors; a view that starts between them takes the two passes)
-  bool fused = one_pass(c, kt < T || kh < H || kw < W, d);
-  for (int i = 0; i < n; ++i) fused = fused && (uintptr_t)f.in[i] % 16 == 0;
-  if (fused && n == 3 && c.keep_outputs) {   // the third tensor's scratch is taken: two tensors, then one
-    if ((e = forward_transform_mfma(c, segs, 2, st, keep, energy_slot, tot_slot, width)) != hipSuccess) return e;
-    return forward_transform_mfma(c, segs + 2, 1, st, keep, energy_slot >= 0 ? energy_slot + 2 : -1, tot_slot >= 0 ? tot_slot + 2 : -1, width);
-  }
-  if (fused) {
-    f.Mh = c.d_F16[1]; f.Mw = c.d_F16[2];
-    f.range_flag = c.d_range_flag;
-    if (tot_slot >= 0) f.tot_part = c.d_tot_part + (size_t)tot_slot * DCT_MAX_WAVES * 64;
-    if ((e = launch_wh_pass(f, c.num_cu, st, &slots)) != hipSuccess) return e;
-    if (tot_slot >= 0) c.tot_waves[tot_slot] = slots;
-  } else if (n > 1) {   // one after the other: the passes share tmp0 and tmp1
-    for (int i = 0; i < nseg; ++i)
-      if ((e = forward_transform_mfma(c, segs + i, 1, st, keep, energy_slot >= 0 ? energy_slot + i : -1, tot_slot >= 0 ? tot_slot + i : -1, width)) != hipSuccess) return e;
-    return hipSuccess;
-  } else {
-    DctPassArgs a{};
-    a.d = d; a.Ntok = c.N; a.slice_elems = c.N * d;
-    a.in = f.in[0]; a.slice_list = f.slice_list[0]; a.list_in = 1; a.out = c.tmp0; a.M = c.d_F16[2]; a.ldm = W; a.n = W; a.n_out = kw;
-    a.inner = d; a.outer = (int64_t)T * H; a.nslab = (int64_t)total * T * H; a.in_bf16 = 1;
-    if (tot_slot >= 0) a.tot_part = c.d_tot_part + (size_t)tot_slot * DCT_MAX_WAVES * 64;
-    if ((e = launch_mfma_dct_pass(a, c.num_cu, st, &slots)) != hipSuccess) return e;
-    if (tot_slot >= 0) c.tot_waves[tot_slot] = slots;
-
-    DctPassArgs b{};
-    b.d = d; b.Ntok = c.N;
-    b.in = c.tmp0; b.out = c.tmp1; b.M = c.d_F16[1]; b.ldm = H; b.n = H; b.n_out = kh; b.inner = (int64_t)kw * d;
-    b.nslab = (int64_t)total * T; b.outer = b.nslab; b.out_swap = 1; b.sw = T; b.sw_total = T; b.sw_off = 0;
-    if ((e = launch_mfma_dct_pass(b, c.num_cu, st)) != hipSuccess) return e;
-  }
-
   t.d = d; t.Ntok = c.N;
-  t.M = c.d_F16[0]; t.ldm = T; t.n = T; t.n_out = kt; t.inner = (int64_t)kw * d;
-  t.nslab = (int64_t)total * kh; t.outer = kh;
-  t.perm_out = c.d_perm_t; t.perm_k = 1; t.perm_o = W; t.perm_scale = T;
+  t.M = c.d_F16[0]; t.ldm = c.shape.T; t.n = c.shape.T; t.n_out = k.keep[0]; t.inner = (int64_t)k.keep[2] * d;
+  t.outer = k.keep[1];
+  t.perm_out = c.d_perm_t; t.perm_k = 1; t.perm_o = c.shape.W; t.perm_scale = c.shape.T;
   t.range_flag = c.d_range_flag;
-  if (energy_slot >= 0) {
-    t.energy_part = c.d_energy_part + (size_t)energy_slot * DCT_MAX_WAVES * 3 * 64;
-    t.en_omul = W; t.en_div = W;  // the tile's other coordinates are (kh, kw)
+  if (k.energy_slot >= 0) {
+    t.energy_part = c.d_energy_part + (size_t)k.energy_slot * DCT_MAX_WAVES * 3 * 64;
+    t.en_omul = c.shape.W; t.en_div = c.shape.W;  // the tile's other coordinates are (kh, kw)
     t.low_u = c.low_box[1]; t.low_v = c.low_box[2]; t.low_a = c.low_box[0];
     t.mid_u = c.mid_box[1]; t.mid_v = c.mid_box[2]; t.mid_a = c.mid_box[0];
   }
+  return t;
+}
+
+// Whether the T pass of a class joins the launch of the class that keeps the most (`lead`).  It has to be small (fewer than four tiles per wave
+// of a chip with two workgroups on every compute unit); and so has the lead on long axes, whose kernels pay for arguments that depend on
+// the workgroup (k_dct_passes) more than a small launch takes.
+static bool dct_passes_share(const DctPassArgs& lead, const DctPassArgs& a, int num_cu) {
+  auto tiles = [](const DctPassArgs& x) { return x.nslab * (x.inner / 64); };
+  if (a.n != lead.n || mfma_dct_tiles(a.n, a.n_out) != mfma_dct_tiles(lead.n, lead.n_out)) return false;
+  return tiles(a) < 32 * (int64_t)num_cu && (lead.n <= 32 || tiles(lead) < 32 * (int64_t)num_cu);
+}
+
+// One tensor through two passes (W axis, tmp0; H axis, tmp1) and the T pass.
+static hipError_t transform_by_axes(Ctx& c, const TransformClass& k, int i, hipStream_t st, int d) {
+  const TransformSeg& x = k.seg[i];
+  const int T = c.shape.T, H = c.shape.H, W = c.shape.W, kh = k.keep[1], kw = k.keep[2], ns = x.ns;
+  hipError_t e;
+  int slots = 0;
+  DctPassArgs a{};
+  a.d = d; a.Ntok = c.N; a.slice_elems = c.N * d;
+  a.in = x.x; a.slice_list = x.slice_list; a.list_in = 1; a.out = c.tmp0; a.M = c.d_F16[2]; a.ldm = W; a.n = W; a.n_out = kw;
+  a.inner = d; a.outer = (int64_t)T * H; a.nslab = (int64_t)ns * T * H; a.in_bf16 = 1;
+  if (k.tot_slot >= 0) a.tot_part = c.d_tot_part + (size_t)(k.tot_slot + i) * DCT_MAX_WAVES * 64;
+  if ((e = launch_mfma_dct_pass(a, c.num_cu, st, &slots)) != hipSuccess) return e;
+  if (k.tot_slot >= 0) c.tot_waves[k.tot_slot + i] = slots;
+
+  DctPassArgs b{};
+  b.d = d; b.Ntok = c.N;
+  b.in = c.tmp0; b.out = c.tmp1; b.M = c.d_F16[1]; b.ldm = H; b.n = H; b.n_out = kh; b.inner = (int64_t)kw * d;
+  b.nslab = (int64_t)ns * T; b.outer = b.nslab; b.out_swap = 1; b.sw = T; b.sw_total = T; b.sw_off = 0;
+  if ((e = launch_mfma_dct_pass(b, c.num_cu, st)) != hipSuccess) return e;
+
+  TransformClass one = k;
+  if (k.energy_slot >= 0) one.energy_slot += i;
+  DctPassArgs t = t_pass_args(c, one, d);
+  t.in_seg[0] = c.tmp1; t.out_seg[0] = x.spec; t.list_seg[0] = x.slice_list;
+  for (int j = 0; j < 3; ++j) t.seg_end[j] = ns;
+  t.nslab = (int64_t)ns * kh;
   if ((e = launch_mfma_dct_pass(t, c.num_cu, st, &slots)) != hipSuccess) return e;
-  if (energy_slot >= 0) c.energy_waves[energy_slot] = slots;
+  if (k.energy_slot >= 0) c.energy_waves[one.energy_slot] = slots;
   return hipSuccess;
 }
 
-// MFMA path, inverse (section 3.7) for `ns` slices: the T axis pass gathers band-major rows into tmp1 in [h][t]
-// order, then H axis (tmp1 -> tmp0) and W axis (tmp0 -> out, bf16).  Two forms:
+// MFMA path, forward, for up to three classes of slices, the one that keeps the most last: W and H axes in one pass where
+// one_pass says so, else W axis and H axis pass by pass; both leave [h][t] order behind so that the rows of the T pass are W*d
+// elements apart.  The T pass scatters into the band-major spectral buffers.
+// Classes share launches: a class of few slices leaves most of the chip idle by itself.  A class that fills it gets tiles of
+// its own size, in a launch of its own unless it is the one that keeps the most.
+// `d`: channels per token (the projected forward transforms X, [batch][N][d_model], as batch slices).
+static hipError_t transform_classes(Ctx& c, const TransformClass* cls, int ncls, hipStream_t st, int d) {
+  const int T = c.shape.T, H = c.shape.H, W = c.shape.W;
+  hipError_t e;
+  char* const scratch[3] = {(char*)c.tmp1, (char*)c.tmp0, (char*)c.Y};   // (Y is free until the band operators)
+  WhPassArgs f[3];
+  DctPassArgs t[3];
+  const TransformClass* who[3];
+  int n = 0, used[3] = {0, 0, 0};   // classes in one pass; slices of each tensor's scratch that they take
+  bool by_axes[3] = {false, false, false};
+  for (int k = 0; k < ncls; ++k) {
+    const TransformClass& x = cls[k];
+    // (the pass loads whole 16-byte pieces of the caller's tensors; a view that starts between them takes the two passes)
+    bool fused = one_pass(c, x.keep[0] < T || x.keep[1] < H || x.keep[2] < W, d);
+    for (int i = 0; i < 3; ++i) fused = fused && (x.seg[i].ns <= 0 || (uintptr_t)x.seg[i].x % 16 == 0);
+    by_axes[k] = !fused;
+    if (!fused) continue;
+    WhPassArgs& g = f[n];
+    DctPassArgs& u = t[n];
+    g = wh_pass_args(c, x, d);
+    u = t_pass_args(c, x, d);
+    int m = 0, total = 0;
+    for (int i = 0; i < 3; ++i) {
+      const TransformSeg& y = x.seg[i];
+      if (y.ns <= 0) continue;
+      void* mid = scratch[i] + (size_t)used[i] * c.N * d * sizeof(half_t);
+      used[i] += y.ns;
+      total += y.ns;
+      g.in[m] = y.x; g.out[m] = mid; g.slice_list[m] = y.slice_list; g.seg_end[m] = total;
+      u.in_seg[m] = mid; u.out_seg[m] = y.spec; u.list_seg[m] = y.slice_list; u.seg_end[m] = total;
+      ++m;
+    }
+    if (total == 0) continue;
+    for (int i = m; i < 3; ++i) g.seg_end[i] = u.seg_end[i] = total;
+    u.nslab = (int64_t)total * x.keep[1];
+    who[n++] = &x;
+  }
+  // One launch each for the classes that go with the last one left, until none is left
+  bool done[3] = {false, false, false};
+  for (int i = n - 1; i >= 0; --i) {
+    if (done[i]) continue;
+    WhPassArgs sub[3];
+    int at[3], m = 0, slots[3] = {0, 0, 0};
+    for (int j = i; j >= 0; --j)
+      if (!done[j] && (j == i || (wh_items(f[j]) < 2 * c.num_cu && f[j].out_rows <= f[i].out_rows))) { sub[m] = f[j]; at[m++] = j; done[j] = true; }
+    if ((e = launch_wh_pass(sub, m, c.num_cu, st, slots)) != hipSuccess) return e;
+    for (int j = 0; j < m; ++j)
+      if (who[at[j]]->tot_slot >= 0) c.tot_waves[who[at[j]]->tot_slot] = slots[j];
+  }
+  for (bool& b : done) b = false;
+  for (int i = n - 1; i >= 0; --i) {
+    if (done[i]) continue;
+    DctPassArgs sub[3];
+    int at[3], m = 0, slots[3] = {0, 0, 0};
+    for (int j = i; j >= 0; --j)
+      if (!done[j] && (j == i || (dct_passes_share(t[i], t[j], c.num_cu) && !t[j].energy_part == !t[i].energy_part))) {
+        sub[m] = t[j]; at[m++] = j; done[j] = true;
+      }
+    if ((e = launch_mfma_dct_pass(sub, m, c.num_cu, st, slots)) != hipSuccess) return e;
+    for (int j = 0; j < m; ++j)
+      if (who[at[j]]->energy_slot >= 0) c.energy_waves[who[at[j]]->energy_slot] = slots[j];
+  }
+  for (int k = 0; k < ncls; ++k)   // one tensor after the other: the passes share tmp0 and tmp1
+    if (by_axes[k])
+      for (int i = 0; i < 3; ++i)
+        if (cls[k].seg[i].ns > 0 && (e = transform_by_axes(c, cls[k], i, st, d)) != hipSuccess) return e;
+  return hipSuccess;
+}
+
+static hipError_t forward_transforms_mfma(Ctx& c, const TransformClass* cls, int ncls, hipStream_t st, int width = 0) {
+  const int d = width > 0 ? width : c.d;
+  if (!c.keep_outputs) return transform_classes(c, cls, ncls, st, d);
+  for (int k = 0; k < ncls; ++k) {   // the third tensor's scratch is taken: two tensors, then one, with statistics slots of its own
+    TransformClass two = cls[k], third{{cls[k].seg[2], {}, {}}, cls[k].keep, cls[k].energy_slot, cls[k].tot_slot};
+    two.seg[2] = {};
+    if (third.energy_slot >= 0) third.energy_slot += 2;
+    if (third.tot_slot >= 0) third.tot_slot += 2;
+    hipError_t e = transform_classes(c, &two, 1, st, d);
+    if (e == hipSuccess) e = transform_classes(c, &third, 1, st, d);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// MFMA path, inverse (section 3.7) for up to three classes of slices: the T axis pass gathers band-major rows into tmp1 in [h][t]
+// order, then H and W axes in one pass or pass by pass (tmp1 -> tmp0 -> out, bf16).  Two forms:
 //   select (delta = false): rows come from Y where the band is active for the slice, else from V~;
 //   delta  (delta = true):  rows are Y - V~ on the active bands and zero elsewhere, restricted to the box keep[] that
 //                           contains the active bands, and the last pass adds the input V:  out = V + F^-1(Y^ - V~),
 //                           which is the same sum because F^-1(V~) = V.
-// `wide` != nullptr: the same three passes on one band-major tensor of `width` channels per token ([ns][N][width], every
+// Classes share launches as in the forward direction.
+// `wide` != nullptr: the same passes on one band-major tensor of `width` channels per token ([ns][N][width], every
 // band read from it; `wide_masks` device [ns], all 7).
-static hipError_t inverse_transform_mfma(Ctx& c, void* out, const void* v_in, hipStream_t st, const int32_t* slice_list,
-                                         int ns, const int keep[3], bool delta, const void* wide = nullptr, int width = 0,
-                                         const int32_t* wide_masks = nullptr) {
-  if (ns <= 0) return hipSuccess;
+struct InverseClass { const int32_t* slice_list; int ns; const int* keep; bool delta; };
+
+static hipError_t inverse_transforms_mfma(Ctx& c, void* out, const void* v_in, hipStream_t st, const InverseClass* cls, int ncls,
+                                          const void* wide = nullptr, int width = 0, const int32_t* wide_masks = nullptr) {
   const int T = c.shape.T, H = c.shape.H, W = c.shape.W, d = wide ? width : c.d;
-  const int kt = keep[0], kh = keep[1], kw = keep[2];
   hipError_t e;
-  DctPassArgs a{};
-  a.d = d; a.Ntok = c.N;
-  a.in = wide ? wide : c.Y; a.in_alt = wide ? wide : c.specV; a.masks = wide ? wide_masks : c.d_lists + c.off_masks;
-  a.slice_list = slice_list; a.delta = delta ? 1 : 0;
-  a.band_off1 = (int32_t)c.band_off[1]; a.band_off2 = (int32_t)c.band_off[2];
-  a.band_off3 = (int32_t)(c.nb > 3 ? c.band_off[3] : c.N);
-  a.perm_in = c.d_perm_t; a.perm_k = 1; a.perm_o = W; a.perm_scale = T;
-  a.out = c.tmp1; a.M = c.d_Ft16[0]; a.ldm = T; a.n = kt; a.n_out = T; a.inner = (int64_t)kw * d;
-  a.nslab = (int64_t)ns * kh; a.outer = kh;
-  if ((e = launch_mfma_dct_pass(a, c.num_cu, st)) != hipSuccess) return e;
+  DctPassArgs t[3];
+  WhPassArgs g[3];
+  const InverseClass* who[3];
+  int n = 0, used = 0;
+  for (int k = 0; k < ncls; ++k) {
+    const InverseClass& x = cls[k];
+    if (x.ns <= 0) continue;
+    void* mid = (char*)c.tmp1 + (size_t)used * c.N * d * sizeof(half_t);
+    used += x.ns;
+    DctPassArgs& a = t[n];
+    a = DctPassArgs{};
+    a.d = d; a.Ntok = c.N;
+    a.in = wide ? wide : c.Y; a.in_alt = wide ? wide : c.specV; a.masks = wide ? wide_masks : c.d_lists + c.off_masks;
+    a.slice_list = x.slice_list; a.delta = x.delta ? 1 : 0;
+    a.band_off1 = (int32_t)c.band_off[1]; a.band_off2 = (int32_t)c.band_off[2];
+    a.band_off3 = (int32_t)(c.nb > 3 ? c.band_off[3] : c.N);
+    a.perm_in = c.d_perm_t; a.perm_k = 1; a.perm_o = W; a.perm_scale = T;
+    a.out = mid; a.M = c.d_Ft16[0]; a.ldm = T; a.n = x.keep[0]; a.n_out = T; a.inner = (int64_t)x.keep[2] * d;
+    a.nslab = (int64_t)x.ns * x.keep[1]; a.outer = x.keep[1];
+    WhPassArgs& b = g[n];
+    b = WhPassArgs{};
+    b.in[0] = mid; b.out[0] = out; b.slice_list[0] = x.slice_list; b.resid = x.delta ? v_in : nullptr;
+    for (int i = 0; i < 3; ++i) b.seg_end[i] = x.ns;
+    b.T = T; b.d = d; b.rows = x.keep[1]; b.cols = x.keep[2]; b.out_rows = b.ldh = H; b.out_cols = b.ldw = W;
+    b.Mh = c.d_Ft16[1]; b.Mw = c.d_Ft16[2];
+    who[n++] = &x;
+  }
+  bool done[3] = {false, false, false};
+  for (int i = n - 1; i >= 0; --i) {
+    if (done[i]) continue;
+    DctPassArgs sub[3];
+    int m = 0;
+    for (int j = i; j >= 0; --j)
+      if (!done[j] && (j == i || dct_passes_share(t[i], t[j], c.num_cu))) { sub[m++] = t[j]; done[j] = true; }
+    if ((e = launch_mfma_dct_pass(sub, m, c.num_cu, st)) != hipSuccess) return e;
+  }
+  for (bool& b : done) b = false;
+  for (int i = n - 1; i >= 0; --i) {
+    if (done[i]) continue;
+    IwhPassArgs f{};
+    f.in = g[i].in[0]; f.out = out; f.resid = g[i].resid; f.slice_list = who[i]->slice_list; f.n_slices = who[i]->ns;
+    f.T = T; f.H = H; f.W = W; f.d = d; f.kh = g[i].rows; f.kw = g[i].cols; f.Fh = c.d_Ft16[1]; f.Fw = c.d_Ft16[2];
+    if (!wide && iwh_fits(f, c.num_cu)) {   // H and W axes in one pass, small boxes
+      if ((e = launch_iwh_pass(f, c.num_cu, st)) != hipSuccess) return e;
+      continue;
+    }
+    if (hw_fits(g[i])) {   // the same, boxes of any size
+      // (boxes that the launch below takes together; those that fill the chip run alone as well)
+      auto narrow = [&](int j) { return g[j].cols == 16 || g[j].cols == 32 || g[j].cols == 64; };
+      WhPassArgs sub[3];
+      int m = 0;
+      for (int j = i; j >= 0; --j) {
+        if (done[j]) continue;
+        IwhPassArgs h = f;
+        h.n_slices = who[j]->ns; h.kh = g[j].rows; h.kw = g[j].cols;
+        if (j == i || (narrow(i) && narrow(j) && hw_fits(g[j]) && wh_items(g[j]) < 2 * c.num_cu && (wide || !iwh_fits(h, c.num_cu)))) {
+          sub[m++] = g[j];
+          done[j] = true;
+        }
+      }
+      if ((e = launch_hw_inverse(sub, m, c.num_cu, st)) != hipSuccess) return e;
+      continue;
+    }
+    const int kh = g[i].rows, kw = g[i].cols, ns = who[i]->ns;
+    DctPassArgs b{};
+    b.d = d; b.Ntok = c.N;
+    b.in = g[i].in[0]; b.out = c.tmp0; b.M = c.d_Ft16[1]; b.ldm = H; b.n = kh; b.n_out = H; b.inner = (int64_t)kw * d;
+    b.nslab = (int64_t)ns * T; b.outer = b.nslab; b.in_swap = 1; b.sw = T; b.sw_total = T; b.sw_off = 0;
+    if ((e = launch_mfma_dct_pass(b, c.num_cu, st)) != hipSuccess) return e;
 
-  IwhPassArgs f{};
-  f.in = c.tmp1; f.out = out; f.resid = delta ? v_in : nullptr; f.slice_list = slice_list; f.n_slices = ns;
-  f.T = T; f.H = H; f.W = W; f.d = d; f.kh = kh; f.kw = kw; f.Fh = c.d_Ft16[1]; f.Fw = c.d_Ft16[2];
-  if (!wide && iwh_fits(f, c.num_cu)) return launch_iwh_pass(f, c.num_cu, st);   // H and W axes in one pass
-  WhPassArgs g{};
-  g.in[0] = c.tmp1; g.out[0] = out; g.slice_list[0] = slice_list; g.resid = delta ? v_in : nullptr;
-  for (int i = 0; i < 3; ++i) g.seg_end[i] = ns;
-  g.T = T; g.d = d; g.rows = kh; g.cols = kw; g.out_rows = g.ldh = H; g.out_cols = g.ldw = W;
-  g.Mh = c.d_Ft16[1]; g.Mw = c.d_Ft16[2];
-  if (hw_fits(g)) return launch_hw_inverse(g, c.num_cu, st);   // the same, boxes of any size
-
-  DctPassArgs b{};
-  b.d = d; b.Ntok = c.N;
-  b.in = c.tmp1; b.out = c.tmp0; b.M = c.d_Ft16[1]; b.ldm = H; b.n = kh; b.n_out = H; b.inner = (int64_t)kw * d;
-  b.nslab = (int64_t)ns * T; b.outer = b.nslab; b.in_swap = 1; b.sw = T; b.sw_total = T; b.sw_off = 0;
-  if ((e = launch_mfma_dct_pass(b, c.num_cu, st)) != hipSuccess) return e;
-
-  DctPassArgs w{};
-  w.d = d; w.Ntok = c.N; w.slice_elems = c.N * d;
-  w.in = c.tmp0; w.out = out; w.M = c.d_Ft16[2]; w.ldm = W; w.n = kw; w.n_out = W; w.inner = d;
-  w.nslab = (int64_t)ns * T * H; w.outer = (int64_t)T * H; w.slice_list = slice_list; w.list_out = 1; w.out_bf16 = 1;
-  w.resid = delta ? v_in : nullptr;
-  return launch_mfma_dct_pass(w, c.num_cu, st);
+    DctPassArgs w{};
+    w.d = d; w.Ntok = c.N; w.slice_elems = c.N * d;
+    w.in = c.tmp0; w.out = out; w.M = c.d_Ft16[2]; w.ldm = W; w.n = kw; w.n_out = W; w.inner = d;
+    w.nslab = (int64_t)ns * T * H; w.outer = (int64_t)T * H; w.slice_list = who[i]->slice_list; w.list_out = 1; w.out_bf16 = 1;
+    w.resid = g[i].resid;
+    if ((e = launch_mfma_dct_pass(w, c.num_cu, st)) != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // One pass of the generic path along axis `ax` (0 T, 1 H, 2 W) of whole [slices, N, d] tensors.
@@ -899,9 +1025,9 @@ static hipError_t inverse_transform(Ctx& c, void* out, const void* v_in, hipStre
     // (a box that is the whole grid saves nothing, and out = V + F^-1(Y^ - V~) would then cancel most of V against its own
     // round trip through the fp16 transform: such a class takes the select form)
     auto boxed = [&](const int* keep) { return keep[0] < T || keep[1] < H || keep[2] < W; };
-    if ((e = inverse_transform_mfma(c, out, v_in, st, L + c.off_cls[0], c.n_cls[0], low, boxed(low))) != hipSuccess) return e;
-    if ((e = inverse_transform_mfma(c, out, v_in, st, L + c.off_cls[1], c.n_cls[1], mid, boxed(mid))) != hipSuccess) return e;
-    if ((e = inverse_transform_mfma(c, out, v_in, st, L + c.off_cls[2], c.n_cls[2], full, false)) != hipSuccess) return e;
+    const InverseClass cls[3] = {{L + c.off_cls[0], c.n_cls[0], low, boxed(low)}, {L + c.off_cls[1], c.n_cls[1], mid, boxed(mid)},
+                                 {L + c.off_cls[2], c.n_cls[2], full, false}};
+    if ((e = inverse_transforms_mfma(c, out, v_in, st, cls, 3)) != hipSuccess) return e;
     return launch_copy_slices(v_in, out, L + c.off_cls[3], c.n_cls[3], c.N * c.d * 2, st);
   }
   AxisPassArgs w = generic_pass(c, 2, true), h = generic_pass(c, 1, true), t = generic_pass(c, 0, true);
@@ -989,18 +1115,18 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
       for (int i = 0; i < c->n_cls[2]; ++i) c->qk_full[(size_t)hl[i]] = c->v_full[(size_t)hl[i]] = 1;
       const int32_t *lo = L + c->off_nonhigh, *hi = L + c->off_cls[2];
       const int nl = c->n_nonhigh, nh = c->n_cls[2];
-      const TransformSeg box[3] = {{q, c->specQ, lo, nl}, {k, c->specK, lo, nl}, {v, c->specV, lo, nl}};
-      const TransformSeg whole[3] = {{q, c->specQ, hi, nh}, {k, c->specK, hi, nh},
-                                     vbox ? TransformSeg{v, c->specV, hi, nh} : TransformSeg{v, c->specV, nullptr, c->slices}};
-      HIP_TRY(c, forward_transform_mfma(*c, box, vbox ? 3 : 2, st, mid, 0, 0));
-      HIP_TRY(c, forward_transform_mfma(*c, whole, 3, st, full, 3, -1));
+      const TransformClass cls[2] = {
+        {{{q, c->specQ, lo, nl}, {k, c->specK, lo, nl}, vbox ? TransformSeg{v, c->specV, lo, nl} : TransformSeg{}}, mid, 0, 0},
+        {{{q, c->specQ, hi, nh}, {k, c->specK, hi, nh}, vbox ? TransformSeg{v, c->specV, hi, nh} : TransformSeg{v, c->specV, nullptr, c->slices}}, full, 3, -1}};
+      HIP_TRY(c, forward_transforms_mfma(*c, cls, 2, st));
     } else {
-      const TransformSeg all[3] = {{q, c->specQ, nullptr, c->slices}, {k, c->specK, nullptr, c->slices}, {v, c->specV, nullptr, c->slices}};
+      const TransformSeg aq{q, c->specQ, nullptr, c->slices}, ak{k, c->specK, nullptr, c->slices}, av{v, c->specV, nullptr, c->slices};
+      const TransformClass whole{{aq, ak, av}, full, 0, -1}, box{{aq, ak, vbox ? av : TransformSeg{}}, mid, 0, 0}, v_whole{{av, {}, {}}, full, 5, -1};
       if (!pruned) {
-        HIP_TRY(c, forward_transform_mfma(*c, all, 3, st, full, 0, -1));
+        HIP_TRY(c, forward_transforms_mfma(*c, &whole, 1, st));
       } else {
-        HIP_TRY(c, forward_transform_mfma(*c, all, vbox ? 3 : 2, st, mid, 0, 0));
-        if (!vbox) HIP_TRY(c, forward_transform_mfma(*c, all + 2, 1, st, full, 5, -1));
+        HIP_TRY(c, forward_transforms_mfma(*c, &box, 1, st));
+        if (!vbox) HIP_TRY(c, forward_transforms_mfma(*c, &v_whole, 1, st));
       }
     }
     EnergyWaves nw;
@@ -1023,13 +1149,11 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
     c->v_full.assign((size_t)c->slices, vbox ? 0 : 1);
     if (vbox)
       for (int i = 0; i < n2; ++i) c->v_full[(size_t)(c->h_lists + c->off_cls[2])[i]] = 1;
-    const TransformSeg lows[2] = {{q, c->specQ, l0, n0}, {k, c->specK, l0, n0}};
-    const TransformSeg mids[3] = {{q, c->specQ, l1, n1}, {k, c->specK, l1, n1}, {v, c->specV, L + c->off_nonhigh, vbox ? c->n_nonhigh : 0}};
-    const TransformSeg fulls[3] = {{q, c->specQ, l2, n2}, {k, c->specK, l2, n2},
-                                   vbox ? TransformSeg{v, c->specV, l2, n2} : TransformSeg{v, c->specV, nullptr, c->slices}};
-    HIP_TRY(c, forward_transform_mfma(*c, lows, 2, st, low, -1, -1));
-    HIP_TRY(c, forward_transform_mfma(*c, mids, 3, st, mid, -1, -1));
-    HIP_TRY(c, forward_transform_mfma(*c, fulls, 3, st, full, -1, -1));
+    const TransformClass cls[3] = {
+      {{{q, c->specQ, l0, n0}, {k, c->specK, l0, n0}, {}}, low, -1, -1},
+      {{{q, c->specQ, l1, n1}, {k, c->specK, l1, n1}, {v, c->specV, L + c->off_nonhigh, vbox ? c->n_nonhigh : 0}}, mid, -1, -1},
+      {{{q, c->specQ, l2, n2}, {k, c->specK, l2, n2}, vbox ? TransformSeg{v, c->specV, l2, n2} : TransformSeg{v, c->specV, nullptr, c->slices}}, full, -1, -1}};
+    HIP_TRY(c, forward_transforms_mfma(*c, cls, 3, st));
     return FREQATTN_OK;
   }
   c->v_full.assign((size_t)c->slices, 1);
@@ -1068,10 +1192,10 @@ static freqattn_status settle_forms(freqattn_ctx* c, const void* q, const void* 
   if (n_full + n_box == 0) return FREQATTN_OK;
   HIP_TRY(c, hipMemcpyAsync(c->d_lists + c->off_fix, fix, (size_t)(n_full + n_box) * sizeof(int32_t), hipMemcpyHostToDevice, st));
   const int32_t *lf = c->d_lists + c->off_fix, *lb = lf + n_full;
-  const TransformSeg whole[3] = {{q, c->specQ, lf, n_full}, {k, c->specK, lf, n_full}, {v, c->specV, lf, v_too ? n_full : 0}};
-  const TransformSeg box[3] = {{q, c->specQ, lb, n_box}, {k, c->specK, lb, n_box}, {v, c->specV, lb, c->v_box_ok ? n_box : 0}};
-  HIP_TRY(c, forward_transform_mfma(*c, whole, 3, st, full, -1, -1));
-  HIP_TRY(c, forward_transform_mfma(*c, box, 3, st, mid, -1, -1));
+  const TransformClass cls[2] = {
+    {{{q, c->specQ, lb, n_box}, {k, c->specK, lb, n_box}, {v, c->specV, lb, c->v_box_ok ? n_box : 0}}, mid, -1, -1},
+    {{{q, c->specQ, lf, n_full}, {k, c->specK, lf, n_full}, {v, c->specV, lf, v_too ? n_full : 0}}, full, -1, -1}};
+  HIP_TRY(c, forward_transforms_mfma(*c, cls, 2, st));
   return FREQATTN_OK;
 }
 
@@ -1558,8 +1682,8 @@ extern "C" freqattn_status freqattn_forward_projected(freqattn_ctx* c, const voi
     }
     tm.done("weights");
     const int full[3] = {c->shape.T, c->shape.H, c->shape.W};
-    const TransformSeg xseg{x, c->projX, nullptr, B};
-    HIP_TRY(c, forward_transform_mfma(*c, &xseg, 1, st, full, -1, -1, d_model));
+    const TransformClass xcls{{{x, c->projX, nullptr, B}, {}, {}}, full, -1, -1};
+    HIP_TRY(c, forward_transforms_mfma(*c, &xcls, 1, st, d_model));
     tm.done("x_transform");
     fs = products(0);
     if (fs != FREQATTN_OK) return fs;
@@ -1580,7 +1704,8 @@ extern "C" freqattn_status freqattn_forward_projected(freqattn_ctx* c, const voi
     fs = products(1);
     if (fs != FREQATTN_OK) return fs;
     tm.done("o_projection");
-    HIP_TRY(c, inverse_transform_mfma(*c, out, nullptr, st, nullptr, B, full, false, c->projZ, d_model, c->proj_ones));
+    const InverseClass zcls{nullptr, B, full, false};
+    HIP_TRY(c, inverse_transforms_mfma(*c, out, nullptr, st, &zcls, 1, c->projZ, d_model, c->proj_ones));
     tm.done("inverse_transform");
     return FREQATTN_OK;
   });

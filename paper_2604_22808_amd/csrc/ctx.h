@@ -313,7 +313,13 @@ struct DctPassArgs {
   int en_omul, en_div, low_u, low_v, low_a, mid_u, mid_v, mid_a;  // flat index of the tile = o*en_omul + col0/d
 };
 #define DCT_MAX_WAVES 65536   // upper bound of waves in one launch of the DCT pass (sizes energy_part)
-hipError_t launch_mfma_dct_pass(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out = nullptr);
+int mfma_dct_tiles(int n_in, int n_out);   // output tiles of 32 of the variant a pass takes
+// `n` passes (at most three) of one variant - rows contracted, output tiles, kind of input and output - in one launch; waves_out[i]: waves
+// of the i-th that store partial sums.
+hipError_t launch_mfma_dct_pass(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out = nullptr);
+inline hipError_t launch_mfma_dct_pass(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out = nullptr) {
+  return launch_mfma_dct_pass(&a, 1, num_cu, st, waves_out);
+}
 bool mfma_dct_supported(int n_in, int n_out);
 // W and H axes of the forward transform in one pass, or those of the inverse (mfma_wh_impl.h): input rows of `cols` values
 // through the W matrix, `rows` of them through the H matrix.
@@ -333,13 +339,16 @@ struct WhPassArgs {
 };
 // Whether the pass takes kh x kw coefficients of H x W planes with d channels per token.
 bool wh_fits(int d, int H, int W, int kh, int kw);
-hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W <= 64
-hipError_t launch_wh_pass_1(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out);   // W > 64
-inline hipError_t launch_wh_pass(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
-  return a.cols <= 64 ? launch_wh_pass_0(a, num_cu, st, slots_out) : launch_wh_pass_1(a, num_cu, st, slots_out);
+int wh_items(const WhPassArgs& a);   // workgroups' worth of work in it
+// `n` passes (at most three) over planes of the same width in one launch, with the tiles that suit the first, which keeps the most rows
+// (inverse: over planes of one size, from boxes 16, 32 or 64 wide if there are several); slots_out[i]: slots of tot_part of the i-th.
+hipError_t launch_wh_pass_0(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out);   // W <= 64
+hipError_t launch_wh_pass_1(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out);   // W > 64
+inline hipError_t launch_wh_pass(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out) {
+  return subs[0].cols <= 64 ? launch_wh_pass_0(subs, n, num_cu, st, slots_out) : launch_wh_pass_1(subs, n, num_cu, st, slots_out);
 }
 bool hw_fits(const WhPassArgs& a);   // whether the inverse takes these sizes and is faster than an axis at a time
-hipError_t launch_hw_inverse(const WhPassArgs& a, int num_cu, hipStream_t st);
+hipError_t launch_hw_inverse(const WhPassArgs* subs, int n, int num_cu, hipStream_t st);
 // H and W axes of the inverse transform in one pass (mfma_iwh_impl.h).
 struct IwhPassArgs {
   const void* in; void* out; const void* resid;     // in: fp16 [n_slices][kh][T][kw][d]; out: bf16 [slices][T][H][W][d]; resid: like out, added, or NULL

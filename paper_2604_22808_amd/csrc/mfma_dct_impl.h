@@ -71,9 +71,14 @@ template <int NI, int MT, int MODE> constexpr int dct_min_waves() {
   return w;
 }
 
-template <int NI, int MT, int MODE>
-__global__ void __launch_bounds__(64 * DCT_WAVES) __attribute__((amdgpu_waves_per_eu(dct_min_waves<NI, MT, MODE>())))
-k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
+// One launch: up to three passes of the same variant (the slices that keep different boxes), workgroups
+// [first[i], first[i + 1]) run the i-th.
+struct DctLaunch { DctPassArgs sub[3]; uint32_t n_tiles[3]; int chunks_per_slab[3], first[4]; };
+
+// Workgroup `block` of the `blocks` of a pass.  (Args: the arguments by value, or a reference to them where their address depends on the
+// workgroup; the one costs the other kernel registers.)
+template <int NI, int MT, int MODE, typename Args>
+__device__ __forceinline__ void dct_pass(const Args a, const uint32_t n_tiles32, const int chunks_per_slab, const uint32_t block, const uint32_t blocks) {
   // NI input rows are contracted into up to 32*MT output rows, of which the first a.n_out are stored.
   constexpr int RC = (NI % 32 == 0) ? 32 : 16;  // rows staged per step
   constexpr int NCH = NI / RC;                  // staging steps per tile
@@ -189,9 +194,8 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
 
   // A wave strides over the tile list by the size of the grid: at any time the resident waves work on one narrow,
   // advancing range of tiles.
-  const uint32_t tile_step = gridDim.x * DCT_WAVES;
-  uint32_t tile = blockIdx.x * DCT_WAVES + wave;
-  const uint32_t n_tiles32 = (uint32_t)n_tiles;
+  const uint32_t tile_step = blocks * DCT_WAVES;
+  uint32_t tile = block * DCT_WAVES + wave;
   // staging steps requested ahead of their use (of this tile, then of the next); step c lives in R[c % PD], which
   // carries over to the next tile only when PD divides NCH
   constexpr int PD = (NCH % 2 == 0) ? 2 : 1;
@@ -387,7 +391,7 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
   }
   if (PERM_OUT && a.range_flag && out_of_range) *a.range_flag = 1;   // (every writer stores the same value)
   if (ENERGY || TOT) {
-    const int gwave = blockIdx.x * DCT_WAVES + wave;
+    const int gwave = block * DCT_WAVES + wave;
     if (ENERGY) {
 #pragma unroll
       for (int b = 0; b < 3; ++b)
@@ -412,9 +416,26 @@ k_dct_pass(DctPassArgs a, int64_t n_tiles, int chunks_per_slab) {
 }
 
 template <int NI, int MT, int MODE>
-static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out) {
+__global__ void __launch_bounds__(64 * DCT_WAVES) __attribute__((amdgpu_waves_per_eu(dct_min_waves<NI, MT, MODE>())))
+k_dct_pass(DctPassArgs a, uint32_t n_tiles, int chunks_per_slab) {
+  dct_pass<NI, MT, MODE, DctPassArgs>(a, n_tiles, chunks_per_slab, blockIdx.x, gridDim.x);
+}
+
+// (A kernel of its own: arguments at an address that depends on the workgroup cost registers and time - gather over 64 rows 466 -> 640 us,
+// scatter 1268 -> 1302.)
+template <int NI, int MT, int MODE>
+__global__ void __launch_bounds__(64 * DCT_WAVES) __attribute__((amdgpu_waves_per_eu(dct_min_waves<NI, MT, MODE>())))
+k_dct_passes(DctLaunch m) {
+  const int i = ((int)blockIdx.x >= m.first[1]) + ((int)blockIdx.x >= m.first[2]);
+  dct_pass<NI, MT, MODE, const DctPassArgs&>(m.sub[i], m.n_tiles[i], m.chunks_per_slab[i], blockIdx.x - (uint32_t)m.first[i], (uint32_t)(m.first[i + 1] - m.first[i]));
+}
+
+// Workgroups of one pass of a launch; 0 tiles: none.
+template <int NI, int MT, int MODE>
+static hipError_t size_pass(const DctPassArgs& a, int num_cu, int* blocks_out, uint32_t* tiles_out, int* chunks_out, int* waves_out) {
   const int chunks = (int)(a.inner / 64);
   const int64_t n_tiles = a.nslab * chunks;
+  *blocks_out = 0; *tiles_out = (uint32_t)n_tiles; *chunks_out = chunks;
   if (n_tiles == 0) return hipSuccess;
   if (n_tiles > 0x7fffffff) return hipErrorInvalidValue;
   {
@@ -484,6 +505,25 @@ static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int
       return hipErrorInvalidValue;
     *waves_out = (int)(blocks * DCT_WAVES);
   }
+  *blocks_out = (int)blocks;
+  return hipSuccess;
+}
+
+template <int NI, int MT, int MODE>
+static hipError_t launch_n(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out) {
+  DctLaunch m{};
+  constexpr int lds_bytes = (32 * MT * (NI + 8) + DCT_WAVES * 32 * DCT_XS_STRIDE) * 2;
+  for (int i = 0; i < 3; ++i) {
+    int blocks = 0;
+    if (i < n) {
+      m.sub[i] = subs[i];
+      const hipError_t e = size_pass<NI, MT, MODE>(subs[i], num_cu, &blocks, &m.n_tiles[i], &m.chunks_per_slab[i], waves_out ? waves_out + i : nullptr);
+      if (e != hipSuccess) return e;
+    }
+    m.first[i + 1] = m.first[i] + blocks;
+  }
+  const int64_t blocks = m.first[3];
+  if (blocks == 0) return hipSuccess;
   // Workgroups per compute unit.  The passes over 64 rows and fewer run best with all the waves their registers allow
   // (three or four per SIMD: a tile is 8 KB, and the loads in flight are what keeps the memory system busy); the passes
   // over 128 rows measured 3 % faster held to two workgroups per unit, which is enforced by asking for LDS the kernel does
@@ -494,22 +534,34 @@ static hipError_t launch_n(const DctPassArgs& a, int num_cu, hipStream_t st, int
     const int per = wgs > 0 ? (160 * 1024 / wgs) / 1024 * 1024 : 0;
     return std::max(0, per - lds_bytes);
   }();
+  constexpr bool SHARED = MODE == DCT_SCATTER || MODE == DCT_SCATTER_EN || MODE == DCT_GATHER;   // passes of several classes of slices
+  if (n > 1 && !SHARED) return hipErrorInvalidValue;
+  if constexpr (SHARED)
+    if (n > 1) {
+      if (dyn_lds > 0) {
+        static OncePerDevice limit;
+        const hipError_t e = allow_lds(limit, (const void*)k_dct_passes<NI, MT, MODE>, dyn_lds);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL((k_dct_passes<NI, MT, MODE>), dim3((unsigned)blocks), dim3(64 * DCT_WAVES), (size_t)dyn_lds, st, m);
+      return hipGetLastError();
+    }
   if (dyn_lds > 0) {
     static OncePerDevice limit;
     const hipError_t e = allow_lds(limit, (const void*)k_dct_pass<NI, MT, MODE>, dyn_lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_dct_pass<NI, MT, MODE>), dim3((unsigned)blocks), dim3(64 * DCT_WAVES), (size_t)dyn_lds, st, a, n_tiles, chunks);
+  hipLaunchKernelGGL((k_dct_pass<NI, MT, MODE>), dim3((unsigned)blocks), dim3(64 * DCT_WAVES), (size_t)dyn_lds, st, m.sub[0], m.n_tiles[0], m.chunks_per_slab[0]);
   return hipGetLastError();
 }
 
 
 // Size dispatch of one mode; every translation unit that includes this file instantiates one mode.
 template <int MODE>
-static hipError_t dispatch_mode(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out) {
-  int mt = (a.n_out + 31) / 32;
-  if (mt == 3 && (a.n == 16 || a.n == 32 || a.n == 64 || a.n == 128)) mt = 4;
-#define FA_DCT_CASE(NI_, MT_) if (a.n == NI_ && mt == MT_) return launch_n<NI_, MT_, MODE>(a, num_cu, st, waves_out);
+static hipError_t dispatch_mode(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out) {
+  const DctPassArgs& a = subs[0];
+  const int mt = mfma_dct_tiles(a.n, a.n_out);
+#define FA_DCT_CASE(NI_, MT_) if (a.n == NI_ && mt == MT_) return launch_n<NI_, MT_, MODE>(subs, n, num_cu, st, waves_out);
   FA_DCT_CASE(16, 1) FA_DCT_CASE(16, 2) FA_DCT_CASE(16, 4)
   FA_DCT_CASE(32, 1) FA_DCT_CASE(32, 2) FA_DCT_CASE(32, 4)
   FA_DCT_CASE(64, 1) FA_DCT_CASE(64, 2) FA_DCT_CASE(64, 4)

@@ -2,7 +2,7 @@
 #include "mfma_dct_impl.h"
 
 namespace fa {
-hipError_t launch_mfma_dct_scatter(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out) {
-  return dispatch_mode<2>(a, num_cu, st, waves_out);
+hipError_t launch_mfma_dct_scatter(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out) {
+  return dispatch_mode<2>(subs, n, num_cu, st, waves_out);
 }
 }  // namespace fa

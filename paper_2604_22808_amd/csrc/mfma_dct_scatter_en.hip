@@ -2,7 +2,7 @@
 #include "mfma_dct_impl.h"
 
 namespace fa {
-hipError_t launch_mfma_dct_scatter_en(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out) {
-  return dispatch_mode<3>(a, num_cu, st, waves_out);
+hipError_t launch_mfma_dct_scatter_en(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out) {
+  return dispatch_mode<3>(subs, n, num_cu, st, waves_out);
 }
 }  // namespace fa

@@ -5,12 +5,12 @@ bool wh_fits(int d, int H, int W, int kh, int kw) {
   if (H % 16 != 0 || W % 16 != 0 || H > 128 || W > 128 || kh % 16 != 0 || kw % 16 != 0) return false;
   return kh <= 64 && d % 64 == 0;   // (more than 64 H coefficients do not fit the accumulators)
 }
-hipError_t launch_wh_pass_0(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
-  switch (a.cols / 16) {
-    case 1: return wh_dispatch<1, false>(a, num_cu, st, slots_out);
-    case 2: return wh_dispatch<2, false>(a, num_cu, st, slots_out);
-    case 3: return wh_dispatch<3, false>(a, num_cu, st, slots_out);
-    case 4: return wh_dispatch<4, false>(a, num_cu, st, slots_out);
+hipError_t launch_wh_pass_0(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out) {
+  switch (subs[0].cols / 16) {
+    case 1: return wh_dispatch<1, false>(subs, n, num_cu, st, slots_out);
+    case 2: return wh_dispatch<2, false>(subs, n, num_cu, st, slots_out);
+    case 3: return wh_dispatch<3, false>(subs, n, num_cu, st, slots_out);
+    case 4: return wh_dispatch<4, false>(subs, n, num_cu, st, slots_out);
   }
   return hipErrorInvalidValue;
 }

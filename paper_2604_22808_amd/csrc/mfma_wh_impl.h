@@ -65,8 +65,12 @@ __device__ __forceinline__ uint32_t wh_from_other(uint32_t own, uint32_t other, 
                       : __builtin_amdgcn_update_dpp((int)own, (int)other, 0x128, 0xf, 0x3, false);
 }
 
+// One launch: up to three passes (the slices that keep different boxes), workgroups [first[i], first[i + 1]) run the i-th.
+struct WhLaunch { WhPassArgs sub[3]; int first[4]; };
+
+// Workgroup `block` of the `blocks` of a pass.
 template <int NW16, int KT, int KH, bool INV>
-__global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 2, KT, KH)) k_wh_pass(WhPassArgs a) {
+__device__ __forceinline__ void wh_pass(const WhPassArgs& a, const int block, const int blocks) {
   constexpr int W = 16 * NW16;                 // positions (inverse: coefficients) of an input row
   constexpr int TERMS = INV ? 1 : 2;           // terms the W matrix is split into
   constexpr int KW = (NW16 + 1) / 2;           // steps of 32 positions w per row (the last one of 16 when NW16 is odd)
@@ -88,7 +92,7 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
   // blockIdx); the R workgroups of a plane have neighbouring places in their XCD's list.  With 64, 128, 256 or 512 channels per
   // token the channel chunk (plane index mod channels / 64) is then the same for all items of a workgroup.
   const int cpt = a.d >> 6, R = a.members;
-  const int xcd = blockIdx.x & 7, J = gridDim.x >> 3;
+  const int xcd = block & 7, J = blocks >> 3;
   const int n_planes = a.seg_end[2] * a.T * cpt;
   const int n_items = n_planes > xcd ? ((n_planes - xcd + 7) >> 3) * R : 0;
   // Rows of the caller's tensors are [slice][t][h][w], rows of the other side [segment's slice][kh][t][kw].
@@ -113,8 +117,8 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
   };
   // Workgroup r of a plane: column part r % Rc (KT tiles of 16), row part r / Rc (KH tiles of 16; forward passes have one)
   const int Rc = a.col_parts;
-  if ((int)(blockIdx.x >> 3) >= n_items) {   // nothing to do: zero sums
-    if (a.tot_part) a.tot_part[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = 0.f;
+  if ((block >> 3) >= n_items) {   // nothing to do: zero sums
+    if (a.tot_part) a.tot_part[((size_t)wave * blocks + block) * 64 + lane] = 0.f;
     return;
   }
 
@@ -163,7 +167,7 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
   const uint32_t get0 = ys_at + (uint32_t)((4 * q + (l16 >> 2)) * RB + ((2 * (l16 & 3) + (q & 1)) * 8));
   const uint32_t get1 = get0 ^ 8u;   // (b = 1)
 
-  int l = blockIdx.x >> 3;
+  int l = block >> 3;
   Item it = decode(l);
   Order ord = order(it.r);
   const char* rows = it.in + ord.first * row_bytes;   // this wave's first row of the round
@@ -421,31 +425,84 @@ __global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 
   if constexpr (INV) return;
   // an input that fp16 cannot hold (the spectral buffers' range contract), infinities and NaN included
   if (a.range_flag && (amax[0] >= 0x4780 || amax[1] >= 0x4780)) *a.range_flag = 1;
-  if (a.tot_part) a.tot_part[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = tot[tid];   // per channel of the workgroup's chunk
+  if (a.tot_part) a.tot_part[((size_t)wave * blocks + block) * 64 + lane] = tot[tid];   // per channel of the workgroup's chunk
 }
 
 template <int NW16, int KT, int KH, bool INV>
-static hipError_t wh_launch(WhPassArgs a, int num_cu, hipStream_t st, int* slots_out) {
+__global__ void __launch_bounds__(64 * WH_WAVES, wh_waves_per_simd((NW16 + 1) / 2, KT, KH)) k_wh_pass(WhLaunch m) {
+  const int i = ((int)blockIdx.x >= m.first[1]) + ((int)blockIdx.x >= m.first[2]);
+  wh_pass<NW16, KT, KH, INV>(m.sub[i], (int)blockIdx.x - m.first[i], m.first[i + 1] - m.first[i]);
+}
+
+// Inverse passes from boxes of different widths (16, 32, 64) to planes of one size.
+template <int KT, int KH>
+__global__ void __launch_bounds__(64 * WH_WAVES, 2) k_hw_mixed(WhLaunch m) {
+  const int i = ((int)blockIdx.x >= m.first[1]) + ((int)blockIdx.x >= m.first[2]);
+  const int block = (int)blockIdx.x - m.first[i], blocks = m.first[i + 1] - m.first[i];
+  switch (m.sub[i].cols >> 4) {   // (uniform)
+    case 1: wh_pass<1, KT, KH, true>(m.sub[i], block, blocks); break;
+    case 2: wh_pass<2, KT, KH, true>(m.sub[i], block, blocks); break;
+    case 4: wh_pass<4, KT, KH, true>(m.sub[i], block, blocks); break;
+  }
+}
+
+// Fills in a launch of `n` passes with tiles of KT x KH; NW16: of the widest.
+template <int NW16, int KT, int KH, bool INV>
+static hipError_t wh_size(const WhPassArgs* subs, int n, int num_cu, int per_simd, WhLaunch* m, int* lds_out, int* slots_out) {
   constexpr int FIXED = 2 * 16 * wh_row_bytes(KT) + KT * ((NW16 + 1) / 2) * (INV ? 1024 : 2048) + WH_WAVES * 64 * 4;
   static_assert(FIXED + 16 * KH * (128 + 8) * 2 <= 160 * 1024, "LDS of one compute unit");
-  const int lds = FIXED + 16 * KH * (a.rows + 8) * 2;
-  a.col_parts = (a.out_cols / 16 + KT - 1) / KT;
-  a.members = a.col_parts * ((a.out_rows / 16 + KH - 1) / KH);
-  const int64_t planes = (int64_t)a.seg_end[2] * a.T * (a.d / 64);
-  if (planes <= 0) return hipSuccess;
-  if (planes * a.members > 0x3fffffff) return hipErrorInvalidValue;
-  // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
-  if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
-  // per-lane byte offsets are unsigned 32-bit numbers: 16 rows of the output, 16 positions of the input
-  if ((INV ? 1 : (int64_t)a.T) * a.out_cols * a.d * 2 * 16 > 0xffffffffLL) return hipErrorInvalidValue;
-  const int per_cu = std::min(wh_waves_per_simd((NW16 + 1) / 2, KT, KH) / 2, 160 * 1024 / lds);
-  const int64_t per_xcd = (planes + 7) / 8 * a.members;   // items of the fullest XCD
-  const int grid = 8 * (int)std::min<int64_t>(per_xcd, std::max(1, num_cu / 8) * per_cu);
+  *m = WhLaunch{};
+  int rows = 0;
+  for (int i = 0; i < n; ++i) rows = std::max(rows, subs[i].rows);
+  const int lds = FIXED + 16 * KH * (rows + 8) * 2;
+  const int per_cu = std::min(per_simd / 2, 160 * 1024 / lds);
+  for (int i = 0; i < 3; ++i) {
+    m->first[i + 1] = m->first[i];
+    if (i >= n) continue;
+    WhPassArgs& a = m->sub[i];
+    a = subs[i];
+    a.col_parts = (a.out_cols / 16 + KT - 1) / KT;
+    a.members = a.col_parts * ((a.out_rows / 16 + KH - 1) / KH);
+    if (!INV && a.members != a.col_parts) return hipErrorInvalidValue;
+    const int64_t planes = (int64_t)a.seg_end[2] * a.T * (a.d / 64);
+    if (planes <= 0) continue;
+    if (planes * a.members > 0x3fffffff) return hipErrorInvalidValue;
+    // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
+    if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
+    // per-lane byte offsets are unsigned 32-bit numbers: 16 rows of the output, 16 positions of the input
+    if ((INV ? 1 : (int64_t)a.T) * a.out_cols * a.d * 2 * 16 > 0xffffffffLL) return hipErrorInvalidValue;
+    const int64_t per_xcd = (planes + 7) / 8 * a.members;   // items of the fullest XCD
+    const int grid = 8 * (int)std::min<int64_t>(per_xcd, std::max(1, num_cu / 8) * per_cu);
+    if (slots_out) slots_out[i] = grid * WH_WAVES;
+    m->first[i + 1] += grid;   // (a multiple of 8: every pass deals its planes to the XCDs the same way)
+  }
+  *lds_out = lds;
+  return hipSuccess;
+}
+
+template <int NW16, int KT, int KH, bool INV>
+static hipError_t wh_launch(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out) {
+  WhLaunch m;
+  int lds;
+  hipError_t e = wh_size<NW16, KT, KH, INV>(subs, n, num_cu, wh_waves_per_simd((NW16 + 1) / 2, KT, KH), &m, &lds, slots_out);
+  if (e != hipSuccess || m.first[3] == 0) return e;
   static OncePerDevice limit;
-  hipError_t e = allow_lds(limit, (const void*)k_wh_pass<NW16, KT, KH, INV>, 160 * 1024);
+  e = allow_lds(limit, (const void*)k_wh_pass<NW16, KT, KH, INV>, 160 * 1024);
   if (e != hipSuccess) return e;
-  if (slots_out) *slots_out = grid * WH_WAVES;
-  hipLaunchKernelGGL((k_wh_pass<NW16, KT, KH, INV>), dim3((unsigned)grid), dim3(64 * WH_WAVES), (size_t)lds, st, a);
+  hipLaunchKernelGGL((k_wh_pass<NW16, KT, KH, INV>), dim3((unsigned)m.first[3]), dim3(64 * WH_WAVES), (size_t)lds, st, m);
+  return hipGetLastError();
+}
+
+template <int KT, int KH>
+static hipError_t hw_mixed_launch(const WhPassArgs* subs, int n, int num_cu, hipStream_t st) {
+  WhLaunch m;
+  int lds;
+  hipError_t e = wh_size<4, KT, KH, true>(subs, n, num_cu, 2, &m, &lds, nullptr);
+  if (e != hipSuccess || m.first[3] == 0) return e;
+  static OncePerDevice limit;
+  e = allow_lds(limit, (const void*)k_hw_mixed<KT, KH>, 160 * 1024);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_hw_mixed<KT, KH>), dim3((unsigned)m.first[3]), dim3(64 * WH_WAVES), (size_t)lds, st, m);
   return hipGetLastError();
 }
 
@@ -459,22 +516,24 @@ static inline void wh_tiles(const WhPassArgs& a, int* kt, int* kh, int* members)
   if (members) *members = (a.out_cols / 16 + t - 1) / t * ((tiles + h - 1) / h);
 }
 
+// The passes have input rows of the same width; the tiles are those of the first pass.
 template <int NW16, bool INV>
-static hipError_t wh_dispatch(const WhPassArgs& a, int num_cu, hipStream_t st, int* slots_out) {
+static hipError_t wh_dispatch(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out) {
   int kt, kh;
-  wh_tiles(a, &kt, &kh, nullptr);
-  if (!INV && a.out_rows > 64) return hipErrorInvalidValue;
+  wh_tiles(subs[0], &kt, &kh, nullptr);
+  for (int i = 0; i < n; ++i)
+    if (subs[i].cols != 16 * NW16 || (!INV && subs[i].out_rows > 16 * kh)) return hipErrorInvalidValue;
   // A single W tile: the whole axis of 16, or (forward) the box of an axis that can be cut that far (a power of two).
   if constexpr (INV ? NW16 == 1 : (NW16 & (NW16 - 1)) == 0) {
-    if (kt == 1 && kh == 1) return wh_launch<NW16, 1, 1, INV>(a, num_cu, st, slots_out);
-    if (kt == 1 && kh == 2) return wh_launch<NW16, 1, 2, INV>(a, num_cu, st, slots_out);
+    if (kt == 1 && kh == 1) return wh_launch<NW16, 1, 1, INV>(subs, n, num_cu, st, slots_out);
+    if (kt == 1 && kh == 2) return wh_launch<NW16, 1, 2, INV>(subs, n, num_cu, st, slots_out);
   }
   if constexpr (INV || NW16 > 1) {
-    if (kt == 2 && kh == 1) return wh_launch<NW16, 2, 1, INV>(a, num_cu, st, slots_out);
-    if (kt == 2 && kh == 2) return wh_launch<NW16, 2, 2, INV>(a, num_cu, st, slots_out);
+    if (kt == 2 && kh == 1) return wh_launch<NW16, 2, 1, INV>(subs, n, num_cu, st, slots_out);
+    if (kt == 2 && kh == 2) return wh_launch<NW16, 2, 2, INV>(subs, n, num_cu, st, slots_out);
   }
-  if (kh == 3) return wh_launch<NW16, 1, 3, INV>(a, num_cu, st, slots_out);
-  if (kh == 4) return wh_launch<NW16, 1, 4, INV>(a, num_cu, st, slots_out);
+  if (kh == 3) return wh_launch<NW16, 1, 3, INV>(subs, n, num_cu, st, slots_out);
+  if (kh == 4) return wh_launch<NW16, 1, 4, INV>(subs, n, num_cu, st, slots_out);
   return hipErrorInvalidValue;
 }
 

@@ -120,6 +120,27 @@ def test_outputs_of_one_pass_inverse(grid, d, n):
         assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (h, mx, rl)
 
 
+# classes of slices that keep different boxes and are small enough to share launches: boxes one, two and four tiles of 16 wide, one to
+# four tiles of rows, T axes that can be cut (the gather passes then stay apart) and not, a class that is missing
+@pytest.mark.parametrize("grid,d,alloc", [((16, 32, 32), 64, (1, 2, 4)), ((16, 64, 64), 128, (1, 2, 4, 6, 0)), ((32, 16, 64), 64, (1, 1, 4)),
+                                          ((64, 32, 16), 64, (2, 4, 2)), ((16, 128, 32), 64, (1, 2, 4)), ((16, 32, 128), 64, (1, 2, 4)),
+                                          ((16, 48, 64), 64, (1, 2, 4)), ((32, 32, 32), 64, (1, 3, 5))])
+def test_shared_launches_give_the_bits_of_launches_of_their_own(grid, d, alloc):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(23)
+    N, n = int(np.prod(grid)), len(alloc)
+    q, k, v = ((0.5 * torch.randn((1, n, N, d), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(3))
+    # (no summaries: sums over tokens are split by the number of slices; fewer slices than the small-box inverse takes)
+    cfg = B.make_cfg(**dict(WL.WORKLOADS["16k"].band, n_summary=0))
+    ctx, one = B.Context(1, n, d, grid, B.BF16, cfg, path=B.PATH_MFMA), B.Context(1, 1, d, grid, B.BF16, cfg, path=B.PATH_MFMA)
+    out, alone = torch.empty_like(q), torch.empty((1, 1, N, d), dtype=torch.bfloat16, device="cuda")
+    ctx.forward(q, k, v, alloc, out)
+    for h in range(n):
+        one.forward(*(x[:, h:h + 1].contiguous() for x in (q, k, v)), alloc[h:h + 1], alone)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0, h], alone[0, 0]), (h, float((out[0, h].float() - alone[0, 0].float()).abs().max()))
+
+
 @pytest.mark.parametrize("path", [B.PATH_MFMA, B.PATH_GENERIC])
 def test_routing_leaves_the_band_outputs_readable(path, monkeypatch):
     """The transforms of a routing call that is no forward use scratch that is not the last forward's result."""
