@@ -105,7 +105,8 @@ struct Ctx {
   bool qk_on_mid_box = false;                     // the last routed transforms left Q~, K~ on the low+mid box only
   int energy_waves[6] = {0, 0, 0, 0, 0, 0};       // waves that stored band statistics in the last T-axis pass, per statistics slot
   int low_box[3] = {0, 0, 0}, mid_box[3] = {0, 0, 0};  // extent of the low / low+mid box per axis
-  float* h_stats = nullptr;                       // pinned mirror
+  float* h_stats = nullptr;                       // pinned mirror and the range flag behind it
+  float* h_stats_dev = nullptr;                   // the same where the device writes it (MFMA path)
 
   // per-forward lists (device + pinned host mirror)
   int32_t* d_lists = nullptr; int32_t* h_lists = nullptr; size_t lists_bytes = 0;
@@ -265,7 +266,7 @@ hipError_t launch_copy_slices(const void* in, void* out, const int32_t* slice_li
 struct EnergyWaves { int en[6]; int tot[3]; };   // waves whose slots hold this forward's partial sums, per statistics slot
 hipError_t launch_energy_reduce(const float* energy_part /*[6][DCT_MAX_WAVES][3][64]: Q, K, V (box), Q, K, V (whole grid)*/,
                                 const float* tot_part /*[3][DCT_MAX_WAVES][64] or NULL*/, float* stats /*[3][d] + ENERGY_PART_FLOATS of scratch*/, int d,
-                                const EnergyWaves& nw, hipStream_t st);
+                                const EnergyWaves& nw, float* host /*[3][d] + 1, pinned*/, const int32_t* range_flag, hipStream_t st);
 
 // Lets `kernel` ask for `bytes` of dynamic LDS on the current device.
 inline hipError_t allow_lds(OncePerDevice& limit, const void* kernel, int bytes) {

@@ -487,8 +487,10 @@ __global__ void __launch_bounds__(768) k_energy_reduce1(const float* __restrict_
   if (q == 0) part1[(size_t)b * 192 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
-// One workgroup per band and channel chunk: 16 rows of 64 threads share the chunk's partial sums.
-__global__ void __launch_bounds__(1024) k_energy_reduce2(const float* __restrict__ part1, float* __restrict__ stats, int d, int parseval) {
+// One workgroup per band and channel chunk: 16 rows of 64 threads share the chunk's partial sums.  `host` ([3][d] + 1, pinned): the
+// sums and the range flag once more, where the host reads them after waiting for the stream (two copies less in front of it).
+__global__ void __launch_bounds__(1024) k_energy_reduce2(const float* __restrict__ part1, float* __restrict__ stats, int d, int parseval,
+                                                         float* __restrict__ host, const int32_t* __restrict__ range_flag) {
   __shared__ float red[16][64];
   const int chunks = d / 64, band = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
   const int row = threadIdx.x >> 6, col = threadIdx.x & 63;
@@ -501,17 +503,20 @@ __global__ void __launch_bounds__(1024) k_energy_reduce2(const float* __restrict
   for (int r = 1; r < 16; ++r) t += red[r][col];
   // The Parseval difference of a band that holds (almost) no energy can come out slightly negative (the low and mid
   // sums carry the rounding of the fp16 transform): an energy is never below zero.
-  stats[band * d + chunk * 64 + col] = (parseval && band == 2 && t < 0.f) ? 0.f : t;   // (a NaN stays a NaN: the host reports it)
+  t = (parseval && band == 2 && t < 0.f) ? 0.f : t;   // (a NaN stays a NaN: the host reports it)
+  stats[band * d + chunk * 64 + col] = t;
+  host[band * d + chunk * 64 + col] = t;
+  if (blockIdx.x == 0 && col == 0) host[3 * d] = __int_as_float(*range_flag);
 }
 
 // stats: [3][d] results followed by ENERGY_PART_FLOATS of scratch (the stage-1 sums)
 hipError_t launch_energy_reduce(const float* energy_part, const float* tot_part, float* stats, int d, const EnergyWaves& nw,
-                                hipStream_t st) {
+                                float* host, const int32_t* range_flag, hipStream_t st) {
   if (d <= 0 || d % 64 != 0 || ENERGY_PARTS % (d / 64) != 0) return hipErrorInvalidValue;
   static_assert(ENERGY_PARTS * 192 == ENERGY_PART_FLOATS, "scratch of the stage-1 sums");
   float* part1 = stats + 3 * d;
   hipLaunchKernelGGL(k_energy_reduce1, dim3(ENERGY_PARTS), dim3(768), 0, st, energy_part, tot_part, part1, nw);
-  hipLaunchKernelGGL(k_energy_reduce2, dim3(3 * (d / 64)), dim3(1024), 0, st, part1, stats, d, tot_part != nullptr ? 1 : 0);
+  hipLaunchKernelGGL(k_energy_reduce2, dim3(3 * (d / 64)), dim3(1024), 0, st, part1, stats, d, tot_part != nullptr ? 1 : 0, host, range_flag);
   return hipGetLastError();
 }
 

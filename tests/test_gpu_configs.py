@@ -523,3 +523,33 @@ def test_block_sparse_items_with_more_than_64_key_blocks():
         mx, rl = U.errors(got[0, s], want[0, s])
         print(f"dense block pattern mask {alloc[s]}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
         assert mx <= 2e-2 and rl <= 5e-3
+
+
+@pytest.mark.parametrize("d,hidden", [(64, 1), (128, 65), (192, 64)])
+def test_statistics_of_one_routed_call_after_another(d, hidden):
+    """The reduction leaves the statistics where the host reads them (d = 192 takes the generic path, which copies them): every call
+    has those of its own inputs, in every channel chunk and band, also right after a call with others.  Tolerances as for the configurations above."""
+    grid = (16, 32, 32)
+    wl = WL.WORKLOADS["64k"]
+    band, cfg = dict(wl.band), O.BandConfig(**wl.band)
+    w = WL.router_weights(hidden, 3)
+    ctx = B.Context(1, 2, d, grid, B.BF16, B.make_cfg(**band))
+    assert ctx.get_path() == (B.PATH_GENERIC if d == 192 else B.PATH_MFMA)
+    rng = np.random.default_rng(d)
+    n, sets = grid[0] * grid[1] * grid[2], []
+    for smooth in (0, 1):
+        x = rng.standard_normal((3, 1, 2, *grid, d)) * (1 + np.arange(d) / d)
+        if smooth:
+            x = x + np.roll(x, 1, 2) + np.roll(x, 1, 3) + np.roll(x, 1, 4)
+        x = [WL.round_to_io(a.reshape(1, 2, n, d).astype(np.float32), "bf16") for a in x]
+        sets.append(([U.to_device(a, "bf16") for a in x], O.band_statistics(*x, grid, cfg), O.route_mlp(*x, grid, cfg, 0.5, *w)))
+    assert np.abs(sets[0][1] - sets[1][1]).max() > 0.1
+    first = {}
+    for i in (0, 1, 0, 1):
+        x, stats, (alloc, pi) = sets[i]
+        got_alloc, got_pi, got_stats = ctx.route_mlp(*x, 0.5, *w)
+        print(f"d {d} inputs {i}: stats {np.abs(got_stats - stats).max():.2e} pi {np.abs(got_pi - pi).max():.2e}", flush=True)
+        assert np.abs(got_stats - stats).max() < 5e-3 and np.abs(got_pi - pi).max() < 2e-3
+        assert np.array_equal(got_alloc, alloc)
+        assert np.array_equal(first.setdefault(i, got_stats), got_stats)
+    ctx.destroy()
