@@ -707,8 +707,8 @@ static bool mid_keep(const Ctx& c, int keep[3]) {
 // 1722 / 1344; 128 (eight; 12 of 16 x 64 x 128 x 128) 1436 / 1229; low+mid box of 8 of 32 x 128 x 96 x 128 1966 / 1391.
 static bool one_pass(const Ctx& c, bool box, int d) {
   int mid[3];
-  const int H = c.shape.H, W = c.shape.W;
-  return box && mid_keep(c, mid) ? wh_fits(d, H, W, mid[1], mid[2]) : wh_fits(d, H, W, H, W);
+  const int T = c.shape.T, H = c.shape.H, W = c.shape.W;
+  return box && mid_keep(c, mid) ? wh_fits(T, d, H, W, mid[1], mid[2]) : wh_fits(T, d, H, W, H, W);
 }
 
 // One tensor of a forward transform: `ns` slices (slice_list on the device, NULL = slices 0..ns-1) of x into the band-major

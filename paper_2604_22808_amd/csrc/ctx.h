@@ -277,6 +277,9 @@ inline hipError_t allow_lds(OncePerDevice& limit, const void* kernel, int bytes)
 }
 
 // ---- MFMA kernels (mfma_dct.hip, mfma_attn.hip) -------------------------------------------------------------------
+// The transform passes add what a lane's place within 8 rows takes to a wave-uniform 64-bit address, as an unsigned 32-bit number of
+// bytes: whether rows `stride` 16-bit elements apart leave room for that.
+inline bool eight_rows_fit(int64_t stride) { return stride * 8 * 2 + 128 <= 0xffffffffLL; }
 struct DctPassArgs {
   const void* in; void* out;
   const half_t* M;          // fp16, row stride ldm: out[k] = sum_{j < n} M[k*ldm + j] in[j], k < n_out
@@ -338,8 +341,8 @@ struct WhPassArgs {
   int32_t* range_flag;                              // forward: set when an input value leaves the fp16 range
   int members, col_parts;                           // (filled in by the launcher) workgroups that share a plane
 };
-// Whether the pass takes kh x kw coefficients of H x W planes with d channels per token.
-bool wh_fits(int d, int H, int W, int kh, int kw);
+// Whether the pass takes kh x kw coefficients of T planes of H x W with d channels per token.
+bool wh_fits(int T, int d, int H, int W, int kh, int kw);
 int wh_items(const WhPassArgs& a);   // workgroups' worth of work in it
 // `n` passes (at most three) over planes of the same width in one launch, with the tiles that suit the first, which keeps the most rows
 // (inverse: over planes of one size, from boxes 16, 32 or 64 wide if there are several); slots_out[i]: slots of tot_part of the i-th.

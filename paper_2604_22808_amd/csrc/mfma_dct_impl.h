@@ -442,7 +442,7 @@ static hipError_t size_pass(const DctPassArgs& a, int num_cu, int* blocks_out, u
     // the kernel adds per-lane byte offsets as unsigned 32-bit numbers: 8 rows of the larger row stride, 8 rows of the
     // permutation table (band-major rows times the row width are formed in 64 bits)
     const int64_t stride = (a.in_swap || a.out_swap) ? (int64_t)a.sw_total * a.inner : a.inner;
-    if (stride * 8 * 2 + 128 > 0xffffffffLL) return hipErrorInvalidValue;
+    if (!eight_rows_fit(stride)) return hipErrorInvalidValue;
     if (a.perm_out && (a.in_swap || a.list_in || (int64_t)a.seg_end[2] * a.outer != a.nslab)) return hipErrorInvalidValue;
     if ((a.perm_in || a.perm_out) && (a.Ntok > 0x7fffffffLL || a.perm_k * 8 * 4 > 0xffffffffLL)) return hipErrorInvalidValue;
   }

@@ -1,9 +1,10 @@
 // W + H pass of the forward transform, W = 16 .. 64 (see mfma_wh_impl.h).
 #include "mfma_wh_impl.h"
 namespace fa {
-bool wh_fits(int d, int H, int W, int kh, int kw) {
+bool wh_fits(int T, int d, int H, int W, int kh, int kw) {
   if (H % 16 != 0 || W % 16 != 0 || H > 128 || W > 128 || kh % 16 != 0 || kw % 16 != 0) return false;
-  return kh <= 64 && d % 64 == 0;   // (more than 64 H coefficients do not fit the accumulators)
+  // (more than 64 H coefficients do not fit the accumulators; the launcher refuses rows that lie too far apart)
+  return kh <= 64 && d % 64 == 0 && eight_rows_fit((int64_t)T * kw * d);
 }
 hipError_t launch_wh_pass_0(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out) {
   switch (subs[0].cols / 16) {

@@ -8,6 +8,7 @@ namespace fa {
 bool hw_fits(const WhPassArgs& a) {
   if (a.rows % 16 || a.cols % 16 || a.out_rows % 16 || a.out_cols % 16 || a.rows > 128 || a.cols > 128 || a.out_rows > 128 || a.out_cols > 128 || a.d % 64)
     return false;
+  if (!eight_rows_fit((int64_t)a.out_cols * a.d)) return false;   // (the launcher refuses them)
   int members;
   wh_tiles(a, nullptr, nullptr, &members);
   return (int64_t)members * a.rows * a.cols <= 10 * (int64_t)a.out_rows * a.out_cols;

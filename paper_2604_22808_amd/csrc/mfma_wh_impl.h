@@ -464,13 +464,13 @@ static hipError_t wh_size(const WhPassArgs* subs, int n, int num_cu, int per_sim
     a.col_parts = (a.out_cols / 16 + KT - 1) / KT;
     a.members = a.col_parts * ((a.out_rows / 16 + KH - 1) / KH);
     if (!INV && a.members != a.col_parts) return hipErrorInvalidValue;
+    // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
+    if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
+    // a lane reaches 8 rows of the output; and 16 positions of the input, which is less (wh_fits and hw_fits ask for the same)
+    if (!eight_rows_fit((INV ? 1 : (int64_t)a.T) * a.out_cols * a.d)) return hipErrorInvalidValue;
     const int64_t planes = (int64_t)a.seg_end[2] * a.T * (a.d / 64);
     if (planes <= 0) continue;
     if (planes * a.members > 0x3fffffff) return hipErrorInvalidValue;
-    // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
-    if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
-    // per-lane byte offsets are unsigned 32-bit numbers: 16 rows of the output, 16 positions of the input
-    if ((INV ? 1 : (int64_t)a.T) * a.out_cols * a.d * 2 * 16 > 0xffffffffLL) return hipErrorInvalidValue;
     const int64_t per_xcd = (planes + 7) / 8 * a.members;   // items of the fullest XCD
     const int grid = 8 * (int)std::min<int64_t>(per_xcd, std::max(1, num_cu / 8) * per_cu);
     if (slots_out) slots_out[i] = grid * WH_WAVES;

@@ -218,3 +218,21 @@ def test_projected_forward_of_narrow_models(d_model):
     mx, rl = U.errors(U.to_host64(out), O.forward_projected(x, *w, grid, O.BandConfig(**band), alloc))
     print(f"projected d_model={d_model}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
     assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
+
+
+def test_projected_forward_of_a_model_of_8192_channels():
+    """Rows of the transformed X 4 MB apart and more.  Heads that run no band: the layer is X W_V W_O.  Tolerance of the other outputs."""
+    import torch
+    grid, d, heads, d_model = (128, 16, 128), 128, 64, 8192
+    gen = torch.Generator(device="cuda").manual_seed(29)
+    N = int(np.prod(grid))
+    x = 0.5 * torch.randn((1, N, d_model), device="cuda", generator=gen, dtype=torch.bfloat16)
+    wv, wo = (torch.randn((d_model, d_model), device="cuda", generator=gen, dtype=torch.bfloat16) / d_model ** 0.5 for _ in range(2))
+    ctx = B.Context(1, heads, d, grid, B.BF16, B.make_cfg(**WL.WORKLOADS["16k"].band), path=B.PATH_MFMA)
+    out = torch.empty_like(x)
+    ctx.forward_projected(x, wv, wv, wv, wo, [0] * heads, out)
+    rows = torch.randperm(N, device="cuda", generator=gen)[:4096]
+    mx, rl = U.errors(U.to_host64(out[0, rows]), U.to_host64(x[0, rows].float() @ (wv.float() @ wo.float())))
+    print(f"projected d_model={d_model}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    ctx.destroy()
+    assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
