@@ -701,7 +701,8 @@ static bool mid_keep(const Ctx& c, int keep[3]) {
 // Whether the W and H axes of a forward transform go through the one-pass kernel, for the boxes of the grid (low, low+mid) and for
 // the whole of it.  The kernel and the two passes it replaces sum in another order and round another input, so this is
 // decided once for both boxes: a low head's coefficients come from either, by the entry point, and must be the same bits
-// (settle_forms takes care of the whole grid where it goes the other way).
+// (settle_forms takes care of the whole grid where it goes the other way).  For the same reason it does not look at where a tensor
+// starts: classes of one call hold different tensors.  (Both forms load 16 bytes per lane from global memory at any address.)
 // Up to 64 H coefficients it is the faster one with any number of workgroups on a plane; forward transforms, two passes / one, us,
 // whole grid: W = 96 (six workgroups; 12 slices of 32 x 64 x 96 x 64) 1054 / 791; 112 (seven; 8 of 32 x 64 x 112 x 128)
 // 1722 / 1344; 128 (eight; 12 of 16 x 64 x 128 x 128) 1436 / 1229; low+mid box of 8 of 32 x 128 x 96 x 128 1966 / 1391.
@@ -802,11 +803,8 @@ static hipError_t transform_classes(Ctx& c, const TransformClass* cls, int ncls,
   bool by_axes[3] = {false, false, false};
   for (int k = 0; k < ncls; ++k) {
     const TransformClass& x = cls[k];
-    // (the pass loads whole 16-byte pieces of the caller's tensors; a view that starts between them takes the two passes)
-    bool fused = one_pass(c, x.keep[0] < T || x.keep[1] < H || x.keep[2] < W, d);
-    for (int i = 0; i < 3; ++i) fused = fused && (x.seg[i].ns <= 0 || (uintptr_t)x.seg[i].x % 16 == 0);
-    by_axes[k] = !fused;
-    if (!fused) continue;
+    by_axes[k] = !one_pass(c, x.keep[0] < T || x.keep[1] < H || x.keep[2] < W, d);
+    if (by_axes[k]) continue;
     WhPassArgs& g = f[n];
     DctPassArgs& u = t[n];
     g = wh_pass_args(c, x, d);

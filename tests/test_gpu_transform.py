@@ -184,6 +184,32 @@ def test_outputs_do_not_depend_on_the_box(grid, noise, vbox, monkeypatch):
     assert len(seen) >= 2, seen   # the sequence really changes the allocation
 
 
+@pytest.mark.parametrize("skip", [(0, 0, 1, 0), (1, 0, 0, 0), (2, 4, 6, 1)])   # elements in front of q, k, v and out
+def test_outputs_do_not_depend_on_where_tensors_start(skip, monkeypatch):
+    """Contiguous views that start between 16-byte pieces, some or all: the bits of aligned tensors, by either entry point."""
+    import torch
+    monkeypatch.setenv("FREQATTN_V_BOX", "1")
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    grid, d = (16, 64, 64), 64
+    shape = (1, 6, int(np.prod(grid)), d)
+
+    def view(x, n):
+        t = torch.zeros(x.numel() + 8, dtype=torch.bfloat16, device="cuda")
+        return t[n:n + x.numel()].view(shape).copy_(x)
+    aligned = [torch.randn(shape, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(3)]
+    views, out, want = [view(x, n) for x, n in zip(aligned, skip)], view(torch.zeros_like(aligned[0]), skip[3]), torch.empty_like(aligned[0])
+    ctx, ref = (B.Context(1, 6, d, grid, B.BF16, B.make_cfg(**WL.WORKLOADS["64k"].band), path=B.PATH_MFMA) for _ in range(2))
+    for t in (0.95, 0.95, 0.05):   # nothing to guess from, a right guess, a wrong one
+        alloc, _ = ctx.forward_routed(*views, t, *WL.router_weights(), out)
+        ref.forward(*aligned, alloc, want)
+        torch.cuda.synchronize()
+        assert 1 in alloc and torch.equal(out, want), ("routed", t, list(alloc), float((out.float() - want.float()).abs().max()))
+        out.zero_()
+        ref.forward(*views, alloc, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), ("given", t, list(alloc), float((out.float() - want.float()).abs().max()))
+
+
 @pytest.mark.parametrize("value", [65536.0, float("inf"), float("nan")])
 def test_input_outside_fp16_is_reported(value):
     """One input value that fp16 cannot hold, in a plane that several workgroups share."""
