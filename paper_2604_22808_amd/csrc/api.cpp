@@ -1050,6 +1050,10 @@ static hipError_t inverse_transform(Ctx& c, void* out, const void* v_in, hipStre
 #define LOW_FILL_MAX 16
 static int low_fill(const Ctx& c) { return c.cfg.low_compress <= LOW_FILL_MAX ? c.cfg.low_compress : 1; }
 
+// The window as the kernels get it: one that is longer than the band is the whole band, and then row indices plus the window, at most
+// 2^30 each, fit the 32-bit numbers that the kernels form them in.
+static int32_t kernel_window(const Ctx& c) { return (int32_t)std::min<int64_t>(c.cfg.high_window, c.band_n[HIGH]); }
+
 static void fill_attn_params(const Ctx& c, AttnParams& p, float scale) {
   std::memset(&p, 0, sizeof(p));
   p.specQ = c.specQ; p.specK = c.specK; p.specV = c.specV; p.Y = c.Y;
@@ -1063,7 +1067,7 @@ static void fill_attn_params(const Ctx& c, AttnParams& p, float scale) {
     p.n_c[l] = c.n_c[l];
   }
   p.N = (int32_t)c.N; p.d = c.d; p.nbar = (int32_t)c.nbar; p.m2 = (c.nb - 1) * std::max(c.cfg.n_summary, 1);
-  p.mid_block = c.cfg.mid_block; p.high_window = c.cfg.high_window; p.scale = scale;
+  p.mid_block = c.cfg.mid_block; p.high_window = kernel_window(c); p.scale = scale;
 }
 
 struct StageTimer {
@@ -1305,7 +1309,7 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
       const int64_t o = c->band_off[l] * c->d;
       s.Q = (const float*)c->specQ + o; s.K = (const float*)c->specK + o; s.V = (const float*)c->specV + o; s.O = (float*)c->Y + o;
       s.slice_stride = s.kv_slice_stride = s.o_slice_stride = Nd; s.nq = s.nk = s.n_out = (int)c->band_n[l]; s.rep = s.fill = 1;
-      s.mode = l == HIGH ? 2 : 1; s.window = c->cfg.high_window; s.block = c->cfg.mid_block;
+      s.mode = l == HIGH ? 2 : 1; s.window = kernel_window(*c); s.block = c->cfg.mid_block;
       s.row_ptr = l == MID2 ? c->d_row_ptr2 : c->d_row_ptr; s.col_idx = l == MID2 ? c->d_col_idx2 : c->d_col_idx;
     }
     if (c->launch_mode == FREQATTN_LAUNCH_FUSED) {

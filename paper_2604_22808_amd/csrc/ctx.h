@@ -45,7 +45,7 @@ struct AttnParams {
   int32_t low_c;      // compression factor c: group i's output belongs to low-band rows i c .. i c + c - 1
   int32_t low_fill;   // rows of a group the band operator writes itself: c, or 1 when launch_expand_low fills the rest
   int32_t N, d, nbar, m2;  // m2 = (nb-1) m = rows reserved per band in C
-  int32_t mid_block, high_window;
+  int32_t mid_block, high_window;   // (high_window at most band_n[HIGH])
   float scale;
   // dense baseline
   const void* denseQ; const void* denseK; const void* denseV; void* denseO;   // fp16
@@ -208,7 +208,7 @@ struct GAttnSeg {
   int64_t kv_slice_stride;  // elements between slices for K/V (differs from Q for the exchange)
   int nq, nk;
   int mode;                 // 0 dense, 1 block list, 2 window
-  const int32_t* row_ptr; const int32_t* col_idx; int block; int window;
+  const int32_t* row_ptr; const int32_t* col_idx; int block; int window;   // (window at most nk)
   int residual;             // O = Q + attention (exchange)
   int rep, fill, n_out;     // query row i is written to output rows i rep .. i rep + fill - 1 below n_out (low band: its group)
   int rows, tiles, first_block;   // filled in by the launcher: query rows per workgroup, workgroups per slice, first workgroup

@@ -40,6 +40,26 @@ def test_generic_attention_blocks_and_windows(block, window, c):
     _check((7, 24, 26), 64, 2, (7, 7), mid_block=block, mid_stride=3, high_window=window, n_summary=9, low_compress=c)
 
 
+@pytest.mark.parametrize("dtype,path,grid", [("f32", B.PATH_GENERIC, (7, 24, 26)), ("bf16", B.PATH_GENERIC, (5, 9, 11)),
+                                             ("bf16", B.PATH_MFMA, (16, 32, 48))])
+def test_windows_of_everything(dtype, path, grid):
+    """Every window from one row short of the band's length up is the whole band, up to the longest that a configuration can hold."""
+    rng = np.random.default_rng(8)
+    N = int(np.prod(grid))
+    x = [WL.round_to_io(0.7 * rng.standard_normal((1, 1, N, 64)), dtype) for _ in range(3)]
+    cfgd = dict(WL.WORKLOADS["16k"].band)
+    n = len(O.band_partition(*grid, O.BandConfig(**cfgd))[2])
+    outs = []
+    for window in (n - 1, n, n + 1, 2 ** 31 - n, 2 ** 31 - 2, 2 ** 31 - 1):
+        ctx = B.Context(1, 1, 64, grid, B.F32 if dtype == "f32" else B.BF16, B.make_cfg(**dict(cfgd, high_window=window)), path=path)
+        outs.append(U.run_forward(ctx, *x, dtype, (4,)))
+        ctx.destroy()
+        assert np.array_equal(outs[-1], outs[0]), window
+    mx, rl = U.errors(outs[0], O.forward(*x, grid, O.BandConfig(**dict(cfgd, high_window=n)), (4,)))
+    print(f"window of everything {dtype} {grid}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= U.TOL[dtype][0] and rl <= U.TOL[dtype][1], (mx, rl)
+
+
 @pytest.mark.parametrize("block,window", [(16, 48), (48, 100), (80, 17), (40, 16)])
 def test_generic_attention_of_large_scores(block, window):
     """Scores of up to about +-40 before the softmax (rounded at 2^-24 of themselves: 2.4e-6 in a probability), block lists whose
