@@ -361,8 +361,9 @@ def main():
     vbox = ctx.get_v_box()   # V~ of a slice without the high band on the low+mid box: V follows Q and K class by class
     nonhigh_present = cls_present[0] or cls_present[1] or any(m == 0 for m in masks)
     # Launches: tensors that keep the same coefficient box share a W + H pass and a T pass where the one-pass kernels take the
-    # box (one_pass in csrc/api.cpp, csrc/mfma_iwh.hip, csrc/mfma_wh_2.hip), else every axis of every tensor is a launch.  (Classes
-    # of slices too small to fill the chip share launches among them: not counted here.)
+    # box (one_pass in csrc/api.cpp, csrc/mfma_iwh.hip, csrc/mfma_wh_2.hip), else every axis of every tensor is a launch.  Classes
+    # of slices too small to fill the chip share launches with the class that keeps the most: where one is that small the
+    # launches are not counted (None).
     T, H, W = wl.grid
     def passes(n_in, n_out):   # the axis pass exists: any number of rows for powers of two, square otherwise
         return n_in & (n_in - 1) == 0 or (n_out + 31) // 32 == (n_in + 31) // 32
@@ -370,25 +371,37 @@ def main():
         rounded = [min(n, -(-(-(-num * n // 4)) // 16) * 16) for n in (T, H, W)]
         return [r if passes(n, r) and passes(r, n) else n for r, n in zip(rounded, (T, H, W))]
     low_k, mid_k, full_k = kept(1), kept(2), [T, H, W]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    def shares(classes):   # (slices of all tensors, box) per class, the one that keeps the most last
+        present = [(n * (wl.head_dim // 64), k) for n, k in classes if n > 0]
+        return any(n * T < 2 * cus or n * k[1] * k[2] < 32 * cus for n, k in present[:-1])
     def fwd_group(tensors, k):
         kh = mid_k[1] if k != full_k and mid_k != full_k else H
         return 0 if tensors == 0 else 2 if kh <= 64 else 3 * tensors
     def inv_group(mask_of_class, k):
         n = sum(1 for m in masks if mask_of_class(m)) * wl.batch
-        cus = torch.cuda.get_device_properties(0).multi_processor_count
         small = k[1] * k[2] <= 512 and W in (16, 32, 64) and n * T * (wl.head_dim // 64) * (H // 16) >= 2 * cus
         parts = (H // 16 + 3) // 4                                          # of a plane's rows, 3 or 4 tiles of 16 each
         cols = 2 if (H // 16 + parts - 1) // parts <= 2 and W > 16 else 1   # tiles of 16 columns per workgroup
         readers = parts * -(-(W // 16) // cols)
         return 0 if n == 0 else 2 if small or readers * k[1] * k[2] <= 10 * H * W else 3
+    n_cls = [sum(1 for m in masks if f(m)) * wl.batch for f in (lambda m: m & 1 and not m & 6, lambda m: m & 2 and not m & 4, lambda m: m & 4)]
+    n_not_high = wl.batch * len(masks) - n_cls[2]
+    v_full = n_cls[2] if vbox else wl.batch * len(masks)
     if router is not None:   # routed: slices split into "ran the high band last time" and the rest
         fwd_launches = fwd_group((3 if vbox else 2) if nonhigh_present else 0, mid_k) + fwd_group(3 if cls_present[2] else 0 if vbox else 1, full_k)
+        fwd_classes = [((3 if vbox else 2) * n_not_high, mid_k), (2 * n_cls[2] + v_full, full_k)]
     else:
         fwd_launches = (fwd_group(2 if cls_present[0] else 0, low_k)
                         + fwd_group((2 if cls_present[1] else 0) + (1 if vbox and nonhigh_present else 0), mid_k)
                         + fwd_group(3 if cls_present[2] else 0 if vbox else 1, full_k))
+        fwd_classes = [(2 * n_cls[0], low_k), (2 * n_cls[1] + (n_not_high if vbox else 0), mid_k), (2 * n_cls[2] + v_full, full_k)]
     inv_launches = (inv_group(lambda m: m & 1 and not m & 6, low_k) + inv_group(lambda m: m & 2 and not m & 4, mid_k)
                     + inv_group(lambda m: m & 4, full_k) + (1 if any(m == 0 for m in masks) else 0))
+    if shares(fwd_classes):
+        fwd_launches = None
+    if shares(list(zip(n_cls, (low_k, mid_k, full_k)))):
+        inv_launches = None
     # single-band slices run their exchange inside the band items: its flops then belong to the band attention launch
     one_band = [m in (1, 2, 4) for m in masks]
     if any(one_band):
@@ -406,7 +419,7 @@ def main():
                 work[name] = ("mfma", work[name][1] + moved_band[l], 1)
             work["exchange"] = ("mfma", max(work["exchange"][1] - moved, 0.0), 1)
     work["forward_transform"] = (work["forward_transform"][0], work["forward_transform"][1], fwd_launches)
-    work["inverse_transform"] = (work["inverse_transform"][0], work["inverse_transform"][1], max(1, inv_launches))
+    work["inverse_transform"] = (work["inverse_transform"][0], work["inverse_transform"][1], inv_launches)
     stage_report = {}
     for name, ms in stages:
         entry = {"ms": round(ms, 4)}
@@ -419,22 +432,22 @@ def main():
         stage_report[name] = entry
     dom = max((s for s in stages if s[0] in work), key=lambda s: s[1])
     bound, amount, launches = work[dom[0]]
-    per_launch_s = dom[1] * 1e-3 / launches
+    stage_s = dom[1] * 1e-3
     if bound == "hbm":
-        achieved, peak, unit = amount / launches / per_launch_s / 1e9, HBM_PEAK_GBS, "GB/s"
+        achieved, peak, unit = amount / stage_s / 1e9, HBM_PEAK_GBS, "GB/s"
     else:
-        achieved, peak, unit = amount / launches / per_launch_s / 1e12, MFMA_PEAK_TFLOPS, "TFLOP/s"
+        achieved, peak, unit = amount / stage_s / 1e12, MFMA_PEAK_TFLOPS, "TFLOP/s"
     traffic, traffic_commit = measured_traffic(wl.name, dom[0]) if args.transform == "dct" and args.t is None else (None, None)
     # what this machine sustains for a plain streaming copy and for a loop of the MFMA instruction the kernels use
     copy_bps, mfma_fps = ctx.measure_peaks()
     measured = copy_bps / 1e9 if bound == "hbm" else mfma_fps / 1e12
     roofline = {"bound": bound, "kernel": dom[0], "launches_per_step": launches,
-                "avg_launch_ms": round(per_launch_s * 1e3, 4), "achieved": round(achieved, 2), "peak": peak, "unit": unit,
+                "avg_launch_ms": round(stage_s * 1e3 / launches, 4) if launches else None, "achieved": round(achieved, 2), "peak": peak, "unit": unit,
                 "frac": round(achieved / peak, 4), "traffic": traffic, "traffic_measured_at_commit": traffic_commit,
                 "measured_peak": round(measured, 1), "frac_of_measured": round(achieved / measured, 4)}
-    if traffic and bound == "hbm":   # what the stage's kernels really move (counter bytes of the committed profile) per second
-        roofline["hbm_rate_at_measured_traffic"] = round(traffic / per_launch_s / 1e9, 1)
-        roofline["frac_at_measured_traffic"] = round(traffic / per_launch_s / 1e9 / peak, 4)
+    if traffic and launches and bound == "hbm":   # what the stage's kernels really move (counter bytes of the committed profile) per second
+        roofline["hbm_rate_at_measured_traffic"] = round(traffic * launches / stage_s / 1e9, 1)
+        roofline["frac_at_measured_traffic"] = round(traffic * launches / stage_s / 1e9 / peak, 4)
     if dom[0] in work_min:   # the same stage against the bytes the pruned scheme strictly needs
         ach_min = work_min[dom[0]] / (dom[1] * 1e-3) / 1e9
         roofline["achieved_pruned_minimum"] = round(ach_min, 2)
