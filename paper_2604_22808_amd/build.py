@@ -17,7 +17,7 @@ SOURCES = ["mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_wh_2.hip", "mfma_iwh.hip", "m
            "generic_attn.hip", "generic_axis.hip", "mfma_dct.hip"]
 
 
-# Kernels that wait for their own copies into LDS by count: a spilled register's reload would wait for all of them.
+# Kernels that keep rows requested steps ahead in registers: a spilled register's reload would wait behind all of them.
 NO_SCRATCH = ("mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_wh_2.hip")
 
 

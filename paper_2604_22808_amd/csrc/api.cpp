@@ -748,7 +748,10 @@ static DctPassArgs t_pass_args(const Ctx& c, const TransformClass& k, int d) {
 
 // Whether the T pass of a class joins the launch of the class that keeps the most (`lead`).  It has to be small (fewer than four tiles per wave
 // of a chip with two workgroups on every compute unit); and so has the lead on long axes, whose kernels pay for arguments that depend on
-// the workgroup (k_dct_passes) more than a small launch takes.
+// the workgroup (k_dct_passes) more than a small launch takes.  Forward transforms apart / together, us, low heads beside two high
+// ones: 16 x 64 x 64 x 64, 4 tiles per compute unit (2 heads) 100 / 93, 24 (12) 184 / 175; beyond the line 48 (24) 272 / 261, 256 (32 mid heads)
+// 346 / 341; 32 x 64 x 64 x 128, 128 (32) 1051 / 1023.  Beside one high head of 64^3 x 128, where the lead is large, 4 to 32 heads:
+// 451 / 447, 658 / 652, 1467 / 1456, 1870 / 1853 (mid heads: the same).  So the line is on the safe side; the gain beyond it is 1-4 %.
 static bool dct_passes_share(const DctPassArgs& lead, const DctPassArgs& a, int num_cu) {
   auto tiles = [](const DctPassArgs& x) { return x.nslab * (x.inner / 64); };
   if (a.n != lead.n || mfma_dct_tiles(a.n, a.n_out) != mfma_dct_tiles(lead.n, lead.n_out)) return false;
@@ -790,7 +793,11 @@ static hipError_t transform_by_axes(Ctx& c, const TransformClass& k, int i, hipS
 // one_pass says so, else W axis and H axis pass by pass; both leave [h][t] order behind so that the rows of the T pass are W*d
 // elements apart.  The T pass scatters into the band-major spectral buffers.
 // Classes share launches: a class of few slices leaves most of the chip idle by itself.  A class that fills it gets tiles of
-// its own size, in a launch of its own unless it is the one that keeps the most.
+// its own size, in a launch of its own unless it is the one that keeps the most.  W + H pass, two workgroups' worth per compute unit as
+// the line; forward transforms apart / together, us, beside two high heads: 16 x 64 x 64 x 64, 0.2 per unit (2 low heads) 100 / 74, 1 (8)
+// 151 / 131, 1.5 (12) 184 / 170; beyond the line 3 (24) 272 / 251, 4 (32) 329 / 308, 4 (32 mid heads) 346 / 338; 32 x 64 x 64 x 128, 16 (32)
+// 1051 / 1025, mid heads 1199 / 1196.  Beside one high head of 64^3 x 128, 32 low heads 1870 / 1851, but 12, 16 and 32 mid heads 978 / 981,
+// 1226 / 1233, 2216 / 2251: their own tiles are the better ones.
 // `d`: channels per token (the projected forward transforms X, [batch][N][d_model], as batch slices).
 static hipError_t transform_classes(Ctx& c, const TransformClass* cls, int ncls, hipStream_t st, int d) {
   const int T = c.shape.T, H = c.shape.H, W = c.shape.W;
@@ -934,7 +941,10 @@ static hipError_t inverse_transforms_mfma(Ctx& c, void* out, const void* v_in, h
       continue;
     }
     if (hw_fits(g[i])) {   // the same, boxes of any size
-      // (boxes that the launch below takes together; those that fill the chip run alone as well)
+      // Boxes that the launch below takes together: it is built for the widths that cut axes keep (a whole axis of another width runs
+      // alone).  Those that fill the chip run alone as well: 2 % and less beyond two workgroups' worth per compute unit (inverse
+      // transforms apart / together, us, mid heads beside two high ones: 16 x 64 x 64 x 64, 2 heads 48 / 35, 8 heads 81 / 78, 24 heads 158 / 154;
+      // beside one of 64^3 x 128, 4 heads 241 / 239, 32 heads 1237 / 1236).
       auto narrow = [&](int j) { return g[j].cols == 16 || g[j].cols == 32 || g[j].cols == 64; };
       WhPassArgs sub[3];
       int m = 0;
