@@ -27,7 +27,7 @@ int main() {   // lines "direction W d chosen refused"; launches of no slices: t
 def test_what_the_one_pass_transforms_are_chosen_for_they_take(tmp_path):
     (tmp_path / "t.cpp").write_text(PROGRAM)
     lib = Path(B.LIB_PATH).parent
-    subprocess.check_call([hipcc(), "-std=c++17", "--offload-arch=gfx950", f"-I{ROOT / 'include'}", f"-I{lib / 'csrc'}", str(tmp_path / "t.cpp"),
+    subprocess.check_call([hipcc(), "-std=c++17", "--offload-host-only", f"-I{ROOT / 'include'}", f"-I{lib / 'csrc'}", str(tmp_path / "t.cpp"),
                            "-o", str(tmp_path / "t"), f"-L{lib}", "-lfreqattn", f"-Wl,-rpath,{lib}"])
     lines = [line.split() for line in subprocess.check_output([str(tmp_path / "t")], text=True).splitlines()]
     took = {"f": {}, "i": {}}
