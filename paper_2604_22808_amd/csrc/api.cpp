@@ -294,7 +294,14 @@ static hipError_t device_setup(freqattn_ctx* c, hipStream_t st) {
   {
     const int dims[3] = {s.T, s.H, s.W};
     bool smaller = false;
-    for (int a = 0; a < 3; ++a) smaller = smaller || keep_rows(c->mid_box[a], dims[a]) < dims[a];
+    // (An axis that counts is cut to as many tiles of 32 as it has, or both lengths are powers of two.  Grids without one keep V~ whole,
+    // and its high band readable: the weights take half a second per million tokens to make.)
+    auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
+    for (int a = 0; a < 3; ++a) {
+      const int n = dims[a], r = keep_rows(c->mid_box[a], n);
+      const bool same = (r + 31) / 32 == (n + 31) / 32;
+      smaller = smaller || (r < n && (same || (pow2(n) && pow2(r))));
+    }
     // (FREQATTN_V_BOX = 0 / 1 switches it off / on whatever the size; by default grids below 64K tokens keep the
     // whole-grid V~: the extra launches cost more there than the smaller passes save)
     const char* env = getenv("FREQATTN_V_BOX");
@@ -679,13 +686,9 @@ static freqattn_status ensure_lists(freqattn_ctx* c, const int32_t* head_alloc, 
 }
 
 // ------------------------------------------------------------------------------------------------ transforms
-// Forward transform of one [slices, N, d] tensor into a band-major spectral buffer (sections 3.2, 3.3).
-// Coefficients kept per axis when only the box [0, box) of an axis is needed: rounded up to the kernel's granularity,
-// or the full axis when the rectangular pass is not available for that pair of sizes.
-static int keep_rows(int box, int n) {
-  const int r = std::min(n, (box + 15) / 16 * 16);
-  return (r < n && mfma_dct_supported(n, r) && mfma_dct_supported(r, n)) ? r : n;
-}
+// Coefficients kept per axis when only the box [0, box) of an axis is needed: rounded up to whole tiles of the passes.
+// (Boxes of axes that are no power of two used to take the whole axis: 24 slices of 32 x 48 x 80 x 128, 3349 -> 2627 us per forward.)
+static int keep_rows(int box, int n) { return std::min(n, (box + 15) / 16 * 16); }
 
 // The box kept for the low and mid bands per axis; false when that is the whole grid.
 static bool mid_keep(const Ctx& c, int keep[3]) {
@@ -716,7 +719,7 @@ static bool one_pass(const Ctx& c, bool box, int d) {
 // buffer spec.
 struct TransformSeg { const void* x; void* spec; const int32_t* slice_list; int ns; };
 
-// Up to three tensors (Q, K, V) that keep the same coefficients: keep[] per axis (T, H, W).  A head that only runs the low (low and
+// Up to three tensors (Q, K, V) that keep the same coefficients: keep[] per axis (T, H, W), any number up to the axis.  A head that only runs the low (low and
 // mid) band needs Q~ and K~ on that box only, and every pass after the first then moves a fraction of the tensor.
 // energy_slot >= 0 adds up the router's band statistics in the T pass, tot_slot >= 0 the inputs' sum of squares in the first
 // pass (of all tensors together: the router adds them anyway).

@@ -13,15 +13,12 @@ hipError_t launch_mfma_dct_scatter_en(const DctPassArgs* subs, int n, int num_cu
 hipError_t launch_mfma_dct_gather(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out);
 
 bool mfma_dct_supported(int n_in, int n_out) {
-  if (n_in % 16 || n_in < 16 || n_in > 128 || n_out < 1 || n_out > 128) return false;
-  const bool pow2 = n_in == 16 || n_in == 32 || n_in == 64 || n_in == 128;
-  if (pow2) return true;                      // any number of output tiles
-  return (n_out + 31) / 32 == (n_in + 31) / 32;  // other lengths: square passes only
+  return n_in % 16 == 0 && n_in >= 16 && n_in <= 128 && n_out >= 1 && n_out <= 128;
 }
 
 int mfma_dct_tiles(int n_in, int n_out) {
   const int mt = (n_out + 31) / 32;
-  return mt == 3 && (n_in == 16 || n_in == 32 || n_in == 64 || n_in == 128) ? 4 : mt;
+  return mt == 3 && n_in != 48 && n_in != 80 && n_in != 96 ? 4 : mt;   // (dispatch_mode: variants with three tiles exist for these)
 }
 
 hipError_t launch_mfma_dct_pass(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out) {

@@ -561,12 +561,18 @@ template <int MODE>
 static hipError_t dispatch_mode(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out) {
   const DctPassArgs& a = subs[0];
   const int mt = mfma_dct_tiles(a.n, a.n_out);
-#define FA_DCT_CASE(NI_, MT_) if (a.n == NI_ && mt == MT_) return launch_n<NI_, MT_, MODE>(subs, n, num_cu, st, waves_out);
+  // Which variants a mode can meet: the forward transform keeps at most as many rows as it reads, the inverse makes at least as many.
+#define FA_DCT_CASE(NI_, MT_)                                                                       \
+  if constexpr ((MODE == DCT_PLAIN || (MODE == DCT_GATHER ? 32 * MT_ >= NI_ : 32 * (MT_ - 1) < NI_)))  \
+    if (a.n == NI_ && mt == MT_) return launch_n<NI_, MT_, MODE>(subs, n, num_cu, st, waves_out);
   FA_DCT_CASE(16, 1) FA_DCT_CASE(16, 2) FA_DCT_CASE(16, 4)
   FA_DCT_CASE(32, 1) FA_DCT_CASE(32, 2) FA_DCT_CASE(32, 4)
+  FA_DCT_CASE(48, 1) FA_DCT_CASE(48, 2) FA_DCT_CASE(48, 3) FA_DCT_CASE(48, 4)
   FA_DCT_CASE(64, 1) FA_DCT_CASE(64, 2) FA_DCT_CASE(64, 4)
+  FA_DCT_CASE(80, 1) FA_DCT_CASE(80, 2) FA_DCT_CASE(80, 3) FA_DCT_CASE(80, 4)
+  FA_DCT_CASE(96, 1) FA_DCT_CASE(96, 2) FA_DCT_CASE(96, 3) FA_DCT_CASE(96, 4)
+  FA_DCT_CASE(112, 1) FA_DCT_CASE(112, 2) FA_DCT_CASE(112, 4)
   FA_DCT_CASE(128, 1) FA_DCT_CASE(128, 2) FA_DCT_CASE(128, 4)
-  FA_DCT_CASE(48, 2) FA_DCT_CASE(80, 3) FA_DCT_CASE(96, 3) FA_DCT_CASE(112, 4)
 #undef FA_DCT_CASE
   return hipErrorInvalidValue;
 }

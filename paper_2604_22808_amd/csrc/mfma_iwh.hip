@@ -2,7 +2,7 @@
 #include "mfma_iwh_impl.h"
 namespace fa {
 bool iwh_fits(const IwhPassArgs& a, int num_cu) {
-  if (a.H % 16 != 0 || a.H > 128 || (a.W != 16 && a.W != 32 && a.W != 64)) return false;   // (an axis of 48 is kept whole)
+  if (a.H % 16 != 0 || a.H > 128 || (a.W != 16 && a.W != 32 && a.W != 64)) return false;
   // A workgroup expands its rows one after the other: with fewer than two items of 16 rows per compute unit
   // the two passes are faster (6 slices of 16 x 64 x 64 x 64 from the 32 x 32 box: 42 us, one pass 66; 16K tokens 10 us, one
   // pass 18).  From larger boxes the pass that keeps the output in its accumulators (mfma_wh_impl.h) is faster: 5 slices of

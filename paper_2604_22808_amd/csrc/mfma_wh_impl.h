@@ -523,8 +523,8 @@ static hipError_t wh_dispatch(const WhPassArgs* subs, int n, int num_cu, hipStre
   wh_tiles(subs[0], &kt, &kh, nullptr);
   for (int i = 0; i < n; ++i)
     if (subs[i].cols != 16 * NW16 || (!INV && subs[i].out_rows > 16 * kh)) return hipErrorInvalidValue;
-  // A single W tile: the whole axis of 16, or (forward) the box of an axis that can be cut that far (a power of two).
-  if constexpr (INV ? NW16 == 1 : (NW16 & (NW16 - 1)) == 0) {
+  // A single W tile: the whole axis of 16, or (forward) the box of any axis.
+  if constexpr (!INV || NW16 == 1) {
     if (kt == 1 && kh == 1) return wh_launch<NW16, 1, 1, INV>(subs, n, num_cu, st, slots_out);
     if (kt == 1 && kh == 2) return wh_launch<NW16, 1, 2, INV>(subs, n, num_cu, st, slots_out);
   }

@@ -120,6 +120,44 @@ def test_outputs_of_one_pass_inverse(grid, d, n):
         assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (h, mx, rl)
 
 
+# boxes of axes that are no powers of two, on every axis: one to three tiles of 32 rows kept of two, three and four, and back; edges at
+# other fractions keep 48, 80 and 96 rows, also with more than 64 rows along H (an axis at a time)
+@pytest.mark.parametrize("grid,low,mid", [((48, 48, 80), (1, 4), (1, 2)), ((80, 16, 48), (1, 4), (1, 2)), ((96, 96, 16), (1, 4), (1, 2)),
+                                          ((112, 16, 112), (1, 4), (1, 2)), ((112, 16, 48), (1, 8), (3, 8)), ((96, 16, 80), (1, 6), (5, 6)),
+                                          ((128, 16, 96), (1, 8), (5, 8)), ((128, 48, 16), (1, 2), (3, 4)), ((16, 112, 96), (1, 4), (5, 7)),
+                                          ((16, 128, 80), (1, 8), (3, 4)), ((16, 80, 112), (1, 8), (3, 5))])
+def test_boxes_of_axes_of_any_length(grid, low, mid):
+    import torch
+    from scipy.fft import dctn, idctn
+    gen = torch.Generator(device="cuda").manual_seed(37)
+    N, d, alloc = int(np.prod(grid)), 64, (1, 2, 4)
+    q, k, v = ((0.5 * torch.randn((1, 3, N, d), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(3))
+    band = dict(WL.WORKLOADS["16k"].band, n_summary=0, high_window=16, low_num=low[0], low_den=low[1], mid_num=mid[0], mid_den=mid[1])
+    ctx = B.Context(1, 3, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    out = torch.empty_like(q)
+    ctx.forward(q, k, v, alloc, out)
+    index, worst = O.band_partition(*grid, U.oracle_cfg(band)), 0.0
+    for h, l in enumerate((0, 1, 2)):   # the coefficients each head attends with
+        for which, x in enumerate((q, k, v)):
+            if len(index[l]):
+                want = dctn(U.to_host64(x[0, h]).reshape(grid + (d,)), type=2, norm="ortho", axes=(0, 1, 2)).reshape(N, d)
+                worst = max(worst, U.errors(ctx.read_spectral(which, h, l), want[index[l]])[1])
+    assert worst <= 2e-3, worst
+    for h, l in enumerate((0, 1)):      # the inverse alone, from the band outputs as the library left them
+        spec = np.zeros((N, d))
+        if len(index[l]):
+            spec[index[l]] = ctx.read_spectral(3, h, l) - ctx.read_spectral(2, h, l)
+        want = idctn(spec.reshape(grid + (d,)), type=2, norm="ortho", axes=(0, 1, 2)).reshape(N, d) + U.to_host64(v[0, h])
+        mx, rl = U.errors(U.to_host64(out[0, h]), want)
+        assert mx <= U.TOL["bf16"][0] and rl <= U.TOL["bf16"][1], (h, mx, rl)
+
+
+# the same bits from the low box, the low+mid box and the whole grid, and after any guess, where axes of 48 to 112 are cut
+@pytest.mark.parametrize("grid", [(48, 48, 80), (32, 96, 48), (16, 112, 112)])
+def test_outputs_do_not_depend_on_the_box_of_axes_of_any_length(grid, monkeypatch):
+    test_outputs_do_not_depend_on_the_box(grid, 1.0, "1", monkeypatch)
+
+
 # classes of slices that keep different boxes and are small enough to share launches: boxes one, two and four tiles of 16 wide, one to
 # four tiles of rows, T axes that can be cut (the gather passes then stay apart) and not, a class that is missing
 @pytest.mark.parametrize("grid,d,alloc", [((16, 32, 32), 64, (1, 2, 4)), ((16, 64, 64), 128, (1, 2, 4, 6, 0)), ((32, 16, 64), 64, (1, 1, 4)),
