@@ -686,7 +686,8 @@ static freqattn_status ensure_lists(freqattn_ctx* c, const int32_t* head_alloc, 
 }
 
 // ------------------------------------------------------------------------------------------------ transforms
-// Coefficients kept per axis when only the box [0, box) of an axis is needed: rounded up to whole tiles of the passes.
+// Coefficients of an axis that the inverse transform reads when only the box [0, box) of it is active, and that the forward passes
+// compute tiles for: whole tiles of 16.  (What the forward passes store is the box itself: see transforms_phase.)
 // (Boxes of axes that are no power of two used to take the whole axis: 24 slices of 32 x 48 x 80 x 128, 3349 -> 2627 us per forward.)
 static int keep_rows(int box, int n) { return std::min(n, (box + 15) / 16 * 16); }
 
@@ -1134,12 +1135,12 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
       const int32_t *lo = L + c->off_nonhigh, *hi = L + c->off_cls[2];
       const int nl = c->n_nonhigh, nh = c->n_cls[2];
       const TransformClass cls[2] = {
-        {{{q, c->specQ, lo, nl}, {k, c->specK, lo, nl}, vbox ? TransformSeg{v, c->specV, lo, nl} : TransformSeg{}}, mid, 0, 0},
+        {{{q, c->specQ, lo, nl}, {k, c->specK, lo, nl}, vbox ? TransformSeg{v, c->specV, lo, nl} : TransformSeg{}}, c->mid_box, 0, 0},
         {{{q, c->specQ, hi, nh}, {k, c->specK, hi, nh}, vbox ? TransformSeg{v, c->specV, hi, nh} : TransformSeg{v, c->specV, nullptr, c->slices}}, full, 3, -1}};
       HIP_TRY(c, forward_transforms_mfma(*c, cls, 2, st));
     } else {
       const TransformSeg aq{q, c->specQ, nullptr, c->slices}, ak{k, c->specK, nullptr, c->slices}, av{v, c->specV, nullptr, c->slices};
-      const TransformClass whole{{aq, ak, av}, full, 0, -1}, box{{aq, ak, vbox ? av : TransformSeg{}}, mid, 0, 0}, v_whole{{av, {}, {}}, full, 5, -1};
+      const TransformClass whole{{aq, ak, av}, full, 0, -1}, box{{aq, ak, vbox ? av : TransformSeg{}}, c->mid_box, 0, 0}, v_whole{{av, {}, {}}, full, 5, -1};
       if (!pruned) {
         HIP_TRY(c, forward_transforms_mfma(*c, &whole, 1, st));
       } else {
@@ -1156,8 +1157,6 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
   if (c->path == FREQATTN_PATH_MFMA && !with_stats) {
     // allocation known: Q~ and K~ are only needed on the bands a slice runs (none at all for an idle slice)
     const int full[3] = {c->shape.T, c->shape.H, c->shape.W};
-    int low[3], mid[3];
-    for (int a = 0; a < 3; ++a) { low[a] = keep_rows(c->low_box[a], full[a]); mid[a] = keep_rows(c->mid_box[a], full[a]); }
     const int32_t* L = c->d_lists;
     const int32_t *l0 = L + c->off_cls[0], *l1 = L + c->off_cls[1], *l2 = L + c->off_cls[2];
     const int n0 = c->n_cls[0], n1 = c->n_cls[1], n2 = c->n_cls[2];
@@ -1167,9 +1166,12 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
     c->v_full.assign((size_t)c->slices, vbox ? 0 : 1);
     if (vbox)
       for (int i = 0; i < n2; ++i) c->v_full[(size_t)(c->h_lists + c->off_cls[2])[i]] = 1;
+    // The boxes as they are, not whole tiles of 16: what lies beyond is read by nobody (the inverse only looks at active bands
+    // there), and the T pass then has fewer tiles.  24 slices of 32 x 48 x 80 x 128 2627 -> 2554 us per forward, 24 of 16 x 64 x 64 x 64
+    // (routed) 612 -> 605, 8 of 16 x 32 x 32 x 64 106 -> 105.
     const TransformClass cls[3] = {
-      {{{q, c->specQ, l0, n0}, {k, c->specK, l0, n0}, {}}, low, -1, -1},
-      {{{q, c->specQ, l1, n1}, {k, c->specK, l1, n1}, {v, c->specV, L + c->off_nonhigh, vbox ? c->n_nonhigh : 0}}, mid, -1, -1},
+      {{{q, c->specQ, l0, n0}, {k, c->specK, l0, n0}, {}}, c->low_box, -1, -1},
+      {{{q, c->specQ, l1, n1}, {k, c->specK, l1, n1}, {v, c->specV, L + c->off_nonhigh, vbox ? c->n_nonhigh : 0}}, c->mid_box, -1, -1},
       {{{q, c->specQ, l2, n2}, {k, c->specK, l2, n2}, vbox ? TransformSeg{v, c->specV, l2, n2} : TransformSeg{v, c->specV, nullptr, c->slices}}, full, -1, -1}};
     HIP_TRY(c, forward_transforms_mfma(*c, cls, 3, st));
     return FREQATTN_OK;
@@ -1190,8 +1192,6 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
 static freqattn_status settle_forms(freqattn_ctx* c, const void* q, const void* k, const void* v, hipStream_t st) {
   if (c->path != FREQATTN_PATH_MFMA) return FREQATTN_OK;
   const int full[3] = {c->shape.T, c->shape.H, c->shape.W};
-  int mid[3];
-  (void)mid_keep(*c, mid);
   int32_t* fix = c->h_lists + c->off_fix;   // slices to complete, then slices to take from the box
   const int32_t* high = c->h_lists + c->off_cls[2];
   const int32_t* nonhigh = c->h_lists + c->off_nonhigh;
@@ -1211,7 +1211,7 @@ static freqattn_status settle_forms(freqattn_ctx* c, const void* q, const void* 
   HIP_TRY(c, hipMemcpyAsync(c->d_lists + c->off_fix, fix, (size_t)(n_full + n_box) * sizeof(int32_t), hipMemcpyHostToDevice, st));
   const int32_t *lf = c->d_lists + c->off_fix, *lb = lf + n_full;
   const TransformClass cls[2] = {
-    {{{q, c->specQ, lb, n_box}, {k, c->specK, lb, n_box}, {v, c->specV, lb, c->v_box_ok ? n_box : 0}}, mid, -1, -1},
+    {{{q, c->specQ, lb, n_box}, {k, c->specK, lb, n_box}, {v, c->specV, lb, c->v_box_ok ? n_box : 0}}, c->mid_box, -1, -1},
     {{{q, c->specQ, lf, n_full}, {k, c->specK, lf, n_full}, {v, c->specV, lf, v_too ? n_full : 0}}, full, -1, -1}};
   HIP_TRY(c, forward_transforms_mfma(*c, cls, 2, st));
   return FREQATTN_OK;

@@ -334,8 +334,8 @@ struct WhPassArgs {
   // inverse: in (compact) fp16 [segment's slices][rows][T][cols][d], out (caller's) bf16 [slices][T][out_rows][out_cols][d]
   const void* in[3]; void* out[3];
   const int32_t* slice_list[3]; int seg_end[3];
-  int T, d, rows, cols, out_rows, out_cols;         // d: channels per token (a multiple of 64); the rest multiples of 16
-  const half_t* Mh; const half_t* Mw; int ldh, ldw; // fp16 [out_rows][>= rows], [out_cols][>= cols] with their row strides
+  int T, d, rows, cols, out_rows, out_cols;         // d: channels per token (a multiple of 64); rows and cols multiples of 16, inverse: all four
+  const half_t* Mh; const half_t* Mw; int ldh, ldw; // fp16 [out_rows][>= rows], [out_cols, to whole tiles of 16][>= cols] with their row strides
   const void* resid;                                // inverse: bf16, addressed like out, added, or NULL
   float* tot_part;                                  // forward: [slot][64]: sum of squares of the inputs per channel, or NULL
   int32_t* range_flag;                              // forward: set when an input value leaves the fp16 range

@@ -370,13 +370,13 @@ __device__ __forceinline__ void wh_pass(const WhPassArgs& a, const int block, co
             rs[i & 1][p] = *(const uint4v __attribute__((address_space(1)))*)(at + lane_out);
           }
       };
-      if (col0 < a.out_cols) {   // (of whole tiles)
+      if (col0 < a.out_cols) {
         if (INV && add) request_v(0);
 #pragma unroll
         for (int i = 0; i < 2 * KT * KH; ++i) {
           const int k = i / KH, n = i % KH;
           if (INV && add && i + 1 < 2 * KT * KH) request_v(i + 1);
-          if (row0 + 16 * n >= a.out_rows) continue;
+          if (row0 + 16 * n >= a.out_rows || (!INV && col0 + k >= a.out_cols)) continue;
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
             if (INV && !add) {
@@ -411,7 +411,7 @@ __device__ __forceinline__ void wh_pass(const WhPassArgs& a, const int block, co
             typedef char __attribute__((address_space(1))) * ptr;
             ptr at = (ptr)(first + (16 * n + 8 * p) * out_stride + k * a.d);
             asm("" : "+s"(at));
-            *(uint4v __attribute__((address_space(1)))*)(at + lane_out) = v;
+            if (INV || row0 + 16 * n + 8 * p + (ln >> 3) < a.out_rows) *(uint4v __attribute__((address_space(1)))*)(at + lane_out) = v;
           }
           __builtin_amdgcn_wave_barrier();
         }
@@ -461,9 +461,10 @@ static hipError_t wh_size(const WhPassArgs* subs, int n, int num_cu, int per_sim
     if (i >= n) continue;
     WhPassArgs& a = m->sub[i];
     a = subs[i];
-    a.col_parts = (a.out_cols / 16 + KT - 1) / KT;
-    a.members = a.col_parts * ((a.out_rows / 16 + KH - 1) / KH);
-    if (!INV && a.members != a.col_parts) return hipErrorInvalidValue;
+    if (a.rows % 16 || a.cols % 16 || (INV && (a.out_rows % 16 || a.out_cols % 16))) return hipErrorInvalidValue;
+    a.col_parts = ((a.out_cols + 15) / 16 + KT - 1) / KT;
+    a.members = a.col_parts * (((a.out_rows + 15) / 16 + KH - 1) / KH);
+    if (!INV && (a.members != a.col_parts || a.out_rows > a.rows || a.out_cols > a.cols)) return hipErrorInvalidValue;
     // a workgroup's sums of squares are of one chunk of channels only if the planes of an XCD are
     if (a.tot_part && 8 % (a.d / 64) != 0) return hipErrorInvalidValue;
     // a lane reaches 8 rows of the output; and 16 positions of the input, which is less (wh_fits and hw_fits ask for the same)
@@ -509,11 +510,11 @@ static hipError_t hw_mixed_launch(const WhPassArgs* subs, int n, int num_cu, hip
 // Tiles of output rows and columns (16 each) of a workgroup: as many as the accumulators take, the rows first; rows beyond four
 // tiles are cut into equal parts (the inverse only: the forward pass keeps at most 64 rows).
 static inline void wh_tiles(const WhPassArgs& a, int* kt, int* kh, int* members) {
-  const int tiles = a.out_rows / 16, parts = (tiles + 3) / 4, h = (tiles + parts - 1) / parts;
+  const int tiles = (a.out_rows + 15) / 16, parts = (tiles + 3) / 4, h = (tiles + parts - 1) / parts;
   const int t = h <= 2 && a.out_cols > 16 ? 2 : 1;
   if (kt) *kt = t;
   if (kh) *kh = h;
-  if (members) *members = (a.out_cols / 16 + t - 1) / t * ((tiles + h - 1) / h);
+  if (members) *members = ((a.out_cols + 15) / 16 + t - 1) / t * ((tiles + h - 1) / h);
 }
 
 // The passes have input rows of the same width; the tiles are those of the first pass.
