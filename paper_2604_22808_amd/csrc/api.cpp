@@ -259,6 +259,7 @@ static hipError_t device_setup(freqattn_ctx* c, hipStream_t st) {
       }
     }
   }
+  if (!mf) A(allow_generic_axis_pair());
   // ---- scratch
   const size_t es = esize(*c);
   const size_t slab = (size_t)c->slices * (size_t)c->N * (size_t)c->d * es;
@@ -995,9 +996,18 @@ static AxisPassArgs generic_pass(const Ctx& c, int ax, bool inverse) {
   return a;
 }
 
+static AxisPairArgs generic_pair(const Ctx& c, bool inverse) {
+  AxisPairArgs a{};
+  a.T = c.shape.T; a.H = c.shape.H; a.slices = c.slices; a.d = c.d; a.inner = (int64_t)c.shape.W * c.d;
+  a.ldt = (a.T + 15) / 16 * 16; a.ldh = (a.H + 15) / 16 * 16;
+  a.Mt = inverse ? c.d_Ft32[0] : c.d_F32[0];
+  a.Mh = inverse ? c.d_Ft32[1] : c.d_F32[1];
+  return a;
+}
+
 // Generic path: Q, K and V [slices, N, d] into the band-major spectral buffers (sections 3.2, 3.3), T axis, H axis, then
-// the W axis, which scatters.  The three tensors share every launch: the T pass leaves its results in the spectral
-// buffers themselves, the H pass in the scratch that is free until the inverse transform (tmp0, tmp1, Y).
+// the W axis, which scatters, T and H in one pass where that fits.  The three tensors share every launch: the T pass leaves its
+// results in the spectral buffers themselves, the H pass in the scratch that is free until the inverse transform (tmp0, tmp1, Y).
 static hipError_t forward_transform_generic(Ctx& c, const void* q, const void* k, const void* v, hipStream_t st) {
   const void* in[3] = {q, k, v};
   void* spec[3] = {c.specQ, c.specK, c.specV};
@@ -1012,6 +1022,20 @@ static hipError_t forward_transform_generic(Ctx& c, const void* q, const void* k
   t.in_bf16 = c.shape.dtype == FREQATTN_BF16;
   w.perm_out = c.d_perm;
   hipError_t e;
+  AxisPairArgs th = generic_pair(c, false);
+  if (generic_pair_fits(th)) {
+    th.in_bf16 = t.in_bf16;
+    for (int first = 0; first < 3; first += th.n_tensors) {
+      th.n_tensors = w.n_tensors = !c.keep_outputs ? 3 : first == 0 ? 2 : 1;   // (two tensors, then one where the third's scratch is taken)
+      for (int i = 0; i < th.n_tensors; ++i) {
+        th.in[i] = in[first + i]; th.out[i] = mid[i];
+        w.in[i] = mid[i]; w.out[i] = spec[first + i];
+      }
+      if ((e = launch_generic_axis_pair(th, st)) != hipSuccess) return e;
+      if ((e = launch_generic_axis_pass(w, st)) != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   if ((e = launch_generic_axis_pass(t, st)) != hipSuccess) return e;
   if (c.keep_outputs) {   // the third tensor's scratch is taken: two tensors, then one
     h.n_tensors = w.n_tensors = 2;
@@ -1053,6 +1077,9 @@ static hipError_t inverse_transform(Ctx& c, void* out, const void* v_in, hipStre
   h.in[0] = c.tmp0; h.out[0] = c.tmp1;
   t.in[0] = c.tmp1; t.out[0] = out; t.out_bf16 = c.shape.dtype == FREQATTN_BF16;
   if ((e = launch_generic_axis_pass(w, st)) != hipSuccess) return e;
+  AxisPairArgs th = generic_pair(c, true);
+  th.n_tensors = 1; th.in[0] = c.tmp0; th.out[0] = out; th.out_bf16 = t.out_bf16;
+  if (generic_pair_fits(th)) return launch_generic_axis_pair(th, st);
   if ((e = launch_generic_axis_pass(h, st)) != hipSuccess) return e;
   return launch_generic_axis_pass(t, st);
 }

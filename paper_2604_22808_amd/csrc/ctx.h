@@ -199,6 +199,16 @@ struct AxisPassArgs {      // (generic_axis.hip)
   int in_bf16, out_bf16;    // element type: bf16 when set, else fp32
 };
 hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st);
+// T and H axes of [slices][T][H][inner] tensors in one pass, in the forward or (with the transposed matrices) the inverse direction.
+struct AxisPairArgs {
+  const void* in[3]; void* out[3]; int n_tensors;
+  const float* Mt; const float* Mh; int ldt, ldh;   // as in AxisPassArgs
+  int T, H, slices; int64_t inner; int d;
+  int in_bf16, out_bf16;
+};
+bool generic_pair_fits(const AxisPairArgs& a);   // whether the pass takes these sizes and is the faster way
+hipError_t allow_generic_axis_pair();            // lets its kernels ask for their LDS (when a context is set up: its calls may be captured)
+hipError_t launch_generic_axis_pair(const AxisPairArgs& a, hipStream_t st);
 
 // One branch of a generic attention launch (generic_attn.hip): query rows [0, nq) of every listed slice.
 struct GAttnSeg {

@@ -174,15 +174,164 @@ hipError_t launch_kt(const AxisPassArgs& a, int64_t ncols, bool vec, hipStream_t
   return launch_io<KT, 0, 0>(a, ncols, vec, st);
 }
 
+// T and H axes in one pass:  out[s, kt, kh, i] = sum_h Mh[kh][h] sum_t Mt[kt][t] in[s, t, h, i],  the tensor between the axes in LDS.
+// A workgroup of 8 waves owns 64 columns i of one slice, all T H rows of them: a wave takes the T axis of one row h after the other
+// from memory (lane (n, g) holds columns 4 n .. 4 n + 3 of its rows), leaves the results in LDS as [kt][h][64], and takes
+// the H axis of (kt, 16 output rows) one after the other from there.  Product r of R = ceil(n / 4) takes rows j = g R + r, so an axis of n
+// takes R products and not whole steps of 16.  (Against 64 bits both orders come out the same: mean over
+// eight inputs of 256 tokens 1.42e-7 in two passes, 1.43e-7 here, of 504 x 64 1.72e-7 and 1.71e-7, of 2,592 x 64 1.878e-7 and 1.879e-7.)
+//
+// What bounds it: memory, read once and written once for two axes, and at the sizes it is used at the chain load - products - LDS -
+// products - store of a workgroup.  Two passes / this, Q, K and V: 12,150 tokens (9 x 30 x 45) x 4 heads x 64 in fp32 42 / 25 us, 6,160
+// (7 x 22 x 40) x 6 x 128 from bf16 62 / 34 us; 256 tokens x 2 x 32 8.5 / 5 us; the inverse 18 / 12, 27 / 14 and 8.5 / 4.5 us.
+template <int IN, int OUT, bool VEC>
+__global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float th_smem[];
+  constexpr int NWAVE = 8, IE = IN ? 2 : 4, OE = OUT ? 2 : 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int T = a.T, H = a.H, mstr = a.ldh + 4, rt = (T + 3) / 4, rh = (H + 3) / 4;
+  float* Y = th_smem;                       // [T][H][64]
+  float* Mh = th_smem + T * H * 64;         // [ldh][mstr]
+  const int tensor = blockIdx.z, slice = blockIdx.y;
+  const int64_t col = (int64_t)blockIdx.x * 64 + 4 * n;
+  const int nlive = (int)(a.inner - col < 4 ? a.inner - col : 4);   // columns of this lane's four that exist (VEC: all or none)
+  const int64_t base = (int64_t)slice * T * H * a.inner + col;
+  const char* in = (const char*)a.in[tensor] + base * IE;
+  char* out = (char*)a.out[tensor] + base * OE;
+  const int64_t t_stride = (int64_t)H * a.inner;
+
+  auto load = [&](int h, float4v (&x)[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      x[r] = float4v{0.f, 0.f, 0.f, 0.f};
+      const int t = g * rt + r;
+      if (r >= rt || t >= T || nlive <= 0) continue;
+      const char* src = in + (t * t_stride + (int64_t)h * a.inner) * IE;
+      if (!VEC) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (c < nlive) x[r][c] = IN ? __uint_as_float((uint32_t)*(const uint16_t*)(src + c * IE) << 16) : *(const float*)(src + c * IE);
+      } else if (IN) {
+        const uint2 u = *(const uint2*)src;
+        x[r][0] = __uint_as_float(u.x << 16); x[r][1] = __uint_as_float(u.x & 0xffff0000u);
+        x[r][2] = __uint_as_float(u.y << 16); x[r][3] = __uint_as_float(u.y & 0xffff0000u);
+      } else {
+        x[r] = *(const float4v*)src;
+      }
+    }
+  };
+  float4v x[2][4];
+  if (wave < H) load(wave, x[0]);
+  if (wave + NWAVE < H) load(wave + NWAVE, x[1]);
+  float At[4];   // operand of the T matrix (padded with zeros to 16 x 16)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) At[r] = r < rt ? a.Mt[n * a.ldt + g * rt + r] : 0.f;
+  for (int e = tid; e < a.ldh * (a.ldh / 4); e += 512) {
+    const int row = e / (a.ldh / 4), c4 = e % (a.ldh / 4) * 4;
+    *(float4v*)(Mh + row * mstr + c4) = *(const float4v*)(a.Mh + row * a.ldh + c4);
+  }
+  for (int h = wave; h < H; h += 2 * NWAVE)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int hb = h + b * NWAVE;
+      if (hb >= H) break;   // (uniform)
+      float4v acc[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (r < rt)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[r], x[b][r][c], acc[c], 0, 0, 0);
+      if (hb + 2 * NWAVE < H) load(hb + 2 * NWAVE, x[b]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)   // result row 4 g + r
+        if (4 * g + r < T) *(float4v*)(Y + ((4 * g + r) * H + hb) * 64 + 4 * n) = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+    }
+  __syncthreads();
+  const int tiles = (H + 15) / 16;
+  for (int u = wave; u < T * tiles; u += NWAVE) {
+    const int kt = u / tiles, tile = u - kt * tiles;
+    float4v acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = float4v{0.f, 0.f, 0.f, 0.f};
+    const float* y = Y + (kt * H + g * rh) * 64 + 4 * n;
+    const float* m = Mh + (16 * tile + n) * mstr + g * rh;
+#pragma unroll 4
+    for (int r = 0; r < rh; ++r) {
+      // (rows past the axis: the matrix is zero there, and what lies behind is a row of the next kt or of the matrix, finite either way)
+      const float A = m[r];
+      const float4v b = *(const float4v*)(y + r * 64);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(A, b[c], acc[c], 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int kh = 16 * tile + 4 * g + r;
+      if (kh >= H || nlive <= 0) continue;
+      char* dst = out + (kt * t_stride + (int64_t)kh * a.inner) * OE;
+      if (!VEC) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (c < nlive) {
+            if (OUT) *(uint16_t*)(dst + c * OE) = (uint16_t)gx_bf16(acc[c][r]);
+            else *(float*)(dst + c * OE) = acc[c][r];
+          }
+      } else if (OUT) {
+        uint2 w;
+        w.x = gx_bf16(acc[0][r]) | (gx_bf16(acc[1][r]) << 16);
+        w.y = gx_bf16(acc[2][r]) | (gx_bf16(acc[3][r]) << 16);
+        *(uint2*)dst = w;
+      } else {
+        *(float4v*)dst = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+      }
+    }
+  }
+}
+
+// Four columns are adjacent, aligned and of one row.
+bool gx_aligned(int d, const void* const* in, void* const* out, int n, bool in_bf16, bool out_bf16) {
+  bool vec = d % 4 == 0;
+  for (int i = 0; i < n; ++i)   // (a caller's tensor may be a view that starts anywhere)
+    vec = vec && (uintptr_t)in[i] % (in_bf16 ? 8 : 16) == 0 && (uintptr_t)out[i] % (out_bf16 ? 8 : 16) == 0;
+  return vec;
+}
+
+typedef void (*ThKernel)(AxisPairArgs);
+// [in bf16, out bf16, neither][VEC]
+const ThKernel th_kernel[3][2] = {{k_gaxis_th<1, 0, false>, k_gaxis_th<1, 0, true>},
+                                  {k_gaxis_th<0, 1, false>, k_gaxis_th<0, 1, true>},
+                                  {k_gaxis_th<0, 0, false>, k_gaxis_th<0, 0, true>}};
+
 }  // namespace
+
+// By sizes alone: the two forms sum in another order, and the bits must not depend on where a tensor starts.  The tensor between the
+// axes takes 256 bytes of LDS for each of the T H rows, at most 440 here; with more than 300 a compute unit holds one workgroup and the pass is
+// still the faster way (whole forwards, two passes / this: 8,184 tokens of 11 x 31 x 24 x 4 heads x 32 70.5 / 64.3 us).
+bool generic_pair_fits(const AxisPairArgs& a) {
+  return a.T <= 16 && a.H <= 64 && a.slices <= 65535 && a.inner <= (int64_t)64 * 0x7fffffff && (a.T * a.H * 64 + a.ldh * (a.ldh + 4)) * 4 <= 112 * 1024;
+}
+hipError_t allow_generic_axis_pair() {
+  static OncePerDevice limit[3][2];
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < 6 && e == hipSuccess; ++i) e = allow_lds(limit[i / 2][i % 2], (const void*)th_kernel[i / 2][i % 2], 160 * 1024);
+  return e;
+}
+hipError_t launch_generic_axis_pair(const AxisPairArgs& a, hipStream_t st) {
+  if (a.slices == 0 || a.n_tensors == 0) return hipSuccess;
+  if (!generic_pair_fits(a) || a.ldt < 16 || a.ldh < a.H || a.ldh % 16 != 0 || (a.in_bf16 && a.out_bf16)) return hipErrorInvalidValue;
+  const int lds = (a.T * a.H * 64 + a.ldh * (a.ldh + 4)) * 4;
+  const ThKernel k = th_kernel[a.in_bf16 ? 0 : a.out_bf16 ? 1 : 2][gx_aligned(a.d, a.in, a.out, a.n_tensors, a.in_bf16, a.out_bf16)];
+  hipLaunchKernelGGL(k, dim3((unsigned)((a.inner + 63) / 64), (unsigned)a.slices, (unsigned)a.n_tensors), dim3(512), (size_t)lds, st, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st) {
   const int64_t ncols = a.nslab * a.inner;
   if (ncols == 0 || a.n_tensors == 0) return hipSuccess;
   if (a.ldm < a.n || a.ldm % 16 != 0 || (a.perm_in && a.perm_out)) return hipErrorInvalidValue;
-  bool vec = a.d % 4 == 0;
-  for (int i = 0; i < a.n_tensors; ++i)   // (a caller's tensor may be a view that starts anywhere)
-    vec = vec && (uintptr_t)a.in[i] % (a.in_bf16 ? 8 : 16) == 0 && (uintptr_t)a.out[i] % (a.out_bf16 ? 8 : 16) == 0;
+  const bool vec = gx_aligned(a.d, a.in, a.out, a.n_tensors, a.in_bf16, a.out_bf16);
   switch ((std::min(a.n_out, 64) + 15) / 16) {
     case 1: return launch_kt<1>(a, ncols, vec, st);
     case 2: return launch_kt<2>(a, ncols, vec, st);

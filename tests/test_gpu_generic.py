@@ -84,6 +84,30 @@ def test_generic_axis_lengths(grid, d, dtype):
     _check(grid, d, 3, (0, 5, 7), dtype, n_summary=3)
 
 
+# T and H axes in one pass: T of one step of four rows with and without a remainder up to four, H of one to four tiles, the most rows that
+# fit a workgroup and one too many; rows of whole 64-column groups, less than one, a remainder of no multiple of four
+@pytest.mark.parametrize("grid,d,dtype", [((1, 2, 3), 64, "f32"), ((4, 16, 5), 32, "bf16"), ((5, 17, 3), 33, "f32"), ((16, 26, 2), 20, "bf16"),
+                                          ((6, 64, 3), 12, "f32"), ((12, 34, 3), 36, "f32"), ((13, 34, 3), 36, "f32"), ((3, 49, 4), 6, "bf16")])
+def test_generic_axes_in_pairs(grid, d, dtype):
+    """Outputs against the oracle, and the same bits wherever the tensors start."""
+    import torch
+    rng = np.random.default_rng(9)
+    N, alloc, tdt = int(np.prod(grid)), (1, 6, 4), torch.float32 if dtype == "f32" else torch.bfloat16
+    cfgd = dict(WL.WORKLOADS["tiny_f32"].band, n_summary=3)
+    ctx = B.Context(1, 3, d, grid, B.F32 if dtype == "f32" else B.BF16, B.make_cfg(**cfgd), path=B.PATH_GENERIC)
+    host = [WL.round_to_io(0.7 * rng.standard_normal((1, 3, N, d)), dtype) for _ in range(3)]
+    outs = []
+    for skip in (0, 1):
+        q, k, v, out = (torch.zeros(x.size + 8, dtype=tdt, device="cuda")[skip:skip + x.size].view(x.shape).copy_(torch.from_numpy(x))
+                        for x in host + [np.zeros_like(host[0])])
+        ctx.forward(q, k, v, alloc, out)
+        outs.append(U.to_host64(out))
+    assert np.array_equal(outs[0], outs[1])
+    mx, rl = U.errors(outs[0], O.forward(*host, grid, O.BandConfig(**cfgd), alloc))
+    print(f"generic pairs {grid} d={d} {dtype}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= U.TOL[dtype][0] and rl <= U.TOL[dtype][1], (mx, rl)
+
+
 @pytest.mark.parametrize("bands", [3, 4])
 def test_generic_branches_in_launches_of_their_own(bands):
     """One launch per branch: the stages are the branches' own and the outputs the same bits as from one launch."""
