@@ -227,9 +227,11 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   float At[4];   // operand of the T matrix (padded with zeros to 16 x 16)
 #pragma unroll
   for (int r = 0; r < 4; ++r) At[r] = r < rt ? a.Mt[n * a.ldt + g * rt + r] : 0.f;
-  for (int e = tid; e < a.ldh * (a.ldh / 4); e += 512) {
-    const int row = e / (a.ldh / 4), c4 = e % (a.ldh / 4) * 4;
-    *(float4v*)(Mh + row * mstr + c4) = *(const float4v*)(a.Mh + row * a.ldh + c4);
+  for (int e = tid; e < a.ldh * (mstr / 4); e += 512) {   // (the padding too: the last rows' products below reach into it)
+    const int row = e / (mstr / 4), c4 = e % (mstr / 4) * 4;
+    float4v m = {0.f, 0.f, 0.f, 0.f};
+    if (c4 < a.ldh) m = *(const float4v*)(a.Mh + row * a.ldh + c4);
+    *(float4v*)(Mh + row * mstr + c4) = m;
   }
   for (int h = wave; h < H; h += 2 * NWAVE)
 #pragma unroll
