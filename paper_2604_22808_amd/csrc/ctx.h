@@ -183,6 +183,8 @@ void build_summary_weights(const Ctx& c, int band, std::vector<float>& out);   /
 void pack_vsum_weights(const std::vector<float>& w, int m, int64_t N, std::vector<uint16_t>& out);  // bf16 [N/64][64][64], see mfma_vsum.hip
 
 // ---- generic fp32 kernels (generic_kernels.hip) -----------------------------------------------------------------
+// The box of coefficients a slice's bands live in, by its band mask (T, H, W): the first n tensors of a launch (Q and K) are only made there.
+struct AxisBoxes { const int32_t* masks; int n; int low[3], mid[3], full[3]; };
 struct AxisPassArgs {      // (generic_axis.hip)
   const void* in[3]; void* out[3]; int n_tensors;   // Q, K, V go through one launch
   const float* M;           // [ldm][ldm], zero outside [n_out][n]: out[k] = sum_j M[k][j] in[j]
@@ -197,6 +199,7 @@ struct AxisPassArgs {      // (generic_axis.hip)
   // `in` when bit l of masks[hb] is set, else from `in_alt`.
   const void* in_alt; const int32_t* masks; int32_t band_off1, band_off2, band_off3;   // first rows of bands 1, 2, 3 (band_off3 = Ntok without a fourth band)
   int in_bf16, out_bf16;    // element type: bf16 when set, else fp32
+  AxisBoxes box;            // (W axis, forward)
 };
 hipError_t launch_generic_axis_pass(const AxisPassArgs& a, hipStream_t st);
 // T and H axes of [slices][T][H][inner] tensors in one pass, in the forward or (with the transposed matrices) the inverse direction.
@@ -205,6 +208,7 @@ struct AxisPairArgs {
   const float* Mt; const float* Mh; int ldt, ldh;   // as in AxisPassArgs
   int T, H, slices; int64_t inner; int d;
   int in_bf16, out_bf16;
+  AxisBoxes box;            // (forward)
 };
 bool generic_pair_fits(const AxisPairArgs& a);   // whether the pass takes these sizes and is the faster way
 hipError_t allow_generic_axis_pair();            // lets its kernels ask for their LDS (when a context is set up: its calls may be captured)

@@ -29,6 +29,12 @@ __device__ __forceinline__ uint32_t gx_bf16(float f) {   // round to nearest eve
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
+// Coefficients of axis `ax` that tensor `tensor` of a slice is made for.
+__device__ __forceinline__ int gx_extent(const AxisBoxes& b, int tensor, int mask, int ax) {
+  if (tensor >= b.n || (mask & 12)) return b.full[ax];   // (the high band and the second mid band lie outside the boxes)
+  return mask & 2 ? b.mid[ax] : mask & 1 ? b.low[ax] : 0;
+}
+
 // IN / OUT: 0 fp32, 1 bf16.  VEC: head_dim is a multiple of 4 and the tensors start at a multiple of four elements, so four
 // columns are adjacent, aligned and of one slab.
 template <int KT, int IN, int OUT, bool VEC>
@@ -46,7 +52,7 @@ __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
   // this lane's four columns: element offset of input row 0 / output row 0, and what the looked-up rows need
   constexpr int NC = VEC ? 1 : 4;   // columns with an address of their own
   int64_t in_off[NC], out_off[NC], slice_off[NC];
-  int32_t pbase[NC], mask[NC];
+  int32_t pbase[NC], mask[NC], kend[NC];   // (kend: output rows made)
   bool live[NC];
 #pragma unroll
   for (int t = 0; t < NC; ++t) {
@@ -58,13 +64,24 @@ __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
     else { s = cc / (uint64_t)a.inner; i = cc % (uint64_t)a.inner; }
     in_off[t] = s * a.n * a.inner + i;
     out_off[t] = s * a.n_out * a.inner + i;
-    slice_off[t] = 0; pbase[t] = 0; mask[t] = 0;
+    slice_off[t] = 0; pbase[t] = 0; mask[t] = 0; kend[t] = a.n_out;
     if (a.perm_in || a.perm_out) {
       const int64_t slice = s / a.outer, o = s - slice * a.outer;
       slice_off[t] = slice * a.Ntok * a.inner + i;
       pbase[t] = (int32_t)(o * (a.perm_in ? a.n : a.n_out));
       if (a.masks) mask[t] = a.masks[slice];
+      if (tensor < a.box.n) {
+        const int m = a.box.masks[slice], h = (int)(o % a.box.full[1]), z = (int)(o / a.box.full[1]);
+        live[t] = live[t] && z < gx_extent(a.box, tensor, m, 0) && h < gx_extent(a.box, tensor, m, 1);
+        kend[t] = gx_extent(a.box, tensor, m, 2);
+      }
     }
+  }
+  if (tensor < a.box.n) {   // nothing of this wave is needed
+    bool any = false;
+#pragma unroll
+    for (int t = 0; t < NC; ++t) any = any || (live[t] && k0 < kend[t]);
+    if (__builtin_amdgcn_ballot_w64(any) == 0) return;
   }
   auto load = [&](int j) -> float4v {
     float4v v = {0.f, 0.f, 0.f, 0.f};
@@ -137,7 +154,7 @@ __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
       if (k >= a.n_out) continue;
 #pragma unroll
       for (int t = 0; t < NC; ++t) {
-        if (!live[t]) continue;
+        if (!live[t] || k >= kend[t]) continue;
         const int64_t e = a.perm_out ? slice_off[t] + (int64_t)a.perm_out[pbase[t] + k] * a.inner : out_off[t] + (int64_t)k * a.inner;
         char* dst = out + e * OE;
         if (VEC && OUT) {
@@ -184,6 +201,8 @@ hipError_t launch_kt(const AxisPassArgs& a, int64_t ncols, bool vec, hipStream_t
 // What bounds it: memory, read once and written once for two axes, and at the sizes it is used at the chain load - products - LDS -
 // products - store of a workgroup.  Two passes / this, Q, K and V: 12,150 tokens (9 x 30 x 45) x 4 heads x 64 in fp32 42 / 25 us, 6,160
 // (7 x 22 x 40) x 6 x 128 from bf16 62 / 34 us; 256 tokens x 2 x 32 8.5 / 5 us; the inverse 18 / 12, 27 / 14 and 8.5 / 4.5 us.
+// Q~ and K~ made only on the box a slice's bands live in, forwards, whole / boxes: 125 / 120 us (two of four heads without the high band),
+// 193 / 174 (four of six); nothing at 256 tokens.
 template <int IN, int OUT, bool VEC>
 __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   extern __shared__ __attribute__((aligned(16))) float th_smem[];
@@ -195,6 +214,8 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   float* Mh = th_smem + T * H * 64;         // [ldh][mstr]
   const int tensor = blockIdx.z, slice = blockIdx.y;
   const int64_t col = (int64_t)blockIdx.x * 64 + 4 * n;
+  const int mask = tensor < a.box.n ? a.box.masks[slice] : 0;
+  const int KT = tensor < a.box.n ? gx_extent(a.box, tensor, mask, 0) : T, KH = tensor < a.box.n ? gx_extent(a.box, tensor, mask, 1) : H;   // coefficients made
   const int nlive = (int)(a.inner - col < 4 ? a.inner - col : 4);   // columns of this lane's four that exist (VEC: all or none)
   const int64_t base = (int64_t)slice * T * H * a.inner + col;
   const char* in = (const char*)a.in[tensor] + base * IE;
@@ -224,6 +245,7 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   float4v x[2][4];
   if (wave < H) load(wave, x[0]);
   if (wave + NWAVE < H) load(wave + NWAVE, x[1]);
+  if (KT == 0) return;   // (uniform over the workgroup; behind the loads, which need not wait for the mask)
   float At[4];   // operand of the T matrix (padded with zeros to 16 x 16)
 #pragma unroll
   for (int r = 0; r < 4; ++r) At[r] = r < rt ? a.Mt[n * a.ldt + g * rt + r] : 0.f;
@@ -249,11 +271,11 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
       if (hb + 2 * NWAVE < H) load(hb + 2 * NWAVE, x[b]);
 #pragma unroll
       for (int r = 0; r < 4; ++r)   // result row 4 g + r
-        if (4 * g + r < T) *(float4v*)(Y + ((4 * g + r) * H + hb) * 64 + 4 * n) = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+        if (4 * g + r < T && 4 * g + r <= KT) *(float4v*)(Y + ((4 * g + r) * H + hb) * 64 + 4 * n) = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
     }
   __syncthreads();
-  const int tiles = (H + 15) / 16;
-  for (int u = wave; u < T * tiles; u += NWAVE) {
+  const int tiles = (KH + 15) / 16;
+  for (int u = wave; u < KT * tiles; u += NWAVE) {
     const int kt = u / tiles, tile = u - kt * tiles;
     float4v acc[4];
 #pragma unroll
@@ -262,7 +284,8 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
     const float* m = Mh + (16 * tile + n) * mstr + g * rh;
 #pragma unroll 4
     for (int r = 0; r < rh; ++r) {
-      // (rows past the axis: the matrix is zero there, and what lies behind is a row of the next kt or of the matrix, finite either way)
+      // (rows past the axis: the matrix is zero there, and what lies behind is a row of the next kt - made for this if it is not needed
+      // itself - or of the matrix)
       const float A = m[r];
       const float4v b = *(const float4v*)(y + r * 64);
 #pragma unroll
@@ -271,7 +294,7 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int kh = 16 * tile + 4 * g + r;
-      if (kh >= H || nlive <= 0) continue;
+      if (kh >= KH || nlive <= 0) continue;
       char* dst = out + (kt * t_stride + (int64_t)kh * a.inner) * OE;
       if (!VEC) {
 #pragma unroll

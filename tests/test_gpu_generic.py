@@ -214,7 +214,7 @@ def test_more_than_256_slices(dtype, path, grid, d):
 
 # every mask of a slice's bands beside slices that need everything: coefficients that are not made (boxes of one row too, Q~ and K~ of an
 # idle slice) must not reach an output, whatever lies in the scratch; grids whose T and H axes go in one pass and in two
-@pytest.mark.parametrize("grid,d", [((9, 10, 13), 64), ((3, 4, 5), 30), ((17, 6, 7), 64), ((2, 65, 4), 32)])
+@pytest.mark.parametrize("grid,d", [((9, 10, 13), 64), ((3, 4, 5), 30), ((5, 13, 24), 50), ((17, 6, 11), 64), ((2, 65, 13), 64)])
 @pytest.mark.parametrize("bands", [3, 4])
 def test_generic_boxes_of_all_masks(grid, d, bands):
     import torch
