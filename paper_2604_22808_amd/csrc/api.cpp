@@ -1327,6 +1327,17 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
     tm.done(split_summaries ? "low_compress_summaries" : "low_compress");
   }
 
+  // Generic path: where every slice runs a single band, all summary tokens exist by now, and the band launch takes the exchange as well.  (The
+  // same arithmetic, the same bits.)  With one slice that runs several, the exchange launch is needed anyway and the longer band items cost
+  // more than they spare it.  Forwards, exchange launch / inside, us: 256 tokens x 2 x 32 33.7 / 30.8, 9 x 30 x 45 x 4 x 64 120.0 / 116.6, 3 x 24 x 28
+  // x 6 x 64 53.5 / 51.5; only the single-band slices inside, beside others: 10 x 10 x 28 x 2 x 128 60.8 / 66.2, 10 x 6 x 32 x 4 x 128 67.9 / 71.4.
+  bool exchange_inside = split_summaries;
+  for (int h = 0; h < c->shape.heads; ++h) {
+    int bands = 0;
+    for (int l = 0; l < c->nb; ++l) bands += c->band_n[l] > 0 && (c->h_alloc[(size_t)h] >> l & 1);
+    exchange_inside = exchange_inside && bands <= 1;
+  }
+
   // section 3.4: the three band operators
   if (mf) {
     if (c->launch_mode == FREQATTN_LAUNCH_FUSED) {
@@ -1351,6 +1362,7 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
       if (l >= c->nb || c->n_list[l] == 0) continue;
       GAttnSeg& s = g.seg[i];
       s.slice_list = L + c->off_list[l]; s.n_slices = c->n_list[l];
+      if (exchange_inside && c->n_c[l] > 0) { s.C = (const float*)c->Cbuf + (int64_t)l * ap.m2 * c->d; s.c_slice_stride = (int64_t)c->nb * ap.m2 * c->d; s.nc = c->n_c[l]; }
       if (l == LOW) {
         s.Q = (const float*)c->lowQ; s.K = (const float*)c->lowK; s.V = (const float*)c->lowV; s.O = (float*)c->Y;
         s.slice_stride = s.kv_slice_stride = c->nbar * c->d; s.o_slice_stride = Nd; s.nq = s.nk = (int)c->nbar; s.mode = 0;
@@ -1391,7 +1403,7 @@ static freqattn_status bands_core(freqattn_ctx* c, float scale, const void* v_in
     } else {
       GAttnArgs g{};
       g.d = c->d; g.scale = scale;
-      for (int l = 0; l < c->nb; ++l) {
+      for (int l = 0; l < c->nb && !exchange_inside; ++l) {
         if (c->n_list[l] == 0 || c->n_c[l] == 0) continue;
         GAttnSeg& x = g.seg[g.nseg++];
         x.mode = 0; x.residual = 1;

@@ -224,6 +224,7 @@ struct GAttnSeg {
   int mode;                 // 0 dense, 1 block list, 2 window
   const int32_t* row_ptr; const int32_t* col_idx; int block; int window;   // (window at most nk)
   int residual;             // O = Q + attention (exchange)
+  const float* C; int64_t c_slice_stride; int nc;   // summary tokens the rows attend to after the band's keys (the exchange in the same launch), or NULL
   int rep, fill, n_out;     // query row i is written to output rows i rep .. i rep + fill - 1 below n_out (low band: its group)
   int rows, tiles, first_block;   // filled in by the launcher: query rows per workgroup, workgroups per slice, first workgroup
 };

@@ -37,7 +37,8 @@ __device__ __forceinline__ float4v row4(const float* row, int ch, int d) {
   return v;
 }
 
-template <int DC, int NQ, bool EXACT>
+// XCHG: some segments have summary tokens to attend to as well.
+template <int DC, int NQ, bool EXACT, bool XCHG>
 __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale, int tile, int sl, float* lds) {
   constexpr int ROWS = 16 * NQ, DP = 16 * DC, LROW = DP + 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -47,6 +48,11 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
   const float* K = s.K + (int64_t)slice * s.kv_slice_stride;
   const float* V = s.V + (int64_t)slice * s.kv_slice_stride;
   float* O = s.O + (int64_t)slice * s.o_slice_stride;
+
+  // With C the rows attend to the other bands' summary tokens as well (section 3.6), in a second phase with the first one's result as
+  // the query and the residual.
+  const int n_phases = XCHG && s.C ? 2 : 1;
+  int mode = s.mode, nk = s.nk;
 
   // query rows [q0, qend), keys j = 0 .. nkeys - 1 of the rows' own numbering
   int q0, qend, e0 = 0, k0 = 0, nkeys;
@@ -70,7 +76,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
   }
   // key row of list position j: the identity plus k0, or through the block list
   auto key_of = [&](int j) -> int {
-    if (s.mode != 1) return k0 + j;
+    if (mode != 1) return k0 + j;
     const int jj = min(j, nkeys - 1), b = jj / s.block;
     return s.col_idx[e0 + b] * s.block + (jj - b * s.block);
   };
@@ -82,6 +88,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
 #pragma unroll
     for (int c = 0; c < DC; ++c) Qr[u][c] = row4<EXACT>(row, 16 * c + 4 * g, d);
   }
+  for (int phase = 0;; ++phase) {
   float4v acc[NQ][DC];
   const float scale2 = scale * 1.44269504088896341f;
   float m_run[NQ], l_run[NQ];   // maximum over the tiles of this wave (an exponent of two); sum of this lane's keys only
@@ -95,10 +102,10 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
   // A tile of 16 keys per wave and step, the four waves' tiles side by side.  Its rows follow one another, from a row that all
   // lanes share, unless the blocks of a list are no multiples of 16.
   constexpr int TK = 16, STEP = 4 * TK;
-  const bool scattered = s.mode == 1 && s.block % TK != 0;
+  const bool scattered = mode == 1 && s.block % TK != 0;
   // first key row of the tile at list position jt (for tiles whose rows follow one another)
   auto base_of = [&](int jt) -> int {
-    if (s.mode != 1) return k0 + jt;
+    if (mode != 1) return k0 + jt;
     const int b = jt / s.block;
     return s.col_idx[e0 + b] * s.block + (jt - b * s.block);
   };
@@ -107,10 +114,10 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
   auto load_k = [&](int jt) {
     const float* row;
     if (scattered) {
-      row = K + (int64_t)min(key_of(jt + n), s.nk - 1) * d;
+      row = K + (int64_t)min(key_of(jt + n), nk - 1) * d;
     } else {
       kb = base_of(jt);
-      row = K + (int64_t)kb * d + min(n, s.nk - 1 - kb) * d;
+      row = K + (int64_t)kb * d + min(n, nk - 1 - kb) * d;
     }
 #pragma unroll
     for (int c = 0; c < DC; ++c) Kr[c] = row4<EXACT>(row, 16 * c + 4 * g, d);
@@ -124,7 +131,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       key[r] = scattered ? key_of(jt + 4 * g + r) : kt + 4 * g + r;
-      const float* row = scattered ? V + (int64_t)min(key[r], s.nk - 1) * d : V + (int64_t)kt * d + min(4 * g + r, s.nk - 1 - kt) * d;
+      const float* row = scattered ? V + (int64_t)min(key[r], nk - 1) * d : V + (int64_t)kt * d + min(4 * g + r, nk - 1 - kt) * d;
       if (EXACT && DC % 4 == 0) {
 #pragma unroll
         for (int c = 0; c < DC; c += 4) *(float4v*)&Vr[r][c] = *(const float4v*)(row + n * DC + c);
@@ -145,16 +152,16 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
           S[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(Kr[c][r], Qr[u][c][r], S[u], 0, 0, 0);
     if (jt + STEP < nkeys) load_k(jt + STEP);
     // (tiles inside the list and inside every row's window need no masks)
-    const bool inside = jt + TK <= nkeys && !scattered && kt + TK <= s.nk &&
-                        (s.mode != 2 || (kt + s.window >= qend - 1 && kt + TK - 1 - s.window <= q0));
+    const bool inside = jt + TK <= nkeys && !scattered && kt + TK <= nk &&
+                        (mode != 2 || (kt + s.window >= qend - 1 && kt + TK - 1 - s.window <= q0));
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       const int q = q0 + 16 * u + n;
       if (!inside)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          bool ok = jt + 4 * g + r < nkeys && key[r] < s.nk;
-          if (s.mode == 2) ok = ok && key[r] >= q - s.window && key[r] - s.window <= q;
+          bool ok = jt + 4 * g + r < nkeys && key[r] < nk;
+          if (mode == 2) ok = ok && key[r] >= q - s.window && key[r] - s.window <= q;
           S[u][r] = ok ? S[u][r] : -INFINITY;
         }
       // Scores times scale2 are exponents of two; the product and the difference to the running maximum are one rounding.
@@ -194,6 +201,7 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
       for (int c = 0; c < DC; ++c) lds[row * LROW + (4 * g + r) * DC + c] = acc[u][c][r];
   }
   __syncthreads();
+  const bool last = !XCHG || phase + 1 == n_phases;
   for (int e = tid; e < ROWS * (DP / 4); e += 256) {
     const int row = e / (DP / 4), ch = (e % (DP / 4)) * 4;
     if (q0 + row >= qend || ch >= d) continue;
@@ -211,20 +219,34 @@ __device__ __forceinline__ void gattn_body(const GAttnSeg& s, int d, float scale
     o *= 1.f / l;
     const int64_t q = q0 + row;
     if (s.residual) o += row4<EXACT>(Q + q * d, ch, d);
-    for (int64_t r = q * s.rep; r < min(q * s.rep + s.fill, (int64_t)s.n_out); ++r) {
+    if (XCHG && phase > 0) o += row4<EXACT>(O + q * s.rep * d, ch, d);   // (the first phase's result, stored by this thread)
+    if (!last) *(float4v*)(lds + row * LROW + ch) = o;           // (where only this thread has read: the second phase's queries)
+    for (int64_t r = q * s.rep; r < min(q * s.rep + (last ? s.fill : 1), (int64_t)s.n_out); ++r) {
       float* dst = O + r * d + ch;
       if (EXACT) {
         *(float4v*)dst = o;
       } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (ch + i < d) dst[i] = o[i];
+        for (int j = 0; j < 4; ++j)
+          if (ch + j < d) dst[j] = o[j];
       }
     }
   }
+  if (!XCHG || last) return;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NQ; ++u) {
+    const float* row = lds + min(16 * u + n, qend - 1 - q0) * LROW;
+#pragma unroll
+    for (int c = 0; c < DC; ++c) Qr[u][c] = row4<EXACT>(row, 16 * c + 4 * g, d);
+  }
+  __syncthreads();   // (before the results of the second phase take the place)
+  mode = 0; k0 = 0; nk = nkeys = s.nc;
+  K = V = s.C + (int64_t)slice * s.c_slice_stride;
+  }
 }
 
-template <int DC, bool EXACT>
+template <int DC, bool EXACT, bool XCHG>
 __global__ void __launch_bounds__(256, DC <= 4 ? 3 : DC <= 8 ? 2 : 1) k_gattn(GAttnArgs a) {
   constexpr int NQMAX = DC <= 8 ? 2 : 1;
   __shared__ __attribute__((aligned(16))) float lds[4 * 16 * NQMAX * (16 * DC + 4) + 4 * 16 * NQMAX * 2];
@@ -232,14 +254,19 @@ __global__ void __launch_bounds__(256, DC <= 4 ? 3 : DC <= 8 ? 2 : 1) k_gattn(GA
   while (k + 1 < a.nseg && (int)blockIdx.x >= a.seg[k + 1].first_block) ++k;
   const GAttnSeg& s = a.seg[k];
   const int b = blockIdx.x - s.first_block, sl = b / s.tiles, tile = b - sl * s.tiles;
-  if (NQMAX == 2 && s.rows == 32) gattn_body<DC, NQMAX, EXACT>(s, a.d, a.scale, tile, sl, lds);
-  else gattn_body<DC, 1, EXACT>(s, a.d, a.scale, tile, sl, lds);
+  if (NQMAX == 2 && s.rows == 32) gattn_body<DC, NQMAX, EXACT, XCHG>(s, a.d, a.scale, tile, sl, lds);
+  else gattn_body<DC, 1, EXACT, XCHG>(s, a.d, a.scale, tile, sl, lds);
 }
 
+// (Variants without the second phase: its loop costs the first one registers, and launches that have none up to 3 %.)
 template <int DC>
 hipError_t launch_dc(const GAttnArgs& a, int blocks, hipStream_t st) {
-  if (a.d == 16 * DC) hipLaunchKernelGGL((k_gattn<DC, true>), dim3((unsigned)blocks), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((k_gattn<DC, false>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+  bool xchg = false;
+  for (int i = 0; i < a.nseg; ++i) xchg = xchg || a.seg[i].C;
+  const bool exact = a.d == 16 * DC;
+  void (*const k)(GAttnArgs) = exact ? (xchg ? k_gattn<DC, true, true> : k_gattn<DC, true, false>)
+                                     : (xchg ? k_gattn<DC, false, true> : k_gattn<DC, false, false>);
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -229,3 +229,20 @@ def test_generic_boxes_of_all_masks(grid, d, bands):
     mx, rl = U.errors(got, O.forward(q, k, v, grid, U.oracle_cfg(cfgd), alloc))
     print(f"generic boxes {grid} d={d} bands={bands}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
     assert mx <= U.TOL["f32"][0] and rl <= U.TOL["f32"][1], (mx, rl)
+
+
+@pytest.mark.parametrize("d,block,window,c", [(64, 16, 32, 4), (30, 5, 7, 17), (128, 40, 300, 1), (256, 16, 20, 3)])
+def test_generic_exchange_inside_the_band_launch(d, block, window, c):
+    """Slices that run one band each have their exchange in the band's launch; beside a slice that runs two it is a launch of its own.
+    The outputs are the oracle's, and those of a slice the same bits either way."""
+    rng = np.random.default_rng(12)
+    grid, alloc = (7, 12, 14), (1, 2, 4, 0)
+    N = int(np.prod(grid))
+    cfgd = dict(WL.WORKLOADS["tiny_f32"].band, mid_block=block, high_window=window, low_compress=c, n_summary=11)
+    ctx = B.Context(1, 4, d, grid, B.F32, B.make_cfg(**cfgd), path=B.PATH_GENERIC)
+    q, k, v = (0.7 * rng.standard_normal((1, 4, N, d)).astype(np.float32).astype(np.float64) for _ in range(3))
+    inside, apart = (U.run_forward(ctx, q, k, v, "f32", a) for a in (alloc, alloc[:3] + (6,)))
+    assert np.array_equal(inside[:, :3], apart[:, :3])
+    mx, rl = U.errors(inside, O.forward(q, k, v, grid, U.oracle_cfg(cfgd), alloc))
+    print(f"generic exchange d={d}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= U.TOL["f32"][0] and rl <= U.TOL["f32"][1], (mx, rl)
