@@ -28,10 +28,12 @@ typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 
 namespace {
 
-__device__ __forceinline__ void gemm_dma16(const void* src, const half_t* dst) {
-  // one wave-wide copy of 16 bytes per lane into LDS at dst + 16 * lane (dst wave-uniform); issued as assembly so that the
+__device__ __forceinline__ unsigned gemm_lds(const half_t* p) {   // byte address within LDS of a wave-uniform place
+  return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(const __attribute__((address_space(3))) half_t*)p);
+}
+__device__ __forceinline__ void gemm_dma16(const void* src, unsigned base) {
+  // one wave-wide copy of 16 bytes per lane into LDS at byte base + 16 * lane (base wave-uniform); issued as assembly so that the
   // compiler does not order every later LDS read behind it - the kernel waits for its copies itself
-  const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(const __attribute__((address_space(3))) half_t*)dst);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ uint32_t gemm_pack_h2(float a, float b) {
@@ -73,8 +75,8 @@ __global__ void __launch_bounds__(256, 2) k_gemm_nt(const GemmProblem* __restric
     for (int i = 0; i < 4; ++i) {
       const int r = (wave * 4 + i) * 8 + lr;
       const int chunk = (lc ^ fK(r)) << 3;
-      gemm_dma16(sg.A + (int64_t)a_row[i] * sg.lda + k0 + chunk, As[buf] + (wave * 4 + i) * 8 * GK);
-      gemm_dma16(sg.B + (int64_t)b_row[i] * sg.ldb + k0 + chunk, Bs[buf] + (wave * 4 + i) * 8 * GK);
+      gemm_dma16(sg.A + (int64_t)a_row[i] * sg.lda + k0 + chunk, gemm_lds(As[buf] + (wave * 4 + i) * 8 * GK));
+      gemm_dma16(sg.B + (int64_t)b_row[i] * sg.ldb + k0 + chunk, gemm_lds(Bs[buf] + (wave * 4 + i) * 8 * GK));
     }
   };
 
@@ -145,25 +147,33 @@ __global__ void __launch_bounds__(256, 2) k_gemm_nt(const GemmProblem* __restric
     }
 }
 
-// The same product with a 256 x 256 tile per workgroup of eight waves (a wave owns 64 rows x 128 columns: per K step of 16
-// it reads 2 + 4 operands from LDS for 8 MFMAs, and the tile brings half the bytes per flop into LDS that the 128 x 128
-// tile above does).  One workgroup per compute unit; K advances in steps of 64 through two LDS buffers of 64 KB (a
-// variant with steps of 32 through four buffers - three steps in flight - measured 6 % slower, and so did touching the
-// lines of later steps ahead of time to have them in L2, and so did spreading a step's copies between its MFMAs).
-// What it spends its time on, from timing copies with a part left out, 262,144 rows, d_model 2048, 16 heads of 128, Q~ / K~ / V~ products
-// and output product: as it is 1.70 and 2.78 ms (0.97 PFLOP/s); without the operand reads from LDS 1.67 and 2.71; without the copies
-// into LDS 1.35 and 2.12 (1.27 PFLOP/s, where a loop of products alone reaches 1.9).  The copies move 15 bytes per cycle and
-// compute unit meanwhile.
+// The same product with a 256 x 256 tile per workgroup of eight waves, one workgroup per compute unit, K in steps of 64.
+//
+// The tiles of A and B of a step are halves of 128 rows, 16 KB each in LDS, two copies of everything (128 KB).  A wave owns 32 rows of
+// either half of A and 64 columns of either half of B, and a step is four phases of 8 MFMAs, one per pair of halves, in an order
+// in which every phase changes one half only: A0 B0, A0 B1, A1 B1, A1 B0, then (next step) A0 B1, A0 B0, A1 B0, A1 B1.  So half number j
+// of the sequence A0 B0 B1 A1 | A0 B1 B0 A1 | A0 B0 .. is, in phase
+//   j - 9   copied from memory into the place of half j - 8, which every wave has read in phase j - 10,
+//   j - 2   read into registers by every wave, beside the MFMAs of that phase,
+//   j - 1 .. j + 2   multiplied.
+// A copy has seven phases to arrive, six of them are always in flight (96 KB per compute unit), and no wait in the loop is for the
+// latest ones; a phase starts with its operands in registers.
+//
+// What bounds it: power.  262,144 rows, d_model 2048, 16 heads of 128, Q~ / K~ / V~ products and output product: one step ahead and a wait for all
+// of it at every step 1.70 and 2.78 ms (0.97 PFLOP/s, matrix cores busy 53 % of the cycles at 1.9 GHz), this 1.57 and 2.53 (1.07 PFLOP/s, busy
+// 63 % at 1.7 GHz); a loop of products alone, busy all the time, is held to 1.93 GHz.  The copies are no limit of the machine: it takes 137
+// bytes per ns and compute unit from L2 into LDS or into registers, the loop 35.
+//
 // The columns of a launch run over all its problems back to back (problem p owns columns [p n, (p + 1) n), n a
 // multiple of 32), so that a tile can span several narrow problems - the per-head projections are 64 or 128 columns
 // wide.  All problems of a launch must have the same A segments (pointers, strides and K); B and C are the problem's own.
-constexpr int WM = 256, WN = 256, WK = 64, WST = 2;
+constexpr int WM = 256, WN = 256, WK = 64;
+constexpr int HALF = 128 * WK;   // elements of half a tile
 
-__global__ void __launch_bounds__(512, 1) k_gemm_nt_wide(const GemmProblem* __restrict__ probs, const GemmSeg* __restrict__ segs,
+__global__ void __launch_bounds__(512, 2) k_gemm_nt_wide(const GemmProblem* __restrict__ probs, const GemmSeg* __restrict__ segs,
                                                          int per, int n, int tiles_m, int tiles_n) {
-  static_assert((WM + WN) * WK * 2 * WST <= 160 * 1024, "LDS budget");
-  __shared__ __attribute__((aligned(16))) half_t As[WST][WM * WK];
-  __shared__ __attribute__((aligned(16))) half_t Bs[WST][WN * WK];
+  static_assert(8 * HALF * 2 <= 160 * 1024, "LDS budget");
+  __shared__ __attribute__((aligned(16))) half_t lds[4][2][HALF];   // [A0, A1, B0, B1][step & 1]
   const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
   const int mt = (seq / tiles_n) * 8 + xcd;
   if (mt >= tiles_m) return;   // (uniform over the workgroup: the grid is padded to whole rounds of 8 row tiles)
@@ -171,40 +181,45 @@ __global__ void __launch_bounds__(512, 1) k_gemm_nt_wide(const GemmProblem* __re
   const int n_total = per * n;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nn = lane & 31, g = lane >> 5;
-  const int wm = wave & 3, wn = wave >> 2;              // this wave's 64 rows and 128 columns of the tile
+  const int wm = wave & 3, wn = wave >> 2;              // this wave's 32 rows and 64 columns of every half
   // Rows are WK halfs in LDS; the 16-byte chunks of row r are permuted through the source address so that the operand
   // reads of 16 consecutive rows fall on 16 different 16-byte bank groups
-  constexpr int CPR = WK / 8;                           // chunks per row
-  constexpr int RPI = 64 / CPR;                         // rows per copy instruction (64 lanes x 16 bytes)
-  constexpr int IPW = 32 / RPI;                         // copy instructions per wave, step and matrix
   auto fK = [](int r) -> int { return (r >> 1) & 7; };
-  const int lr = lane / CPR, lc = lane % CPR;
 
-  // the copies: wave w moves rows [32 w, 32 w + 32) of the A tile and of the B tile
-  const int bcol0 = gc0 + 32 * wave;                                    // first B row (= column of C) this wave copies
-  const int pb = min(bcol0, n_total - 1) / n;                           // its problem (n % 32 == 0: one problem per wave)
-  const GemmProblem prb = probs[pb];
-  const int m = prb.m;
-  int a_row[IPW], b_row[IPW];   // row within the tile's A rows / within the problem's B rows, clamped to what exists
+  // the copies: wave w moves rows [16 w, 16 w + 16) of a half, 8 per instruction
+  int lr = lane >> 3, chunk = ((lane & 7) ^ fK(lane >> 3)) << 3;   // this lane's row and (even instructions) its chunk
+  int pb[2];   // problem of the wave's rows of B0 and B1 (16 rows are one problem's)
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) {
-    const int r = 32 * wave + RPI * i + lr;
-    a_row[i] = min(m0 + r, m - 1) - m0;
-    b_row[i] = min(bcol0 + RPI * i + lr, n_total - 1) - pb * n;
-  }
-  auto stage = [&](const GemmSeg& sg, int k0, int buf) {
-    const half_t* abase = sg.A + (int64_t)m0 * sg.lda + k0;   // wave-uniform
-    const half_t* bbase = sg.B + k0;
+  for (int h = 0; h < 2; ++h) pb[h] = min(gc0 + 128 * h + 16 * wave, n_total - 1) / n;
+  const int m = probs[pb[0]].m, nseg = probs[pb[0]].nseg;
+  const int seg0[2] = {probs[pb[0]].seg0, probs[pb[1]].seg0};
+  int seg_i = 0, k_i = 0, total_steps = 0;   // position of the step that is copied next
+  for (int s = 0; s < nseg; ++s) total_steps += segs[seg0[0] + s].K / WK;
+  GemmSeg sg = segs[seg0[0]];
+  const half_t* bp[2] = {sg.B, segs[seg0[1]].B};
+  const unsigned copy_at = gemm_lds(lds[0][0] + 16 * wave * WK);
+  auto copy = [&](int buf, int which) {   // 0, 1: A0, A1; 2, 3: B0, B1
+    const int h = which & 1;
+    const bool b = which >= 2;
+    const half_t* base = b ? bp[h] + k_i : sg.A + (int64_t)m0 * sg.lda + k_i;   // wave-uniform
+    const int last = b ? n_total - 1 - pb[h] * n : m - 1 - m0, first = 128 * h + 16 * wave + (b ? gc0 - pb[h] * n : 0);   // (rows clamped to what exists)
+    asm volatile("" : "+v"(lr), "+v"(chunk));   // (addresses formed here: kept for the whole loop they would take the operands' registers)
 #pragma unroll
-    for (int i = 0; i < IPW; ++i) {
-      const int r = 32 * wave + RPI * i + lr;
-      const int chunk = (lc ^ fK(r)) << 3;
-      gemm_dma16(abase + (uint32_t)(a_row[i] * sg.lda + chunk), As[buf] + (32 * wave + RPI * i) * WK);
-      gemm_dma16(bbase + (uint32_t)(b_row[i] * sg.ldb + chunk), Bs[buf] + (32 * wave + RPI * i) * WK);
+    for (int i = 0; i < 2; ++i)
+      gemm_dma16(base + (uint32_t)(min(first + 8 * i + lr, last) * (b ? sg.ldb : sg.lda) + (chunk ^ (i * 32))), copy_at + ((which * 2 + buf) * HALF + 8 * i * WK) * 2);
+  };
+  auto advance = [&]() {   // (behind the last step: that step again, into places that nobody reads)
+    if (k_i + WK < sg.K) {
+      k_i += WK;
+    } else if (seg_i + 1 < nseg) {
+      k_i = 0;
+      ++seg_i;
+      sg = segs[seg0[0] + seg_i];
+      bp[0] = sg.B; bp[1] = segs[seg0[1] + seg_i].B;
     }
   };
 
-  float16v acc[4][2];   // [column tile][row tile]
+  float16v acc[4][2];   // [column tile: half of B, 32 columns][row tile: half of A]
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
@@ -212,59 +227,70 @@ __global__ void __launch_bounds__(512, 1) k_gemm_nt_wide(const GemmProblem* __re
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[ct][rt][r] = 0.f;
 
-  int seg_i = 0, k_i = 0;   // position of the step that is copied next
-  GemmSeg sg = segs[prb.seg0];
-  int total_steps = 0;
-  for (int s2 = 0; s2 < prb.nseg; ++s2) total_steps += segs[prb.seg0 + s2].K / WK;
-  auto advance = [&]() {
-    k_i += WK;
-    if (k_i >= sg.K) {
-      k_i = 0;
-      ++seg_i;
-      if (seg_i < prb.nseg) sg = segs[prb.seg0 + seg_i];
-    }
-  };
-  if (total_steps > 0) { stage(sg, k_i, 0); advance(); }
-  for (int step = 0; step < total_steps; ++step) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of step `step` has landed
-    __syncthreads();   // step `step` is in LDS for every wave, and nobody reads the buffer of step - 1 any more
-    if (step + 1 < total_steps) { stage(sg, k_i, (step + 1) % WST); advance(); }
-    const int buf = step % WST;
-    const half_t* Ab = As[buf] + (64 * wm + nn) * WK;
-    const half_t* Bb = Bs[buf] + (128 * wn + nn) * WK;
-    constexpr int NKS = WK / 16;
-    half8 rows[2][2], cols[2][4];
-    auto operands = [&](int ks, int set) {
-      const int pos = ((2 * ks + g) ^ fK(nn)) << 3;        // fK(32 t + nn) = fK(nn)
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) rows[set][rt] = *(const half8*)(Ab + rt * 32 * WK + pos);
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) cols[set][ct] = *(const half8*)(Bb + ct * 32 * WK + pos);
-    };
-    operands(0, 0);
+  constexpr int NKS = WK / 16;
+  half8 ra[2][NKS], rb[2][NKS][2];   // operands: halves of A and of B
+  const half_t* const a_at = lds[0][0] + (32 * wm + nn) * WK;
+  const half_t* const b_at = lds[2][0] + (64 * wn + nn) * WK;
+  auto read = [&](int buf, int which) {
+    const int h = which & 1;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
-      if (ks + 1 < NKS) operands(ks + 1, (ks + 1) & 1);
+      const int pos = ((2 * ks + g) ^ fK(nn)) << 3;        // fK(32 t + nn) = fK(nn)
+      if (which < 2) {
+        ra[h][ks] = *(const half8*)(a_at + (2 * h + buf) * HALF + pos);
+      } else {
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-          acc[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cols[ks & 1][ct], rows[ks & 1][rt], acc[ct][rt], 0, 0, 0);
+        for (int c = 0; c < 2; ++c) rb[h][ks][c] = *(const half8*)(b_at + (2 * h + buf) * HALF + c * 32 * WK + pos);
+      }
     }
+  };
+  // One phase: half of A `a`, half of B `b` multiplied; the half `rd` read; the half `cp` copied.
+  auto phase = [&](int a, int b, int rd_buf, int rd, int cp_buf, int cp) {
+    // The half to be read has landed (this wave's part; with the barrier, everybody's), and everybody has the half that was read last.
+    asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    copy(cp_buf, cp);
+    read(rd_buf, rd);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        acc[2 * b + c][a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(rb[b][ks][c], ra[a][ks], acc[2 * b + c][a], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  if (total_steps > 0) {
+    copy(0, 0); copy(0, 2); copy(0, 3); copy(0, 1); advance();   // halves 0 .. 3
+    copy(1, 0); copy(1, 3); copy(1, 2); copy(1, 1); advance();   // 4 .. 7
+    asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");
+    read(0, 0); read(0, 2);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    copy(0, 0);                                                   // 8
+    for (int step = 0; step < total_steps; step += 2) {
+      phase(0, 0, 0, 3, 0, 2);
+      phase(0, 1, 0, 1, 0, 3);
+      phase(1, 1, 1, 0, 0, 1); advance();
+      phase(1, 0, 1, 3, 1, 0);
+      if (step + 1 == total_steps) break;
+      phase(0, 1, 1, 2, 1, 3);
+      phase(0, 0, 1, 1, 1, 2);
+      phase(1, 0, 0, 0, 1, 1); advance();
+      phase(1, 1, 0, 2, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (copies into this workgroup's LDS)
   }
 
   // store: lane = row of C, registers = columns; a register swap with the partner lane (lane ^ 32, same row) leaves
   // every lane with 8 consecutive columns, i.e. 16-byte stores.  Every 32-column tile looks up its own problem.
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
-    const int gc = gc0 + 128 * wn + 32 * ct;
-    if (gc >= n_total) break;
+    const int gc = gc0 + 128 * (ct >> 1) + 64 * wn + 32 * (ct & 1);
+    if (gc >= n_total) continue;
     const int pc = gc / n;
     const GemmProblem pr = probs[pc];
     const int col0 = gc - pc * n;
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
-      const int row = m0 + 64 * wm + 32 * rt + nn;
+      const int row = m0 + 128 * rt + 32 * wm + nn;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         float o[8];   // columns col0 + j*16 + g*8 + 0..7

@@ -284,6 +284,26 @@ def test_projected_forward_of_narrow_models(d_model):
     assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
 
 
+@pytest.mark.parametrize("d_model,heads,alloc", [(256, 4, (1, 2, 4, 0)), (320, 5, (1, 2, 4, 7, 4)), (448, 7, (2, 2, 1, 1, 4, 6, 7))])
+def test_projected_forward_of_products_in_wide_tiles(d_model, heads, alloc):
+    """Products of 256 rows and columns and more: even and odd numbers of steps of 64, one segment and several, tiles whose second half is cut
+    short by the columns or the rows, and tiles that span several problems."""
+    rng = np.random.default_rng(18)
+    grid, d = (16, 32, 32), 64
+    N, hd = int(np.prod(grid)), heads * d
+    x = WL.round_to_io(0.5 * rng.standard_normal((1, N, d_model)), "bf16")
+    w = [WL.round_to_io(rng.standard_normal(s) / np.sqrt(s[0]), "bf16") for s in ((d_model, hd),) * 3 + ((hd, d_model),)]
+    band = WL.WORKLOADS["16k"].band
+    ctx = B.Context(1, heads, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    import torch
+    dx, *dw = (U.to_device(a, "bf16") for a in [x] + w)
+    out = torch.empty_like(dx)
+    ctx.forward_projected(dx, *dw, alloc, out)
+    mx, rl = U.errors(U.to_host64(out), O.forward_projected(x, *w, grid, O.BandConfig(**band), alloc))
+    print(f"projected d_model={d_model}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
+
+
 def test_projected_forward_of_a_model_of_8192_channels():
     """Rows of the transformed X 4 MB apart and more.  Heads that run no band: the layer is X W_V W_O.  Tolerance of the other outputs."""
     import torch
