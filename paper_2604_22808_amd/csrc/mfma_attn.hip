@@ -32,8 +32,6 @@ typedef float float16v __attribute__((ext_vector_type(16)));
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 
-#define KT 64  // keys per tile
-
 __device__ __forceinline__ uint32_t pack_h2(float a, float b) {
   const _Float16 ha = (_Float16)a, hb = (_Float16)b;
   return (uint32_t)__builtin_bit_cast(uint16_t, ha) | ((uint32_t)__builtin_bit_cast(uint16_t, hb) << 16);
@@ -49,13 +47,17 @@ __device__ __forceinline__ void lds_dma16(const void* src, const half_t* dst) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base) : "memory", "m0");
 }
 
-template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(AttnParams p, const AttnItem* __restrict__ items, int n_items) {
+// KT: keys per tile.  Items of 64 rows (two waves) at D = 128 take 32: with 64 the tiles of two waves take 64 KB of LDS, which leaves a SIMD one wave,
+// with 32 it has two.  Forwards with mid blocks of 64, 64 keys / 32, us: 8 heads of 32 x 64 x 64 x 128, four of them high 1292 / 1110, seven of them
+// mid 652 / 602; 16 of 80 x 96 x 32 (routed) 4273 / 2750.
+template <int D, int NW, int KT>
+__global__ void __launch_bounds__(64 * NW, 2) k_attn(AttnParams p, const AttnItem* __restrict__ items, int n_items) {
   constexpr int DT = D / 32;    // 32-channel tiles of the output
   constexpr int DK = D / 16;    // MFMA steps over the channels for S
   constexpr int NT = 64 * NW;
   constexpr int ROWS = 32 * NW;  // query rows per item
   constexpr int WROWS = 32;      // query rows per wave
+  constexpr int T2 = KT / 32;    // score tiles
   // two copies of the K / V tiles: tile i+1 is written while tile i is still being read, one barrier per tile
   __shared__ __attribute__((aligned(16))) half_t Ks2[2][KT * D];
   __shared__ __attribute__((aligned(16))) half_t Vt2[2][KT * D];
@@ -311,8 +313,8 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
           continue;
         }
 
-        // ---- S^T = K Q^T for the two 32-key halves of the tile
-        float16v S[2];   // (each starts from Minit)
+        // ---- S^T = K Q^T for each 32 keys of the tile
+        float16v S[T2];   // (each starts from Minit)
         // K operands are requested PF steps ahead of the MFMA that consumes them, so LDS latency overlaps the matrix core
         // The wave takes the higher issue priority for the score stage (its operand reads, its MFMAs and the next tile's
         // copies spread between them) and gives it back for the softmax: with two waves per SIMD the one that starts a
@@ -321,7 +323,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
         __builtin_amdgcn_s_setprio(1);
         constexpr int PF = 8;
         {
-          constexpr int NS = 2 * DK;
+          constexpr int NS = T2 * DK;
           auto kptr = [&](int i) -> const half8* {
             return (const half8*)(Ks + (i / DK) * 32 * D + koff_row + kx[i % DK]);   // fK(t2*32 + nn) = fK(nn)
           };
@@ -354,7 +356,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
         // one: it moves only when a score exceeds it by more than 2^kBump (or when the row sees its first valid key), so
         // probabilities stay within [0, 2^kBump] - exact in the ratio P / sum(P) - and the rescale is rare.
         constexpr float kBump = 8.f;
-        half8 P[2][2];
+        half8 P[T2][2];
         if (need_mask) {
           // valid keys of this lane's row form one interval [lo, hi]; relative to the lane's first key of the tile,
           // register r holds key offset c_r (a compile-time constant), valid iff (unsigned)(c_r - lo') <= (unsigned)(hi' - lo')
@@ -363,13 +365,13 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
           if (kind_p == 2) { lo = row - w > 0 ? row - w : 0; hi = row + w < nkp - 1 ? row + w : nkp - 1; }
           const int base = key0 + 4 * g;
           int dlo = lo - base, dhi = hi - base;
-          dlo = dlo < -1 ? -1 : (dlo > 65 ? 65 : dlo);    // clamped: only the range of c_r matters
-          dhi = dhi < -1 ? -1 : (dhi > 65 ? 65 : dhi);
+          dlo = dlo < -1 ? -1 : (dlo > KT + 1 ? KT + 1 : dlo);    // clamped: only the range of c_r matters
+          dhi = dhi < -1 ? -1 : (dhi > KT + 1 ? KT + 1 : dhi);
           unsigned range = (unsigned)(dhi - dlo);
           if (dhi < dlo) { dlo = 1000; range = 0u; }      // empty interval: no c_r passes
           const unsigned ndlo = (unsigned)(-dlo);
 #pragma unroll
-          for (int t2 = 0; t2 < 2; ++t2)
+          for (int t2 = 0; t2 < T2; ++t2)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
               const unsigned cr = (unsigned)(t2 * 32 + 8 * (r >> 2) + (r & 3));
@@ -380,7 +382,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
         // swap (v_permlane32_swap leaves [lo, lo] / [hi, hi] in the two registers; no trip through the LDS pipe)
         float mc[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2)
+        for (int t2 = 0; t2 < T2; ++t2)
 #pragma unroll
           for (int r = 0; r < 16; r += 2)
             mc[(r >> 1) & 3] = __builtin_fmaxf(__builtin_fmaxf(mc[(r >> 1) & 3], S[t2][r]), S[t2][r + 1]);
@@ -398,7 +400,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
           float ps[4] = {0.f, 0.f, 0.f, 0.f};
           const half2v ones = {(_Float16)1.f, (_Float16)1.f};
 #pragma unroll
-          for (int t2 = 0; t2 < 2; ++t2)
+          for (int t2 = 0; t2 < T2; ++t2)
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2) {
               uint4v pk;
@@ -427,7 +429,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
             asm volatile("" : "+v"(Minit));   // (sixteen registers on purpose, not one value spread again per tile)
           }
 #pragma unroll
-          for (int t2 = 0; t2 < 2; ++t2)
+          for (int t2 = 0; t2 < T2; ++t2)
 #pragma unroll
             for (int r = 0; r < 16; ++r) S[t2][r] -= delta;
 #pragma unroll
@@ -439,7 +441,7 @@ __global__ void __launch_bounds__(64 * NW, (D == 64 || NW == 4) ? 2 : 1) k_attn(
         l_run += psum;
         // ---- O^T += V^T P^T
         {
-          constexpr int NS = 4 * DT;   // (t2, s2, dt) flattened, dt fastest
+          constexpr int NS = 2 * T2 * DT;   // (t2, s2, dt) flattened, dt fastest
           // V is row-major in LDS; the operand (lane = channel, 8 keys in the order of P's registers) comes from two
           // transposing reads, each delivering 4 consecutive keys: keys 16 ts + 8 h + 4 g + 0..3 for read h
           auto vread = [&](int i) -> half8 {
@@ -536,25 +538,24 @@ hipError_t launch_probe_mfma(float* out, int blocks, int iters, hipStream_t st) 
   return hipGetLastError();
 }
 
-template <int D, int NW>
+template <int D, int NW, int KT>
 static hipError_t launch_dn(const AttnParams& p, const AttnItem* items, int n_items, int num_cu, hipStream_t st) {
   // resident workgroups per CU: register-limited waves per SIMD, 4 SIMDs per CU (matches the kernel's launch bounds)
-  const int waves_per_simd = (D == 64 || NW == 4) ? 2 : 1;
-  int occ = waves_per_simd * 4 / NW;
-  if (occ < 1) occ = 1;
+  constexpr int occ = 2 * 4 / NW;
+  static_assert(occ * 4 * KT * D * 2 <= 160 * 1024, "LDS of one compute unit");
   int64_t blocks = (int64_t)num_cu * occ;
   if (blocks > n_items) blocks = n_items;
   if (blocks > 8) blocks -= blocks % 8;   // whole runs per XCD (see the kernel's item mapping)
-  hipLaunchKernelGGL((k_attn<D, NW>), dim3((unsigned)blocks), dim3(64 * NW), 0, st, p, items, n_items);
+  hipLaunchKernelGGL((k_attn<D, NW, KT>), dim3((unsigned)blocks), dim3(64 * NW), 0, st, p, items, n_items);
   return hipGetLastError();
 }
 
 hipError_t launch_mfma_attn(const AttnParams& p, const AttnItem* items, int n_items, int rows_per_item, int num_cu,
                             hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-#define FA_ATTN_CASE(D_, R_, NW_) \
-  if (p.d == D_ && rows_per_item == R_) return launch_dn<D_, NW_>(p, items, n_items, num_cu, st);
-  FA_ATTN_CASE(64, 64, 2) FA_ATTN_CASE(64, 128, 4) FA_ATTN_CASE(128, 64, 2) FA_ATTN_CASE(128, 128, 4)
+#define FA_ATTN_CASE(D_, R_, NW_, KT_) \
+  if (p.d == D_ && rows_per_item == R_) return launch_dn<D_, NW_, KT_>(p, items, n_items, num_cu, st);
+  FA_ATTN_CASE(64, 64, 2, 64) FA_ATTN_CASE(64, 128, 4, 64) FA_ATTN_CASE(128, 64, 2, 32) FA_ATTN_CASE(128, 128, 4, 64)
 #undef FA_ATTN_CASE
   return hipErrorInvalidValue;
 }

@@ -198,6 +198,23 @@ def test_16k_bf16_parameter_edges(band, v_box, monkeypatch):
     _check(got, want, "bf16", f"16k edges {band}")
 
 
+# mid blocks of odd and even numbers of 64 rows, the band's last block cut short (1,376 rows: 21 blocks and a half); residue classes of
+# even and odd sizes, of one block each, one class of all; windows around the key tiles, shorter and longer than a query tile
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("block,diag,stride,window", [(64, 1, 4, 31), (64, 0, 5, 33), (64, 2, 11, 0), (64, 1, 100, 64), (64, 3, 1, 500), (192, 1, 3, 95),
+                                                      (320, 0, 2, 96), (128, 1, 4, 130), (1408, 0, 7, 1)])
+def test_mfma_mid_blocks(block, diag, stride, window, d):
+    rng = np.random.default_rng(6)
+    grid, alloc = (16, 48, 16), (2, 6, 1, 4)
+    N = int(np.prod(grid))
+    q, k, v = (WL.round_to_io(0.5 * rng.standard_normal((1, 4, N, d)), "bf16") for _ in range(3))
+    band = dict(WL.WORKLOADS["16k"].band, low_den=5, mid_block=block, mid_diag=diag, mid_stride=stride, mid_block0=int(block != 192),
+                high_window=window, n_summary=11, low_compress=1)
+    ctx = B.Context(1, 4, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    assert int(ctx.band_sizes()[1]) == 1376
+    _check(U.run_forward(ctx, q, k, v, "bf16", alloc), O.forward(q, k, v, grid, O.BandConfig(**band), alloc), "bf16", f"mid blocks of {block}, d={d}")
+
+
 @pytest.mark.parametrize("v_box,alloc", [("0", (7, 4)), ("1", (7, 4)), ("1", (1, 2, 3))])
 def test_mfma_ragged_grid_bf16(v_box, alloc, monkeypatch):
     """Grid 16x48x80 (axis lengths that are not powers of two), head_dim 128, ragged tails in every band; also with V~ of
