@@ -20,6 +20,8 @@
 // reads.  All tensors are fp16 (the dense comparison converts its bf16 tensors into fp16 scratch first).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "ctx.h"
 
 namespace fa {
@@ -38,13 +40,15 @@ __device__ __forceinline__ uint32_t pack_h2(float a, float b) {
 }
 
 // One wave-wide 16-byte-per-lane copy from global memory straight into LDS: lane l's 16 bytes land at dst + 16 l,
-// dst wave-uniform.  Issued as assembly on purpose: the compiler orders every LDS read behind a pending copy of this
+// dst (an LDS address) wave-uniform.  Issued as assembly on purpose: the compiler orders every LDS read behind a pending copy of this
 // kind that it knows of (it cannot tell the two LDS tile copies apart), which would put the whole latency of the next
 // tile's fetch in front of the current tile's arithmetic.  The kernel waits for these copies itself (vmcnt(0) in front
 // of the barrier that publishes the tile); the compiler's own waits for its global loads only become stricter.
-__device__ __forceinline__ void lds_dma16(const void* src, const half_t* dst) {
-  const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(const __attribute__((address_space(3))) half_t*)dst);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base) : "memory", "m0");
+__device__ __forceinline__ void lds_dma16(const void* base, unsigned off, unsigned dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(dst) : "memory", "m0");
+}
+__device__ __forceinline__ unsigned lds_address(const half_t* p) {
+  return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) half_t*)p;
 }
 
 // KT: keys per tile.  Items of 64 rows (two waves) at D = 128 take 32: with 64 the tiles of two waves take 64 KB of LDS, which leaves a SIMD one wave,
@@ -167,8 +171,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_attn(AttnParams p, const AttnIte
       const int r = rowbase + lr;
       int key = key0 + r;
       if (key > nkeys - 1) key = nkeys - 1;
-      if ((pi & 1) == 0) lds_dma16(Ksrc + (int64_t)key * D + ((c ^ fK(r)) << 3), Ks2[buf] + rowbase * D);
-      else lds_dma16(Vsrc + (int64_t)key * D + ((c ^ fV(r)) << 3), Vt2[buf] + rowbase * D);
+      if ((pi & 1) == 0) lds_dma16(Ksrc, 2 * ((unsigned)key * D + ((c ^ fK(r)) << 3)), lds_address(Ks2[0]) + 2 * (buf * KT + rowbase) * D);
+      else lds_dma16(Vsrc, 2 * ((unsigned)key * D + ((c ^ fV(r)) << 3)), lds_address(Vt2[0]) + 2 * (buf * KT + rowbase) * D);
     };
 
     // An item runs one or two phases over the same query rows.  Phase 0 is the band operator.  Phase 1 (items marked
@@ -322,8 +326,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_attn(AttnParams p, const AttnIte
         // 6 % faster, window branch 2 %; priority in the other stages instead, or in all MFMA stages, gains less).
         __builtin_amdgcn_s_setprio(1);
         constexpr int PF = 8;
-        {
-          constexpr int NS = T2 * DK;
+        auto scores = [&](auto copies) {
+          constexpr int NS = T2 * DK, PF = decltype(copies)::value ? 8 : 4;
           auto kptr = [&](int i) -> const half8* {
             return (const half8*)(Ks + (i / DK) * 32 * D + koff_row + kx[i % DK]);   // fK(t2*32 + nn) = fK(nn)
           };
@@ -337,7 +341,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_attn(AttnParams p, const AttnIte
             if (i + PF < NS)
               Abuf[i % PF] = *kptr(i + PF);
             S[t2] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, Qr[ks], ks == 0 ? Minit : S[t2], 0, 0, 0);
-            if (dma_next) {
+            if (copies.value) {
 #pragma unroll
               for (int pi = i * (2 * NIW) / NS; pi < (i + 1) * (2 * NIW) / NS; ++pi) dma_piece(Kn, Vn, nkn, key0_next, buf ^ 1, pi);
             }
@@ -350,7 +354,9 @@ __global__ void __launch_bounds__(64 * NW, 2) k_attn(AttnParams p, const AttnIte
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
           }
           __builtin_amdgcn_sched_group_barrier(0x008, PF, 0);
-        }
+        };
+        if (dma_next) scores(std::true_type{});
+        else scores(std::false_type{});
         __builtin_amdgcn_s_setprio(0);
         // ---- mask, running softmax (lane = query row; registers = keys).  m_run is a reference maximum, not the exact
         // one: it moves only when a score exceeds it by more than 2^kBump (or when the row sees its first valid key), so
@@ -466,6 +472,14 @@ __global__ void __launch_bounds__(64 * NW, 2) k_attn(AttnParams p, const AttnIte
             if (i + PF < NS) Abuf[i % PF] = vread(i + PF);
             O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, P[ts >> 1][ts & 1], O[dt], 0, 0, 0);
           }
+          // pin the order: PF operands up front, then one operand (two reads) per MFMA
+          __builtin_amdgcn_sched_group_barrier(0x100, 2 * PF, 0);
+#pragma unroll
+          for (int i = 0; i < NS - PF; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          }
+          __builtin_amdgcn_sched_group_barrier(0x008, PF, 0);
         }
       }
       tile_base += n_tt;
