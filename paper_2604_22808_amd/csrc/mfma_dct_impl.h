@@ -92,6 +92,12 @@ __device__ __forceinline__ void dct_pass(const Args a, const uint32_t n_tiles32,
   const int nn = lane & 31, g = lane >> 5;
   constexpr bool PERM_IN = MODE == DCT_GATHER, PERM_OUT = MODE == DCT_SCATTER || MODE == DCT_SCATTER_EN;
   constexpr bool ENERGY = MODE == DCT_SCATTER_EN, TOT = MODE == DCT_PLAIN_TOT;
+  // The epilogue takes its 32 rows eight at a time and leaves out those that are not kept (8 of 32 in a box of an axis of 16), and adds up
+  // the statistics four rows at a time: the passes over few rows are short of issue slots.  T pass with statistics of 66 tensors of
+  // 16 x 64 x 64 x 64 on the low+mid box 70 -> 50 us, without statistics 36 on the whole grid 81 -> 75.  Passes with statistics over more rows wait
+  // for memory, and lose 4 % by either (12 tensors of 64 x 128 x 128 x 128 428 -> 453 us).
+  constexpr bool QUADS = ENERGY && NI <= 32;
+  constexpr int GROUPS = ENERGY && !QUADS ? 1 : 4;
   const int NO = a.n_out;
   const int pscale = a.perm_scale > 1 ? a.perm_scale : 1;
   // transform matrix -> LDS, rows beyond n_out zero
@@ -311,14 +317,18 @@ __device__ __forceinline__ void dct_pass(const Args a, const uint32_t n_tiles32,
     // Router statistics (ENERGY): en[0] collects the squares of rows below t1, en[1] of rows below t2, en[2] of all rows;
     // the bands are differences of these.  The sums are taken inside the epilogue below, group of 32 rows by group, where
     // each accumulator register is read anyway and dies right after.
+    int t1 = 0, t2 = 0;   // less 4 g: to be compared with row numbers that are the same for all lanes
+    bool cut = false;
     float f1 = 0.f, f2 = 0.f;
     if (ENERGY) {
       // flat index over the two axes the pass does not transform (perm_o == tokens per slab row on this pass)
       const int32_t other = cur.pidx;
       const int u = other / a.en_div, v = other % a.en_div;
-      const int t1 = (u < a.low_u && v < a.low_v) ? a.low_a : 0;
-      const int t2 = (u < a.mid_u && v < a.mid_v) ? a.mid_a : 0;
-      f1 = (float)(t1 - 4 * g); f2 = (float)(t2 - 4 * g);
+      t1 = (u < a.low_u && v < a.low_v) ? a.low_a : 0;
+      t2 = (u < a.mid_u && v < a.mid_v) ? a.mid_a : 0;
+      cut = ((t1 | t2) & 3) != 0;
+      t1 -= 4 * g; t2 -= 4 * g;
+      f1 = (float)t1; f2 = (float)t2;
     }
 
     // epilogue: 32 output rows at a time through the staging buffer
@@ -338,27 +348,55 @@ __device__ __forceinline__ void dct_pass(const Args a, const uint32_t n_tiles32,
       }
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int rg = 0; rg < GROUPS; ++rg) {
+        const int k0 = mt * 32 + 32 / GROUPS * rg;   // first output row of the group
+        if (k0 >= NO) break;
+        float v2[2] = {0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = 8 * (r >> 2) + 4 * g + (r & 3);
-          const float val = acc[mt][nt][r];
-          if (ENERGY) {
-            // row = rc + 4*g; row < t  <=>  clamp(t - row, 0, 1) == 1 for integers (kept in floats: no lane masks to hold);
-            // rows >= n_out hold exact zeros
-            const float rc = (float)(mt * 32 + 8 * (r >> 2) + (r & 3));
-            const float w1 = __builtin_amdgcn_fmed3f(f1 - rc, 0.f, 1.f), w2 = __builtin_amdgcn_fmed3f(f2 - rc, 0.f, 1.f);
-            const float v2 = val * val;
-            en[0][nt] = fmaf(v2, w1, en[0][nt]);
-            en[1][nt] = fmaf(v2, w2, en[1][nt]);
-            en[2][nt] += v2;
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+          for (int r = 16 / GROUPS * rg; r < 16 / GROUPS * (rg + 1); ++r) {
+            const int row = 8 * (r >> 2) + 4 * g + (r & 3);
+            const float val = acc[mt][nt][r];
+            if (QUADS) {
+              v2[nt] = fmaf(val, val, v2[nt]);
+            } else if (ENERGY) {
+              // row < t  <=>  clamp(t - row, 0, 1) == 1 for integers (kept in floats: no lane masks to hold); rows >= n_out hold exact zeros
+              const float rc = (float)(mt * 32 + 8 * (r >> 2) + (r & 3));
+              const float w1 = __builtin_amdgcn_fmed3f(f1 - rc, 0.f, 1.f), w2 = __builtin_amdgcn_fmed3f(f2 - rc, 0.f, 1.f);
+              const float sq = val * val;
+              en[0][nt] = fmaf(sq, w1, en[0][nt]);
+              en[1][nt] = fmaf(sq, w2, en[1][nt]);
+              en[2][nt] += sq;
+            }
+            if (PERM_OUT) out_of_range = out_of_range || !(__builtin_fabsf(val) <= 65504.f);
+            uint16_t bits;
+            if (stage_bf16) bits = dct_f32_to_bf16(val);
+            else { const _Float16 hv = (_Float16)val; bits = __builtin_bit_cast(uint16_t, hv); }
+            Xo[row * DCT_XO_STRIDE + nt * 32 + nn] = bits;
           }
-          if (PERM_OUT) out_of_range = out_of_range || !(__builtin_fabsf(val) <= 65504.f);
-          uint16_t bits;
-          if (stage_bf16) bits = dct_f32_to_bf16(val);
-          else { const _Float16 hv = (_Float16)val; bits = __builtin_bit_cast(uint16_t, hv); }
-          Xo[row * DCT_XO_STRIDE + nt * 32 + nn] = bits;
+        if (QUADS) {
+          // This lane's four rows lie on one side of t1 and of t2 unless these are no multiples of 4.
+          const float w1 = k0 < t1 ? 1.f : 0.f, w2 = k0 < t2 ? 1.f : 0.f;
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) {
+            en[2][nt] += v2[nt];
+            if (!cut) {
+              en[0][nt] = fmaf(v2[nt], w1, en[0][nt]);
+              en[1][nt] = fmaf(v2[nt], w2, en[1][nt]);
+            } else {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float val = acc[mt][nt][4 * rg + r];
+                const int row = k0 + r;
+                en[0][nt] += row < t1 ? val * val : 0.f;
+                en[1][nt] += row < t2 ? val * val : 0.f;
+              }
+            }
+            asm volatile("" : "+v"(en[0][nt]), "+v"(en[1][nt]), "+v"(en[2][nt]));   // (summed here, so that the accumulators die here)
+          }
         }
+      }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -492,6 +530,7 @@ static hipError_t size_pass(const DctPassArgs& a, int num_cu, int* blocks_out, u
       }();
       const int64_t round = (int64_t)num_cu * places;
       if (blocks > round) blocks -= blocks % round;
+      else if (blocks > num_cu) blocks -= blocks % num_cu;
     }
   } else if (blocks > cap) {
     blocks = cap;

@@ -195,6 +195,20 @@ def test_routing_leaves_the_band_outputs_readable(path, monkeypatch):
         assert np.array_equal(ctx.read_spectral(3, h, h), before[h]), h
 
 
+# T axes that the statistics of a short pass add up four rows at a time, with band edges at multiples of 4 and between them (5.33 and 10 of
+# 16, 10.67 and 20 of 32), on the low+mid box and on the whole grid.  Tolerance as for the other statistics: 5e-3 on logarithms of energies of fp16 spectra.
+@pytest.mark.parametrize("low,mid", [((1, 4), (1, 2)), ((1, 3), (5, 8)), ((1, 16), (7, 16))])
+@pytest.mark.parametrize("grid,d", [((16, 16, 32), 64), ((16, 48, 32), 128), ((32, 32, 16), 64)])
+def test_router_statistics_at_band_edges(grid, d, low, mid, monkeypatch):
+    monkeypatch.setenv("FREQATTN_V_BOX", "1")
+    rng = np.random.default_rng(29)
+    q, k, v = (WL.round_to_io(rng.standard_normal((1, 3, int(np.prod(grid)), d)), "bf16") for _ in range(3))
+    band = dict(WL.WORKLOADS["16k"].band, low_num=low[0], low_den=low[1], mid_num=mid[0], mid_den=mid[1])
+    ctx = B.Context(1, 3, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    got = ctx.route_mlp(*(U.to_device(x, "bf16") for x in (q, k, v)), 0.5, *WL.router_weights())[2]
+    assert np.abs(got - O.band_statistics(q, k, v, grid, O.BandConfig(**band))).max() < 5e-3
+
+
 # planes of which the boxes go through the one-pass kernel and the whole does not, with a narrow and a wide low+mid box; the last
 # one goes through it whole
 @pytest.mark.parametrize("grid", [(16, 128, 64), (16, 128, 96), (16, 64, 128), (16, 32, 128)])
