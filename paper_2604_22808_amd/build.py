@@ -11,14 +11,14 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfreqattn.so")
-SOURCES = ["mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_wh_2.hip", "mfma_iwh.hip", "mfma_dct_plain.hip", "mfma_dct_plain_tot.hip",
+SOURCES = ["mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_wh_2.hip", "mfma_wh_3.hip", "mfma_iwh.hip", "mfma_dct_plain.hip", "mfma_dct_plain_tot.hip",
            "mfma_dct_scatter.hip",
            "mfma_dct_scatter_en.hip", "mfma_dct_gather.hip", "mfma_attn.hip", "mfma_vsum.hip", "mfma_gemm.hip", "api.cpp", "tables.cpp", "generic_kernels.hip",
            "generic_attn.hip", "generic_axis.hip", "mfma_dct.hip"]
 
 
 # Kernels that keep rows requested steps ahead in registers: a spilled register's reload would wait behind all of them.
-NO_SCRATCH = ("mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_wh_2.hip")
+NO_SCRATCH = ("mfma_wh_0.hip", "mfma_wh_1.hip", "mfma_wh_2.hip", "mfma_wh_3.hip")
 
 
 def hipcc() -> str:

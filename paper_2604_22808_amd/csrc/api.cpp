@@ -849,7 +849,23 @@ static hipError_t transform_classes(Ctx& c, const TransformClass* cls, int ncls,
     int at[3], m = 0, slots[3] = {0, 0, 0};
     for (int j = i; j >= 0; --j)
       if (!done[j] && (j == i || (wh_items(f[j]) < 2 * c.num_cu && f[j].out_rows <= f[i].out_rows))) { sub[m] = f[j]; at[m++] = j; done[j] = true; }
-    if ((e = launch_wh_pass(sub, m, c.num_cu, st, slots)) != hipSuccess) return e;
+    // The next class, if it runs alone as well, in the same launch, before this one: it keeps less
+    int two = -1;
+    if (m == 1 && i > 0 && !done[i - 1] && wh_two_fits(f[i - 1], f[i], c.num_cu)) {
+      two = i - 1;
+      for (int j = i - 2; j >= 0; --j)
+        if (wh_items(f[j]) < 2 * c.num_cu && f[j].out_rows <= f[two].out_rows) two = -1;   // (it has company)
+    }
+    if (two >= 0) {
+      done[two] = true;
+      sub[1] = sub[0]; sub[0] = f[two];
+      at[1] = at[0]; at[0] = two;
+      m = 2;
+      e = launch_wh_two(sub[0], sub[1], c.num_cu, st, slots);
+    } else {
+      e = launch_wh_pass(sub, m, c.num_cu, st, slots);
+    }
+    if (e != hipSuccess) return e;
     for (int j = 0; j < m; ++j)
       if (who[at[j]]->tot_slot >= 0) c.tot_waves[who[at[j]]->tot_slot] = slots[j];
   }

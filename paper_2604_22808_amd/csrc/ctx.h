@@ -366,6 +366,9 @@ hipError_t launch_wh_pass_1(const WhPassArgs* subs, int n, int num_cu, hipStream
 inline hipError_t launch_wh_pass(const WhPassArgs* subs, int n, int num_cu, hipStream_t st, int* slots_out) {
   return subs[0].cols <= 64 ? launch_wh_pass_0(subs, n, num_cu, st, slots_out) : launch_wh_pass_1(subs, n, num_cu, st, slots_out);
 }
+// Two forward passes one after the other in one launch, the first on a box of at most 32 rows, the second keeping more than 32.
+bool wh_two_fits(const WhPassArgs& a, const WhPassArgs& b, int num_cu);
+hipError_t launch_wh_two(const WhPassArgs& a, const WhPassArgs& b, int num_cu, hipStream_t st, int slots_out[2]);
 bool hw_fits(const WhPassArgs& a);   // whether the inverse takes these sizes and is faster than an axis at a time
 hipError_t launch_hw_inverse(const WhPassArgs* subs, int n, int num_cu, hipStream_t st);
 // H and W axes of the inverse transform in one pass (mfma_iwh_impl.h).

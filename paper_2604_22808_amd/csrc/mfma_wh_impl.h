@@ -70,7 +70,7 @@ struct WhLaunch { WhPassArgs sub[3]; int first[4]; };
 
 // Workgroup `block` of the `blocks` of a pass.
 template <int NW16, int KT, int KH, bool INV>
-__device__ __forceinline__ void wh_pass(const WhPassArgs& a, const int block, const int blocks) {
+__device__ __forceinline__ void wh_pass(const WhPassArgs& a, const int block, const int blocks, const int tid = threadIdx.x) {
   constexpr int W = 16 * NW16;                 // positions (inverse: coefficients) of an input row
   constexpr int TERMS = INV ? 1 : 2;           // terms the W matrix is split into
   constexpr int KW = (NW16 + 1) / 2;           // steps of 32 positions w per row (the last one of 16 when NW16 is odd)
@@ -84,7 +84,7 @@ __device__ __forceinline__ void wh_pass(const WhPassArgs& a, const int block, co
   float* tot = (float*)(Aw + KT * KW * TERMS * 64);             // [wave][64]: sums of squares of the rows a wave has taken
   half_t* Mh = (half_t*)(tot + WH_WAVES * 64);                  // [16 KH][mstr]
   const int mstr = a.rows + 8;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q = lane >> 4;
 
@@ -536,6 +536,54 @@ static hipError_t wh_dispatch(const WhPassArgs* subs, int n, int num_cu, hipStre
   if (kh == 3) return wh_launch<NW16, 1, 3, INV>(subs, n, num_cu, st, slots_out);
   if (kh == 4) return wh_launch<NW16, 1, 4, INV>(subs, n, num_cu, st, slots_out);
   return hipErrorInvalidValue;
+}
+
+// Two passes, one after the other in every workgroup: the first with tiles of 2 x 2, the second with 1 x KH.
+//
+// What it saves is the last round of each.  A workgroup holds a compute unit for whole items, and those of a pass seldom come out even:
+// 66 tensors of 16 x 64 x 64 x 64 on the low+mid box are 1,056 on 256 workgroups, five rounds for four and an eighth; the whole of
+// six more 384 smaller ones, two rounds for one and a half.  The second pass is dealt to the workgroups from the other end, and not to those
+// with one item more of the first where that costs it no round: 168 + 42 us apart, 178 together (the forward 580 -> 556).  With many
+// rounds there is little to save (64^3 x 128, 66 tensors on the box and 6 whole: 1,342 us apart, 1,320 together).
+template <int NW16, int KH>
+__global__ void __launch_bounds__(64 * WH_WAVES, 2) k_wh_two(WhLaunch m) {
+  const int blocks = m.first[1];
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    int i = pass, tid = threadIdx.x;
+    asm volatile("" : "+s"(i), "+v"(tid));   // (what a pass needs is made in it, and not kept for both)
+    if (pass == 0) {
+      wh_pass<NW16, 2, 2, false>(m.sub[i], (int)blockIdx.x, blocks, tid);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (before the second one writes where others still read)
+    } else {
+      const int block = ((blocks >> 3) - 1 - (int)(blockIdx.x >> 3)) * 8 + (int)(blockIdx.x & 7);   // (of the same XCD)
+      if (block < m.first[2]) wh_pass<NW16, 1, KH, false>(m.sub[i], block, m.first[2], tid);
+    }
+  }
+}
+
+template <int NW16, int KH>
+static hipError_t wh_two_launch(const WhPassArgs& a, const WhPassArgs& b, int num_cu, hipStream_t st, int slots_out[2]) {
+  WhLaunch ma, mb;
+  int lds_a, lds_b;
+  hipError_t e = wh_size<NW16, 2, 2, false>(&a, 1, num_cu, 2, &ma, &lds_a, &slots_out[0]);
+  if (e == hipSuccess) e = wh_size<NW16, 1, KH, false>(&b, 1, num_cu, 2, &mb, &lds_b, &slots_out[1]);
+  if (e != hipSuccess) return e;
+  const int blocks = ma.first[3];
+  if (blocks == 0 || mb.first[3] != blocks) return hipErrorInvalidValue;   // (wh_two_fits: both fill the chip)
+  const int per = blocks / 8;   // workgroups of an XCD
+  auto items = [](const WhPassArgs& x) { return (((int64_t)x.seg_end[2] * x.T * (x.d / 64) + 7) / 8) * x.members; };   // (of the fullest)
+  const int64_t over = items(ma.sub[0]) % per, n_b = items(mb.sub[0]);
+  int blocks_b = blocks;
+  if (over > 0 && (n_b + per - over - 1) / (per - over) == (n_b + per - 1) / per) blocks_b = 8 * (int)(per - over);
+  slots_out[1] = blocks_b * WH_WAVES;
+  ma.sub[1] = mb.sub[0];
+  ma.first[2] = blocks_b;   // (here: workgroups of the second pass)
+  static OncePerDevice limit;
+  e = allow_lds(limit, (const void*)k_wh_two<NW16, KH>, 160 * 1024);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_wh_two<NW16, KH>), dim3((unsigned)blocks), dim3(64 * WH_WAVES), (size_t)std::max(lds_a, lds_b), st, ma);
+  return hipGetLastError();
 }
 
 }  // namespace

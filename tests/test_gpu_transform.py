@@ -179,6 +179,26 @@ def test_shared_launches_give_the_bits_of_launches_of_their_own(grid, d, alloc):
         assert torch.equal(out[0, h], alone[0, 0]), (h, float((out[0, h].float() - alone[0, 0].float()).abs().max()))
 
 
+# low+mid boxes and whole grids of enough slices to fill the chip, which go through one launch: three and four tiles of rows, W with and
+# without a remainder of a step, items that come out even and not
+@pytest.mark.parametrize("grid,mid,high", [((16, 64, 64), 11, 2), ((16, 64, 48), 16, 3), ((16, 48, 80), 7, 2), ((16, 48, 96), 6, 3), ((16, 64, 112), 6, 1),
+                                           ((32, 64, 128), 4, 2)])
+def test_boxes_and_whole_grids_in_one_launch(grid, mid, high):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(37)
+    N, d, n = int(np.prod(grid)), 64, mid + high
+    alloc = (2,) * mid + (4,) * high
+    q, k, v = ((0.5 * torch.randn((1, n, N, d), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(3))
+    cfg = B.make_cfg(**dict(WL.WORKLOADS["16k"].band, n_summary=0))   # (sums over tokens are split by the number of slices)
+    ctx, one = B.Context(1, n, d, grid, B.BF16, cfg, path=B.PATH_MFMA), B.Context(1, 1, d, grid, B.BF16, cfg, path=B.PATH_MFMA)
+    out, alone = torch.empty_like(q), torch.empty((1, 1, N, d), dtype=torch.bfloat16, device="cuda")
+    ctx.forward(q, k, v, alloc, out)
+    for h in range(n):
+        one.forward(*(x[:, h:h + 1].contiguous() for x in (q, k, v)), alloc[h:h + 1], alone)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0, h], alone[0, 0]), (h, float((out[0, h].float() - alone[0, 0].float()).abs().max()))
+
+
 @pytest.mark.parametrize("path", [B.PATH_MFMA, B.PATH_GENERIC])
 def test_routing_leaves_the_band_outputs_readable(path, monkeypatch):
     """The transforms of a routing call that is no forward use scratch that is not the last forward's result."""
