@@ -50,7 +50,8 @@ __device__ __forceinline__ int nth_set_bit(const uint64_t bits[4], int j) {
 
 struct VsumBits { uint64_t w[4]; };
 
-template <int D>
+// MU: groups of 32 chunks that are summed.
+template <int D, int MU>
 __global__ void __launch_bounds__(256, 2) k_vsum(const uint16_t* __restrict__ V, const uint16_t* __restrict__ Wsum,
                                                  float* __restrict__ part, VsumBits sel, int nsel, int64_t N,
                                                  int tiles_per_split, int nsplit) {
@@ -61,10 +62,10 @@ __global__ void __launch_bounds__(256, 2) k_vsum(const uint16_t* __restrict__ V,
   constexpr int CPR = D / 8;        // 16-byte chunks per V row
   constexpr int RPI = 64 / CPR;     // V rows per copy instruction
   constexpr int NIW = KT / (RPI * 4);   // V copy instructions per wave and tile
-  constexpr int PW = NIW + 2;       // copy instructions per wave and tile: V rows, then two of the weight tile's eight
+  constexpr int PW = NIW + MU;      // copy instructions per wave and tile: V rows, then its share of the weight tile's rows that count
   constexpr int NB = 3;             // tiles in LDS: one in use, two on their way
   __shared__ __attribute__((aligned(16))) uint16_t Vt3[NB][KT * D];
-  __shared__ __attribute__((aligned(16))) uint16_t Wt3[NB][64 * KT];   // [chunk u][64 tokens], 16-byte pieces at c ^ (u & 7)
+  __shared__ __attribute__((aligned(16))) uint16_t Wt3[NB][32 * MU * KT];   // [chunk u][64 tokens], 16-byte pieces at c ^ (u & 7)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nn = lane & 31, g = lane >> 5;
   const int jsel = blockIdx.x % nsel, split = blockIdx.x / nsel;
@@ -89,15 +90,15 @@ __global__ void __launch_bounds__(256, 2) k_vsum(const uint16_t* __restrict__ V,
       vs_lds_dma16(Vs + (tile * KT + r) * D + ((c ^ fV(r)) << 3), Vt3[buf] + rowbase * D);
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {   // weight tile: 8 rows of 128 bytes per instruction
-      const int rowbase = (wave * 2 + j) * 8;
+    for (int j = 0; j < MU; ++j) {   // weight tile: 8 rows of 128 bytes per instruction
+      const int rowbase = (wave * MU + j) * 8;
       const int u = rowbase + (lane >> 3), c = lane & 7;
       vs_lds_dma16(Wsum + tile * (64 * KT) + u * KT + ((c ^ (u & 7)) << 3), Wt3[buf] + rowbase * KT);
     }
   };
-  float16v acc[2];
+  float16v acc[MU];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < MU; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
   // the copies of a wave complete in the order they were issued: waiting until at most PW are outstanding leaves only
@@ -130,7 +131,7 @@ __global__ void __launch_bounds__(256, 2) k_vsum(const uint16_t* __restrict__ V,
       }
       const bf16x8 A = __builtin_bit_cast(bf16x8, a4);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < MU; ++j) {
         const int u = 32 * j + nn;
         const uint4v b4 = *(const uint4v*)(Wt + u * KT + (((2 * ks + g) ^ (u & 7)) << 3));
         acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, __builtin_bit_cast(bf16x8, b4), acc[j], 0, 0, 0);
@@ -143,7 +144,7 @@ __global__ void __launch_bounds__(256, 2) k_vsum(const uint16_t* __restrict__ V,
   // partial sums: part[jsel][split * SUBS + sub][ch][u]
   float* dst = part + ((int64_t)(jsel * nsplit * SUBS + split * SUBS + sub) * D) * 64;
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < MU; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int ch = 32 * dt + 8 * (r >> 2) + 4 * g + (r & 3);
@@ -186,10 +187,10 @@ hipError_t launch_vsum(const void* V, const void* Wsum, float* part, void* C, co
   const int64_t ntiles = N / 64;
   const int tps = (int)((ntiles + nsplit - 1) / nsplit);   // (the caller sized `part` for nsel * nsplit token ranges)
   const dim3 grid((unsigned)(nsel * nsplit));
-  if (d == 128)
-    hipLaunchKernelGGL(k_vsum<128>, grid, dim3(256), 0, st, (const uint16_t*)V, (const uint16_t*)Wsum, part, b, nsel, N, tps, nsplit);
-  else
-    hipLaunchKernelGGL(k_vsum<64>, grid, dim3(256), 0, st, (const uint16_t*)V, (const uint16_t*)Wsum, part, b, nsel, N, tps, nsplit);
+  // (up to 32 chunks: the other half of the weights, a fifth to a third of what is copied into LDS, and of the products stays out)
+  const bool half = m_eff[2] <= 32;
+  const auto k = d == 128 ? (half ? k_vsum<128, 1> : k_vsum<128, 2>) : (half ? k_vsum<64, 1> : k_vsum<64, 2>);
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, (const uint16_t*)V, (const uint16_t*)Wsum, part, b, nsel, N, tps, nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int nparts = nsplit * (d == 128 ? 1 : 2);

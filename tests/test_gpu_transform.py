@@ -229,6 +229,21 @@ def test_router_statistics_at_band_edges(grid, d, low, mid, monkeypatch):
     assert np.abs(got - O.band_statistics(q, k, v, grid, O.BandConfig(**band))).max() < 5e-3
 
 
+# High-band summaries from the untransformed V of slices that do not run it: one and two groups of 32 chunks.  Tolerance as for the other
+# forwards (bf16 rounding of the output 1.6e-3, fp16 spectra 4.6e-4; relative L2 3e-3).
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("m", [1, 31, 32, 33, 64])
+def test_summaries_of_bands_that_no_slice_runs(m, d, monkeypatch):
+    monkeypatch.setenv("FREQATTN_V_BOX", "1")
+    rng = np.random.default_rng(41)
+    grid, alloc = (16, 16, 32), (1, 2, 3)
+    q, k, v = (WL.round_to_io(rng.standard_normal((1, 3, int(np.prod(grid)), d)), "bf16") for _ in range(3))
+    band = dict(WL.WORKLOADS["16k"].band, n_summary=m)
+    ctx = B.Context(1, 3, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    got = U.run_forward(ctx, q, k, v, "bf16", alloc)
+    assert U.errors(got, O.forward(q, k, v, grid, O.BandConfig(**band), alloc))[1] < 3e-3
+
+
 # planes of which the boxes go through the one-pass kernel and the whole does not, with a narrow and a wide low+mid box; the last
 # one goes through it whole
 @pytest.mark.parametrize("grid", [(16, 128, 64), (16, 128, 96), (16, 64, 128), (16, 32, 128)])
