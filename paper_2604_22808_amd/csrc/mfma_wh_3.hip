@@ -5,6 +5,8 @@ bool wh_two_fits(const WhPassArgs& a, const WhPassArgs& b, int num_cu) {
   int kt_a, kh_a, kt_b, kh_b;
   wh_tiles(a, &kt_a, &kh_a, nullptr);
   wh_tiles(b, &kt_b, &kh_b, nullptr);
+  // (Up to 16 rounds together: beyond, the two last rounds are little.  64^3 x 128, 33 + 12 full rounds: the forward within 0.5 % either way.)
+  if ((int64_t)wh_items(a) + wh_items(b) > 16 * (int64_t)num_cu) return false;
   return a.cols == b.cols && a.T == b.T && a.d == b.d && kt_a == 2 && kh_a == 2 && kt_b == 1 && kh_b >= 3 && wh_items(a) >= num_cu && wh_items(b) >= num_cu;
 }
 hipError_t launch_wh_two(const WhPassArgs& a, const WhPassArgs& b, int num_cu, hipStream_t st, int slots_out[2]) {

@@ -543,8 +543,7 @@ static hipError_t wh_dispatch(const WhPassArgs* subs, int n, int num_cu, hipStre
 // What it saves is the last round of each.  A workgroup holds a compute unit for whole items, and those of a pass seldom come out even:
 // 66 tensors of 16 x 64 x 64 x 64 on the low+mid box are 1,056 on 256 workgroups, five rounds for four and an eighth; the whole of
 // six more 384 smaller ones, two rounds for one and a half.  The second pass is dealt to the workgroups from the other end, and not to those
-// with one item more of the first where that costs it no round: 168 + 42 us apart, 178 together (the forward 580 -> 556).  With many
-// rounds there is little to save (64^3 x 128, 66 tensors on the box and 6 whole: 1,342 us apart, 1,320 together).
+// with one item more of the first where that costs it no round: 168 + 42 us apart, 178 together (the forward 580 -> 556).
 template <int NW16, int KH>
 __global__ void __launch_bounds__(64 * WH_WAVES, 2) k_wh_two(WhLaunch m) {
   const int blocks = m.first[1];
