@@ -365,11 +365,8 @@ def main():
     # of slices too small to fill the chip share launches with the class that keeps the most: where one is that small the
     # launches are not counted (None).
     T, H, W = wl.grid
-    def passes(n_in, n_out):   # the axis pass exists: any number of rows for powers of two, square otherwise
-        return n_in & (n_in - 1) == 0 or (n_out + 31) // 32 == (n_in + 31) // 32
-    def kept(num):   # coefficients kept per axis for the box num/4 of it
-        rounded = [min(n, -(-(-(-num * n // 4)) // 16) * 16) for n in (T, H, W)]
-        return [r if passes(n, r) and passes(r, n) else n for r, n in zip(rounded, (T, H, W))]
+    def kept(num):   # coefficients kept per axis for the box num/4 of it, to whole tiles of 16
+        return [min(n, -(-(-(-num * n // 4)) // 16) * 16) for n in (T, H, W)]
     low_k, mid_k, full_k = kept(1), kept(2), [T, H, W]
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     def shares(classes):   # (slices of all tensors, box) per class, the one that keeps the most last
@@ -400,6 +397,10 @@ def main():
                     + inv_group(lambda m: m & 4, full_k) + (1 if any(m == 0 for m in masks) else 0))
     if shares(fwd_classes):
         fwd_launches = None
+    elif fwd_classes[-2][0] > 0 and fwd_classes[-1][0] > 0 and 32 < H <= 64 and W > 32:
+        # the W + H passes of the low+mid box and of the whole grid in one launch, if they are few (wh_two_fits in csrc/mfma_wh_3.hip)
+        items = [n * (wl.head_dim // 64) * T * parts for (n, _), parts in zip(fwd_classes[-2:], (-(-W // 64), W // 16))]
+        fwd_launches -= cus <= items[1] and sum(items) <= 16 * cus
     if shares(list(zip(n_cls, (low_k, mid_k, full_k)))):
         inv_launches = None
     # single-band slices run their exchange inside the band items: its flops then belong to the band attention launch
