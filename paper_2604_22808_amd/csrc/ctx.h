@@ -210,6 +210,13 @@ struct AxisPairArgs {
   int in_bf16, out_bf16;
   AxisBoxes box;            // (forward)
 };
+// Rows kt of the T axis that the pass keeps in LDS when KT of them are wanted.  The products along H take rows in fours, so those of the last
+// kt read up to row 4 ceil(H / 4) - 1 from its first: up to three rows on, which are as many kt where H is 1 and one kt where it is more.  (The
+// matrix is zero there, but zero times what another kernel left in LDS is not if that is no number.)  Behind row T lies the H matrix.
+constexpr int th_rows(int T, int H, int KT) {
+  const int last = (KT - 1) * H + (H + 3) / 4 * 4 - 1;   // last row (kt, h) that is read
+  return KT <= 0 ? 0 : last / H + 1 < T ? last / H + 1 : T;
+}
 bool generic_pair_fits(const AxisPairArgs& a);   // whether the pass takes these sizes and is the faster way
 hipError_t allow_generic_axis_pair();            // lets its kernels ask for their LDS (when a context is set up: its calls may be captured)
 hipError_t launch_generic_axis_pair(const AxisPairArgs& a, hipStream_t st);

@@ -216,6 +216,7 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   const int64_t col = (int64_t)blockIdx.x * 64 + 4 * n;
   const int mask = tensor < a.box.n ? a.box.masks[slice] : 0;
   const int KT = tensor < a.box.n ? gx_extent(a.box, tensor, mask, 0) : T, KH = tensor < a.box.n ? gx_extent(a.box, tensor, mask, 1) : H;   // coefficients made
+  const int t_rows = th_rows(T, H, KT);   // rows kt that the H axis reads
   const int nlive = (int)(a.inner - col < 4 ? a.inner - col : 4);   // columns of this lane's four that exist (VEC: all or none)
   const int64_t base = (int64_t)slice * T * H * a.inner + col;
   const char* in = (const char*)a.in[tensor] + base * IE;
@@ -271,7 +272,7 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
       if (hb + 2 * NWAVE < H) load(hb + 2 * NWAVE, x[b]);
 #pragma unroll
       for (int r = 0; r < 4; ++r)   // result row 4 g + r
-        if (4 * g + r < T && 4 * g + r <= KT) *(float4v*)(Y + ((4 * g + r) * H + hb) * 64 + 4 * n) = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+        if (4 * g + r < t_rows) *(float4v*)(Y + ((4 * g + r) * H + hb) * 64 + 4 * n) = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
     }
   __syncthreads();
   const int tiles = (KH + 15) / 16;
@@ -284,8 +285,8 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
     const float* m = Mh + (16 * tile + n) * mstr + g * rh;
 #pragma unroll 4
     for (int r = 0; r < rh; ++r) {
-      // (rows past the axis: the matrix is zero there, and what lies behind is a row of the next kt - made for this if it is not needed
-      // itself - or of the matrix)
+      // (rows past the axis: the matrix is zero there, and what lies behind is a row of a later kt - made for this if it is not needed
+      // itself, see th_rows - or of the matrix)
       const float A = m[r];
       const float4v b = *(const float4v*)(y + r * 64);
 #pragma unroll

@@ -213,18 +213,22 @@ def test_more_than_256_slices(dtype, path, grid, d):
 
 
 # every mask of a slice's bands beside slices that need everything: coefficients that are not made (boxes of one row too, Q~ and K~ of an
-# idle slice) must not reach an output, whatever lies in the scratch; grids whose T and H axes go in one pass and in two
-@pytest.mark.parametrize("grid,d", [((9, 10, 13), 64), ((3, 4, 5), 30), ((5, 13, 24), 50), ((17, 6, 11), 64), ((2, 65, 13), 64)])
+# idle slice) must not reach an output, whatever lies in the scratch and in LDS; grids whose T and H axes go in one pass and in two, axes of
+# length one and H axes around the four rows that a product takes
+@pytest.mark.parametrize("grid,d", [((9, 10, 13), 64), ((3, 4, 5), 250), ((5, 13, 24), 50), ((17, 6, 11), 64), ((2, 65, 13), 64), ((16, 1, 67), 64),
+                                    ((3, 1, 400), 64), ((15, 2, 40), 64), ((7, 3, 61), 64), ((1, 9, 130), 64), ((8, 40, 1), 250)])
 @pytest.mark.parametrize("bands", [3, 4])
 def test_generic_boxes_of_all_masks(grid, d, bands):
     import torch
     rng = np.random.default_rng(10)
-    N, alloc = int(np.prod(grid)), tuple(range(1 << bands))
+    N = int(np.prod(grid))
+    alloc = tuple(range(1 << bands)) * -(-(1 << 19) // (N * d << bands))
+    assert len(alloc) * N * d >= 1 << 19   # (below, everything is made)
     cfgd = dict(WL.WORKLOADS["tiny_f32"].band, n_summary=3, **(dict(mid2_num=3, mid2_den=4) if bands == 4 else {}))
     ctx = B.Context(1, len(alloc), d, grid, B.F32, B.make_cfg(**cfgd), path=B.PATH_GENERIC)
     q, k, v = (0.7 * rng.standard_normal((1, len(alloc), N, d)).astype(np.float32).astype(np.float64) for _ in range(3))
     nan = np.full_like(q, np.nan)
-    U.run_forward(ctx, nan, nan, nan, "f32", (alloc[-1],) * len(alloc))   # (leaves NaN in all of the scratch)
+    U.run_forward(ctx, nan, nan, nan, "f32", (alloc[-1],) * len(alloc))   # (leaves NaN in all of the scratch, and where its last pass kept the tensor between T and H)
     got = U.run_forward(ctx, q, k, v, "f32", alloc)
     mx, rl = U.errors(got, O.forward(q, k, v, grid, U.oracle_cfg(cfgd), alloc))
     print(f"generic boxes {grid} d={d} bands={bands}: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)

@@ -24,12 +24,42 @@ int main() {   // lines "direction W d chosen refused"; launches of no slices: t
 """
 
 
-def test_what_the_one_pass_transforms_are_chosen_for_they_take(tmp_path):
-    (tmp_path / "t.cpp").write_text(PROGRAM)
+def _run(program, tmp_path):
+    (tmp_path / "t.cpp").write_text(program)
     lib = Path(B.LIB_PATH).parent
     subprocess.check_call([hipcc(), "-std=c++17", "--offload-host-only", f"-I{ROOT / 'include'}", f"-I{lib / 'csrc'}", str(tmp_path / "t.cpp"),
                            "-o", str(tmp_path / "t"), f"-L{lib}", "-lfreqattn", f"-Wl,-rpath,{lib}"])
-    lines = [line.split() for line in subprocess.check_output([str(tmp_path / "t")], text=True).splitlines()]
+    return [line.split() for line in subprocess.check_output([str(tmp_path / "t")], text=True).splitlines()]
+
+
+# rows (kt, h) in LDS that the H axis of the generic T + H pass reads for `KT` rows kt: lane group g takes rows g R .. g R + R - 1 of each kt
+PAIR_PROGRAM = r"""
+#include <cstdio>
+#include "ctx.h"
+using namespace fa;
+int main() {
+  for (int T = 1; T <= 16; ++T)
+    for (int H = 1; H <= 64; ++H)
+      for (int KT = 0; KT <= T; ++KT) {
+        const int R = (H + 3) / 4, ldh = (H + 15) / 16 * 16, made = th_rows(T, H, KT);
+        bool ok = made >= KT && made <= T;
+        for (int kt = 0; kt < KT; ++kt)
+          for (int j = 0; j < 4 * R; ++j) {
+            const int row = kt * H + j;
+            ok = ok && (row < T * H ? row / H < made : (row + 1 - T * H) * 64 <= ldh * (ldh + 4));   // (made, or of the matrix behind)
+          }
+        if (!ok) std::printf("%d %d %d\n", T, H, KT);
+      }
+}
+"""
+
+
+def test_rows_that_the_generic_pair_of_axes_reads_are_made(tmp_path):
+    assert _run(PAIR_PROGRAM, tmp_path) == []
+
+
+def test_what_the_one_pass_transforms_are_chosen_for_they_take(tmp_path):
+    lines = _run(PROGRAM, tmp_path)
     took = {"f": {}, "i": {}}
     for way, w, d, chosen, refused in lines:
         assert not (chosen == "1" and refused == "1"), (way, w, d)
