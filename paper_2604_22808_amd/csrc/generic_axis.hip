@@ -192,7 +192,7 @@ hipError_t launch_kt(const AxisPassArgs& a, int64_t ncols, bool vec, hipStream_t
 }
 
 // T and H axes in one pass:  out[s, kt, kh, i] = sum_h Mh[kh][h] sum_t Mt[kt][t] in[s, t, h, i],  the tensor between the axes in LDS.
-// A workgroup of 8 waves owns 64 columns i of one slice, all T H rows of them: a wave takes the T axis of one row h after the other
+// A workgroup of up to 8 waves owns 64 columns i of one slice, all T H rows of them: a wave takes the T axis of one row h after the other
 // from memory (lane (n, g) holds columns 4 n .. 4 n + 3 of its rows), leaves the results in LDS as [kt][h][64], and takes
 // the H axis of (kt, 16 output rows) one after the other from there.  Product r of R = ceil(n / 4) takes rows j = g R + r, so an axis of n
 // takes R products and not whole steps of 16.  (Against 64 bits both orders come out the same: mean over
@@ -206,7 +206,8 @@ hipError_t launch_kt(const AxisPassArgs& a, int64_t ncols, bool vec, hipStream_t
 template <int IN, int OUT, bool VEC>
 __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   extern __shared__ __attribute__((aligned(16))) float th_smem[];
-  constexpr int NWAVE = 8, IE = IN ? 2 : 4, OE = OUT ? 2 : 4;
+  constexpr int IE = IN ? 2 : 4, OE = OUT ? 2 : 4;
+  const int n_waves = (int)blockDim.x >> 6;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int T = a.T, H = a.H, mstr = a.ldh + 4, rt = (T + 3) / 4, rh = (H + 3) / 4;
@@ -245,21 +246,21 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
   };
   float4v x[2][4];
   if (wave < H) load(wave, x[0]);
-  if (wave + NWAVE < H) load(wave + NWAVE, x[1]);
+  if (wave + n_waves < H) load(wave + n_waves, x[1]);
   if (KT == 0) return;   // (uniform over the workgroup; behind the loads, which need not wait for the mask)
   float At[4];   // operand of the T matrix (padded with zeros to 16 x 16)
 #pragma unroll
   for (int r = 0; r < 4; ++r) At[r] = r < rt ? a.Mt[n * a.ldt + g * rt + r] : 0.f;
-  for (int e = tid; e < a.ldh * (mstr / 4); e += 512) {   // (the padding too: the last rows' products below reach into it)
+  for (int e = tid; e < a.ldh * (mstr / 4); e += (int)blockDim.x) {   // (the padding too: the last rows' products below reach into it)
     const int row = e / (mstr / 4), c4 = e % (mstr / 4) * 4;
     float4v m = {0.f, 0.f, 0.f, 0.f};
     if (c4 < a.ldh) m = *(const float4v*)(a.Mh + row * a.ldh + c4);
     *(float4v*)(Mh + row * mstr + c4) = m;
   }
-  for (int h = wave; h < H; h += 2 * NWAVE)
+  for (int h = wave; h < H; h += 2 * n_waves)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const int hb = h + b * NWAVE;
+      const int hb = h + b * n_waves;
       if (hb >= H) break;   // (uniform)
       float4v acc[4];
 #pragma unroll
@@ -269,14 +270,14 @@ __global__ void __launch_bounds__(512) k_gaxis_th(AxisPairArgs a) {
         if (r < rt)
 #pragma unroll
           for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[r], x[b][r][c], acc[c], 0, 0, 0);
-      if (hb + 2 * NWAVE < H) load(hb + 2 * NWAVE, x[b]);
+      if (hb + 2 * n_waves < H) load(hb + 2 * n_waves, x[b]);
 #pragma unroll
       for (int r = 0; r < 4; ++r)   // result row 4 g + r
         if (4 * g + r < t_rows) *(float4v*)(Y + ((4 * g + r) * H + hb) * 64 + 4 * n) = float4v{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
     }
   __syncthreads();
   const int tiles = (KH + 15) / 16;
-  for (int u = wave; u < KT * tiles; u += NWAVE) {
+  for (int u = wave; u < KT * tiles; u += n_waves) {
     const int kt = u / tiles, tile = u - kt * tiles;
     float4v acc[4];
 #pragma unroll
@@ -349,7 +350,10 @@ hipError_t launch_generic_axis_pair(const AxisPairArgs& a, hipStream_t st) {
   if (!generic_pair_fits(a) || a.ldt < 16 || a.ldh < a.H || a.ldh % 16 != 0 || (a.in_bf16 && a.out_bf16)) return hipErrorInvalidValue;
   const int lds = (a.T * a.H * 64 + a.ldh * (a.ldh + 4)) * 4;
   const ThKernel k = th_kernel[a.in_bf16 ? 0 : a.out_bf16 ? 1 : 2][gx_aligned(a.d, a.in, a.out, a.n_tensors, a.in_bf16, a.out_bf16)];
-  hipLaunchKernelGGL(k, dim3((unsigned)((a.inner + 63) / 64), (unsigned)a.slices, (unsigned)a.n_tensors), dim3(512), (size_t)lds, st, a);
+  // No more waves than there are rows or row tiles, and four rows for each: 1 x 1 x 1000 x 4 heads x 64 with eight waves 409 us a forward, with one 360 (an
+  // axis at a time 373); 2 x 4 x 1000 475 / 432 (470), 16 x 1 x 1000 594 / 549 (634), 1 x 16 x 64 59 / 58 (72).
+  const int waves = std::min({8, std::max(a.H, a.T * (a.ldh / 16)), (a.T * a.H + 3) / 4});
+  hipLaunchKernelGGL(k, dim3((unsigned)((a.inner + 63) / 64), (unsigned)a.slices, (unsigned)a.n_tensors), dim3(64 * waves), (size_t)lds, st, a);
   return hipGetLastError();
 }
 
