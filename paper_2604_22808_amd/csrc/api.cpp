@@ -1625,6 +1625,12 @@ static int build_gemm_tables(Ctx& c, bool fold) {
   half_t* X = (half_t*)c.projX;
   int np = 0, ns = 0;
   c.gemm_groups.clear();
+  auto steps = [&](int p) {
+    const GemmProblem& pr = c.h_gemm_prob[p];
+    int k = 0;
+    for (int s = 0; s < pr.nseg; ++s) k += c.h_gemm_seg[pr.seg0 + s].K;
+    return k / 64;
+  };
   auto hull = [&](int h, int64_t& r0, int64_t& r1) -> bool {
     const int mask = c.h_alloc[(size_t)h];
     int lo = -1, hi = -1;
@@ -1652,7 +1658,7 @@ static int build_gemm_tables(Ctx& c, bool fold) {
           c.h_gemm_prob[np++] = GemmProblem{spec, d, (int)(r1 - r0), d, ns++, 1, 0};
         }
       }
-      c.gemm_groups.push_back({first, np - first, (int)(r1 - r0), d, 0});
+      c.gemm_groups.push_back({first, np - first, (int)(r1 - r0), d, steps(first), 0});
     }
     if (!fold) {
       const int first = np;
@@ -1661,7 +1667,7 @@ static int build_gemm_tables(Ctx& c, bool fold) {
         c.h_gemm_seg[ns] = GemmSeg{X + (int64_t)b * c.N * dm, c.projWv + (size_t)h * d * dm, dm, dm, dm, 0};
         c.h_gemm_prob[np++] = GemmProblem{(half_t*)c.specV + slice * c.N * d, d, (int)c.N, d, ns++, 1, 0};
       }
-      c.gemm_groups.push_back({first, heads, (int)c.N, d, 0});
+      c.gemm_groups.push_back({first, heads, (int)c.N, d, steps(first), 0});
     }
   }
   bool passing[NBMAX] = {false, false, false, false};
@@ -1675,7 +1681,7 @@ static int build_gemm_tables(Ctx& c, bool fold) {
       if (ns == seg0) continue;
       passing[l] = true;
       c.h_gemm_prob[np] = GemmProblem{c.projM + (size_t)l * dm * dm, dm, dm, dm, seg0, ns - seg0, 0};
-      c.gemm_groups.push_back({np, 1, dm, dm, 2});
+      c.gemm_groups.push_back({np, 1, dm, dm, steps(np), 2});
       ++np;
     }
   if (fold && c.cfg.n_summary > 0) {
@@ -1687,7 +1693,7 @@ static int build_gemm_tables(Ctx& c, bool fold) {
         c.h_gemm_seg[ns] = GemmSeg{c.projPool + (size_t)b * c.nb * mrows * dm, c.projWv + (size_t)h * d * dm, dm, dm, dm, 0};
         c.h_gemm_prob[np++] = GemmProblem{c.projCtmp + (size_t)slice * c.nb * mrows * d, d, c.nb * mrows, d, ns++, 1, 0};
       }
-      c.gemm_groups.push_back({first, heads, c.nb * mrows, d, 3});
+      c.gemm_groups.push_back({first, heads, c.nb * mrows, d, steps(first), 3});
     }
   }
   for (int b = 0; b < B; ++b)
@@ -1704,7 +1710,7 @@ static int build_gemm_tables(Ctx& c, bool fold) {
       if (fold && passing[l])
         c.h_gemm_seg[ns++] = GemmSeg{X + ((int64_t)b * c.N + c.band_off[l]) * dm, c.projM + (size_t)l * dm * dm, dm, dm, dm, 0};
       c.h_gemm_prob[np] = GemmProblem{(half_t*)c.projZ + ((int64_t)b * c.N + c.band_off[l]) * dm, dm, (int)c.band_n[l], dm, seg0, ns - seg0, 0};
-      c.gemm_groups.push_back({np, 1, (int)c.band_n[l], dm, 1});
+      c.gemm_groups.push_back({np, 1, (int)c.band_n[l], dm, steps(np), 1});
       ++np;
     }
   return np;
@@ -1762,7 +1768,7 @@ extern "C" freqattn_status freqattn_forward_projected(freqattn_ctx* c, const voi
     HIP_TRY(c, launch_transpose_bf16_to_f16(wo, c->projWo, hd, d_model, st));
     auto products = [&](int stage) -> freqattn_status {
       for (const Ctx::GemmGroup& gg : c->gemm_groups)
-        if (gg.stage == stage) HIP_TRY(c, launch_gemm_nt(c->d_gemm_prob + gg.first, c->d_gemm_seg, gg.per, gg.m, gg.n, st));
+        if (gg.stage == stage) HIP_TRY(c, launch_gemm_nt(c->d_gemm_prob + gg.first, c->d_gemm_seg, gg.per, gg.m, gg.n, gg.steps, st));
       return FREQATTN_OK;
     };
     if (fold) {

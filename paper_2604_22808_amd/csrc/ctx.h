@@ -164,7 +164,7 @@ struct Ctx {
   GemmProblem* d_gemm_prob = nullptr; GemmProblem* h_gemm_prob = nullptr;   // device table + pinned mirror
   GemmSeg* d_gemm_seg = nullptr; GemmSeg* h_gemm_seg = nullptr;
   int gemm_cap_prob = 0, gemm_cap_seg = 0;
-  struct GemmGroup { int first, per, m, n, stage; };       // one launch: problems [first, first + per) of equal m, n and A rows
+  struct GemmGroup { int first, per, m, n, steps, stage; };   // one launch: problems [first, first + per) of equal m, n and A rows; steps of 64 along K
   std::vector<GemmGroup> gemm_groups;                     // stage 0: Q~/K~ and V~ projections, stage 1: output projection
   bool gemm_tables_valid = false;                         // built for the current allocation (h_alloc)
 
@@ -388,7 +388,7 @@ struct IwhPassArgs {
 };
 bool iwh_fits(const IwhPassArgs& a, int num_cu);   // whether the pass takes these sizes and is the faster way
 hipError_t launch_iwh_pass(const IwhPassArgs& a, int num_cu, hipStream_t st);
-hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, hipStream_t st);
+hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, int steps, hipStream_t st);
 hipError_t launch_transpose_bf16_to_f16(const void* in /*[R][Cc] bf16*/, void* out /*[Cc][R] fp16*/, int R, int Cc, hipStream_t st);
 hipError_t launch_mfma_attn(const AttnParams& p, const AttnItem* items, int n_items, int rows_per_item, int num_cu,
                             hipStream_t st);

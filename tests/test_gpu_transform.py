@@ -333,10 +333,12 @@ def test_projected_forward_of_narrow_models(d_model):
     assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
 
 
-@pytest.mark.parametrize("d_model,heads,alloc", [(256, 4, (1, 2, 4, 0)), (320, 5, (1, 2, 4, 7, 4)), (448, 7, (2, 2, 1, 1, 4, 6, 7))])
+@pytest.mark.parametrize("d_model,heads,alloc", [(256, 4, (1, 2, 4, 0)), (320, 5, (1, 2, 4, 7, 4)), (448, 7, (2, 2, 1, 1, 4, 6, 7)),
+                                                 (704, 11, (1, 2, 4) * 3 + (6, 7)), (768, 12, (1, 2, 4) * 4),
+                                                 (832, 13, (1, 2, 4) * 4 + (0,))])
 def test_projected_forward_of_products_in_wide_tiles(d_model, heads, alloc):
-    """Products of 256 rows and columns and more: even and odd numbers of steps of 64, one segment and several, tiles whose second half is cut
-    short by the columns or the rows, and tiles that span several problems."""
+    """Products of 256 rows and columns and more: even and odd numbers of steps of 64, below 12 and from 12 on, one segment and several, tiles whose second
+    half is cut short by the columns or the rows, and tiles that span several problems."""
     rng = np.random.default_rng(18)
     grid, d = (16, 32, 32), 64
     N, hd = int(np.prod(grid)), heads * d
