@@ -755,18 +755,6 @@ static DctPassArgs t_pass_args(const Ctx& c, const TransformClass& k, int d) {
   return t;
 }
 
-// Whether the T pass of a class joins the launch of the class that keeps the most (`lead`).  It has to be small (fewer than four tiles per wave
-// of a chip with two workgroups on every compute unit); and so has the lead on long axes, whose kernels pay for arguments that depend on
-// the workgroup (k_dct_passes) more than a small launch takes.  Forward transforms apart / together, us, low heads beside two high
-// ones: 16 x 64 x 64 x 64, 4 tiles per compute unit (2 heads) 100 / 93, 24 (12) 184 / 175; beyond the line 48 (24) 272 / 261, 256 (32 mid heads)
-// 346 / 341; 32 x 64 x 64 x 128, 128 (32) 1051 / 1023.  Beside one high head of 64^3 x 128, where the lead is large, 4 to 32 heads:
-// 451 / 447, 658 / 652, 1467 / 1456, 1870 / 1853 (mid heads: the same).  So the line is on the safe side; the gain beyond it is 1-4 %.
-static bool dct_passes_share(const DctPassArgs& lead, const DctPassArgs& a, int num_cu) {
-  auto tiles = [](const DctPassArgs& x) { return x.nslab * (x.inner / 64); };
-  if (a.n != lead.n || mfma_dct_tiles(a.n, a.n_out) != mfma_dct_tiles(lead.n, lead.n_out)) return false;
-  return tiles(a) < 32 * (int64_t)num_cu && (lead.n <= 32 || tiles(lead) < 32 * (int64_t)num_cu);
-}
-
 // One tensor through two passes (W axis, tmp0; H axis, tmp1) and the T pass.
 static hipError_t transform_by_axes(Ctx& c, const TransformClass& k, int i, hipStream_t st, int d) {
   const TransformSeg& x = k.seg[i];
@@ -954,7 +942,7 @@ static hipError_t inverse_transforms_mfma(Ctx& c, void* out, const void* v_in, h
     DctPassArgs sub[3];
     int m = 0;
     for (int j = i; j >= 0; --j)
-      if (!done[j] && (j == i || dct_passes_share(t[i], t[j], c.num_cu))) { sub[m++] = t[j]; done[j] = true; }
+      if (!done[j] && (j == i || dct_passes_share(t[i], t[j], c.num_cu))) { sub[m] = t[j]; sub[m++].n = t[i].n; done[j] = true; }
     if ((e = launch_mfma_dct_pass(sub, m, c.num_cu, st)) != hipSuccess) return e;
   }
   for (bool& b : done) b = false;

@@ -340,13 +340,29 @@ struct DctPassArgs {
 };
 #define DCT_MAX_WAVES 65536   // upper bound of waves in one launch of the DCT pass (sizes energy_part)
 int mfma_dct_tiles(int n_in, int n_out);   // output tiles of 32 of the variant a pass takes
-// `n` passes (at most three) of one variant - rows contracted, output tiles, kind of input and output - in one launch; waves_out[i]: waves
+// `n` passes (at most three) of one variant - rows contracted, output tiles (at least as many as each keeps), kind of input and output - in one launch; waves_out[i]: waves
 // of the i-th that store partial sums.
 hipError_t launch_mfma_dct_pass(const DctPassArgs* subs, int n, int num_cu, hipStream_t st, int* waves_out = nullptr);
 inline hipError_t launch_mfma_dct_pass(const DctPassArgs& a, int num_cu, hipStream_t st, int* waves_out = nullptr) {
   return launch_mfma_dct_pass(&a, 1, num_cu, st, waves_out);
 }
 bool mfma_dct_supported(int n_in, int n_out);
+// Whether the T pass of a class joins the launch of the class that keeps the most (`lead`).  It has to be small (fewer than four tiles per wave
+// of a chip with two workgroups on every compute unit); and so has the lead on long axes, whose kernels pay for arguments that depend on
+// the workgroup (k_dct_passes) more than a small launch takes.  Forward transforms apart / together, us, low heads beside two high
+// ones: 16 x 64 x 64 x 64, 4 tiles per compute unit (2 heads) 100 / 93, 24 (12) 184 / 175; beyond the line 48 (24) 272 / 261, 256 (32 mid heads)
+// 346 / 341; 32 x 64 x 64 x 128, 128 (32) 1051 / 1023.  Beside one high head of 64^3 x 128, where the lead is large, 4 to 32 heads:
+// 451 / 447, 658 / 652, 1467 / 1456, 1870 / 1853 (mid heads: the same).  So the line is on the safe side; the gain beyond it is 1-4 %.
+// The class goes through the lead's tiles and rows, of which it may keep and read fewer: tiles that it does not keep are dropped, and what a
+// delta gathers beyond its box is zero (the same sums, the same bits).  Forwards, passes of unequal boxes apart / together, us: heads low, mid and
+// high of 64, 64 x 16 x 16 101 / 81, 112 x 16 x 16 142 / 100, 128 x 32 x 64 502 / 466, 32 x 32 x 32 99 / 94; two low, mid and high
+// each and more of 96 x 16 x 16 377 / 352, 128 x 32 x 64 x 128 (4 heads) 926 / 910.  Beside a large lead the gather is slower together: 16 heads of
+// 32 x 128 x 128 x 128, 14 of them high, 12590 / 12745.
+inline bool dct_passes_share(const DctPassArgs& lead, const DctPassArgs& a, int num_cu) {
+  auto tiles = [](const DctPassArgs& x) { return x.nslab * (x.inner / 64); };
+  if (a.n > lead.n || (a.n < lead.n && !(a.perm_in && a.delta)) || mfma_dct_tiles(lead.n, a.n_out) > mfma_dct_tiles(lead.n, lead.n_out)) return false;
+  return tiles(a) < 32 * (int64_t)num_cu && ((lead.n <= 32 && a.n == lead.n) || tiles(lead) < 32 * (int64_t)num_cu);
+}
 // W and H axes of the forward transform in one pass, or those of the inverse (mfma_wh_impl.h): input rows of `cols` values
 // through the W matrix, `rows` of them through the H matrix.
 struct WhPassArgs {

@@ -29,7 +29,7 @@ hipError_t launch_mfma_dct_pass(const DctPassArgs* subs, int n, int num_cu, hipS
     if (a.inner % 64 != 0 || a.inner % a.d != 0 || !mfma_dct_supported(a.n, a.n_out) || a.ldm < a.n) return hipErrorInvalidValue;
     if (a.perm_in && (a.perm_out || !a.masks || !a.in_alt)) return hipErrorInvalidValue;
     if (a.energy_part && !a.perm_out) return hipErrorInvalidValue;
-    if (a.n != first.n || mfma_dct_tiles(a.n, a.n_out) != mfma_dct_tiles(first.n, first.n_out) || !a.perm_in != !first.perm_in ||
+    if (a.n != first.n || mfma_dct_tiles(a.n, a.n_out) > mfma_dct_tiles(first.n, first.n_out) || !a.perm_in != !first.perm_in ||
         !a.perm_out != !first.perm_out || !a.energy_part != !first.energy_part || !a.tot_part != !first.tot_part)
       return hipErrorInvalidValue;
   }

@@ -159,10 +159,11 @@ def test_outputs_do_not_depend_on_the_box_of_axes_of_any_length(grid, monkeypatc
 
 
 # classes of slices that keep different boxes and are small enough to share launches: boxes one, two and four tiles of 16 wide, one to
-# four tiles of rows, T axes that can be cut (the gather passes then stay apart) and not, a class that is missing
+# four tiles of rows, T axes of which a class keeps a tile of 32 less than the one whose launch it joins, and reads less, a class that is missing
 @pytest.mark.parametrize("grid,d,alloc", [((16, 32, 32), 64, (1, 2, 4)), ((16, 64, 64), 128, (1, 2, 4, 6, 0)), ((32, 16, 64), 64, (1, 1, 4)),
                                           ((64, 32, 16), 64, (2, 4, 2)), ((16, 128, 32), 64, (1, 2, 4)), ((16, 32, 128), 64, (1, 2, 4)),
-                                          ((16, 48, 64), 64, (1, 2, 4)), ((32, 32, 32), 64, (1, 3, 5))])
+                                          ((16, 48, 64), 64, (1, 2, 4)), ((32, 32, 32), 64, (1, 3, 5)), ((48, 16, 16), 64, (1, 2, 4)), ((80, 16, 32), 64, (1, 2, 2, 0)),
+                                          ((112, 32, 16), 128, (1, 2, 4)), ((128, 16, 48), 64, (2, 1, 4)), ((96, 16, 16), 64, (1, 0, 4))])
 def test_shared_launches_give_the_bits_of_launches_of_their_own(grid, d, alloc):
     import torch
     gen = torch.Generator(device="cuda").manual_seed(23)

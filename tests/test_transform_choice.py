@@ -58,6 +58,38 @@ def test_rows_that_the_generic_pair_of_axes_reads_are_made(tmp_path):
     assert _run(PAIR_PROGRAM, tmp_path) == []
 
 
+# T passes of a few slices, of the boxes that low (a quarter) and mid (half) bands keep beside the whole grid: forward (k) and inverse (i)
+SHARE_PROGRAM = r"""
+#include <cstdio>
+#include "ctx.h"
+using namespace fa;
+int main() {
+  for (int T = 16; T <= 128; T += 16) {
+    DctPassArgs p[3][2];   // [low, mid, whole][forward, inverse]
+    for (int k = 0; k < 3; ++k) {
+      const int box = k == 2 ? T : T * (k + 1) / 4, side = k == 2 ? 16 : 4 * (k + 1);
+      for (DctPassArgs& a : p[k]) { a = DctPassArgs{}; a.inner = side * 64; a.nslab = 6 * side; }
+      p[k][0].n = T; p[k][0].n_out = box;
+      p[k][1].n = (box + 15) / 16 * 16; p[k][1].n_out = T; p[k][1].perm_in = (const int32_t*)1; p[k][1].delta = k < 2;
+    }
+    for (int way = 0; way < 2; ++way)
+      for (int lead = 1; lead < 3; ++lead)
+        for (int k = 0; k < lead; ++k)
+          if (!dct_passes_share(p[lead][way], p[k][way], 256)) std::printf("%d %d %d %d\n", T, way, lead, k);
+    // a gather that selects reads its own rows only, and a launch has no tiles beyond its lead's
+    DctPassArgs s = p[0][1];
+    s.delta = 0;
+    if (s.n < T && dct_passes_share(p[2][1], s, 256)) std::printf("%d selects\n", T);
+    if (T > 32 && dct_passes_share(p[0][0], p[2][0], 256)) std::printf("%d keeps more\n", T);
+  }
+}
+"""
+
+
+def test_small_t_passes_share_a_launch_whatever_they_keep(tmp_path):
+    assert _run(SHARE_PROGRAM, tmp_path) == []
+
+
 def test_what_the_one_pass_transforms_are_chosen_for_they_take(tmp_path):
     lines = _run(PROGRAM, tmp_path)
     took = {"f": {}, "i": {}}
