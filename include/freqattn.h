@@ -194,7 +194,8 @@ freqattn_status freqattn_dct_matrix(const freqattn_ctx* ctx, int32_t axis, doubl
  * Copies one band of one (batch*heads + head) slice of a spectral buffer to HOST as float [n[band], head_dim],
  * after synchronising `stream`.  which: 0 = Q~, 1 = K~, 2 = V~ (section 3.2/3.3, band-major),
  * 3 = band outputs after the exchange, Y^ (section 3.6).  Rows follow freqattn_band_index.  Q~ and K~ of a band
- * that is inactive for the slice are not defined (they are not computed when not needed). */
+ * that is inactive for the slice are not defined (they are not computed when not needed); on the generic path they are
+ * NaN where the forward did not compute them. */
 freqattn_status freqattn_read_spectral(freqattn_ctx* ctx, int32_t which, int32_t slice, int32_t band, float* host_out,
                                        void* stream);
 

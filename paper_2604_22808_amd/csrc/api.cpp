@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <new>
 
 #include "ctx.h"
@@ -1225,6 +1226,7 @@ static freqattn_status transforms_phase(freqattn_ctx* c, const void* q, const vo
   // wait for the masks.  Forwards, whole / boxes, us: Q of 0.06 MB (256 tokens x 2 x 32) 32.9 / 33.8, 0.9 MB (9 x 8 x 8 x 3 x 128) 52.7 / 53.7,
   // 2.9 MB (10 x 10 x 28 x 2 x 128) 62.0 / 60.8, 4 MB (12 x 9 x 24 x 6 x 64) 52.9 / 50.9, 6.6 MB (8 x 27 x 20 x 3 x 128) 82.5 / 80.2.
   const bool boxed = !with_stats && c->n_cls[2] < c->slices && c->slices * c->N * c->d >= ((int64_t)1 << 19);
+  c->qk_boxed = boxed;
   HIP_TRY(c, forward_transform_generic(*c, q, k, v, boxed, st));
   if (with_stats)
     HIP_TRY(c, launch_band_energy(c->specQ, c->specK, c->specV, c->d_stats, c->slices, c->N, c->d, c->band_off, c->band_n,
@@ -1887,6 +1889,11 @@ extern "C" freqattn_status freqattn_read_spectral(freqattn_ctx* c, int32_t which
   const size_t cnt = (size_t)c->band_n[band] * c->d;
   const size_t off = ((size_t)slice * c->N + c->band_off[band]) * c->d;
   if (cnt == 0) return FREQATTN_OK;
+  // (Boxes hold whole bands: the second mid band's and the high band's are the grid.  What lies elsewhere in the scratch is of other calls.)
+  if (which < 2 && c->qk_boxed && c->h_alloc[slice % c->shape.heads] >> std::min(band, 2) == 0) {
+    std::fill_n(host_out, cnt, std::numeric_limits<float>::quiet_NaN());
+    return FREQATTN_OK;
+  }
   if (c->path == FREQATTN_PATH_MFMA) {
     std::vector<half_t> tmp(cnt);
     HIP_TRY(c, hipMemcpy(tmp.data(), (const half_t*)src + off, cnt * sizeof(half_t), hipMemcpyDeviceToHost));

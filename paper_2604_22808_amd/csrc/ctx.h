@@ -103,6 +103,7 @@ struct Ctx {
   int tot_waves[3] = {0, 0, 0};                   // waves that stored sums of squares in the last W-axis pass, per statistics slot
   bool keep_outputs = false;                      // transforms leave Y alone (routing without a forward: the last forward's Y^ stays readable)
   bool qk_on_mid_box = false;                     // the last routed transforms left Q~, K~ on the low+mid box only
+  bool qk_boxed = false;                          // generic path: the last transforms made Q~, K~ on the box of a slice's bands only
   int energy_waves[6] = {0, 0, 0, 0, 0, 0};       // waves that stored band statistics in the last T-axis pass, per statistics slot
   int low_box[3] = {0, 0, 0}, mid_box[3] = {0, 0, 0};  // extent of the low / low+mid box per axis
   float* h_stats = nullptr;                       // pinned mirror and the range flag behind it

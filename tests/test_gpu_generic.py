@@ -235,6 +235,33 @@ def test_generic_boxes_of_all_masks(grid, d, bands):
     assert mx <= U.TOL["f32"][0] and rl <= U.TOL["f32"][1], (mx, rl)
 
 
+@pytest.mark.parametrize("heads,bands", [(8, 3), (16, 4), (7, 3)])
+def test_generic_coefficients_that_were_not_made_read_as_nan(heads, bands):
+    """Q~ and K~ of the bands a slice runs, and those made along with them, are coefficients of this forward's inputs; of what was not made
+    nothing is handed out that another call left behind.  Below 2^19 elements everything is made."""
+    rng = np.random.default_rng(18)
+    grid, d = (8, 9, 15), 64
+    boxed = heads >= 8
+    N = int(np.prod(grid))
+    assert (heads * N * d >= 1 << 19) == boxed
+    cfgd = dict(WL.WORKLOADS["tiny_f32"].band, n_summary=3, **(dict(mid2_num=3, mid2_den=4) if bands == 4 else {}))
+    ctx = B.Context(1, heads, d, grid, B.F32, B.make_cfg(**cfgd), path=B.PATH_GENERIC)
+    q, k, v = (0.7 * rng.standard_normal((1, heads, N, d)).astype(np.float32).astype(np.float64) for _ in range(3))
+    U.run_forward(ctx, v, q, k, "f32", [(1 << bands) - 1] * heads)   # (other coefficients, in all of the scratch)
+    alloc = [h % (1 << bands) for h in range(heads)]
+    U.run_forward(ctx, q, k, v, "f32", alloc)
+    want = [[O.spectral_forward(x[0, h].reshape(grid + (d,))).reshape(N, d) for h in range(heads)] for x in (q, k)]
+    index = O.band_partition(*grid, U.oracle_cfg(cfgd))
+    for which in range(2):
+        for h in range(heads):
+            for l in range(bands):
+                got = ctx.read_spectral(which, h, l)
+                if boxed and alloc[h] >> min(l, 2) == 0:
+                    assert np.isnan(got).all(), (which, h, l)
+                else:
+                    assert U.errors(got, want[which][h][index[l]])[1] <= 1e-5, (which, h, l)
+
+
 @pytest.mark.parametrize("d,block,window,c", [(64, 16, 32, 4), (30, 5, 7, 17), (128, 40, 300, 1), (256, 16, 20, 3)])
 def test_generic_exchange_inside_the_band_launch(d, block, window, c):
     """Slices that run one band each have their exchange in the band's launch; beside a slice that runs two it is a launch of its own.
