@@ -834,18 +834,19 @@ static hipError_t transform_classes(Ctx& c, const TransformClass* cls, int ncls,
   }
   // One launch each for the classes that go with the last one left, until none is left
   bool done[3] = {false, false, false};
+  auto goes_with = [&](int j, int i) { return !done[j] && wh_items(f[j]) < 2 * c.num_cu && f[j].out_rows <= f[i].out_rows; };
   for (int i = n - 1; i >= 0; --i) {
     if (done[i]) continue;
     WhPassArgs sub[3];
     int at[3], m = 0, slots[3] = {0, 0, 0};
     for (int j = i; j >= 0; --j)
-      if (!done[j] && (j == i || (wh_items(f[j]) < 2 * c.num_cu && f[j].out_rows <= f[i].out_rows))) { sub[m] = f[j]; at[m++] = j; done[j] = true; }
+      if (j == i || goes_with(j, i)) { sub[m] = f[j]; at[m++] = j; done[j] = true; }
     // The next class, if it runs alone as well, in the same launch, before this one: it keeps less
     int two = -1;
     if (m == 1 && i > 0 && !done[i - 1] && wh_two_fits(f[i - 1], f[i], c.num_cu)) {
-      two = i - 1;
-      for (int j = i - 2; j >= 0; --j)
-        if (wh_items(f[j]) < 2 * c.num_cu && f[j].out_rows <= f[two].out_rows) two = -1;   // (it has company)
+      bool company = false;
+      for (int j = i - 2; j >= 0; --j) company = company || goes_with(j, i - 1);
+      if (!company) two = i - 1;
     }
     if (two >= 0) {
       done[two] = true;
