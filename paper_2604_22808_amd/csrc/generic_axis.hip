@@ -36,8 +36,9 @@ __device__ __forceinline__ int gx_extent(const AxisBoxes& b, int tensor, int mas
 }
 
 // IN / OUT: 0 fp32, 1 bf16.  VEC: head_dim is a multiple of 4 and the tensors start at a multiple of four elements, so four
-// columns are adjacent, aligned and of one slab.
-template <int KT, int IN, int OUT, bool VEC>
+// columns are adjacent, aligned and of one slab.  BOX: some tensors are only made on a box (a variant of its own: the test of every output row
+// costs passes that make everything 1-2 %).
+template <int KT, int IN, int OUT, bool VEC, bool BOX>
 __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;
@@ -70,14 +71,14 @@ __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
       slice_off[t] = slice * a.Ntok * a.inner + i;
       pbase[t] = (int32_t)(o * (a.perm_in ? a.n : a.n_out));
       if (a.masks) mask[t] = a.masks[slice];
-      if (tensor < a.box.n) {
+      if (BOX && tensor < a.box.n) {
         const int m = a.box.masks[slice], h = (int)(o % a.box.full[1]), z = (int)(o / a.box.full[1]);
         live[t] = live[t] && z < gx_extent(a.box, tensor, m, 0) && h < gx_extent(a.box, tensor, m, 1);
         kend[t] = gx_extent(a.box, tensor, m, 2);
       }
     }
   }
-  if (tensor < a.box.n) {   // nothing of this wave is needed
+  if (BOX && tensor < a.box.n) {   // nothing of this wave is needed
     bool any = false;
 #pragma unroll
     for (int t = 0; t < NC; ++t) any = any || (live[t] && k0 < kend[t]);
@@ -154,7 +155,7 @@ __global__ void __launch_bounds__(256) k_gaxis(AxisPassArgs a, int64_t ncols) {
       if (k >= a.n_out) continue;
 #pragma unroll
       for (int t = 0; t < NC; ++t) {
-        if (!live[t] || k >= kend[t]) continue;
+        if (!live[t] || (BOX && k >= kend[t])) continue;
         const int64_t e = a.perm_out ? slice_off[t] + (int64_t)a.perm_out[pbase[t] + k] * a.inner : out_off[t] + (int64_t)k * a.inner;
         char* dst = out + e * OE;
         if (VEC && OUT) {
@@ -179,8 +180,11 @@ hipError_t launch_io(const AxisPassArgs& a, int64_t ncols, bool vec, hipStream_t
   const int64_t by = (int64_t)a.n_tensors * ((a.n_out + 16 * KT - 1) / (16 * KT));
   if (bx > 0x7fffffff || by > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)bx, (unsigned)by);
-  if (vec) hipLaunchKernelGGL((k_gaxis<KT, IN, OUT, true>), grid, dim3(256), 0, st, a, ncols);
-  else hipLaunchKernelGGL((k_gaxis<KT, IN, OUT, false>), grid, dim3(256), 0, st, a, ncols);
+  constexpr bool BOXES = !IN && !OUT;   // (the last pass of a forward transform is fp32 on both sides)
+  if (a.box.n > 0 && !BOXES) return hipErrorInvalidValue;
+  void (*const k)(AxisPassArgs, int64_t) = BOXES && a.box.n > 0 ? (vec ? k_gaxis<KT, IN, OUT, true, BOXES> : k_gaxis<KT, IN, OUT, false, BOXES>)
+                                                                : (vec ? k_gaxis<KT, IN, OUT, true, false> : k_gaxis<KT, IN, OUT, false, false>);
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, a, ncols);
   return hipGetLastError();
 }
 template <int KT>
