@@ -1759,7 +1759,7 @@ extern "C" freqattn_status freqattn_forward_projected(freqattn_ctx* c, const voi
     HIP_TRY(c, launch_transpose_bf16_to_f16(wo, c->projWo, hd, d_model, st));
     auto products = [&](int stage) -> freqattn_status {
       for (const Ctx::GemmGroup& gg : c->gemm_groups)
-        if (gg.stage == stage) HIP_TRY(c, launch_gemm_nt(c->d_gemm_prob + gg.first, c->d_gemm_seg, gg.per, gg.m, gg.n, gg.steps, st));
+        if (gg.stage == stage) HIP_TRY(c, launch_gemm_nt(c->d_gemm_prob + gg.first, c->d_gemm_seg, gg.per, gg.m, gg.n, gg.steps, d_model / 64, c->num_cu, st));
       return FREQATTN_OK;
     };
     if (fold) {

@@ -405,7 +405,7 @@ struct IwhPassArgs {
 };
 bool iwh_fits(const IwhPassArgs& a, int num_cu);   // whether the pass takes these sizes and is the faster way
 hipError_t launch_iwh_pass(const IwhPassArgs& a, int num_cu, hipStream_t st);
-hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, int steps, hipStream_t st);
+hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, int steps, int call_steps, int num_cu, hipStream_t st);
 hipError_t launch_transpose_bf16_to_f16(const void* in /*[R][Cc] bf16*/, void* out /*[Cc][R] fp16*/, int R, int Cc, hipStream_t st);
 hipError_t launch_mfma_attn(const AttnParams& p, const AttnItem* items, int n_items, int rows_per_item, int num_cu,
                             hipStream_t st);

@@ -444,8 +444,15 @@ __global__ void __launch_bounds__(256) k_transpose_bf16_to_f16(const uint16_t* _
 }  // namespace
 
 // `per` problems d_probs[0 .. per) of identical m and n (host-checked by the caller).
-// `steps`: steps of 64 of the sum over all segments.
-hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, int steps, hipStream_t st) {
+// `steps`: steps of 64 of the sum over all segments; `call_steps`: of d_model, which nearly all of a call's work has at least.
+// Below 12 steps a product copies one step ahead (k_gemm_nt_wide_few has both sides), and in calls of a d_model below 14 steps so do the large launches,
+// of four rounds of the chip and more, whatever their own steps: the seven phases gain nothing there on any machine and lose up to 4 % on some,
+// and products of both kinds in one call are no better.  12 heads of 64, 262,144 tokens, forwards with one step / seven phases / by 12 steps of
+// the product, us, on four machines: d_model 576 1912 / 1987 / 1973, 1947 / - / 1998, 1992 / 2020 / 2014, 2031 / - / 2025; 704 2142 / 2207 / 2209, 2170 / - / 2242,
+// 2200 / 2250 / 2265, 2255 / - / 2275; 768 2291 / 2338 / 2335, 2303 / - / 2358, 2351 / 2393 / 2396, 2410 / - / 2409; 14 heads, 896 2793 / - / 2831,
+// 2835 / 2859 / 2869, 2913 / - / 2884; 16 heads, 1024 3323 / - / 3347, 3399 / 3394 / 3410, 3490 / - / 3432.  Of 16,384 tokens, where launches are a
+// round and less: 704 333 / 322 / 326, 768 345 / 332 / 334.
+hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int per, int m, int n, int steps, int call_steps, int num_cu, hipStream_t st) {
   if (per <= 0 || m <= 0 || n <= 0) return hipSuccess;
   static int wide = -1;
   if (wide < 0) { const char* e = getenv("FREQATTN_GEMM_WIDE"); wide = e ? atoi(e) : 1; }
@@ -454,7 +461,8 @@ hipError_t launch_gemm_nt(const GemmProblem* d_probs, const GemmSeg* d_segs, int
     const int tiles_m = (m + WM - 1) / WM, tiles_n = (int)(((int64_t)per * n + WN - 1) / WN);
     const int64_t blocks = (int64_t)((tiles_m + 7) / 8) * 8 * tiles_n;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(steps < 12 ? k_gemm_nt_wide_few : k_gemm_nt_wide, dim3((unsigned)blocks), dim3(512), 0, st, d_probs, d_segs, per, n, tiles_m, tiles_n);
+    const bool few = steps < 12 || (call_steps < 14 && blocks >= 4 * (int64_t)num_cu);
+    hipLaunchKernelGGL(few ? k_gemm_nt_wide_few : k_gemm_nt_wide, dim3((unsigned)blocks), dim3(512), 0, st, d_probs, d_segs, per, n, tiles_m, tiles_n);
     return hipGetLastError();
   }
   const int tiles_m = (m + GM - 1) / GM, tiles_n = (n + GN - 1) / GN;

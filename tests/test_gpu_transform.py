@@ -356,6 +356,24 @@ def test_projected_forward_of_products_in_wide_tiles(d_model, heads, alloc):
     assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
 
 
+def test_products_of_large_launches():
+    """From four rounds of the chip on products of 12 steps copy as those of fewer do.  Heads that run no band: the layer is X W_V W_O.  Tolerance of the
+    other outputs."""
+    import torch
+    grid, d, heads, d_model = (32, 64, 64), 64, 12, 768
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    N = int(np.prod(grid))
+    x = 0.5 * torch.randn((1, N, d_model), device="cuda", generator=gen, dtype=torch.bfloat16)
+    wv, wo = (torch.randn((d_model, d_model), device="cuda", generator=gen, dtype=torch.bfloat16) / d_model ** 0.5 for _ in range(2))
+    out = torch.empty_like(x)
+    ctx = B.Context(1, heads, d, grid, B.BF16, B.make_cfg(**dict(WL.WORKLOADS["16k"].band, n_summary=0)), path=B.PATH_MFMA)
+    ctx.forward_projected(x, wv, wv, wv, wo, [0] * heads, out)
+    want = x[0].float() @ (wv.float() @ wo.float())
+    mx, rl = U.errors(U.to_host64(out[0]), U.to_host64(want))
+    print(f"large launches: max-abs {mx:.3e} rel-L2 {rl:.3e}", flush=True)
+    assert mx <= 2e-2 and rl <= 5e-3, (mx, rl)
+
+
 def test_projected_forward_of_a_model_of_8192_channels():
     """Rows of the transformed X 4 MB apart and more.  Heads that run no band: the layer is X W_V W_O.  Tolerance of the other outputs."""
     import torch
