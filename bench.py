@@ -398,7 +398,8 @@ def main():
     if shares(fwd_classes):
         fwd_launches = None
     elif fwd_classes[-2][0] > 0 and fwd_classes[-1][0] > 0 and 32 < H <= 64 and W > 32:
-        # the W + H passes of the low+mid box and of the whole grid in one launch, if they are few (wh_two_fits in csrc/mfma_wh_3.hip)
+        # the W + H passes of the low+mid box and of the whole grid in one launch, if they are few and each fills the chip (wh_two_fits in
+        # csrc/mfma_wh_3.hip; a box that does not is counted out by `shares`)
         items = [n * (wl.head_dim // 64) * T * parts for (n, _), parts in zip(fwd_classes[-2:], (-(-W // 64), W // 16))]
         fwd_launches -= cus <= items[1] and sum(items) <= 16 * cus
     if shares(list(zip(n_cls, (low_k, mid_k, full_k)))):

@@ -296,8 +296,9 @@ static hipError_t device_setup(freqattn_ctx* c, hipStream_t st) {
   {
     const int dims[3] = {s.T, s.H, s.W};
     bool smaller = false;
-    // (An axis that counts is cut to as many tiles of 32 as it has, or both lengths are powers of two.  Grids without one keep V~ whole,
-    // and its high band readable: the weights take half a second per million tokens to make.)
+    // (An axis that counts is cut to as many tiles of 32 as it has, or both lengths are powers of two: the grids whose axes could be cut before
+    // those of any length could.  The others keep V~ whole, and its high band readable, as they did; what the box would save them - against
+    // weights that take half a second per million tokens to make - has not been measured.)
     auto pow2 = [](int n) { return (n & (n - 1)) == 0; };
     for (int a = 0; a < 3; ++a) {
       const int n = dims[a], r = keep_rows(c->mid_box[a], n);
@@ -564,8 +565,9 @@ static bool same_cfg(const freqattn_band_cfg& a, const freqattn_band_cfg& b) {
          std::max(a.mid2_num, 0) == std::max(b.mid2_num, 0) && (a.mid2_num <= 0 || a.mid2_den == b.mid2_den);
 }
 
-// Query rows per item of the dense comparison (which has no blocks that an item must not cross: with the 64 rows of mid blocks of 64 16K tokens
-// take 1004 instead of 537 us at 4 heads of 128, 370 instead of 309 at 4 of 64).
+// Query rows per item of the dense comparison (which has no blocks that an item must not cross).  Items of 64 / 128 rows, us: 16K tokens x 4 heads x
+// 128 575 / 496, 4 x 64 317 / 304; fewer items than compute units: 4K x 1 x 128 113 / 86, 4K x 1 x 64 70 / 69, 8K x 6 x 64 153 / 153, 16K x 3 x 64
+// 282 / 282.
 enum { DENSE_ROWS = 128 };
 
 // Fills the pinned host mirror of the per-forward lists.  The item lists are only read by the MFMA attention kernel;

@@ -5,7 +5,9 @@ bool wh_two_fits(const WhPassArgs& a, const WhPassArgs& b, int num_cu) {
   int kt_a, kh_a, kt_b, kh_b;
   wh_tiles(a, &kt_a, &kh_a, nullptr);
   wh_tiles(b, &kt_b, &kh_b, nullptr);
-  // (Up to 16 rounds together: beyond, the two last rounds are little.  64^3 x 128, 33 + 12 full rounds: the forward within 0.5 % either way.)
+  // Up to 16 rounds together, where the last rounds of two launches count: 64K tokens, 22 + 2 heads of 64 (routed, 6 rounds) 580 / 556 us per
+  // forward apart / together.  Beyond it is worth up to 1.4 %, apart / together: 64 heads of 16 x 64 x 64 x 64, a quarter high (17 rounds) 1508 / 1490, 96
+  // (26) 2206 / 2180, 160 (43) 3592 / 3551; 18 of 64^3 x 64 (20) 1888 / 1864; 48 of 32 x 48 x 80 x 128 (75) 4112 / 4115, 96 of 16 x 64 x 64 x 128 (51) 4071 / 4066.
   if ((int64_t)wh_items(a) + wh_items(b) > 16 * (int64_t)num_cu) return false;
   return a.cols == b.cols && a.T == b.T && a.d == b.d && kt_a == 2 && kh_a == 2 && kt_b == 1 && kh_b >= 3 && wh_items(a) >= num_cu && wh_items(b) >= num_cu;
 }
