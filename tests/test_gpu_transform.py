@@ -230,6 +230,29 @@ def test_router_statistics_at_band_edges(grid, d, low, mid, monkeypatch):
     assert np.abs(got - O.band_statistics(q, k, v, grid, O.BandConfig(**band))).max() < 5e-3
 
 
+# A routed forward whose heads were guessed low, mid and high: the T passes with statistics of the box and of the whole grid share a launch, the box's
+# with fewer rows than tiles.  The same output bits as with launches of a class each (no guess), probabilities to 2e-3 as elsewhere (5e-3 on the statistics).
+@pytest.mark.parametrize("grid", [(48, 16, 16), (64, 16, 16), (80, 16, 32), (112, 16, 16)])
+def test_statistics_of_unequal_boxes_in_one_launch(grid):
+    import torch
+    rng = np.random.default_rng(37)
+    heads, d, t = 4, 64, 0.6
+    q, k, v = (WL.round_to_io(rng.standard_normal((1, heads, int(np.prod(grid)), d)), "bf16") for _ in range(3))
+    band, w = WL.WORKLOADS["16k"].band, WL.router_weights()
+    ctx = B.Context(1, heads, d, grid, B.BF16, B.make_cfg(**band), path=B.PATH_MFMA)
+    x = [U.to_device(a, "bf16") for a in (q, k, v)]
+    outs = []
+    for guess in (False, True):
+        ctx.set_alloc_prediction(guess)
+        ctx.forward(*x, [1, 2, 4, 4], torch.empty_like(x[0]))
+        out = torch.empty_like(x[0])
+        alloc, pi = ctx.forward_routed(*x, t, *w, out)
+        want_alloc, want_pi = O.route_mlp(q, k, v, grid, O.BandConfig(**band), t, *w)
+        assert np.abs(pi - want_pi).max() < 2e-3 and np.array_equal(alloc, want_alloc)
+        outs.append(out)
+    assert torch.equal(*outs)
+
+
 # High-band summaries from the untransformed V of slices that do not run it: one and two groups of 32 chunks.  Tolerance as for the other
 # forwards (bf16 rounding of the output 1.6e-3, fp16 spectra 4.6e-4; relative L2 3e-3).
 @pytest.mark.parametrize("d", [64, 128])
